@@ -561,7 +561,13 @@ apcg_status apcg_info_get(apcg_info info, int32_t index, apcg_solve_info *out);
  * With APCG_MODE_GRAPH/STREAM no kernel waits on the host: the host thread
  * returns once it has enqueued enough work to reach convergence or maxit,
  * having observed the device flag only through events `lookahead` periods
- * behind the queue.  With APCG_MODE_PERSISTENT (or AUTO at n <=
+ * behind the queue.  With APCG_MODE_GRAPH (and AUTO), a system of more than
+ * 8192 rows that fits the chip -- rows of at most 5 entries up to 1,048,576
+ * rows, of at most 7 up to 524,288, columns within about 8,000 of the
+ * diagonal -- is solved by one launch of a team of workgroups instead, each
+ * holding its rows' entries and vectors in registers; its sums run in another
+ * fixed order than the kernels' of STREAM and HOST_CHECK (same tests, same
+ * counts up to rounding).  With APCG_MODE_PERSISTENT (or AUTO at n <=
  * APCG_PERSISTENT_MAX_N) the whole solve is one launch of one 512-thread
  * workgroup that keeps each row's r, D^-1, p and A p in registers and shares
  * p through n doubles of the context's workspace; its sums run in another
@@ -722,8 +728,12 @@ apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec 
  *     copy (same row sums, bit for bit); every other system reads CSR.
  *     The tile product walks 5, 7 or 8 offset slots per row, the fewest
  *     that cover every such system of the batch.
- *   APCG_BATCH_AUTO: persistent when no system costs more than 1/CUs of the
- *     batch, else segmented.
+ *   APCG_BATCH_AUTO: teams when every system's rows hold at most 7 entries and
+ *     it fits the chip (see apcg_ksp_solve): one launch, each system held in
+ *     the registers of as many workgroups as it needs; the segmented
+ *     schedule's sums, bit for bit, whatever copies of the matrices exist.
+ *     Otherwise persistent when no system costs more than 1/CUs of the batch,
+ *     else segmented.
  * A, b, x: arrays of nsys handles on ctx's device; the memory of each x[i]
  * may overlap no other x[j] and no b[j] (checked on the host over the
  * vectors' address ranges: APCG_ERR_INVALID_ARG); x[i] holds x0 (ignored with x0_is_zero) and receives

@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "team_host.h"
 
 namespace apcg {
 
@@ -445,6 +446,30 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
         if ((s = op_begin(ctx, acc.data(), (int)acc.size()))) return s;
         hipStream_t st = ctx->stream;
 
+        // Systems that fit the chip are solved by teams of workgroups, each
+        // system's vectors and matrix in registers from the first iteration
+        // to the last (team.hip): the segmented schedule streams both through
+        // the caches four kernels an iteration, and a persistent workgroup
+        // works on one system from memory.  256 2D systems of 1e3 to 6.5e4
+        // rows: 28.5 ms, segmented 192 (160 on sliced diagonals), persistent
+        // 450.  Same sums as the segmented schedule, bit for bit.
+        if (opts.batch_schedule == APCG_BATCH_AUTO) {
+            int rows = 0;
+            if ((s = team_eligible(ctx, nsys, A, &rows))) return s;
+            if (rows > 0) {
+                std::vector<int32_t> left;
+                if ((s = team_pcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, rows, info->d, nullptr, 0, &left)))
+                    return s;
+                if ((s = op_end(ctx, acc.data(), (int)acc.size()))) return s;
+                apcg_solve_opts single = opts;
+                single.mode = APCG_MODE_STREAM;
+                for (int32_t i : left)  // a launch that was given up (see team.h)
+                    if ((s = pcg_solve_marked(ctx, A[i], b[i], x[i], rtol, maxit, &single, info, i, nullptr, 0)))
+                        return s;
+                return APCG_SUCCESS;
+            }
+        }
+
         // (re)allocate device descriptors and workspace; the old buffers may
         // still be used by queued work, so their release is deferred
         if (bc->sys_cap < nsys || bc->ws_cap < ws_total) {
@@ -726,32 +751,14 @@ __global__ __launch_bounds__(ST) void k_seg_init(SegPlan P, int x0_zero, int pc,
 // Threads of the per-system kernels (one workgroup per system).
 constexpr int SB = 256;
 
-// Adds the slice partials part[k*ns + g] of a system (its slices ga..gb)
-// in a fixed order: thread l takes g = ga + l, ga + l + SB, ..., then the
-// workgroup tree.  Result in thread 0.
+// Adds the slice partials part[k*ns + g] of a system (its slices ga..gb) in
+// a fixed order: the 32 slices of a group by a half wavefront's butterfly,
+// thread l of the workgroup tree the groups l, l + SB, ...  Result in thread
+// 0.  (Groups, so that a member of a team solve, which holds whole groups,
+// adds them on its own and sends one number for 32 slices; team.h.)
 template <int NV>
 __device__ __forceinline__ void sys_sum(const double *part, int ns, int ga, int gb, double (&v)[NV], double *lds) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = 0.0;
-    int g = ga + (int)threadIdx.x;
-    // eight of a thread's partials loaded before they are added (a large
-    // system has thousands of slices); the same order of addition
-    constexpr int UA = 8;
-    for (; g + (UA - 1) * SB < gb; g += UA * SB) {
-        double t[UA][NV];
-#pragma unroll
-        for (int u = 0; u < UA; ++u)
-#pragma unroll
-            for (int k = 0; k < NV; ++k) t[u][k] = part[(int64_t)k * ns + g + u * SB];
-#pragma unroll
-        for (int u = 0; u < UA; ++u)
-#pragma unroll
-            for (int k = 0; k < NV; ++k) v[k] += t[u][k];
-    }
-    for (; g < gb; g += SB) {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) v[k] += part[(int64_t)k * ns + g];
-    }
+    dev::group_tree<SB, NV>(gb - ga, [&](int k, int l) { return part[(int64_t)k * ns + ga + l]; }, v);
     dev::block_sum<SB, NV>(v, lds);
 }
 

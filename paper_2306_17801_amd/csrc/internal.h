@@ -215,6 +215,7 @@ struct apcg_mat_s {
     double *dia_val = nullptr;       // device [dia_ndt][n rounded up to 64]
     apcg::Record rec;
     uint64_t mark_id = 0;
+    int32_t band_below = -1, band_above = -1;  // largest column distance from the diagonal (team solves), -1: not read yet
     std::string tune_class;  // pattern class of the tuning key (tune.hip), computed once
 };
 
@@ -301,6 +302,7 @@ void learn_cache_release(uint64_t ctx_id, int device);  // learn.hip
 void fcg_cache_release(uint64_t ctx_id, int device);    // fcg.hip
 void bfcg_cache_release(uint64_t ctx_id, int device);   // batched_fcg.hip
 void tq_cache_release(uint64_t ctx_id, int device);     // tfqmr.hip
+void team_cache_release(uint64_t ctx_id, int device);   // team.hip
 // dependency-marking ids of library objects (intent.hip): an object's id
 // maps to its Record until the object is destroyed
 uint64_t intent_object_id(uint64_t *slot, int device, Record *rec);
@@ -423,6 +425,61 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double *lds) {
             double s = lds[k * NW];
             for (int w = 1; w < NW; ++w) s += lds[k * NW + w];
             v[k] = s;
+        }
+    }
+}
+
+// Sum of v over the half wavefront's 32 lanes (distances 16, 8, 4, 2, 1), in
+// all of them.
+__device__ __forceinline__ double half_sum(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    v = __longlong_as_double((long long)((uint64_t)h[0] << 32 | l[0])) +
+        __longlong_as_double((long long)((uint64_t)h[1] << 32 | l[1]));
+    v += dpp_row<0x128>(v);
+    v += dpp_row<0x124>(v);
+    v += dpp_row<0x122>(v);
+    v += dpp_row<0x121>(v);
+    return v;
+}
+
+// The leaves of the per-system reduction tree over n slice partials get(k, l):
+// thread t of a BS-thread workgroup receives in v[k] the sum of groups t,
+// t + BS, ... in order, a group being 32 consecutive slices added by a half
+// wavefront's butterfly.  The half wavefronts take the groups in turn, four
+// rounds of loads at a time, and hand the sums over through LDS.
+template <int BS, int NV, class Get>
+__device__ __forceinline__ void group_tree(int n, Get get, double (&v)[NV]) {
+    constexpr int HW = BS / 32, UA = 4, ROUND = BS;  // groups per pass through LDS
+    __shared__ double sums[NV * ROUND];
+    const int half = threadIdx.x >> 5, lane = threadIdx.x & 31;
+    const int ngr = (n + 31) >> 5;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = 0.0;
+    for (int g0 = 0; g0 < ngr; g0 += ROUND) {
+        const int cnt = ngr - g0 < ROUND ? ngr - g0 : ROUND;
+        if (g0) __syncthreads();  // the previous pass has been read
+        for (int a = half; a < cnt; a += UA * HW) {
+            double t[UA][NV];
+#pragma unroll
+            for (int u = 0; u < UA; ++u) {
+                const int l = (g0 + a + u * HW) * 32 + lane;
+#pragma unroll
+                for (int k = 0; k < NV; ++k) t[u][k] = a + u * HW < cnt && l < n ? get(k, l) : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < UA; ++u)
+#pragma unroll
+                for (int k = 0; k < NV; ++k) {
+                    const double s = half_sum(t[u][k]);
+                    if (lane == 0 && a + u * HW < cnt) sums[k * ROUND + a + u * HW] = s;
+                }
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < cnt) {
+#pragma unroll
+            for (int k = 0; k < NV; ++k) v[k] += sums[k * ROUND + threadIdx.x];
         }
     }
 }

@@ -40,6 +40,7 @@
 #include <cstring>
 
 #include "internal.h"
+#include "team_host.h"
 
 namespace apcg {
 
@@ -1810,6 +1811,19 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
         if (A->cfg.schedule == APCG_SPMV_SELL && (s = prepare_sell(A, c->stream))) return s;
         if (A->cfg.schedule == APCG_SPMV_SDIA && (s = prepare_sdia(A, c->stream))) return s;
         if (A->cfg.schedule == APCG_SPMV_DIA && (s = prepare_dia(A, c->stream))) return s;
+        // a system that fits the chip, by a team of workgroups in one launch
+        if (opts.mode == APCG_MODE_GRAPH && !gate && A->n > kTeamMinRows) {
+            int rows = 0;
+            if ((s = team_eligible(c, 1, &A, &rows))) return s;
+            if (rows > 0) {
+                std::vector<int32_t> left;
+                if ((s = team_pcg_solve(c, 1, &A, &b, &x, {0}, rtol, maxit, opts, rows, info->d + info_index, hist,
+                                        hist_cap, &left)))
+                    return s;
+                if (left.empty()) return op_end(c, acc, 4);
+                // given up (see team.h): x is as it was, the kernels below solve it
+            }
+        }
         Plan pl;
         if ((s = make_plan(A, A->cfg, &pl))) return s;
         Bufs bf{A, x->d, b->d, c->ws, c->partials};

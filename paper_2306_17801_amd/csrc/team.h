@@ -1,0 +1,367 @@
+// team.h -- device side of the team solves: a system held on the chip by a
+// team of workgroups that exchange only what crosses their borders.
+//
+// A team of T workgroups owns one system for its whole solve.  Member m owns
+// rows [512 R m, 512 R (m + 1)): its eight wavefronts take the 64-row slices
+// 8 q + wave (q < R) of that range, one row per lane, and keep the matrix
+// entries and every vector of those rows in registers.  The members meet
+// twice per Krylov step, at the two inner products.  A meeting is one
+// message per group of 32 slices, and every member waits for all groups'
+// messages, so it is the grid-wide barrier and the reduction in one: measured
+// on an idle MI355X at 1.2 us (8 members), 1.6 us (64) and 2.4 us (256),
+// where a kernel boundary costs about 4 us once its first loads have
+// arrived.
+//
+// Messages carry their own arrival mark: a double travels as two 64-bit
+// words, each holding half of it and the 32-bit tag of the step, so no flag
+// has to follow the data and be ordered after it.  All traffic between
+// members goes through agent-scope relaxed atomics, which neither stay in an
+// XCD's L2 (stores) nor are served from it (loads).  Vector entries the
+// other members read are stored the same way, and every wavefront waits for
+// its own stores (s_waitcnt vmcnt(0)) before the barrier behind which the
+// message that announces them leaves.  An agent-scope release fence does the
+// same ordering but writes back the whole L2: 58-76 us a meeting at 256
+// members.
+//
+// Members never wait for a workgroup that has not started: work is handed
+// out by ticket (see TeamPlan), so every workgroup that a member waits for
+// is running or is the next to start.  Every wait is bounded all the same.
+#pragma once
+
+#include "internal.h"
+
+namespace apcg {
+namespace team {
+
+// Threads of a member: eight wavefronts with 256 registers each.  (Sixteen
+// with 128 spill from two slices on: 4096 rows took 9.2 us an iteration.)
+constexpr int TT = 512;
+constexpr int TW = TT / 64;      // its wavefronts
+constexpr int kGroup = 32;       // 64-row slices per message: the rows of a member at R = 4
+constexpr int kGroupRows = 64 * kGroup;
+constexpr int kMaxRows = 8;      // slices per wavefront (R): 4 or 8
+// Words from one group's messages to the next: 256 bytes, so that neighbours
+// lie in different memory channels.  Every member reads every message, and
+// packed messages share a few channels: 123 members on 2.5e5 rows took 9.4 us
+// an iteration packed, 7.3 at 64 bytes apart and 6.7 at 256.
+constexpr int kStride = 32;
+constexpr int kTree = 256;       // threads of the reduction tree over groups
+constexpr int kSide = 4;         // border entries a thread may fetch during a meeting
+
+// Longest wait for one message (ticks of the 100 MHz clock): far beyond any
+// solve's step or the time other work may hold a compute unit; then the
+// launch is given up and the host solves what is left with the other
+// schedules.
+constexpr long long kWaitTicks = 800000000ll;
+
+// Global pointers the compiler keeps in scalar registers: the values read
+// from a device table are the same in every lane, which it cannot see.
+template <class T>
+using gptr = dev::glob_t<T> *;
+template <class T>
+__device__ __forceinline__ gptr<T> uniform(T *p) {
+    const uint64_t b = (uint64_t)p;
+    const uint32_t l = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t h = __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return (gptr<T>)((uint64_t)h << 32 | l);
+}
+
+// Entry i of a table with a scalar base and an offset below 4 GiB: one 32-bit
+// register of address per access instead of two.
+template <class T>
+__device__ __forceinline__ gptr<T> at(gptr<T> p, uint32_t i) {
+    return (gptr<T>)((gptr<char>)p + i * (uint32_t)sizeof(T));
+}
+template <class T>
+__device__ __forceinline__ const dev::glob_t<T> *at(const dev::glob_t<T> *p, uint32_t i) {
+    return (const dev::glob_t<T> *)((const dev::glob_t<char> *)p + i * (uint32_t)sizeof(T));
+}
+
+template <class T>
+__device__ __forceinline__ T load_shared(gptr<T> p, uint32_t i) {
+    return __hip_atomic_load(at(p, i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void store_shared(gptr<T> p, uint32_t i, T v) {
+    __hip_atomic_store(at(p, i), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Every store this wavefront has issued has reached the device's point of
+// coherence (stores count in vmcnt on this architecture).
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// A member's place in its team, the same in all its threads.
+struct Member {
+    int T, m;        // members, this one's index
+    int n;           // rows of the system
+    int ngr;         // groups of the system
+    int mw;          // wavefronts that collect messages (the others are free for a side job)
+    gptr<uint32_t> stop;  // nonzero: the launch is given up
+    double *tot;     // LDS: 4 * 4 tree sums
+    int *ok;         // LDS: 0 once a wait has failed
+};
+
+// One look at the clock and the stop word every 256 unsuccessful looks at a
+// message; false when the launch is given up.
+__device__ __forceinline__ bool keep_waiting(const Member &M, int spin, long long &t0) {
+    if ((spin & 255) != 255) return true;
+    const long long now = wall_clock64();
+    if (t0 == 0) t0 = now;
+    if (load_shared<uint32_t>(M.stop, 0)) return false;
+    if (now - t0 <= kWaitTicks) return true;
+    store_shared<uint32_t>(M.stop, 0, 1u);
+    return false;
+}
+
+__device__ __forceinline__ double unpack(uint64_t lo, uint64_t hi) {
+    return __longlong_as_double((long long)((lo & 0xffffffffull) | (hi << 32)));
+}
+
+__device__ __forceinline__ void post(gptr<uint64_t> words, uint32_t i, double v, uint32_t tag) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v), t = (uint64_t)tag << 32;
+    store_shared<uint64_t>(words, i, (b & 0xffffffffull) | t);
+    store_shared<uint64_t>(words, i + 1, (b >> 32) | t);
+}
+
+// The NW words (a multiple of two, 16-byte aligned) at words + i, by 16-byte
+// loads that miss the L2 like load_shared (each word carries its own tag, so
+// nothing is assumed of the two words together).  Half the requests of
+// single words: what the members' looks cost is requests at the channel that
+// holds a message.
+template <int NW>
+__device__ __forceinline__ void load_message(gptr<uint64_t> words, uint32_t i, uint64_t (&w)[NW]) {
+    static_assert(NW == 2 || NW == 4 || NW == 8, "message sizes");
+    typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+    const gptr<uint64_t> p = at(words, i);
+    v4 a, b, c, d;
+    if constexpr (NW == 2)
+        asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(a) : "v"(p) : "memory");
+    if constexpr (NW == 4)
+        asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %2, off offset:16 sc1\n\t"
+                     "s_waitcnt vmcnt(0)" : "=&v"(a), "=&v"(b) : "v"(p) : "memory");
+    if constexpr (NW == 8)
+        asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %4, off offset:16 sc1\n\t"
+                     "global_load_dwordx4 %2, %4, off offset:32 sc1\n\tglobal_load_dwordx4 %3, %4, off offset:48 sc1\n\t"
+                     "s_waitcnt vmcnt(0)" : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d) : "v"(p) : "memory");
+    auto put = [&](int k, const v4 &x) {
+        w[k] = (uint64_t)x[1] << 32 | x[0];
+        w[k + 1] = (uint64_t)x[3] << 32 | x[2];
+    };
+    put(0, a);
+    if constexpr (NW >= 4) put(2, b);
+    if constexpr (NW == 8) {
+        put(4, c);
+        put(6, d);
+    }
+}
+
+// Four pairs of words at once, one from each address.
+__device__ __forceinline__ void load_pairs(gptr<uint64_t> words, const uint32_t (&i)[4], uint64_t (&w)[4][2]) {
+    typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+    v4 a, b, c, d;
+    asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+                 "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
+                 : "v"(at(words, i[0])), "v"(at(words, i[1])), "v"(at(words, i[2])), "v"(at(words, i[3]))
+                 : "memory");
+    auto put = [&](int k, const v4 &x) {
+        w[k][0] = (uint64_t)x[1] << 32 | x[0];
+        w[k][1] = (uint64_t)x[3] << 32 | x[2];
+    };
+    put(0, a);
+    put(1, b);
+    put(2, c);
+    put(3, d);
+}
+
+// Adds the NV doubles of group g's message to acc once it carries `tag`;
+// false when the launch is given up.
+template <int NV>
+__device__ __forceinline__ bool collect(const Member &M, gptr<uint64_t> words, int g, uint32_t tag,
+                                        double (&acc)[NV]) {
+    long long t0 = 0;
+    for (int spin = 0;; ++spin) {
+        uint64_t w[2 * NV];
+        load_message<2 * NV>(words, (uint32_t)(g * kStride), w);
+        bool all = true;
+#pragma unroll
+        for (int k = 0; k < 2 * NV; ++k) all = all && (uint32_t)(w[k] >> 32) == tag;
+        if (all) {
+#pragma unroll
+            for (int k = 0; k < NV; ++k) acc[k] += unpack(w[2 * k], w[2 * k + 1]);
+            return true;
+        }
+        if (!keep_waiting(M, spin, t0)) return false;
+    }
+}
+
+// a + b of the two vectors a half-wave or row swap of (x, y) leaves: lanes of
+// the first half (row) hold x's pair sums, those of the second y's.
+__device__ __forceinline__ double swap_add32(double x, double y) {
+    const uint64_t a = (uint64_t)__double_as_longlong(x), b = (uint64_t)__double_as_longlong(y);
+    const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    return __longlong_as_double((long long)((uint64_t)h[0] << 32 | l[0])) +
+           __longlong_as_double((long long)((uint64_t)h[1] << 32 | l[1]));
+}
+__device__ __forceinline__ double swap_add16(double x, double y) {
+    const uint64_t a = (uint64_t)__double_as_longlong(x), b = (uint64_t)__double_as_longlong(y);
+    const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    return __longlong_as_double((long long)((uint64_t)h[0] << 32 | l[0])) +
+           __longlong_as_double((long long)((uint64_t)h[1] << 32 | l[1]));
+}
+
+// Wavefront sums of N values (N a power of two), each added in the pairs of
+// dev::wave_sum and so to the same bits, four values to a register: the first
+// two steps of four butterflies are three additions instead of eight, and
+// the remaining four steps serve four values at once.  Value i's sum goes to
+// *out(i).
+template <int N, class Out>
+__device__ __forceinline__ void wave_sums(const double (&v)[N], Out out) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < N; i += 4) {
+        const double a = v[i], b = v[i + (N > 1 ? 1 : 0)], c = v[i + (N > 2 ? 2 : 0)], d = v[i + (N > 2 ? 3 : 0)];
+        const double ab = swap_add32(a, b);  // lanes 0..31: a, 32..63: b
+        const double cd = N > 2 ? swap_add32(c, d) : ab;
+        double s = swap_add16(ab, cd);       // rows of 16 lanes: a, c, b, d
+        s += dev::dpp_row<0x128>(s);
+        s += dev::dpp_row<0x124>(s);
+        s += dev::dpp_row<0x122>(s);
+        s += dev::dpp_row<0x121>(s);
+        if ((lane & 15) == 0) {
+            const int row = lane >> 4;
+            const int id = N > 2 ? i + ((row & 1) << 1 | row >> 1) : N > 1 ? row >> 1 : 0;
+            *out(id) = s;  // fewer than four values: rows of equal sums
+        }
+    }
+}
+
+// The sums over the system's rows of NV values per row, in two steps: every
+// wavefront puts the sums of its slices (slices_put), then the team meets
+// (team_meet) and every thread of every member holds the totals.  The order
+// is that of the segmented schedule (sys_sum in batched.hip): the 64 rows of
+// a slice and the 32 slices of a group by butterflies, groups l, l + 256, ...
+// by thread l of a 256-thread tree.  It does not depend on T or R.
+// red: NV areas of 8 R slice sums, one for each value.
+// v[q * NV + k]: value k of this thread's row of slice q0 + q.
+template <int R, int NV, int NQ>
+__device__ __forceinline__ void slices_put(double *red, int q0, const double (&v)[NQ * NV]) {
+    double *mine = red + q0 * TW + (threadIdx.x >> 6);
+    wave_sums<NQ * NV>(v, [=](int i) { return mine + i % NV * (R * TW) + i / NV * TW; });
+}
+
+// words: group 0's message of this meeting (2 NV words, kStride from group to
+// group), tag: its step.
+// ack: wait for this wavefront's shared stores before the message leaves, so
+// that they are visible to whoever has received it.
+// Between its own message and the others' the wavefronts that collect no
+// messages run side(thread, threads) -> bool.  red is free again after the
+// next meeting's (other) red has been put.
+// Returns false when the launch is given up.
+template <int R, int NV, class Side>
+__device__ __forceinline__ bool team_meet(const Member &M, const double *red, gptr<uint64_t> words, uint32_t tag,
+                                          bool ack, double (&total)[NV], Side side) {
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    if (M.T == 1) {  // the whole system is here, in one or two groups: the tree in every wavefront
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const double g = dev::half_sum(lane < R * TW ? red[k * (R * TW) + lane] : 0.0);
+            total[k] = swap_add32(g, g);
+        }
+        return true;
+    }
+    if (ack) wait_stores();
+    __syncthreads();
+    if (tid < R * TW * NV) {  // half wavefront (q, k): value k of the member's group q
+        const int q = tid / (32 * NV), k = tid / 32 % NV, g = M.m * (R * TW / kGroup) + q;
+        const double t = dev::half_sum(red[k * (R * TW) + q * kGroup + (tid & 31)]);
+        if ((tid & 31) == 0 && g < M.ngr) post(words, (uint32_t)(g * kStride + k * 2), t, tag);
+    }
+    bool good = true;
+    double acc[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+    if (wave < M.mw) {
+        for (int g = tid; good && g < M.ngr; g += kTree) good = collect<NV>(M, words, g, tag, acc);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const double t = dev::wave_sum(acc[k]);
+            if (lane == 0) M.tot[k * (kTree / 64) + wave] = t;
+        }
+    } else {
+        good = side(tid - M.mw * 64, TT - M.mw * 64);
+    }
+    if (!good) *M.ok = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        double t = M.tot[k * (kTree / 64)];
+        for (int w = 1; w < M.mw; ++w) t += M.tot[k * (kTree / 64) + w];  // the other wavefronts' sums are zeros
+        total[k] = t;
+    }
+    return *M.ok != 0;
+}
+
+// The rows of a member: matrix entries in registers, the columns relative to
+// its first row.  The member's window is the smallest run of columns holding
+// its own rows and every column they name; its copy of the vector being
+// multiplied lies in LDS.
+constexpr int kBias = 32768;  // columns are kept as 16-bit col - row0 + kBias
+constexpr int kZero = 8;      // places before the window; the last holds 0, the column of absent entries
+template <int R, int L>
+struct Rows {
+    double a[R][L];
+    uint32_t j[R][(L + 1) / 2];  // two 16-bit columns a word
+
+    __device__ __forceinline__ int rel(int q, int t) const { return (int)((j[q][t >> 1] >> (16 * (t & 1))) & 0xffffu); }
+
+    // The packed columns are unpacked where they are used: without this the
+    // compiler keeps every unpacked column in a register of its own across
+    // the iterations, and spills.
+    __device__ __forceinline__ void keep_packed() {
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+#pragma unroll
+            for (int t = 0; t < (L + 1) / 2; ++t) asm volatile("" : "+v"(j[q][t]));
+    }
+
+    // sum_t a_t v(j_t) in storage order, one FMA per entry (an absent one
+    // adds 0 * 0); base: the window's LDS address moved so that base[rel] is
+    // column row0 + rel - kBias
+    __device__ __forceinline__ double dot(int q, const double *base) const {
+        double g[L];
+#pragma unroll
+        for (int t = 0; t < L; ++t) g[t] = base[rel(q, t)];
+        double sum = 0.0;
+#pragma unroll
+        for (int t = 0; t < L; ++t) sum = fma(a[q][t], g[t], sum);
+        return sum;
+    }
+};
+
+// Workgroup minimum and maximum of lo and hi (LDS area of 2 TW ints).
+__device__ __forceinline__ void block_minmax(int &lo, int &hi, int *area) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, __shfl_xor(lo, o, 64));
+        hi = max(hi, __shfl_xor(hi, o, 64));
+    }
+    if (lane == 0) {
+        area[wave] = lo;
+        area[TW + wave] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < TW; ++w) {
+        lo = min(lo, area[w]);
+        hi = max(hi, area[TW + w]);
+    }
+    __syncthreads();
+}
+
+}  // namespace team
+}  // namespace apcg
