@@ -215,7 +215,7 @@ struct apcg_mat_s {
     double *dia_val = nullptr;       // device [dia_ndt][n rounded up to 64]
     apcg::Record rec;
     uint64_t mark_id = 0;
-    int32_t band_below = -1, band_above = -1;  // largest column distance from the diagonal (team solves), -1: not read yet
+    int32_t team_border[2] = {-1, -1};  // most border columns of a team's member of 2048 / 4096 rows, -1: not read yet
     std::string tune_class;  // pattern class of the tuning key (tune.hip), computed once
 };
 
@@ -696,6 +696,19 @@ __device__ inline void feature_vector(const double *st, double var, const double
     f[14] = log10(fmax(relres, 1e-30));  // floored: exact early convergence stays finite
     f[15] = log10(th[0] / hi);
     for (int k = 0; k < 16; ++k) feat[k] = (float)f[k];
+}
+
+// sum_j c_j T_j(2 t / lmax - 1), j <= DEG, by Clenshaw's recurrence.
+template <int DEG>
+__device__ inline double poly_at(const double *c, double t, double lmax) {
+    const double y = 2.0 * t / lmax - 1.0;
+    double b1 = 0.0, b2 = 0.0;
+    for (int j = DEG; j >= 1; --j) {
+        const double b0 = c[j] + 2.0 * y * b1 - b2;
+        b2 = b1;
+        b1 = b0;
+    }
+    return c[0] + y * b1 - b2;
 }
 
 // Row sum of a sliced-diagonal matrix (the layout of the SDIA schedule:

@@ -1799,22 +1799,19 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
         if (s) return s;
         Acc acc[4] = {{&x->rec, ACC_RW}, {&info->rec, ACC_W}, {&A->rec, ACC_R}, {&b->rec, ACC_R}};
         if ((s = op_begin(c, acc, 4))) return s;
-        if ((s = ensure_workspace(c, A->n))) return s;
         const int norm_pre = opts.norm_type == APCG_NORM_PRECONDITIONED;
         hipStream_t st = c->stream;
-        if (opts.mode == APCG_MODE_PERSISTENT) {  // reads the CSR arrays; p in the workspace
-            if ((s = launch_pcg_wg(st, A->n, A->rowptr, A->col, A->val, b->d, x->d, c->ws.p(0), rtol, maxit,
-                                   opts.x0_is_zero ? 1 : 0, opts.pc, norm_pre, A->sell_maxw, info->d + info_index)))
-                return s;
-            return op_end(c, acc, 4);
+        if (opts.mode != APCG_MODE_PERSISTENT) {
+            // the copies are refilled whichever kernels run: what the refill
+            // finds about the values is reported by apcg_mat_get_sdia_info
+            if (A->cfg.schedule == APCG_SPMV_SELL && (s = prepare_sell(A, c->stream))) return s;
+            if (A->cfg.schedule == APCG_SPMV_SDIA && (s = prepare_sdia(A, c->stream))) return s;
+            if (A->cfg.schedule == APCG_SPMV_DIA && (s = prepare_dia(A, c->stream))) return s;
         }
-        if (A->cfg.schedule == APCG_SPMV_SELL && (s = prepare_sell(A, c->stream))) return s;
-        if (A->cfg.schedule == APCG_SPMV_SDIA && (s = prepare_sdia(A, c->stream))) return s;
-        if (A->cfg.schedule == APCG_SPMV_DIA && (s = prepare_dia(A, c->stream))) return s;
         // a system that fits the chip, by a team of workgroups in one launch
         if (opts.mode == APCG_MODE_GRAPH && !gate && A->n > kTeamMinRows) {
             int rows = 0;
-            if ((s = team_eligible(c, 1, &A, &rows))) return s;
+            if ((s = team_eligible(c, 1, &A, 1, &rows))) return s;
             if (rows > 0) {
                 std::vector<int32_t> left;
                 if ((s = team_pcg_solve(c, 1, &A, &b, &x, {0}, rtol, maxit, opts, rows, info->d + info_index, hist,
@@ -1823,6 +1820,13 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
                 if (left.empty()) return op_end(c, acc, 4);
                 // given up (see team.h): x is as it was, the kernels below solve it
             }
+        }
+        if ((s = ensure_workspace(c, A->n))) return s;
+        if (opts.mode == APCG_MODE_PERSISTENT) {  // reads the CSR arrays; p in the workspace
+            if ((s = launch_pcg_wg(st, A->n, A->rowptr, A->col, A->val, b->d, x->d, c->ws.p(0), rtol, maxit,
+                                   opts.x0_is_zero ? 1 : 0, opts.pc, norm_pre, A->sell_maxw, info->d + info_index)))
+                return s;
+            return op_end(c, acc, 4);
         }
         Plan pl;
         if ((s = make_plan(A, A->cfg, &pl))) return s;

@@ -49,10 +49,10 @@ constexpr int kTree = 256;       // threads of the reduction tree over groups
 constexpr int kSide = 4;         // border entries a thread may fetch during a meeting
 
 // Longest wait for one message (ticks of the 100 MHz clock): far beyond any
-// solve's step or the time other work may hold a compute unit; then the
-// launch is given up and the host solves what is left with the other
-// schedules.
-constexpr long long kWaitTicks = 800000000ll;
+// solve's step; then (other work, another process's team, holds the compute
+// units of members that are due) the launch is given up and the host solves
+// what is left with the other schedules.
+constexpr long long kWaitTicks = 200000000ll;
 
 // Global pointers the compiler keeps in scalar registers: the values read
 // from a device table are the same in every lane, which it cannot see.
@@ -116,10 +116,15 @@ __device__ __forceinline__ double unpack(uint64_t lo, uint64_t hi) {
     return __longlong_as_double((long long)((lo & 0xffffffffull) | (hi << 32)));
 }
 
+// Sends v as the two words at words + i (16-byte aligned), in one 16-byte
+// store that does not stay in the L2 (store_shared twice would write every
+// other 8 bytes of a line, and then the rest).  The s_nop keeps the vector
+// unit off the data registers until the store has read them.
 __device__ __forceinline__ void post(gptr<uint64_t> words, uint32_t i, double v, uint32_t tag) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v), t = (uint64_t)tag << 32;
-    store_shared<uint64_t>(words, i, (b & 0xffffffffull) | t);
-    store_shared<uint64_t>(words, i + 1, (b >> 32) | t);
+    typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const v4 d = {(uint32_t)b, tag, (uint32_t)(b >> 32), tag};
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 2" : : "v"(at(words, i)), "v"(d) : "memory");
 }
 
 // The NW words (a multiple of two, 16-byte aligned) at words + i, by 16-byte
@@ -154,24 +159,38 @@ __device__ __forceinline__ void load_message(gptr<uint64_t> words, uint32_t i, u
     }
 }
 
-// Four pairs of words at once, one from each address.
-__device__ __forceinline__ void load_pairs(gptr<uint64_t> words, const uint32_t (&i)[4], uint64_t (&w)[4][2]) {
+// Eight (four) pairs of words at once, one from each place i of the buffer.
+// (Addresses in vector registers: a scalar base written by the vector unit
+// just before would need wait states that the compiler does not put before an
+// asm block.)
+template <int N>
+__device__ __forceinline__ void load_pairs(gptr<uint64_t> words, const uint32_t (&i)[N], uint64_t (&w)[N][2]) {
+    static_assert(N == 4 || N == 8, "pairs in flight");
     typedef uint32_t v4 __attribute__((ext_vector_type(4)));
-    v4 a, b, c, d;
-    asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
-                 "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
-                 : "v"(at(words, i[0])), "v"(at(words, i[1])), "v"(at(words, i[2])), "v"(at(words, i[3]))
-                 : "memory");
-    auto put = [&](int k, const v4 &x) {
-        w[k][0] = (uint64_t)x[1] << 32 | x[0];
-        w[k][1] = (uint64_t)x[3] << 32 | x[2];
-    };
-    put(0, a);
-    put(1, b);
-    put(2, c);
-    put(3, d);
+    v4 a[N];
+    if constexpr (N == 4)
+        asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+                     "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3])
+                     : "v"(at(words, i[0])), "v"(at(words, i[1])), "v"(at(words, i[2])), "v"(at(words, i[3]))
+                     : "memory");
+    else
+        asm volatile("global_load_dwordx4 %0, %8, off sc1\n\tglobal_load_dwordx4 %1, %9, off sc1\n\t"
+                     "global_load_dwordx4 %2, %10, off sc1\n\tglobal_load_dwordx4 %3, %11, off sc1\n\t"
+                     "global_load_dwordx4 %4, %12, off sc1\n\tglobal_load_dwordx4 %5, %13, off sc1\n\t"
+                     "global_load_dwordx4 %6, %14, off sc1\n\tglobal_load_dwordx4 %7, %15, off sc1\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(a[4]), "=&v"(a[5]), "=&v"(a[6]),
+                       "=&v"(a[7])
+                     : "v"(at(words, i[0])), "v"(at(words, i[1])), "v"(at(words, i[2])), "v"(at(words, i[3])),
+                       "v"(at(words, i[4])), "v"(at(words, i[5])), "v"(at(words, i[6])), "v"(at(words, i[7]))
+                     : "memory");
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        w[k][0] = (uint64_t)a[k][1] << 32 | a[k][0];
+        w[k][1] = (uint64_t)a[k][3] << 32 | a[k][2];
+    }
 }
 
 // Adds the NV doubles of group g's message to acc once it carries `tag`;
@@ -305,21 +324,31 @@ __device__ __forceinline__ bool team_meet(const Member &M, const double *red, gp
     return *M.ok != 0;
 }
 
-// The rows of a member: matrix entries in registers, the columns relative to
-// its first row.  The member's window is the smallest run of columns holding
-// its own rows and every column they name; its copy of the vector being
-// multiplied lies in LDS.
-constexpr int kBias = 32768;  // columns are kept as 16-bit col - row0 + kBias
-constexpr int kZero = 8;      // places before the window; the last holds 0, the column of absent entries
+// The rows of a member: matrix entries in registers, the columns as places in
+// the member's window.  A window is the LDS copy of one vector where the
+// member needs it: place 0 holds 0 (the column of absent entries), places
+// kPad on its own rows, then the border -- the columns of other members that
+// some own row names, in column order.
+constexpr int kPad = 8;
+constexpr int kBias = 32768;       // columns relative to the first own row, as 16-bit col - row0 + kBias
+constexpr int kMarkWords = 65536 / 32;  // one bit for each of those
+template <int R>
+constexpr int kOwn = TT * R;       // own places
+// Doubles of LDS of one window with nb border columns.
+constexpr int window_size(int R, int nb) { return (kPad + TT * R + nb + 7) / 8 * 8; }
+
 template <int R, int L>
 struct Rows {
     double a[R][L];
-    uint32_t j[R][(L + 1) / 2];  // two 16-bit columns a word
+    uint32_t j[R][(L + 1) / 2];  // two 16-bit places a word
 
-    __device__ __forceinline__ int rel(int q, int t) const { return (int)((j[q][t >> 1] >> (16 * (t & 1))) & 0xffffu); }
+    __device__ __forceinline__ int place(int q, int t) const { return (int)((j[q][t >> 1] >> (16 * (t & 1))) & 0xffffu); }
+    __device__ __forceinline__ void set(int q, int t, int v) {
+        j[q][t >> 1] = (j[q][t >> 1] & ~(0xffffu << (16 * (t & 1)))) | (uint32_t)v << (16 * (t & 1));
+    }
 
-    // The packed columns are unpacked where they are used: without this the
-    // compiler keeps every unpacked column in a register of its own across
+    // The packed places are unpacked where they are used: without this the
+    // compiler keeps every unpacked place in a register of its own across
     // the iterations, and spills.
     __device__ __forceinline__ void keep_packed() {
 #pragma unroll
@@ -328,13 +357,12 @@ struct Rows {
             for (int t = 0; t < (L + 1) / 2; ++t) asm volatile("" : "+v"(j[q][t]));
     }
 
-    // sum_t a_t v(j_t) in storage order, one FMA per entry (an absent one
-    // adds 0 * 0); base: the window's LDS address moved so that base[rel] is
-    // column row0 + rel - kBias
-    __device__ __forceinline__ double dot(int q, const double *base) const {
+    // sum_t a_t win[j_t] in storage order, one FMA per entry (an absent one
+    // adds 0 * 0)
+    __device__ __forceinline__ double dot(int q, const double *win) const {
         double g[L];
 #pragma unroll
-        for (int t = 0; t < L; ++t) g[t] = base[rel(q, t)];
+        for (int t = 0; t < L; ++t) g[t] = win[place(q, t)];
         double sum = 0.0;
 #pragma unroll
         for (int t = 0; t < L; ++t) sum = fma(a[q][t], g[t], sum);
@@ -342,23 +370,120 @@ struct Rows {
     }
 };
 
-// Workgroup minimum and maximum of lo and hi (LDS area of 2 TW ints).
-__device__ __forceinline__ void block_minmax(int &lo, int &hi, int *area) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+// Loads the member's rows: entries and relative columns; lens: row lengths,
+// four bits each.  row(q, i, in, len, cj, diag, found) does the rest of a
+// row's setup.  False in some thread when an entry does not fit (a row longer
+// than L, a column outside the matrix or too far away): the pattern is not
+// the one this schedule was chosen for.
+template <int R, int L, class Row>
+__device__ __forceinline__ bool load_rows(Rows<R, L> &A, gptr<const int32_t> rowptr, gptr<const int32_t> col,
+                                          gptr<const double> val, int n, int row0, uint64_t &lens, Row row) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    bool fits = true;
+    lens = 0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = min(lo, __shfl_xor(lo, o, 64));
-        hi = max(hi, __shfl_xor(hi, o, 64));
+    for (int q = 0; q < R; ++q) {
+        const int i = row0 + (q * TW + wave) * 64 + lane;
+        const bool in = i < n;
+        const int s = in ? rowptr[i] : 0, len = in ? rowptr[i + 1] - s : 0;
+        fits = fits && len <= L;
+        int32_t cj[L];
+        double diag = 0.0;
+        bool found = false;
+#pragma unroll
+        for (int t = 0; t < (L + 1) / 2; ++t) A.j[q][t] = 0;
+#pragma unroll
+        for (int t = 0; t < L; ++t) {
+            const bool has = t < len;
+            cj[t] = has ? col[s + t] : row0;
+            A.a[q][t] = has ? val[s + t] : 0.0;
+            const int rel = cj[t] - row0 + kBias;
+            fits = fits && cj[t] >= 0 && cj[t] < (has ? n : 0x7fffffff) && rel >= 0 && rel < 65536;
+            A.set(q, t, rel & 0xffff);
+            if (has && cj[t] == i) {
+                diag = A.a[q][t];
+                found = true;
+            }
+        }
+        lens |= (uint64_t)(uint32_t)min(len, 15) << (4 * q);
+        row(q, i, in, len, cj, diag, found);
+        __builtin_amdgcn_sched_barrier(0);  // one slice at a time: the loads of all would not fit the registers
     }
-    if (lane == 0) {
-        area[wave] = lo;
-        area[TW + wave] = hi;
-    }
+    return fits;
+}
+
+// Turns the relative columns into places and lists the border: list[c] is the
+// relative column of border place c.  scratch: kMarkWords uint32 of marks and
+// as many of ranks (LDS, overwritten); area: 8 ints of LDS.  Returns the
+// border's length (more than cap: nothing was listed).  Ends with a barrier.
+template <int R, int L>
+__device__ __forceinline__ int make_border(Rows<R, L> &A, uint64_t lens, int own, uint32_t *scratch, uint16_t *list,
+                                           int cap, int *area) {
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    constexpr int PER = kMarkWords / TT;
+    uint32_t *marks = scratch, *rank = scratch + kMarkWords;
+    for (int i = tid; i < kMarkWords; i += TT) marks[i] = 0u;
     __syncthreads();
+    auto mine = [&](int rel) { return rel >= kBias && rel < kBias + own; };
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+#pragma unroll
+        for (int t = 0; t < L; ++t) {
+            const int rel = A.place(q, t);
+            if (t < ((int)(lens >> (4 * q)) & 15) && !mine(rel)) atomicOr(&marks[rel >> 5], 1u << (rel & 31));
+        }
+    __syncthreads();
+    int cnt = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) cnt += __popc(marks[tid * PER + i]);
+    int scan = cnt;  // inclusive over the wavefront
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(scan, o, 64);
+        if (lane >= o) scan += up;
+    }
+    if (lane == 63) area[wave] = scan;
+    __syncthreads();
+    int first = scan - cnt, nb = 0;
 #pragma unroll
     for (int w = 0; w < TW; ++w) {
-        lo = min(lo, area[w]);
-        hi = max(hi, area[TW + w]);
+        if (w < wave) first += area[w];
+        nb += area[w];
+    }
+    for (int i = 0; i < PER; ++i) {
+        const int word = tid * PER + i;
+        rank[word] = (uint32_t)first;
+        uint32_t m = marks[word];
+        while (m) {
+            const int bit = __ffs(m) - 1;
+            if (first < cap) list[first] = (uint16_t)(word * 32 + bit);
+            ++first;
+            m &= m - 1;
+        }
+    }
+    __syncthreads();
+    if (nb <= cap) {
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+#pragma unroll
+            for (int t = 0; t < L; ++t) {
+                const int rel = A.place(q, t);
+                const int border = (int)rank[rel >> 5] + __popc(marks[rel >> 5] & ((1u << (rel & 31)) - 1u));
+                A.set(q, t, t < ((int)(lens >> (4 * q)) & 15)
+                                ? (mine(rel) ? kPad + rel - kBias : kPad + kOwn<R> + border)
+                                : 0);
+            }
+    }
+    __syncthreads();
+    return nb;
+}
+
+// Gives the launch up: the pattern is not the one the schedule was chosen
+// for.  All threads of the member call it.
+__device__ __forceinline__ void refuse(const Member &M) {
+    if (threadIdx.x == 0) {
+        store_shared<uint32_t>(M.stop, 0, 2u);
+        *M.ok = 0;
     }
     __syncthreads();
 }

@@ -7,11 +7,12 @@
 // nothing but D^-1 r of the rows at the members' borders leaves the compute
 // units between two iterations, and an iteration is bound by its two meetings
 // (1.2 to 1.8 us each).  Microseconds per iteration, before and after:
-//   2D, 30k rows   10.0   4.6        3D, 64^3 (262k rows)   15.8   8.0
-//   2D, 250k rows  15     6.4
-// and 256 2D systems of 1e3 to 6.5e4 rows in one call: 192 ms, now 28.5.  The direction of the border columns is kept
-// and updated by every member that reads it (p = z + beta p, the same
-// operation on the same values), so only z travels.
+//   2D, 30k rows   10.0   4.6        3D, 64^3 (262k rows)   15.8   7.0
+//   2D, 250k rows  15     5.4
+// and 256 2D systems of 1e3 to 6.5e4 rows in one call: 192 ms, now 28.5.  The
+// direction of the border columns is kept and updated by every member that
+// reads it (p = z + beta p, the same operation on the same values), so only z
+// travels.
 //
 // One iteration k of a member:
 //   p = z + beta p for its rows and its window's border columns (LDS);
@@ -55,7 +56,7 @@ struct TeamPlan {
     const int2 *ticket;   // (system, member), a system's members in a row
     uint32_t *next;       // next ticket to hand out
     uint32_t *stop;
-    int32_t tickets, window;  // window: capacity in columns
+    int32_t tickets, border;  // border: most border columns of any member
     double rtol;
     int32_t maxit, x0_zero, pc, norm_pre;
     double *hist;         // one system only: alpha, beta of the first hist_cap iterations
@@ -69,7 +70,8 @@ struct TeamPlan {
 constexpr bool rows_in_lds(int R) { return R == 8; }
 
 template <int R, int L>
-__device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Member &M, double *win, double *red, int *area) {
+__device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Member &M, double *win, double *red,
+                                         int *area) {
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = M.n;
     const gptr<const int32_t> rowptr = uniform(S.rowptr), col = uniform(S.col);
@@ -81,10 +83,15 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
     const bool tagged = R <= 4 && __builtin_amdgcn_readfirstlane(S.tagged) != 0;
     const gptr<uint8_t> need = uniform(S.need);
     Rows<R, L> A;
-    const int row0 = M.m * (TT * R), row1 = min(n, row0 + TT * R);
+    const int row0 = M.m * kOwn<R>, row1 = min(n, row0 + kOwn<R>);
+    // LDS: the window (of p), D^-1 and x where the registers do not hold them,
+    // the border's columns
+    const int wsize = window_size(R, P.border);
+    double *own = win + kPad + wave * 64 + lane;  // this thread's row of slice 0; rows past the last hold zeros
+    double *dl = win + wsize + wave * 64 + lane, *xl = dl + kOwn<R>;
+    uint16_t *list = (uint16_t *)(win + wsize + (rows_in_lds(R) ? 2 * kOwn<R> : 0));
     double r[R], dreg[R], xreg[R];
     // D^-1 and x of this thread's row of slice q
-    double *dl = win + P.window + wave * 64 + lane, *xl = dl + TT * R;
     auto d = [&](int q) -> double & {
         if constexpr (rows_in_lds(R)) return dl[q * TT];
         else return dreg[q];
@@ -94,44 +101,17 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
         else return xreg[q];
     };
     unsigned share = 0;  // bit q: this row of slice q is stored for the other members
-    uint64_t lens = 0;   // row lengths, four bits each
 
-    // ---- setup: entries, window, D^-1, r0, z0 and the four setup sums
-    int lo = row0, hi = max(row1 - 1, row0);
-    bool fits = true;
+    // ---- setup: entries, D^-1, r0, z0 and the four setup sums
+    uint64_t lens;
+    const bool fits = load_rows<R, L>(A, rowptr, col, val, n, row0, lens, [&](int q, int i, bool in, int len,
+                                      const int32_t (&cj)[L], double diag, bool found) {
+        double ax = 0.0;
+        if (!P.x0_zero) {
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-        const int i = row0 + (q * TW + wave) * 64 + lane;
-        const bool in = i < n;
-        const int s = in ? rowptr[i] : 0, len = in ? rowptr[i + 1] - s : 0;
-        fits = fits && len <= L;
-        int32_t cj[L];
-#pragma unroll
-        for (int t = 0; t < L; ++t) {
-            const bool has = t < len;
-            cj[t] = has ? col[s + t] : row0;
-            A.a[q][t] = has ? val[s + t] : 0.0;
-            lo = min(lo, cj[t]);
-            hi = max(hi, cj[t]);
+            for (int t = 0; t < L; ++t)
+                if (t < len) ax = fma(A.a[q][t], sx[cj[t]], ax);
         }
-#pragma unroll
-        for (int t = 0; t < L; t += 2) {
-            const uint32_t even = (uint32_t)(cj[t] - row0 + kBias) & 0xffffu;
-            const uint32_t odd = t + 1 < L ? (uint32_t)(cj[t + 1] - row0 + kBias) & 0xffffu : 0u;
-            A.j[q][t >> 1] = even | odd << 16;
-        }
-        lens |= (uint64_t)(uint32_t)min(len, 15) << (4 * q);
-        double diag = 0.0, ax = 0.0;
-        bool found = false;
-#pragma unroll
-        for (int t = 0; t < L; ++t)
-            if (t < len) {
-                if (cj[t] == i) {
-                    diag = A.a[q][t];
-                    found = true;
-                }
-                if (!P.x0_zero) ax = fma(A.a[q][t], sx[cj[t]], ax);
-            }
         r[q] = d(q) = x(q) = 0.0;
         double v4[4] = {0.0, 0.0, 0.0, 0.0};
         if (in) {
@@ -162,82 +142,31 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
             }
         }
         slices_put<R, 4, 1>(red, q, v4);
-        __builtin_amdgcn_sched_barrier(0);  // one slice at a time: the loads of all would not fit the registers
-    }
-    block_minmax(lo, hi, area);
-    lo &= ~63;
-    hi += 1;
-    fits = fits && lo >= 0 && hi <= max(n, 1) && hi - lo <= P.window;
-    // a row longer than the registers hold or a window wider than the LDS:
-    // the pattern is not the one this schedule was chosen for
-    if (!__syncthreads_and(fits)) {
-        if (tid == 0) {
-            store_shared<uint32_t>(M.stop, 0, 2u);
-            *M.ok = 0;
-        }
-        __syncthreads();
-        return;
-    }
-    for (int i = tid; i < max(hi - lo, row0 - lo + TT * R) + kZero; i += TT) win[i - kZero] = 0.0;
-    const int below = row0 - lo, border = below + max(0, hi - row1);
-    // the window place of border column h
-    auto place = [&](int h) { return h < below ? h : row1 - lo + h - below; };
-    // Which border columns some row names (a member of half a grid plane has
-    // two whole planes in its window and names half of each): bit u of want
-    // for column tid + u TT, of side for the thread's columns in fetch.  Their
-    // owners are told to keep storing z of these rows.
-    uint32_t want = 0, side = 0;
-    if (M.T > 1) {
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < R; ++q)
-#pragma unroll
-            for (int t = 0; t < L; ++t)
-                if (t < ((int)(lens >> (4 * q)) & 15)) win[A.rel(q, t) - kBias + below] = 1.0;
-        __syncthreads();
-        for (int u = 0; tid + u * TT < border; ++u) {
-            const int pl = place(tid + u * TT);
-            if (win[pl] != 0.0) {
-                want |= 1u << u;
-                store_shared<uint8_t>(need, (uint32_t)(lo + pl), 1);
-            }
-        }
-        if (tagged && wave >= M.mw)
-            for (int u = 0; u < kSide; ++u) {
-                const int h = tid - M.mw * 64 + u * (TT - M.mw * 64);
-                if (h < border && win[place(h)] != 0.0) side |= 1u << u;
-            }
-        __syncthreads();
-        for (int i = tid; i < hi - lo; i += TT) win[i] = 0.0;
-    }
-    const double *base = win + (row0 - lo) - kBias;
-    const uint32_t zero = (uint32_t)(kBias - (row0 - lo) - 1);
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-        const int len = (int)(lens >> (4 * q)) & 15;
-#pragma unroll
-        for (int t = 0; t < L; ++t)
-            if (t >= len) A.j[q][t >> 1] = (A.j[q][t >> 1] & ~(0xffffu << (16 * (t & 1)))) | zero << (16 * (t & 1));
-    }
+    });
+    if (!__syncthreads_and(fits)) return refuse(M);
+    const int nb = make_border<R, L>(A, lens, row1 - row0, (uint32_t *)win, list, P.border, area);
+    if (nb > P.border) return refuse(M);
+    for (int i = tid; i < wsize; i += TT) win[i] = 0.0;
+    // the column of border place c; the owners keep storing z of these rows
+    auto column = [&](int c) { return (uint32_t)(row0 + (int)list[c] - kBias); };
+    for (int c = tid; c < nb; c += TT) store_shared<uint8_t>(need, column(c), 1);
     // A short border's z is fetched during the meeting, by the wavefronts that
     // collect no messages, as its tags arrive: neither an acknowledged store
     // before the message nor a round trip after it.
     double zb[kSide];
     auto fetch = [&](uint32_t tag) {
         return [&, tag](int t, int nt) {
+            static_assert(kSide == 4, "load_pairs");
 #pragma unroll
             for (int u = 0; u < kSide; ++u) zb[u] = 0.0;
-            if (!tagged) return true;
-            static_assert(kSide == 4, "load_pairs");
-            uint32_t at4[kSide];  // an unnamed column's place is taken by the first named one's
+            if (!tagged || t >= nb) return true;
+            uint32_t at4[kSide];  // past the border's end: its first column again
 #pragma unroll
-            for (int u = 0; u < kSide; ++u)
-                at4[u] = (uint32_t)(lo + place(t + (side & (1u << u) ? u : max(__ffs(side) - 1, 0)) * nt)) * 2;
-            if (!side) return true;
+            for (int u = 0; u < kSide; ++u) at4[u] = column(t + u * nt < nb ? t + u * nt : t) * 2;
             long long t0 = 0;
             for (int spin = 0;; ++spin) {
                 uint64_t w[kSide][2];
-                load_pairs(z_w, at4, w);
+                load_pairs<kSide>(z_w, at4, w);
                 bool all = true;
 #pragma unroll
                 for (int u = 0; u < kSide; ++u) {
@@ -275,40 +204,32 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
             if (i < n && load_shared<uint8_t>(need, (uint32_t)i)) share |= 1u << q;
         }
     }
-    // this thread's row of slice 0; the places of rows past the last one (of
-    // the last member only, whose window ends with its rows) hold zeros
-    double *own = win + (row0 - lo) + wave * 64 + lane;
     double beta = 0.0;
     for (int k = 1; !status; ++k) {
         A.keep_packed();
         asm volatile("" : "+v"(share));
         // the border columns' direction
-        int first = tid;
-        asm volatile("" : "+v"(first));  // the places are worked out here, not kept in registers
+        double *border = win + kPad + kOwn<R>;
         if (tagged) {
             if (wave >= M.mw) {
 #pragma unroll
                 for (int u = 0; u < kSide; ++u) {
-                    const int pl = place(first - M.mw * 64 + u * (TT - M.mw * 64));
-                    if (side & (1u << u)) win[pl] = fma(beta, win[pl], zb[u]);
+                    const int c = tid - M.mw * 64 + u * (TT - M.mw * 64);
+                    if (c < nb) border[c] = fma(beta, border[c], zb[u]);
                 }
             }
         } else {
-            constexpr int UB = R <= 4 ? 8 : 4;  // loads in flight
-            for (int u0 = 0; first + u0 * TT < border; u0 += UB) {
-                const uint32_t mask = want >> u0;
-                if (!__any(mask & ((1u << UB) - 1u))) continue;
+            constexpr int UB = R <= 4 ? 9 : 4;  // loads in flight (4224 columns of a 64^2 plane's half: one round)
+            for (int c0 = tid; c0 < nb; c0 += UB * TT) {
                 double z[UB];
 #pragma unroll
                 for (int u = 0; u < UB; ++u)
-                    z[u] = mask & (1u << u) ? load_shared<double>(z_sh, (uint32_t)(lo + place(first + (u0 + u) * TT)))
-                                            : 0.0;
+                    z[u] = c0 + u * TT < nb ? load_shared<double>(z_sh, column(c0 + u * TT)) : 0.0;
 #pragma unroll
-                for (int u = 0; u < UB; ++u)
-                    if (mask & (1u << u)) {
-                        const int pl = place(first + (u0 + u) * TT);
-                        win[pl] = fma(beta, win[pl], z[u]);
-                    }
+                for (int u = 0; u < UB; ++u) {
+                    const int c = c0 + u * TT;
+                    if (c < nb) border[c] = fma(beta, border[c], z[u]);
+                }
             }
         }
         constexpr bool kKeep = R <= 4;  // p stays in registers
@@ -325,7 +246,7 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
             double v[H];
 #pragma unroll
             for (int q = 0; q < H; ++q) {
-                w[h + q] = A.dot(h + q, base);
+                w[h + q] = A.dot(h + q, win);
                 v[q] = (kKeep ? p[h + q] : own[(h + q) * TT]) * w[h + q];
             }
             slices_put<R, 1, H>(red + 4 * R * TW, h, v);
@@ -401,7 +322,7 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
 template <int R, int L>
 __global__ __launch_bounds__(TT, 2) void k_team_pcg(TeamPlan P) {
     extern __shared__ double lds[];
-    double *win = lds + kZero;
+    double *win = lds;
     // sums of the setup or the residual (4), and of delta (1)
     __shared__ double red[5 * R * TW], tot[16];
     __shared__ int area[2 * TW], ok, next;
@@ -430,28 +351,41 @@ __global__ __launch_bounds__(256) void k_team_clear(uint64_t *w, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) w[i] = 0;
 }
 
-// Largest distance of a column below and above its row, over a set of
-// matrices (block b strides over matrix blockIdx.y's rows).
-struct BandItem {
+// The most border columns of any member, for members of 2048 and 4096 rows
+// (out[2 y], out[2 y + 1] of matrix blockIdx.y; blockIdx.z: which).  A column
+// outside the 16-bit range counts as more than any border.
+struct BorderItem {
     const int32_t *rowptr, *col;
     int32_t n, pad;
 };
-__global__ __launch_bounds__(256) void k_band(const BandItem *it, int32_t *out) {
-    const BandItem B = it[blockIdx.y];
-    int below = 0, above = 0;
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < B.n; i += gridDim.x * 256)
-        for (int e = B.rowptr[i]; e < B.rowptr[i + 1]; ++e) {
-            below = max(below, i - B.col[e]);
-            above = max(above, B.col[e] - i);
+__global__ __launch_bounds__(256) void k_border(const BorderItem *it, int32_t *out) {
+    const BorderItem B = it[blockIdx.y];
+    const int rows = blockIdx.z ? kOwn<8> : kOwn<4>;
+    __shared__ uint32_t marks[kMarkWords];
+    __shared__ int far;
+    for (int row0 = blockIdx.x * rows; row0 < B.n; row0 += gridDim.x * rows) {
+        const int row1 = min(B.n, row0 + rows);
+        for (int i = threadIdx.x; i < kMarkWords; i += 256) marks[i] = 0u;
+        if (threadIdx.x == 0) far = 0;
+        __syncthreads();
+        const int e1 = B.rowptr[row1];
+        for (int e = B.rowptr[row0] + (int)threadIdx.x; e < e1; e += 256) {
+            const int c = B.col[e], rel = c - row0 + kBias;
+            if (c >= row0 && c < row1) continue;
+            if (rel < 0 || rel >= 65536) far = 1;
+            else atomicOr(&marks[rel >> 5], 1u << (rel & 31));
         }
+        __syncthreads();
+        int cnt = 0;
+        for (int i = threadIdx.x; i < kMarkWords; i += 256) cnt += __popc(marks[i]);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        below = max(below, __shfl_xor(below, o, 64));
-        above = max(above, __shfl_xor(above, o, 64));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        if (below) atomicMax(out + 2 * blockIdx.y, below);
-        if (above) atomicMax(out + 2 * blockIdx.y + 1, above);
+        for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+        __shared__ int part[4];
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = cnt;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            atomicMax(out + 2 * blockIdx.y + blockIdx.z, far ? 1 << 24 : part[0] + part[1] + part[2] + part[3]);
+        __syncthreads();
     }
 }
 
@@ -470,64 +404,13 @@ TeamFn team_fn(int R, int L) { return L <= 5 ? team_fn_r<5>(R) : team_fn_r<7>(R)
 
 // ------------------------------------------------------------------- host
 
-// Team launches in flight on a device: a member waits for the other members
-// of its team, so the workgroups of all team launches that may run at the
-// same time must fit the chip together (one per compute unit).  A launch that
-// would not fit is queued behind the ones in flight.
-struct TeamFlight {
-    EventRef ev;
-    int wgs;
-    hipStream_t stream;
-};
-static std::mutex g_flight_mu;
-static std::vector<TeamFlight> g_flight[64];
+std::mutex g_flight_mu;
+std::vector<TeamFlight> g_flight[64];
 
-// Queues launch() (wgs workgroups) on stream st; cus: what fits side by side.
-template <class F>
-static apcg_status team_launch(int device, hipStream_t st, int wgs, int cus, F launch) {
-    EventRef ev = event_get(device);
-    if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-    std::lock_guard<std::mutex> lk(g_flight_mu);  // admitted and counted in one step
-    auto &fl = g_flight[device & 63];
-    fl.erase(std::remove_if(fl.begin(), fl.end(),
-                            [](const TeamFlight &f) { return hipEventQuery(f.ev->e) == hipSuccess; }),
-             fl.end());
-    (void)hipGetLastError();  // hipErrorNotReady of the queries
-    int sum = wgs;
-    for (const auto &f : fl)
-        if (f.stream != st) sum += f.wgs;  // launches of this stream run one after the other
-    if (sum > cus)
-        for (const auto &f : fl)
-            if (f.stream != st) {
-                g_counters.stream_waits++;
-                APCG_HIP(hipStreamWaitEvent(st, f.ev->e, 0));
-            }
-    apcg_status s = launch();
-    if (s) return s;
-    APCG_HIP(hipEventRecord(ev->e, st));
-    fl.push_back({ev, wgs, st});
-    return APCG_SUCCESS;
-}
-
-// Per-context buffers of the team solves.
-struct TeamCache {
-    int device = 0;
-    int cus = 0;
-    char *d_desc = nullptr;  // TeamSys[], int2 tickets[]
-    int64_t desc_cap = 0;
-    uint64_t desc_hash = 0;
-    char *d_sync = nullptr;  // cleared before every launch: next, stop, done[], words, need marks
-    int64_t sync_cap = 0;
-    double *d_z = nullptr;
-    int64_t z_cap = 0;
-    uint32_t *pinned = nullptr;
-    int64_t pinned_cap = 0;
-    EventRef ev;
-};
 static std::mutex g_team_mu;
 static std::vector<std::pair<uint64_t, TeamCache *>> g_team;
 
-static TeamCache *team_cache(apcg_ctx c) {
+TeamCache *team_cache(apcg_ctx c) {
     std::lock_guard<std::mutex> lk(g_team_mu);
     for (auto &p : g_team)
         if (p.first == c->id) return p.second;
@@ -550,53 +433,106 @@ void team_cache_release(uint64_t ctx_id, int device) {
     }
     if (!t) return;
     hipSetDevice(device);
-    hipFree(t->d_desc);
-    hipFree(t->d_sync);
-    hipFree(t->d_z);
+    hipFree(t->mem);
+    hipFree(t->d_swap);
     if (t->pinned) hipHostFree(t->pinned);
     delete t;
 }
 
-// Grows a device buffer; the old one may still be used by queued work.
-template <typename T>
-static apcg_status grow(T **p, int64_t *cap, int64_t need, int device, hipStream_t st) {
-    if (*p && *cap >= need) return APCG_SUCCESS;
-    if (*p) {
-        EventRef ev = event_get(device);
-        if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-        APCG_HIP(hipEventRecord(ev->e, st));
-        T *old = *p;
-        defer_release({ev}, [old, device]() {
-            hipSetDevice(device);
-            hipFree(old);
-        });
-        *p = nullptr;
-        *cap = 0;
+int64_t team_lds(int R, int nb, int windows, bool own_vectors) {
+    const int64_t doubles = (int64_t)windows * window_size(R, nb) + (own_vectors ? 2 * TT * R : 0);
+    return std::max<int64_t>(8 * doubles, 8 * kMarkWords) + (2 * (int64_t)nb + 15) / 8 * 8;
+}
+
+apcg_status team_memory(TeamCache *t, hipStream_t st, int64_t desc, int64_t sync, int64_t z) {
+    auto up = [](int64_t b) { return (b + 255) / 256 * 256; };
+    const int64_t need = up(desc) + up(sync) + up(z);
+    if (need > t->mem_cap) {
+        apcg_status s = grow(&t->mem, &t->mem_cap, std::max<int64_t>(need, 1 << 20), t->device, st);
+        if (s) return s;
     }
-    APCG_HIP(hipMalloc((void **)p, sizeof(T) * need));
-    *cap = need;
+    t->d_desc = t->mem;
+    t->d_sync = t->mem + up(desc);
+    t->d_z = reinterpret_cast<uint64_t *>(t->d_sync + up(sync));
     return APCG_SUCCESS;
 }
 
-// Window capacity in columns: 8 bytes each of the 160 KiB of LDS, less the
-// kernel's own areas, and at most 32 border columns a thread beside the own
-// rows (the bits of want).
-constexpr int kWindowMax = 32 * TT + 4 * TT;
+apcg_status team_clear(hipStream_t st, uint64_t *words, int64_t n) {
+    if (n <= 0) return APCG_SUCCESS;
+    hipLaunchKernelGGL(k_team_clear, dim3((unsigned)std::min<int64_t>(1024, (n + 255) / 256)), dim3(256), 0, st, words,
+                       n);
+    APCG_CHECK_LAUNCH("k_team_clear");
+    return APCG_SUCCESS;
+}
 
-// LDS taken by x and D^-1 where a member's registers do not hold them.
-static int own_columns(int R) { return rows_in_lds(R) ? 2 * TT * R : 0; }
+apcg_status team_upload(TeamCache *t, hipStream_t st, const void *sys, int64_t sys_bytes,
+                        const std::vector<int32_t> &order, const std::vector<int32_t> &members, const char **d_sys,
+                        const int2 **d_tickets) {
+    int64_t tickets = 0;
+    for (int32_t m : members) tickets += m;
+    std::vector<int2> tk;
+    tk.reserve((size_t)tickets);
+    for (int32_t i : order)
+        for (int m = 0; m < members[i]; ++m) tk.push_back(make_int2(i, m));
+    const int64_t tk_bytes = (int64_t)sizeof(int2) * tickets;
+    t->desc.resize((size_t)(sys_bytes + tk_bytes));
+    memcpy(t->desc.data(), sys, (size_t)sys_bytes);
+    memcpy(t->desc.data() + sys_bytes, tk.data(), (size_t)tk_bytes);
+    uint64_t h = 1469598103934665603ull ^ (uint64_t)(uintptr_t)t->d_desc;
+    for (char ch : t->desc) h = (h ^ (unsigned char)ch) * 1099511628211ull;
+    if (h == 0) h = 1;
+    if (h != t->desc_hash) {
+        g_counters.h2d_copies++;
+        APCG_HIP(hipMemcpyAsync(t->d_desc, t->desc.data(), t->desc.size(), hipMemcpyHostToDevice, st));
+        t->desc_hash = h;
+    }
+    *d_sys = t->d_desc;
+    *d_tickets = reinterpret_cast<const int2 *>(t->d_desc + sys_bytes);
+    return APCG_SUCCESS;
+}
+
+apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const std::vector<int32_t> &members,
+                        const apcg_mat *A, std::vector<int32_t> *left) {
+    hipStream_t st = ctx->stream;
+    // a few counts fit the words the context's polls use (pinning memory
+    // takes longer than a small solve)
+    uint32_t *host = reinterpret_cast<uint32_t *>(ctx->pinned_flags);
+    if (nsys + 2 > kMaxLookahead) {
+        if (t->pinned_cap < nsys + 2) {
+            if (t->pinned) hipHostFree(t->pinned);
+            t->pinned = nullptr;
+            t->pinned_cap = 0;
+            APCG_HIP(hipHostMalloc((void **)&t->pinned, sizeof(uint32_t) * (nsys + 2), hipHostMallocDefault));
+            t->pinned_cap = nsys + 2;
+        }
+        host = t->pinned;
+    }
+    // observed through an event, like the other schedules' stop flags
+    g_counters.d2h_copies++;
+    APCG_HIP(hipMemcpyAsync(host, t->d_sync, sizeof(uint32_t) * (nsys + 2), hipMemcpyDeviceToHost, st));
+    if (!t->ev && !(t->ev = event_get(t->device))) return set_error(APCG_ERR_HIP, "event creation failed");
+    APCG_HIP(hipEventRecord(t->ev->e, st));
+    g_counters.host_polls++;
+    APCG_HIP(hipEventSynchronize(t->ev->e));
+    for (int32_t i = 0; i < nsys; ++i)
+        if (host[2 + i] != (uint32_t)members[i]) left->push_back(i);
+    if (host[1] == 2)  // a pattern changed in place: measured again next time
+        for (int32_t i : *left) A[i]->team_border[0] = A[i]->team_border[1] = -1;
+    if (host[1] == 1) t->rest = 256;  // a wait ran out: the chip is shared, no teams for a while
+    return APCG_SUCCESS;
+}
 
 static int team_width(int maxrow) { return maxrow <= 5 ? 5 : maxrow <= 7 ? 7 : 0; }
 
-// The band of every matrix that does not know it yet, in one launch and one
+// The border of every matrix that does not know it yet, in one launch and one
 // readback (once per matrix; a solve checks on the device that the pattern
 // still fits).
-static apcg_status team_bands(apcg_ctx c, int32_t nsys, const apcg_mat *A) {
-    std::vector<BandItem> items;
+static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A) {
+    std::vector<BorderItem> items;
     std::vector<apcg_mat> mats;
     int32_t nmax = 0;
     for (int32_t i = 0; i < nsys; ++i)
-        if (A[i]->band_below < 0) {
+        if (A[i]->team_border[0] < 0) {
             items.push_back({A[i]->rowptr, A[i]->col, A[i]->n, 0});
             mats.push_back(A[i]);
             nmax = std::max(nmax, A[i]->n);
@@ -605,20 +541,20 @@ static apcg_status team_bands(apcg_ctx c, int32_t nsys, const apcg_mat *A) {
     const size_t ni = items.size();
     TeamCache *t = team_cache(c);
     apcg_status s;
-    const int64_t bytes = (int64_t)(sizeof(BandItem) * ni + sizeof(int32_t) * 2 * ni);
+    const int64_t bytes = (int64_t)(sizeof(BorderItem) * ni + sizeof(int32_t) * 2 * ni);
     t->desc_hash = 0;  // the descriptor buffer is used as scratch
-    if ((s = grow(&t->d_desc, &t->desc_cap, std::max<int64_t>(bytes, 4096), c->device, c->stream))) return s;
-    int32_t *out = reinterpret_cast<int32_t *>(t->d_desc + sizeof(BandItem) * ni);
+    if ((s = team_memory(t, c->stream, bytes, 0, 0))) return s;
+    int32_t *out = reinterpret_cast<int32_t *>(t->d_desc + sizeof(BorderItem) * ni);
     std::vector<int32_t> h(2 * ni, 0);
     g_counters.h2d_copies += 2;
-    APCG_HIP(hipMemcpyAsync(t->d_desc, items.data(), sizeof(BandItem) * ni, hipMemcpyHostToDevice, c->stream));
+    APCG_HIP(hipMemcpyAsync(t->d_desc, items.data(), sizeof(BorderItem) * ni, hipMemcpyHostToDevice, c->stream));
     APCG_HIP(hipMemcpyAsync(out, h.data(), sizeof(int32_t) * 2 * ni, hipMemcpyHostToDevice, c->stream));
-    const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>((nmax + 255) / 256, 256));
+    const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(((int64_t)nmax + 2047) / 2048, 512));
     for (size_t i0 = 0; i0 < ni; i0 += 32768) {  // grid.y is limited
         const unsigned gy = (unsigned)std::min<size_t>(32768, ni - i0);
-        hipLaunchKernelGGL(k_band, dim3(gx, gy), dim3(256), 0, c->stream,
-                           reinterpret_cast<const BandItem *>(t->d_desc) + i0, out + 2 * i0);
-        APCG_CHECK_LAUNCH("k_band");
+        hipLaunchKernelGGL(k_border, dim3(gx, gy, 2), dim3(256), 0, c->stream,
+                           reinterpret_cast<const BorderItem *>(t->d_desc) + i0, out + 2 * i0);
+        APCG_CHECK_LAUNCH("k_border");
     }
     g_counters.d2h_copies++;
     APCG_HIP(hipMemcpyAsync(h.data(), out, sizeof(int32_t) * 2 * ni, hipMemcpyDeviceToHost, c->stream));
@@ -627,8 +563,8 @@ static apcg_status team_bands(apcg_ctx c, int32_t nsys, const apcg_mat *A) {
     g_counters.host_polls++;
     APCG_HIP(hipEventSynchronize(t->ev->e));
     for (size_t i = 0; i < ni; ++i) {
-        mats[i]->band_below = h[2 * i];
-        mats[i]->band_above = h[2 * i + 1];
+        mats[i]->team_border[0] = h[2 * i];
+        mats[i]->team_border[1] = h[2 * i + 1];
     }
     return APCG_SUCCESS;
 }
@@ -637,16 +573,16 @@ static apcg_status team_bands(apcg_ctx c, int32_t nsys, const apcg_mat *A) {
 // run side by side, else eight (of five-entry rows): a member of 4096 rows
 // takes an iteration about 1.25 times as long as one of 2048, so a batch that
 // queues for the compute units finishes sooner.  0: some system does not fit.
-static int team_rows(int32_t nsys, const apcg_mat *A, int cus, int width) {
+static int team_rows(int32_t nsys, const apcg_mat *A, int cus, int width, int windows) {
     int best = 0;
     for (int R : {4, 8}) {
-        if (R == 8 && width > 5) break;
+        if (R == 8 && (width > 5 || windows > 1)) break;
         int64_t total = 0;
         bool ok = true;
         for (int32_t i = 0; i < nsys && ok; ++i) {
             const int64_t T = std::max<int64_t>(1, ((int64_t)A[i]->n + TT * R - 1) / (TT * R));
-            const int64_t window = (T == 1 ? 0 : (int64_t)A[i]->band_below + A[i]->band_above) + TT * R + 64;
-            ok = T <= cus && window <= kWindowMax - own_columns(R);
+            const int nb = A[i]->team_border[R == 8];
+            ok = T <= cus && nb < 1 << 20 && team_lds(R, nb, windows, rows_in_lds(R)) <= kLdsBytes;
             total += T;
         }
         if (!ok) continue;
@@ -656,7 +592,7 @@ static int team_rows(int32_t nsys, const apcg_mat *A, int cus, int width) {
     return best;
 }
 
-apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int *rows) {
+apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windows, int *rows) {
     *rows = 0;
     if (c->type == APCG_STREAM_GLOBAL_BLOCKING) return APCG_SUCCESS;
     int maxrow = 1;
@@ -665,10 +601,14 @@ apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int *rows
         if (!team_width(maxrow) || A[i]->n > 256 * TT * kMaxRows) return APCG_SUCCESS;
     }
     TeamCache *t = team_cache(c);
+    if (t->rest > 0) {
+        --t->rest;
+        return APCG_SUCCESS;
+    }
     if (!t->cus) APCG_HIP(hipDeviceGetAttribute(&t->cus, hipDeviceAttributeMultiprocessorCount, c->device));
     apcg_status s;
-    if ((s = team_bands(c, nsys, A))) return s;
-    *rows = team_rows(nsys, A, t->cus, team_width(maxrow));
+    if ((s = team_borders(c, nsys, A))) return s;
+    *rows = team_rows(nsys, A, t->cus, team_width(maxrow), windows);
     return APCG_SUCCESS;
 }
 
@@ -680,7 +620,7 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
     TeamCache *t = team_cache(c);
     hipStream_t st = c->stream;
     const int R = rows;
-    int maxrow = 1, window = 0;
+    int maxrow = 1, border = 0;
     int64_t zn = 0, marks = 0, words = 0, tickets = 0;
     std::vector<TeamSys> sys(nsys);
     for (int32_t i = 0; i < nsys; ++i) {
@@ -694,11 +634,11 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         s.T = (int32_t)std::max<int64_t>(1, ((int64_t)s.n + TT * R - 1) / (TT * R));
         s.info = info + i;
         maxrow = std::max(maxrow, A[i]->sell_maxw);
-        const int64_t border = s.T == 1 ? 0 : (int64_t)A[i]->band_below + A[i]->band_above + 64;
-        window = std::max<int>(window, (int)std::min<int64_t>(kWindowMax - own_columns(R), TT * R + border));
+        const int nb = s.T == 1 ? 0 : A[i]->team_border[R == 8];
+        border = std::max(border, nb);
         const int64_t ngr = ((int64_t)s.n + kGroupRows - 1) / kGroupRows;
         // what the wavefronts beside at most four that collect messages fetch at once
-        s.tagged = R <= 4 && border <= kSide * (TT - kTree) ? 1 : 0;
+        s.tagged = R <= 4 && nb <= kSide * (TT - kTree) ? 1 : 0;
         s.z = reinterpret_cast<uint64_t *>(zn);
         s.need = reinterpret_cast<uint8_t *>(marks);
         s.words = reinterpret_cast<uint64_t *>(words);
@@ -709,53 +649,32 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         }
         tickets += s.T;
     }
-    std::vector<int2> tk;
-    tk.reserve(tickets);
-    for (int32_t i : order)
-        for (int m = 0; m < sys[i].T; ++m) tk.push_back(make_int2(i, m));
     // cleared area: next, stop, done counts, messages, marks
     const int64_t head = (8 + (int64_t)nsys * 4 + 63) / 64 * 64;
     const int64_t sync_bytes = head + 8 * words + marks;
     apcg_status s;
-    if ((s = grow(&t->d_sync, &t->sync_cap, sync_bytes, t->device, st))) return s;
-    if ((s = grow(&t->d_z, &t->z_cap, std::max<int64_t>(zn, 64), t->device, st))) return s;
+    if ((s = team_memory(t, st, team_desc_bytes((int64_t)sizeof(TeamSys) * nsys, tickets), sync_bytes, 8 * zn))) return s;
     uint32_t *head_p = reinterpret_cast<uint32_t *>(t->d_sync);
     for (int32_t i = 0; i < nsys; ++i) {
         TeamSys &q = sys[i];
-        q.z = reinterpret_cast<uint64_t *>(t->d_z) + reinterpret_cast<int64_t>(q.z);
+        q.z = t->d_z + reinterpret_cast<int64_t>(q.z);
         q.words = reinterpret_cast<uint64_t *>(t->d_sync + head) + reinterpret_cast<int64_t>(q.words);
         q.need = reinterpret_cast<uint8_t *>(t->d_sync + head + 8 * words) + reinterpret_cast<int64_t>(q.need);
         q.done = head_p + 2 + i;
     }
-    const int64_t sys_bytes = (int64_t)sizeof(TeamSys) * nsys, tk_bytes = (int64_t)sizeof(int2) * tickets;
-    if ((s = grow(&t->d_desc, &t->desc_cap, std::max<int64_t>(sys_bytes + tk_bytes, 4096), t->device, st))) return s;
-    std::vector<char> desc((size_t)(sys_bytes + tk_bytes));
-    memcpy(desc.data(), sys.data(), sys_bytes);
-    memcpy(desc.data() + sys_bytes, tk.data(), tk_bytes);
-    uint64_t h = 1469598103934665603ull ^ (uint64_t)(uintptr_t)t->d_desc;
-    for (char ch : desc) h = (h ^ (unsigned char)ch) * 1099511628211ull;
-    if (h == 0) h = 1;
-
-    if (h != t->desc_hash) {
-        g_counters.h2d_copies++;
-        APCG_HIP(hipMemcpyAsync(t->d_desc, desc.data(), desc.size(), hipMemcpyHostToDevice, st));
-        t->desc_hash = h;
-
-    }
-    if (t->pinned_cap < nsys + 2) {
-        if (t->pinned) hipHostFree(t->pinned);
-        t->pinned = nullptr;
-        t->pinned_cap = 0;
-        APCG_HIP(hipHostMalloc((void **)&t->pinned, sizeof(uint32_t) * (nsys + 2), hipHostMallocDefault));
-        t->pinned_cap = nsys + 2;
-    }
+    std::vector<int32_t> members(nsys);
+    for (int32_t i = 0; i < nsys; ++i) members[i] = sys[i].T;
+    const char *d_sys;
+    const int2 *d_tickets;
+    if ((s = team_upload(t, st, sys.data(), (int64_t)sizeof(TeamSys) * nsys, order, members, &d_sys, &d_tickets)))
+        return s;
     TeamPlan P{};
-    P.sys = reinterpret_cast<const TeamSys *>(t->d_desc);
-    P.ticket = reinterpret_cast<const int2 *>(t->d_desc + sys_bytes);
+    P.sys = reinterpret_cast<const TeamSys *>(d_sys);
+    P.ticket = d_tickets;
     P.next = head_p;
     P.stop = head_p + 1;
     P.tickets = (int32_t)tickets;
-    P.window = window;
+    P.border = border;
     P.rtol = rtol;
     P.maxit = maxit;
     P.x0_zero = opts.x0_is_zero ? 1 : 0;
@@ -764,35 +683,18 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
     P.hist = hist;
     P.hist_cap = hist ? hist_cap : 0;
     const TeamFn fn = team_fn(R, team_width(maxrow));
-    const size_t lds = sizeof(double) * (size_t)(window + kZero + own_columns(R));
-    if (lds > 65536 - 4096)
-        APCG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)(sizeof(double) * (kWindowMax + kZero))));
+    const size_t lds = (size_t)team_lds(R, border, 1, rows_in_lds(R));
+    APCG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)kLdsBytes));
     const int grid = (int)std::min<int64_t>(tickets, t->cus);
-    const int64_t cw = (sync_bytes + 7) / 8;
-    hipLaunchKernelGGL(k_team_clear, dim3((unsigned)std::min<int64_t>(1024, (cw + 255) / 256)), dim3(256), 0, st,
-                       reinterpret_cast<uint64_t *>(t->d_sync), cw);
-    APCG_CHECK_LAUNCH("k_team_clear");
+    if ((s = team_clear(st, reinterpret_cast<uint64_t *>(t->d_sync), (sync_bytes + 7) / 8))) return s;
     s = team_launch(t->device, st, grid, t->cus, [&]() -> apcg_status {
         hipLaunchKernelGGL(fn, dim3(grid), dim3(TT), lds, st, P);
         APCG_CHECK_LAUNCH("k_team_pcg");
         return APCG_SUCCESS;
     });
     if (s) return s;
-    // the members that finished, observed through an event like the other
-    // schedules' stop flags
-    g_counters.d2h_copies++;
-    APCG_HIP(hipMemcpyAsync(t->pinned, head_p, sizeof(uint32_t) * (nsys + 2), hipMemcpyDeviceToHost, st));
-    if (!t->ev && !(t->ev = event_get(t->device))) return set_error(APCG_ERR_HIP, "event creation failed");
-    APCG_HIP(hipEventRecord(t->ev->e, st));
-    g_counters.host_polls++;
-    APCG_HIP(hipEventSynchronize(t->ev->e));
-
-    for (int32_t i = 0; i < nsys; ++i)
-        if (t->pinned[2 + i] != (uint32_t)sys[i].T) left->push_back(i);
-    if (t->pinned[1] == 2)  // a pattern changed in place: measured again next time
-        for (int32_t i : *left) A[i]->band_below = A[i]->band_above = -1;
-    return APCG_SUCCESS;
+    return team_finish(c, t, nsys, members, A, left);
 }
 
 }  // namespace apcg

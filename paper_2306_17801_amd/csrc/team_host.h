@@ -1,6 +1,8 @@
-// team_host.h -- host interface of the team solves (team.hip).
+// team_host.h -- host side of the team solves (team.hip, team_fcg.hip).
 #pragma once
 
+#include <algorithm>
+#include <mutex>
 #include <vector>
 
 #include "internal.h"
@@ -10,11 +12,116 @@ namespace apcg {
 // Single solves take the team schedule above this many rows.
 constexpr int32_t kTeamMinRows = 8192;
 
+// Team launches in flight on a device: a member waits for the other members
+// of its team, so the workgroups of all team launches that may run at the
+// same time must fit the chip together (one per compute unit).  A launch that
+// would not fit is queued behind the ones in flight.
+struct TeamFlight {
+    EventRef ev;
+    int wgs;
+    hipStream_t stream;
+};
+extern std::mutex g_flight_mu;
+extern std::vector<TeamFlight> g_flight[64];
+
+// Queues launch() (wgs workgroups) on stream st; cus: what fits side by side.
+template <class F>
+apcg_status team_launch(int device, hipStream_t st, int wgs, int cus, F launch) {
+    EventRef ev = event_get(device);
+    if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
+    std::lock_guard<std::mutex> lk(g_flight_mu);  // admitted and counted in one step
+    auto &fl = g_flight[device & 63];
+    fl.erase(std::remove_if(fl.begin(), fl.end(),
+                            [](const TeamFlight &f) { return hipEventQuery(f.ev->e) == hipSuccess; }),
+             fl.end());
+    (void)hipGetLastError();  // hipErrorNotReady of the queries
+    int sum = wgs;
+    for (const auto &f : fl)
+        if (f.stream != st) sum += f.wgs;  // launches of this stream run one after the other
+    if (sum > cus)
+        for (const auto &f : fl)
+            if (f.stream != st) {
+                g_counters.stream_waits++;
+                APCG_HIP(hipStreamWaitEvent(st, f.ev->e, 0));
+            }
+    apcg_status s = launch();
+    if (s) return s;
+    APCG_HIP(hipEventRecord(ev->e, st));
+    fl.push_back({ev, wgs, st});
+    return APCG_SUCCESS;
+}
+
+// Per-context buffers of the team solves.
+struct TeamCache {
+    int device = 0;
+    int cus = 0;
+    int rest = 0;            // solves to leave to the other schedules after a wait that ran out
+    std::vector<char> desc;  // host copy of d_desc, alive while it is uploaded
+    char *mem = nullptr;     // one buffer for the three below (an allocation costs as much as a small solve)
+    int64_t mem_cap = 0;
+    char *d_desc = nullptr;  // the systems, int2 tickets[]
+    uint64_t desc_hash = 0;
+    char *d_sync = nullptr;  // cleared before every launch: next, stop, done[], words, marks
+    uint64_t *d_z = nullptr; // border values
+    uint64_t *d_swap = nullptr;  // border exchanges of the flexible solve; tags below tag are used up
+    int64_t swap_cap = 0, tag = 1;
+    uint32_t *pinned = nullptr;
+    int64_t pinned_cap = 0;
+    EventRef ev;
+};
+TeamCache *team_cache(apcg_ctx c);
+
+// Grows a device buffer; the old one may still be used by queued work.
+template <typename T>
+apcg_status grow(T **p, int64_t *cap, int64_t need, int device, hipStream_t st) {
+    if (*p && *cap >= need) return APCG_SUCCESS;
+    if (*p) {
+        EventRef ev = event_get(device);
+        if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
+        APCG_HIP(hipEventRecord(ev->e, st));
+        T *old = *p;
+        defer_release({ev}, [old, device]() {
+            hipSetDevice(device);
+            hipFree(old);
+        });
+        *p = nullptr;
+        *cap = 0;
+    }
+    APCG_HIP(hipMalloc((void **)p, sizeof(T) * need));
+    *cap = need;
+    return APCG_SUCCESS;
+}
+
+// LDS a member may take (160 KiB less the kernels' fixed areas), and what
+// `windows` windows take with nb border columns.
+constexpr int64_t kLdsBytes = 163840 - 4096;
+int64_t team_lds(int R, int nb, int windows, bool own_vectors);
+
+// Makes room for so many bytes of descriptors, cleared memory and border
+// values of the next launch.
+apcg_status team_memory(TeamCache *t, hipStream_t st, int64_t desc, int64_t sync, int64_t z);
+inline int64_t team_desc_bytes(int64_t sys_bytes, int64_t tickets) { return sys_bytes + tickets * (int64_t)sizeof(int2); }
+
+// Clears n words on stream st (a kernel: a launch may be captured).
+apcg_status team_clear(hipStream_t st, uint64_t *words, int64_t n);
+
+// Uploads the systems' descriptors and the tickets (members[i] of system i,
+// systems in `order`) unless the device holds them already.
+apcg_status team_upload(TeamCache *t, hipStream_t st, const void *sys, int64_t sys_bytes,
+                        const std::vector<int32_t> &order, const std::vector<int32_t> &members, const char **d_sys,
+                        const int2 **d_tickets);
+
+// Waits for the launch and lists the systems it did not finish; d_sync begins
+// with the next ticket, the stop word and the counts of finished members.
+apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const std::vector<int32_t> &members,
+                        const apcg_mat *A, std::vector<int32_t> *left);
+
 // Whether every system can be solved by teams on ctx's device: rows of at
-// most 7 entries, windows that fit the LDS, no system larger than the chip.
-// *rows receives the 64-row slices per wavefront to use, 0 when it cannot.
-// Reads the matrices' column ranges back once per matrix.
-apcg_status team_eligible(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, int *rows);
+// most 7 entries, `windows` windows that fit the LDS (1: PCG, 2: the flexible
+// solve), no system larger than the chip.  *rows receives the 64-row slices
+// per wavefront to use, 0 when it cannot.  Reads the matrices' borders back
+// once per matrix.
+apcg_status team_eligible(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, int windows, int *rows);
 
 // Jacobi-PCG (or CG) of the systems, started in `order` (largest cost
 // first), results in info[i]; hist as in pcg_solve_marked (one system).
@@ -24,5 +131,14 @@ apcg_status team_pcg_solve(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const 
                            const std::vector<int32_t> &order, double rtol, int32_t maxit, const apcg_solve_opts &opts,
                            int rows, apcg_solve_info *info, double *hist, int32_t hist_cap,
                            std::vector<int32_t> *left);
+
+// FCG(1) of the systems with their polynomials coeffs[i][9], lmax[i] (device),
+// as apcg_ksp_solve_batched_fcg_poly; otherwise as team_pcg_solve.
+apcg_status team_fcg_solve(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
+                           const std::vector<int32_t> &order, double rtol, int32_t maxit, const apcg_solve_opts &opts,
+                           const apcg_fcg_opts &fo, const float *coeffs, const double *lmax, apcg_solve_info *info,
+                           std::vector<int32_t> *left);
+// The tags one flexible launch may use are limited (see team_fcg.hip).
+constexpr int32_t kTeamFcgMaxIts = 100000000;
 
 }  // namespace apcg

@@ -155,7 +155,7 @@ def test_team_pattern_changed_in_place(apcg, ctx):
     import torch
     from paper_2306_17801_amd.device import DeviceCSR, DeviceVec
 
-    n = 40000
+    n = 80000
     i = np.arange(n)
     near, far = i ^ 1, (i + n // 2) % n
     cols = {k: np.sort(np.stack([i, j], 1), axis=1) for k, j in (("near", near), ("far", far))}
