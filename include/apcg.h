@@ -563,8 +563,8 @@ apcg_status apcg_info_get(apcg_info info, int32_t index, apcg_solve_info *out);
  * having observed the device flag only through events `lookahead` periods
  * behind the queue.  With APCG_MODE_GRAPH (and AUTO), a system of more than
  * 8192 rows that fits the chip -- rows of at most 5 entries up to 1,048,576
- * rows, of at most 7 up to 524,288, columns within about 8,000 of the
- * diagonal -- is solved by one launch of a team of workgroups instead, each
+ * rows, of at most 7 up to 524,288, every 2048 (4096) rows naming a few
+ * thousand other rows at most, within 32,768 -- is solved by one launch of a team of workgroups instead, each
  * holding its rows' entries and vectors in registers; its sums run in another
  * fixed order than the kernels' of STREAM and HOST_CHECK (same tests, same
  * counts up to rounding).  With APCG_MODE_PERSISTENT (or AUTO at n <=
@@ -730,7 +730,8 @@ apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec 
  *     that cover every such system of the batch.
  *   APCG_BATCH_AUTO: teams when every system's rows hold at most 7 entries and
  *     it fits the chip (see apcg_ksp_solve): one launch, each system held in
- *     the registers of as many workgroups as it needs; the segmented
+ *     the registers of as many workgroups as it needs (the flexible solves
+ *     below likewise, unless their tiles' sizes are set); the segmented
  *     schedule's sums, bit for bit, whatever copies of the matrices exist.
  *     Otherwise persistent when no system costs more than 1/CUs of the batch,
  *     else segmented.

@@ -31,6 +31,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "team_host.h"
 
 namespace apcg {
 namespace {
@@ -154,35 +155,18 @@ __device__ __forceinline__ double frow(const dev::glob_t<int32_t> *col, const de
 constexpr int FSB = 256;
 
 // The slice partials of system s (global slices sys_slice0[s] ..
-// sys_slice0[s+1] of rows slot0.. of P.part), added in a fixed order (thread
-// l takes slices l, l + FSB, ..., then the workgroup tree; one FSB-thread
-// workgroup); the same sums whatever the tile size.  Result in thread 0.
+// sys_slice0[s+1] of rows slot0.. of P.part), added in a fixed order: the 32
+// slices of a group by a half wavefront's butterfly, thread l of the
+// workgroup tree the groups l, l + FSB, ... (one FSB-thread workgroup); the
+// same sums whatever the tile size, and those of a team solve (team.h).
+// Result in thread 0.
 template <int NV>
 __device__ __forceinline__ void fsys_sum(const FPlan &P, int s, int slot0, double (&v)[NV]) {
     __shared__ double lds[NV * (FSB / 64)];
-#pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = 0.0;
-    const int ge = P.sys_slice0[s + 1];
-    const double *part = P.part + (size_t)slot0 * P.nslices;
-    int g = P.sys_slice0[s] + (int)threadIdx.x;
-    // eight of a thread's partials loaded before they are added (a large
-    // system has thousands of slices); the same order of addition
-    constexpr int UA = 8;
-    for (; g + (UA - 1) * FSB < ge; g += UA * FSB) {
-        double t[UA][NV];
-#pragma unroll
-        for (int u = 0; u < UA; ++u)
-#pragma unroll
-            for (int k = 0; k < NV; ++k) t[u][k] = part[(size_t)k * P.nslices + g + u * FSB];
-#pragma unroll
-        for (int u = 0; u < UA; ++u)
-#pragma unroll
-            for (int k = 0; k < NV; ++k) v[k] += t[u][k];
-    }
-    for (; g < ge; g += FSB) {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) v[k] += part[(size_t)k * P.nslices + g];
-    }
+    const int g0 = P.sys_slice0[s];
+    const double *part = P.part + (size_t)slot0 * P.nslices + g0;
+    dev::group_tree<FSB, NV>(P.sys_slice0[s + 1] - g0,
+                             [&](int k, int l) { return part[(size_t)k * P.nslices + l]; }, v);
     dev::block_sum<FSB, NV>(v, lds);
 }
 
@@ -210,17 +194,6 @@ __device__ __forceinline__ void ftile_store(const FPlan &P, int s, int sl, int s
 #pragma unroll
         for (int k = 0; k < NV; ++k) P.part[(size_t)(slot0 + k) * P.nslices + g] = v[k];
     }
-}
-
-__device__ double fpoly_at(const double *c, double t, double lmax) {  // Clenshaw at one point
-    const double y = 2.0 * t / lmax - 1.0;
-    double b1 = 0.0, b2 = 0.0;
-    for (int j = FDEG; j >= 1; --j) {
-        const double b0 = c[j] + 2.0 * y * b1 - b2;
-        b2 = b1;
-        b1 = b0;
-    }
-    return c[0] + y * b1 - b2;
 }
 
 // Stops system s (thread 0 of its workgroup) with status, adding the fallback
@@ -298,7 +271,7 @@ __global__ __launch_bounds__(FSB) void k_bf_init_final(FPlan P, const float *coe
     const double lm = jac ? 1.0 : lmax[s];
     if (!jac)
         for (int q = threadIdx.x; q < 1024; q += FSB)
-            if (!(fpoly_at(cc, lm * q / 1023.0, lm) > 0.0)) atomicOr(&bad_point, 1);
+            if (!(dev::poly_at<FDEG>(cc, lm * q / 1023.0, lm) > 0.0)) atomicOr(&bad_point, 1);
     __syncthreads();
     if (threadIdx.x != 0) return;
     FState q;
@@ -1282,6 +1255,36 @@ static apcg_status bf_features(apcg_ctx ctx, BfCache *bc, int32_t nsys, const ap
 
 using namespace apcg;
 
+// Systems that fit the chip are solved by teams of workgroups (see
+// apcg_ksp_solve_batched; the same bits as the tiles): 48 mixed systems of 1e3
+// to 1e5 rows 52.2 ms on tiles, 9.6 on teams.  A caller who sets the
+// tiles gets them.  Ends the marked operation when it solves the batch (*done).
+static apcg_status bf_teams(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
+                            double rtol, int32_t maxit, const apcg_solve_opts &opts, const apcg_fcg_opts &fo,
+                            const float *coeffs, const double *lmax, apcg_info info, const std::vector<Acc> &acc,
+                            bool *done) {
+    *done = false;
+    if (opts.batch_schedule != APCG_BATCH_AUTO || opts.batch_tile_rows || opts.batch_tail_tile_rows ||
+        maxit > kTeamFcgMaxIts)
+        return APCG_SUCCESS;
+    int rows = 0;
+    apcg_status s;
+    if ((s = team_eligible(ctx, nsys, A, 2, &rows)) || rows == 0) return s;
+    std::vector<int32_t> order(nsys), left;
+    for (int32_t i = 0; i < nsys; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int32_t p, int32_t q) { return A[p]->n > A[q]->n; });
+    if ((s = team_fcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, fo, coeffs, lmax, info->d, &left))) return s;
+    *done = true;
+    if ((s = op_end(ctx, acc.data(), (int)acc.size()))) return s;
+    apcg_solve_opts single = opts;
+    single.mode = APCG_MODE_STREAM;
+    for (int32_t i : left)  // a launch that was given up (see team.h)
+        if ((s = apcg_ksp_solve_fcg_poly(ctx, A[i], b[i], x[i], rtol, maxit, coeffs + 9 * (int64_t)i, lmax + i, &single,
+                                         &fo, info, i)))
+            return s;
+    return APCG_SUCCESS;
+}
+
 extern "C" apcg_status apcg_ksp_solve_batched_fcg_poly(apcg_ctx ctx, int32_t nsys, const apcg_mat *A,
                                                        const apcg_vec *b, const apcg_vec *x, double rtol,
                                                        int32_t maxit, const float *dev_coeffs,
@@ -1319,6 +1322,9 @@ extern "C" apcg_status apcg_ksp_solve_batched_fcg_poly(apcg_ctx ctx, int32_t nsy
         }
         acc.push_back({&info->rec, ACC_W});
         if ((s = op_begin(ctx, acc.data(), (int)acc.size()))) return s;
+        bool done = false;
+        if ((s = bf_teams(ctx, nsys, A, b, x, rtol, maxit, opts, fo, dev_coeffs, dev_lmax, info, acc, &done)) || done)
+            return s;
         BfRun run;
         run.coeffs = dev_coeffs;
         run.lmax = dev_lmax;
@@ -1391,6 +1397,9 @@ extern "C" apcg_status apcg_ksp_solve_batched_learned(apcg_ctx ctx, int32_t nsys
         BfCache *bc = bf_cache(ctx);
         if ((s = bf_features(ctx, bc, nsys, A, b, nullptr, nullptr))) return s;
         if ((s = mlp_infer(ctx, dev_params, dev_mean, dev_std, bc->d_X, nsys, bc->d_C))) return s;
+        bool done = false;
+        if ((s = bf_teams(ctx, nsys, A, b, x, rtol, maxit, opts, fo, bc->d_C, bc->d_L, info, acc, &done)) || done)
+            return s;
         BfRun run;
         run.coeffs = bc->d_C;
         run.lmax = bc->d_L;

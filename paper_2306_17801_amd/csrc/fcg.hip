@@ -29,6 +29,7 @@
 #include <cstring>
 
 #include "internal.h"
+#include "team_host.h"
 
 namespace apcg {
 namespace {
@@ -479,6 +480,19 @@ extern "C" apcg_status apcg_ksp_solve_fcg_poly(apcg_ctx ctx, apcg_mat A, apcg_ve
         Acc acc[4] = {{&x->rec, ACC_RW}, {&info->rec, ACC_W}, {&A->rec, ACC_R}, {&b->rec, ACC_R}};
         apcg_status s;
         if ((s = op_begin(ctx, acc, 4))) return s;
+        // a system that fits the chip, by a team of workgroups in one launch
+        if (opts.mode == APCG_MODE_GRAPH && A->n > kTeamMinRows && maxit <= kTeamFcgMaxIts) {
+            int rows = 0;
+            if ((s = team_eligible(ctx, 1, &A, 2, &rows))) return s;
+            if (rows > 0) {
+                std::vector<int32_t> left;
+                if ((s = team_fcg_solve(ctx, 1, &A, &b, &x, {0}, rtol, maxit, opts, fo, dev_coeffs, dev_lmax,
+                                        info->d + info_index, &left)))
+                    return s;
+                if (left.empty()) return op_end(ctx, acc, 4);
+                // given up (see team.h): x is as it was, the kernels below solve it
+            }
+        }
         const int64_t n = A->n;
         if (fc->cap < n || !fc->ws) {
             if (fc->ws) {
