@@ -95,8 +95,22 @@ __device__ __forceinline__ void terminate(SolveState *st, int its, int status, d
 }
 
 // ----------------------------------------------------------------- setup
+constexpr int kStage = 512;  // entries a wavefront stages in LDS at a time
+// What a wavefront's lanes have written to its LDS is read by its other lanes
+// from here on (LDS operations of a wavefront complete in order).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // dinv = 1/diag(A) (or 1), r0 = b - A x0 (or b), z0 = dinv r0, p_old = 0; partials of
 // z0.r0, residual norm^2, reference norm^2 and the count of bad diagonals.
+// One row per lane; bound by the read of the matrix, which a lane walking its
+// own row asks for in single words, a row apart from its neighbour's.  So a
+// wavefront brings its 64 rows' entries through LDS, kStage at a time, in
+// whole lines; with x0 = 0 only the columns, and one value where the diagonal
+// is found.  27-entry rows, 96^3: INITMEASURED.
 __global__ __launch_bounds__(VB) void k_pcg_init(int32_t n, const int32_t *__restrict__ rowptr,
                                                  const int32_t *__restrict__ col, const double *__restrict__ val,
                                                  const double *__restrict__ b, double *__restrict__ x,
@@ -107,19 +121,38 @@ __global__ __launch_bounds__(VB) void k_pcg_init(int32_t n, const int32_t *__res
     if (gate && !gate[0]) return;  // gated off: the solve is a no-op
     const dev::Chunk c = dev::block_chunk(n, per_block);
     double rz = 0.0, nres = 0.0, nref = 0.0, bad = 0.0;
-    for (int64_t i = c.lo + threadIdx.x; i < c.hi; i += VB) {
-        const int s = rowptr[i], e = rowptr[i + 1];
+    __shared__ double sv[VB / 64][kStage];
+    __shared__ int32_t sc[VB / 64][kStage];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int64_t base = c.lo + wave * 64; base < c.hi; base += VB) {
+        const int64_t i = base + lane;
+        const bool in = i < c.hi;
+        const int s = rowptr[in ? i : c.hi], e = rowptr[in ? i + 1 : c.hi];
+        const int s0 = rowptr[base], e0 = rowptr[min(base + 64, c.hi)];
         double diag = 0.0, ax = 0.0;
         bool found = false;
-        for (int k = s; k < e; ++k) {
-            const int j = col[k];
-            const double a = val[k];
-            if (j == (int)i) {
-                diag = a;
-                found = true;
+        for (int p0 = s0; p0 < e0; p0 += kStage) {
+            const int p1 = min(e0, p0 + kStage);
+            wave_lds_fence();  // the previous piece has been read
+#pragma unroll
+            for (int q = 0; q < kStage / 64; ++q) {
+                const int k = q * 64 + lane;
+                if (p0 + k < p1) {
+                    sc[wave][k] = col[p0 + k];
+                    if (!x0_zero) sv[wave][k] = val[p0 + k];
+                }
             }
-            if (!x0_zero) ax = fma(a, x[j], ax);
+            wave_lds_fence();
+            for (int k = max(s, p0); k < min(e, p1); ++k) {
+                const int j = sc[wave][k - p0];
+                if (j == (int)i) {
+                    diag = val[k];
+                    found = true;
+                }
+                if (!x0_zero) ax = fma(sv[wave][k - p0], x[j], ax);
+            }
         }
+        if (!in) continue;
         double di = 1.0;
         if (pc == APCG_PC_JACOBI) {
             const bool ok = found && diag > 0.0;
@@ -277,6 +310,152 @@ __global__ __launch_bounds__(TB) void k_pcg_product(int32_t n, const int32_t *__
     dev::store_partials<TB, 1>(v, part_delta, gridDim.x, lb);
 }
 
+
+// The same sums from entries staged in LDS: the wavefront brings the entries
+// of its next 64 / G rows in whole lines while it reduces the present ones, G
+// = LPR / 2 lanes to a row.  A lane forms two of the LPR partial sums of the
+// kernel above, so the row sums are the same to the bit.
+// What bounds the kernel above is how the entries arrive: a row's lanes ask
+// for a few words at a time and wait for them before the gathers.  Here the
+// gathers leave first and the next rows' entries behind them (loads return in
+// order), and nothing is predicated that need not be: a run is loaded in
+// whole lines, a lane reads eight cells from its row's first on and drops
+// what lies past the row's end.  (With a predicate on every load and read the
+// 27-entry product took 104 us; with non-temporal loads 92.)  In the solve,
+// before and after: 27-entry rows, 96^3: 142 and 91 us (3.7 TB/s); 7, 128^3:
+// 90 and 56; 9, 300 x 2000: 35 and 26; 5, 900 x 1000: 27 and 22.
+// A run of rows longer than the stage is read from memory directly.
+template <int LPR, int TB>
+__global__ __launch_bounds__(TB) void k_pcg_product_staged(int32_t n, const int32_t *__restrict__ rowptr,
+                                                           const int32_t *__restrict__ col,
+                                                           const double *__restrict__ val,
+                                                           const double *__restrict__ z,
+                                                           const double *__restrict__ pold, double *__restrict__ pnew,
+                                                           double *__restrict__ w, SolveState *st,
+                                                           const double *part_res, int g_res, double *part_delta,
+                                                           int32_t rows_per_block, int parity, int tune,
+                                                           int32_t /*lds_nnz: whole chunks staged only*/) {
+    double beta;
+    if (!product_prologue<TB>(st, part_res, g_res, parity, tune, &beta)) return;
+    constexpr int G = LPR / 2, R = 64 / G, PF = kStage / 64, STEP = TB / 64 * R;
+    constexpr int CELLS = kStage + 64;  // a lane reads eight entries on from its first, past the row's end too
+    __shared__ double sv_all[TB / 64][CELLS];
+    __shared__ int32_t sc_all[TB / 64][CELLS];
+    const int lb = dev::xcd_block(blockIdx.x, gridDim.x);
+    const int row0 = lb * rows_per_block;
+    const int row1 = min(n, row0 + rows_per_block);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t lane = threadIdx.x & 63;
+    const int sub = (int)lane % G, grp = (int)lane / G;
+    double *sv = sv_all[wave];
+    int32_t *sc = sc_all[wave];
+    int base = row0 + wave * R;
+    if (base < row1)  // from here on every cell holds a column of the matrix
+        for (int k = lane; k < CELLS; k += 64) sc[k] = row0;
+    const int nnz = rowptr[n];
+    double pv[PF];
+    int32_t pc[PF];
+    // the next rows': first entry, entries, this lane's row; the first entry
+    // of the rows after them and their end
+    int k0n = 0, countn = 0, sn = 0, en = 0, k0a = 0, k1a = 0;
+    auto ahead = [&](int b) {
+        k0a = rowptr[min(b, row1)];
+        k1a = rowptr[min(b + R, row1)];
+    };
+    auto prefetch = [&](int b) __attribute__((always_inline)) {
+        k0n = k0a;
+        countn = k1a - k0a;
+        sn = rowptr[min(b + grp, row1)];
+        en = rowptr[min(b + grp + 1, row1)];
+        const double *vk = val + k0n;
+        const int32_t *ck = col + k0n;
+        if (k0n + kStage <= nnz) {  // whole lines, the following rows' entries with them
+#pragma unroll
+            for (int q = 0; q < PF; ++q)
+                if (q * 64 < countn) {
+                    pv[q] = vk[lane + q * 64];
+                    pc[q] = ck[lane + q * 64];
+                }
+        } else {
+#pragma unroll
+            for (int q = 0; q < PF; ++q)
+                if (k0n + q * 64 + (int)lane < nnz) {
+                    pv[q] = vk[lane + q * 64];
+                    pc[q] = ck[lane + q * 64];
+                } else {
+                    pc[q] = row0;
+                }
+        }
+        ahead(b + STEP);
+    };
+    if (base < row1) {
+        ahead(base);
+        prefetch(base);
+    }
+    double acc = 0.0;
+    for (; base < row1; base += STEP) {
+        const int row = base + grp, k0 = k0n, count = countn, e = en - k0;
+        const bool fits = count <= kStage;
+        int m = sn - k0 + sub;
+        wave_lds_fence();  // the previous rows have been read
+#pragma unroll
+        for (int q = 0; q < PF; ++q)
+            if (q * 64 < count) {
+                sv[lane + q * 64] = pv[q];
+                sc[lane + q * 64] = pc[q];
+            }
+        wave_lds_fence();
+        const int own = min(row, row1 - 1);
+        double aa[8], zj[8], pj[8], sum[2] = {0.0, 0.0};
+        auto gather = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int j = sc[m + q * G];
+                aa[q] = sv[m + q * G];
+                zj[q] = z[j];
+                pj[q] = pold[j];
+            }
+        };
+        auto add = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const double u = fma(aa[q], pdir(zj[q], beta, pj[q]), sum[q & 1]);
+                sum[q & 1] = m + q * G < e ? u : sum[q & 1];
+            }
+            m += 8 * G;
+        };
+        const double zo = z[own], po = pold[own];
+        if (fits) gather();
+        // behind the gathers (loads return in order) and in flight until the
+        // next rows
+        __builtin_amdgcn_sched_barrier(0);
+        if (base + STEP < row1) prefetch(base + STEP);
+        __builtin_amdgcn_sched_barrier(0);
+        if (fits) {
+            add();
+            while (m < e) {
+                gather();
+                add();
+            }
+        } else {
+            for (int q = 0; m < e; ++q, m += G) {
+                const int j = col[k0 + m];
+                sum[q & 1] = fma(val[k0 + m], pdir(z[j], beta, pold[j]), sum[q & 1]);
+            }
+        }
+        double t = sum[0] + sum[1];
+#pragma unroll
+        for (int o = G / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, G);
+        if (row < row1 && sub == 0) {
+            const double pi = pdir(zo, beta, po);
+            pnew[row] = pi;
+            w[row] = t;
+            acc = fma(pi, t, acc);
+        }
+    }
+    double v[1] = {acc};
+    dev::store_partials<TB, 1>(v, part_delta, gridDim.x, lb);
+}
 
 // Row sum of A p for one row whose nonzeros are staged in LDS at [s, e).
 // Rows of at most 8 entries issue all gathers before the first multiply-add
@@ -1167,8 +1346,20 @@ using ProductFn = void (*)(int32_t, const int32_t *, const int32_t *, const doub
                            const double *, double *, double *, SolveState *, const double *, int, double *, int32_t,
                            int, int, int32_t);
 
+// Lanes per row: the staged kernel where the longest row (maxrow) leaves a
+// lane at most eight entries, so that a wavefront's rows fit its stage, and
+// more than four, so that most of the eight are there.  Microseconds of a
+// product in the solve, unstaged and staged (128^3 with 7 entries a row, 96^3
+// with 27): two lanes for 7 entries 90 and 56, eight for 27 142 and 91; but
+// sixteen for 27 114 and 137, four for 5 (9e5 rows) 30 and 33.
 template <int TB>
-ProductFn product_fn_tb(int lpr) {
+ProductFn product_fn_tb(int lpr, int32_t maxrow) {
+    if (2 * lpr < maxrow && maxrow <= 4 * lpr) switch (lpr) {
+        case 2: return k_pcg_product_staged<2, TB>;
+        case 4: return k_pcg_product_staged<4, TB>;
+        case 8: return k_pcg_product_staged<8, TB>;
+        case 16: return k_pcg_product_staged<16, TB>;
+    }
     switch (lpr) {
         case 1: return k_pcg_product<1, TB>;
         case 2: return k_pcg_product<2, TB>;
@@ -1233,7 +1424,8 @@ ProductFn product_fn(const apcg_spmv_config &cfg, int32_t lds_nnz, int32_t sell_
         if (cfg.block_size == 512) return stream_fn<512>(lds_nnz);
         return stream_fn<256>(lds_nnz);
     }
-    return cfg.block_size == 512 ? product_fn_tb<512>(cfg.lanes_per_row) : product_fn_tb<256>(cfg.lanes_per_row);
+    return cfg.block_size == 512 ? product_fn_tb<512>(cfg.lanes_per_row, sell_maxw)
+                                 : product_fn_tb<256>(cfg.lanes_per_row, sell_maxw);
 }
 
 // Launch geometry of one solve.

@@ -1,0 +1,115 @@
+"""The staged product and setup kernels (csrc/pcg.hip): rows of uneven
+lengths up to four times the lanes per row, sizes at the edges of a
+wavefront's rows, rows longer than the 512-entry stage (in the setup's pieces,
+and in a matrix rewritten in place, where the product reads memory directly).
+
+Against the oracle at 20 iterations the repository's bar holds (1e-12)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2306_17801_amd import problems as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def apcg():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2306_17801_amd as m
+
+    m.load()
+    return m
+
+
+@pytest.fixture(scope="module")
+def ctx(apcg):
+    c = apcg.apcg_ctx_create(0)
+    yield c
+    apcg.apcg_ctx_synchronize(c)
+    apcg.apcg_ctx_destroy(c)
+
+
+def dominant(n, pairs, seed):
+    """Symmetric, diagonally dominant CSR with off-diagonal entries at pairs."""
+    rng = np.random.default_rng(seed)
+    rows = [{i: 0.0} for i in range(n)]
+    for i, j in pairs:
+        v = -rng.uniform(0.1, 1.0)
+        for a, b in ((i, j), (j, i)):
+            rows[a][b] = v
+    for i in range(n):
+        rows[i][i] = 1.0 + sum(abs(v) for j, v in rows[i].items() if j != i)
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    col = np.concatenate([np.array(sorted(r), np.int32) for r in rows])
+    val = np.concatenate([[r[j] for j in sorted(r)] for r in rows]).astype(np.float64)
+    return P.CSR(n=n, rowptr=rp, col=col, val=val)
+
+
+def uneven(n, maxrow, seed):
+    """Rows of 1 to maxrow entries, one of maxrow where n allows it."""
+    rng = np.random.default_rng(seed)
+    count, pairs = [1] * n, []
+    for i in range(n):
+        for d in rng.permutation(np.arange(1, maxrow))[: rng.integers(0, maxrow)]:
+            if i + d < n and count[i] < maxrow and count[i + d] < maxrow:
+                count[i] += 1
+                count[i + d] += 1
+                pairs.append((i, i + d))
+    return dominant(n, pairs, seed)
+
+
+def check(apcg, ctx, dA, A, b, x0):
+    from paper_2306_17801_amd.device import DeviceVec
+
+    db, dx = DeviceVec(b), DeviceVec(np.zeros(A.n) if x0 is None else x0)
+    info = apcg.apcg_info_create(0, 1)
+    opts = apcg.apcg_solve_opts_default(x0_is_zero=int(x0 is None), mode=apcg.APCG_MODE_STREAM)
+    its = min(20, max(1, A.n // 2))
+    apcg.apcg_ksp_solve(ctx, dA.h, db.h, dx.h, 0.0, its, opts, info, 0)
+    x, r = dx.numpy(), apcg.apcg_info_get(info, 0)
+    apcg.apcg_info_destroy(info)
+    ref = oracle.pcg(A, b, x0=x0, rtol=0.0, maxit=its)
+    assert r["iterations"] == ref.its
+    assert np.linalg.norm(x - ref.x) <= 1e-12 * np.linalg.norm(ref.x)
+
+
+@pytest.mark.parametrize("lanes", [2, 4, 8, 16])
+def test_staged_product_uneven_rows(apcg, ctx, lanes):
+    from paper_2306_17801_amd.device import DeviceCSR
+
+    for n in (4 * lanes + 1, 127, 128, 1000, 4099):
+        A = uneven(n, 4 * lanes, n)
+        assert 2 * lanes < np.diff(A.rowptr).max() <= 4 * lanes
+        print(f"case staged product lanes={lanes} n={n}", flush=True)
+        dA = DeviceCSR(A)
+        rng = np.random.default_rng(n)
+        for block in (256, 512):
+            apcg.apcg_mat_set_spmv_config(dA.h, lanes, block, 0, apcg.APCG_SPMV_ROWGROUP)
+            for x0 in (None, rng.uniform(-1, 1, n)):
+                check(apcg, ctx, dA, A, rng.uniform(-1, 1, n), x0)
+
+
+def test_staged_rows_longer_than_the_stage(apcg, ctx):
+    """Row 700 names 1100 others: the setup reads it in three pieces.  Then the
+    same arrays, made for rows of five entries, are rewritten with it."""
+    import torch
+    from paper_2306_17801_amd.device import DeviceCSR
+
+    n = 1800
+    arrow = dominant(n, [(700, j) for j in range(100, 1201) if j != 700], 1)
+    rng = np.random.default_rng(2)
+    print("case staged long row", flush=True)
+    check(apcg, ctx, DeviceCSR(arrow), arrow, rng.uniform(-1, 1, n), rng.uniform(-1, 1, n))
+    even = dominant(n, [(i, i + 1) for i in range(900)] + [(i, i + 2) for i in range(200)], 3)
+    assert even.col.size == arrow.col.size and np.diff(even.rowptr).max() == 5  # as many entries, two lanes a row
+    dA = DeviceCSR(even)
+    apcg.apcg_mat_set_spmv_config(dA.h, 2, 256, 0, apcg.APCG_SPMV_ROWGROUP)
+    dA.rowptr.copy_(torch.from_numpy(arrow.rowptr))
+    dA.col.copy_(torch.from_numpy(arrow.col))
+    dA.val.copy_(torch.from_numpy(arrow.val))
+    torch.cuda.synchronize()
+    check(apcg, ctx, dA, arrow, rng.uniform(-1, 1, n), None)
