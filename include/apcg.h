@@ -570,7 +570,7 @@ apcg_status apcg_info_get(apcg_info info, int32_t index, apcg_solve_info *out);
  * counts up to rounding).  With APCG_MODE_PERSISTENT (or AUTO at n <=
  * APCG_PERSISTENT_MAX_N) the whole solve is one launch of one 512-thread
  * workgroup that keeps each row's r, D^-1, p and A p in registers and shares
- * p through n doubles of the context's workspace; its sums run in another
+ * p through LDS; its sums run in another
  * fixed order than the multi-kernel modes' (same tests, same counts up to
  * rounding).  n > APCG_PERSISTENT_MAX_N with PERSISTENT returns
  * APCG_ERR_INVALID_ARG.  On a globally blocking context the call returns
@@ -656,20 +656,16 @@ apcg_status apcg_batch_autotune(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, c
 /* No-allocation variant of apcg_ksp_solve with APCG_MODE_PERSISTENT, for
  * callers that cannot allocate device memory: code under stream capture,
  * tight serving loops, harnesses that forbid hipMalloc.  The same
- * one-workgroup Jacobi-PCG kernel (the same sums, the same tests), with its
- * direction vector in a fixed array of APCG_NOALLOC_MAX_N doubles compiled
- * into the library (one per device, held until the process ends) instead of
- * the context's workspace.  Allocates nothing and takes no library objects:
+ * one-workgroup Jacobi-PCG kernel (the same sums, the same tests), which
+ * keeps its vectors in registers and LDS.  Allocates nothing and takes no library objects:
  * raw device pointers to CSR arrays (rowptr int32[n+1], col int32[nnz], val
  * f64[nnz], strictly increasing or not), b and x (f64[n]; x holds x0 unless
  * opts->x0_is_zero) and one device record `info` that receives the result;
  * all of them stay owned by the caller, who orders their other uses against
  * ctx's stream (the call does no dependency marking).  opts: pc, norm_type
  * and x0_is_zero are read (NULL: the defaults), mode is ignored.  Queues one
- * kernel on ctx's stream and returns.  Every call on one device shares that
- * device's array, so two calls that overlap in time on one device (two
- * contexts, or two host threads) race: the caller serialises them, e.g. by
- * using one context.  Errors (returned before anything is queued):
+ * kernel on ctx's stream and returns; calls that overlap in time (two
+ * contexts, two host threads) share nothing.  Errors (returned before anything is queued):
  * APCG_ERR_INVALID_ARG for a NULL context or pointer, a globally blocking
  * context, n < 0, n > APCG_NOALLOC_MAX_N, maxit < 0 or rtol < 0 or NaN;
  * APCG_ERR_UNSUPPORTED for another preconditioner. */

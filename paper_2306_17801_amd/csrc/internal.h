@@ -270,11 +270,11 @@ void tune_insert(const std::string &key, const int32_t v[4], double us);
 constexpr int kDiaMaxDiags = 9;
 apcg_status dia_analyse(apcg_mat_s *A);
 apcg_status prepare_dia(apcg_mat_s *A, hipStream_t s);
-// one-workgroup persistent Jacobi-PCG (persist.hip): p is n doubles of device
-// memory the workgroup shares; maxrow the longest row (< 0: unknown)
+// one-workgroup persistent Jacobi-PCG (persist.hip); maxrow the longest row
+// (< 0: unknown)
 int persistent_rows_per_thread(int64_t n);
 apcg_status launch_pcg_wg(hipStream_t st, int32_t n, const int32_t *rowptr, const int32_t *col, const double *val,
-                          const double *b, double *x, double *p, double rtol, int32_t maxit, int x0_zero, int pc,
+                          const double *b, double *x, double rtol, int32_t maxit, int x0_zero, int pc,
                           int norm_pre, int32_t maxrow, apcg_solve_info *out);
 void batch_cache_release(uint64_t ctx_id, int device);  // batched.hip
 // sliced-diagonal pattern analysis (pcg.hip): synchronous, once per matrix

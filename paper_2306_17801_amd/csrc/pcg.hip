@@ -2013,13 +2013,13 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
                 // given up (see team.h): x is as it was, the kernels below solve it
             }
         }
-        if ((s = ensure_workspace(c, A->n))) return s;
-        if (opts.mode == APCG_MODE_PERSISTENT) {  // reads the CSR arrays; p in the workspace
-            if ((s = launch_pcg_wg(st, A->n, A->rowptr, A->col, A->val, b->d, x->d, c->ws.p(0), rtol, maxit,
+        if (opts.mode == APCG_MODE_PERSISTENT) {  // reads the CSR arrays
+            if ((s = launch_pcg_wg(st, A->n, A->rowptr, A->col, A->val, b->d, x->d, rtol, maxit,
                                    opts.x0_is_zero ? 1 : 0, opts.pc, norm_pre, A->sell_maxw, info->d + info_index)))
                 return s;
             return op_end(c, acc, 4);
         }
+        if ((s = ensure_workspace(c, A->n))) return s;
         Plan pl;
         if ((s = make_plan(A, A->cfg, &pl))) return s;
         Bufs bf{A, x->d, b->d, c->ws, c->partials};

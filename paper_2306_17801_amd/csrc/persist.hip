@@ -9,19 +9,22 @@
 // its scalars and its tests never leave the workgroup.  Each thread owns R
 // rows (row tid + q * 512; R <= 8, so n <= 4096), keeps their x, r, D^-1, p
 // and A p entries in registers and, when the rows are short enough, their
-// matrix entries as well, so after the setup an iteration reads only the
-// direction vector, and x is written once, at the end:
+// matrix entries as well (columns as 16-bit places), so after the setup an
+// iteration reads only the direction vector, from LDS, and x is written once,
+// at the end:
 //
-//   publish p (one store per owned row into a buffer the workgroup shares),
-//   barrier; w = A p for the owned rows, delta = p.w (workgroup sum, barrier);
+//   publish p (one store per owned row into LDS), barrier; w = A p for the owned rows, delta = p.w (workgroup sum, barrier);
 //   alpha, x += alpha p, r -= alpha w, z = D^-1 r, z.r and the stopping norm
 //   (workgroup sum, barrier); the tests; beta; p = z + beta p.
 //
 // Three barriers per iteration.  The two workgroup sums use separate LDS
 // areas, so no barrier is needed after reading one (every reader has passed
-// the next barrier before the area is written again).  The shared direction
-// buffer lives in device memory that the caller provides (a workspace of n
-// doubles); all of its traffic stays in the compute unit's caches.
+// the next barrier before the area is written again).  What bounds it is the
+// chain of one iteration: gathers, two sums, three barriers.  64 x 64 Poisson,
+// 205 iterations: 1412 us with p in a buffer in device memory (the gathers
+// wait for the L1 cache) and shuffles in the sums, 440 here; 16^3 with 7
+// entries a row 14.0 and 2.5 us an iteration; 5^3 2.3 and 1.2, nearly all of
+// it barriers and sums.
 //
 // The sums run in a fixed order (a wavefront butterfly, then a butterfly over
 // the 8 wavefront partials), so every thread holds the same scalars and takes
@@ -32,7 +35,6 @@
 
 #include <chrono>
 #include <cmath>
-#include <mutex>
 
 #include "internal.h"
 
@@ -49,18 +51,18 @@ struct WgArgs {
     const double *val;
     const double *b;
     double *x;
-    double *p;  // n doubles shared by the workgroup (the direction vector)
     apcg_solve_info *out;
     double rtol;
     int32_t n, maxit, x0_zero, pc, norm_pre;
 };
 
 // Workgroup sum of NV values into every thread: wavefront butterfly, one
-// partial per wavefront in `area`, then the WNW partials added by a second
-// butterfly in which lane l < WNW holds partial l (the other lanes 0).  An
-// xor butterfly leaves every lane with the same bits (each step adds the
-// same two values, only in swapped order), and every wavefront reads the same
-// partials into the same lanes, so all threads hold identical sums.  The
+// partial per wavefront in `area`, then the WNW = 8 partials added by a second
+// butterfly over distances 4, 2, 1 (lane l holds partial l modulo 8, so
+// rotations within the rows of 16 bring the partners).  An xor butterfly
+// leaves every lane with the same bits (each step adds the same two values,
+// only in swapped order), and every wavefront reads the same partials into
+// the same lanes, so all threads hold identical sums.  The
 // caller separates two uses of one area by at least one other barrier.
 template <int NV>
 __device__ __forceinline__ void wg_sum(double (&v)[NV], double *area) {
@@ -73,7 +75,14 @@ __device__ __forceinline__ void wg_sum(double (&v)[NV], double *area) {
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = dev::wave_sum(lane < WNW ? area[k * WNW + lane] : 0.0);
+    for (int k = 0; k < NV; ++k) {
+        static_assert(WNW == 8, "three steps");
+        double t = area[k * WNW + lane % WNW];
+        t += dev::dpp_row<0x124>(t);
+        t += dev::dpp_row<0x122>(t);
+        t += dev::dpp_row<0x121>(t);
+        v[k] = t;
+    }
 }
 
 // R rows per thread; L > 0: every row has at most L entries, held in
@@ -82,11 +91,12 @@ __device__ __forceinline__ void wg_sum(double (&v)[NV], double *area) {
 template <int R, int L>
 __global__ __launch_bounds__(WT) void k_pcg_wg(WgArgs a) {
     __shared__ double red[2][4 * WNW];
+    __shared__ double ps[R * WT];  // the direction vector
     constexpr int LC = L > 0 ? L : 1;
     const int tid = threadIdx.x;
     const int n = a.n;
     double rr[R], dr[R], pr[R], wr[R], xr[R];
-    int jj[R][LC];
+    uint32_t jj[R][(LC + 1) / 2];  // two 16-bit columns a word
     double aa[R][LC];
     int rs[R], rl[R];  // row start and length (rows read from the CSR arrays)
 
@@ -99,10 +109,9 @@ __global__ __launch_bounds__(WT) void k_pcg_wg(WgArgs a) {
         rr[q] = dr[q] = pr[q] = wr[q] = xr[q] = 0.0;
         rs[q] = rl[q] = 0;
 #pragma unroll
-        for (int t = 0; t < LC; ++t) {
-            jj[q][t] = 0;
-            aa[q][t] = 0.0;
-        }
+        for (int t = 0; t < (LC + 1) / 2; ++t) jj[q][t] = 0;
+#pragma unroll
+        for (int t = 0; t < LC; ++t) aa[q][t] = 0.0;
         if (i >= n) continue;
         const int s = a.rowptr[i], e = a.rowptr[i + 1];
         rs[q] = s;
@@ -110,20 +119,22 @@ __global__ __launch_bounds__(WT) void k_pcg_wg(WgArgs a) {
         double diag = 0.0, ax = 0.0;
         bool found = false;
         if (L > 0) {
+            int cj[LC];
 #pragma unroll
             for (int t = 0; t < LC; ++t) {
                 const bool in = t < e - s;
-                jj[q][t] = in ? a.col[s + t] : i;
+                cj[t] = in ? a.col[s + t] : i;
                 aa[q][t] = in ? a.val[s + t] : 0.0;
+                jj[q][t / 2] |= (uint32_t)cj[t] << (16 * (t % 2));
             }
 #pragma unroll
             for (int t = 0; t < LC; ++t) {
                 if (t < e - s) {
-                    if (jj[q][t] == i) {
+                    if (cj[t] == i) {
                         diag = aa[q][t];
                         found = true;
                     }
-                    if (!a.x0_zero) ax = fma(aa[q][t], a.x[jj[q][t]], ax);
+                    if (!a.x0_zero) ax = fma(aa[q][t], a.x[cj[t]], ax);
                 }
             }
         } else {
@@ -182,8 +193,14 @@ __global__ __launch_bounds__(WT) void k_pcg_wg(WgArgs a) {
 #pragma unroll
         for (int q = 0; q < R; ++q) {
             const int i = tid + q * WT;
-            if (i < n) a.p[i] = pr[q];
+            if (i < n) ps[i] = pr[q];
         }
+        // the packed columns are unpacked where they are used (kept unpacked
+        // across the iterations they would spill)
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+#pragma unroll
+            for (int t = 0; t < (LC + 1) / 2; ++t) asm volatile("" : "+v"(jj[q][t]));
         __syncthreads();
         double d1[1] = {0.0};
 #pragma unroll
@@ -194,7 +211,7 @@ __global__ __launch_bounds__(WT) void k_pcg_wg(WgArgs a) {
             if (L > 0) {
                 double pj[LC];
 #pragma unroll
-                for (int t = 0; t < LC; ++t) pj[t] = a.p[jj[q][t]];
+                for (int t = 0; t < LC; ++t) pj[t] = ps[jj[q][t / 2] >> (16 * (t % 2)) & 0xffffu];
                 // padding slots add 0 * p_i (a NaN or infinity there stops
                 // the solve through delta anyway)
 #pragma unroll
@@ -211,12 +228,12 @@ __global__ __launch_bounds__(WT) void k_pcg_wg(WgArgs a) {
                         a8[t] = in ? a.val[s + t] : 0.0;
                     }
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) p8[t] = a.p[j8[t]];
+                    for (int t = 0; t < 8; ++t) p8[t] = ps[j8[t]];
 #pragma unroll
                     for (int t = 0; t < 8; ++t)
                         if (t < len) sum = fma(a8[t], p8[t], sum);
                 } else {
-                    for (int t = s; t < s + len; ++t) sum = fma(a.val[t], a.p[a.col[t]], sum);
+                    for (int t = s; t < s + len; ++t) sum = fma(a.val[t], ps[a.col[t]], sum);
                 }
             }
             wr[q] = sum;
@@ -302,23 +319,22 @@ int persistent_rows_per_thread(int64_t n) {
     return 0;
 }
 
-// Queues the one-workgroup solve on stream st.  p: n doubles of device
-// memory (the shared direction vector); maxrow: the longest row's length
-// (< 0: unknown).  The caller has checked n <= APCG_PERSISTENT_MAX_N.
+// Queues the one-workgroup solve on stream st.  maxrow: the longest row's
+// length (< 0: unknown).  The caller has checked n <= APCG_PERSISTENT_MAX_N.
 apcg_status launch_pcg_wg(hipStream_t st, int32_t n, const int32_t *rowptr, const int32_t *col, const double *val,
-                          const double *b, double *x, double *p, double rtol, int32_t maxit, int x0_zero, int pc,
+                          const double *b, double *x, double rtol, int32_t maxit, int x0_zero, int pc,
                           int norm_pre, int32_t maxrow, apcg_solve_info *out) {
-    WgArgs a{rowptr, col, val, b, x, p, out, rtol, n, maxit, x0_zero, pc, norm_pre};
+    WgArgs a{rowptr, col, val, b, x, out, rtol, n, maxit, x0_zero, pc, norm_pre};
     const int R = persistent_rows_per_thread(n < 1 ? 1 : n);
-    // matrix entries in registers when they fit without spilling (rows of
-    // at most 5 entries, or of at most 7 at up to 4 rows per thread)
+    // matrix entries in registers (8 rows of 7 spill 12 registers of 256,
+    // which still beats rereading the entries: 2.5 and 7 us an iteration)
     const bool l5 = maxrow >= 0 && maxrow <= 5, l7 = maxrow >= 0 && maxrow <= 7;
     void (*k)(WgArgs) = nullptr;
     switch (R) {
         case 1: k = l5 ? k_pcg_wg<1, 5> : l7 ? k_pcg_wg<1, 7> : k_pcg_wg<1, 0>; break;
         case 2: k = l5 ? k_pcg_wg<2, 5> : l7 ? k_pcg_wg<2, 7> : k_pcg_wg<2, 0>; break;
         case 4: k = l5 ? k_pcg_wg<4, 5> : l7 ? k_pcg_wg<4, 7> : k_pcg_wg<4, 0>; break;
-        case 8: k = l5 ? k_pcg_wg<8, 5> : k_pcg_wg<8, 0>; break;
+        case 8: k = l5 ? k_pcg_wg<8, 5> : l7 ? k_pcg_wg<8, 7> : k_pcg_wg<8, 0>; break;
         default: return set_error(APCG_ERR_INVALID_ARG, "system too large for the one-workgroup solve");
     }
     hipLaunchKernelGGL(k, dim3(1), dim3(WT), 0, st, a);
@@ -327,37 +343,8 @@ apcg_status launch_pcg_wg(hipStream_t st, int32_t n, const int32_t *rowptr, cons
 }
 
 // ------------------------------------------------- no-allocation variant
-// The direction vector of apcg_ksp_solve_small_noalloc: a fixed array in the
-// code object, one copy per device for the life of the process (32 KiB), so
-// that the entry point allocates nothing.  Host code never passes this name
-// to a kernel (on the host it is a stand-in, not a device address); it looks
-// the device address up once per device and passes that.
 constexpr int kNoAllocMaxN = APCG_NOALLOC_MAX_N;
 static_assert(kNoAllocMaxN <= APCG_PERSISTENT_MAX_N, "the no-allocation solve is the one-workgroup solve");
-static __device__ __align__(256) double scratch[kNoAllocMaxN];
-
-namespace {
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-double *g_scratch_ptr[kMaxDevices] = {};  // device address of `scratch`, per device
-
-// The device address of `scratch` on `device` (looked up on the first call
-// for that device, with the device current).
-apcg_status scratch_address(int device, double **out) {
-    if (device < 0 || device >= kMaxDevices) return set_error(APCG_ERR_INVALID_ARG, "device index out of range");
-    std::lock_guard<std::mutex> lk(g_scratch_mu);
-    if (!g_scratch_ptr[device]) {
-        APCG_HIP(hipSetDevice(device));
-        void *p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess) return hip_error(e, "hipGetSymbolAddress(scratch)");
-        if (!p) return set_error(APCG_ERR_HIP, "hipGetSymbolAddress(scratch) returned NULL");
-        g_scratch_ptr[device] = static_cast<double *>(p);
-    }
-    *out = g_scratch_ptr[device];
-    return APCG_SUCCESS;
-}
-}  // namespace
 
 }  // namespace apcg
 
@@ -372,8 +359,8 @@ extern "C" apcg_status apcg_ksp_solve_small_noalloc(apcg_ctx ctx, int32_t n, con
         return set_error(APCG_ERR_INVALID_ARG, "the no-allocation solve needs a default-stream context");
     if (n < 0) return set_error(APCG_ERR_INVALID_ARG, "n must be >= 0");
     if (n > kNoAllocMaxN)
-        return set_error(APCG_ERR_INVALID_ARG, "n exceeds APCG_NOALLOC_MAX_N (4096 rows), the no-allocation "
-                                               "solve's fixed direction buffer");
+        return set_error(APCG_ERR_INVALID_ARG, "n exceeds APCG_NOALLOC_MAX_N (4096 rows), what the no-allocation "
+                                               "solve's workgroup holds");
     if (!rowptr || !col || !val || !b || !x || !info) return set_error(APCG_ERR_INVALID_ARG, "NULL argument");
     if (n > 0 && (uintptr_t)b < (uintptr_t)(x + n) && (uintptr_t)x < (uintptr_t)(b + n))
         return set_error(APCG_ERR_INVALID_ARG, "b and x must not share memory");
@@ -388,13 +375,10 @@ extern "C" apcg_status apcg_ksp_solve_small_noalloc(apcg_ctx ctx, int32_t n, con
         norm_pre = opts->norm_type == APCG_NORM_PRECONDITIONED;
         x0_zero = opts->x0_is_zero ? 1 : 0;
     }
-    double *p = nullptr;
-    apcg_status s;
-    if ((s = scratch_address(ctx->device, &p))) return s;
     APCG_HIP(hipSetDevice(ctx->device));
     // rows and their lengths are not known on the host: the entries are read
     // from the CSR arrays every iteration (the same sums as the register path)
-    return launch_pcg_wg(ctx->stream, n, rowptr, col, val, b, x, p, rtol, maxit, x0_zero, pc, norm_pre, -1, info);
+    return launch_pcg_wg(ctx->stream, n, rowptr, col, val, b, x, rtol, maxit, x0_zero, pc, norm_pre, -1, info);
 }
 
 extern "C" apcg_status apcg_latency_floors(int32_t device, int32_t reps, double out_us[4]) {
