@@ -330,6 +330,9 @@ inline bool stream_fits(const apcg_mat_s *A, int tb) {
     return (tb == 256 || tb == 512) && A->max_block_nnz[tb == 512 ? 1 : 0] <= kStreamMaxNnz;
 }
 
+// Rows that dev::staged_rows takes one to a lane.
+inline bool one_lane_staged(const apcg_mat_s *A) { return A->sell_maxw > 4 && A->sell_maxw <= 8; }
+
 // Grid and chunk for an elementwise pass over n entries: 2048 workgroups at
 // most, chunks a multiple of 64 entries (512-byte aligned for doubles).
 inline void elementwise_grid(int64_t n, int *G, int64_t *per_block) {
@@ -868,6 +871,143 @@ __device__ __forceinline__ void sdia_slices(const int32_t *__restrict__ soff, co
 // with its transposes (the value-symmetry flag after the partner table).
 __device__ __forceinline__ bool sdia_sym8(const int32_t *soff, int64_t n) {
     return *(const kc32 *)(soff + ((n + 63) >> 6) * 16) != 0;
+}
+
+constexpr int kStage = 512;  // entries a wavefront stages in LDS at a time
+
+// What a wavefront's lanes have written to its LDS is read by its other lanes
+// from here on (LDS operations of a wavefront complete in order).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Row sums of CSR rows [row0, row0 + rows) by a workgroup of TB threads.  A
+// wavefront takes 64 / G rows at a time, G = max(1, LPR / 2) lanes to a row;
+// the sum of a row is that of LPR lanes taking its entries in turn, added by a
+// butterfly (LPR = 1: in storage order), a lane holding two of the LPR partial
+// sums.  load(j) reads what entry j's vector value is made of, value() makes
+// it, done(row, sum, own) receives the sum and load(row) in the row's first
+// lane.
+// What bounds lanes that read their entries themselves is how these arrive: a
+// row's lanes ask for a few words at a time and wait for them before the
+// gathers.  Here a wavefront brings the entries of its next rows in whole
+// lines through LDS; the gathers of the present rows leave first and the next
+// entries behind them (loads return in order), and nothing is predicated that
+// need not be: a lane reads eight cells from its row's first on and drops what
+// lies past the row's end.  (The 27-entry PCG product, 96^3: 142 us unstaged,
+// 104 with a predicate on every load and read, 92 with non-temporal loads, 91
+// as it is.)  A run of rows longer than the stage is read from memory
+// directly.
+template <int LPR, int TB, class Load, class Value, class Done>
+__device__ __forceinline__ void staged_rows(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+                                            const double *__restrict__ val, int row0, int rows, Load load, Value value,
+                                            Done done) {
+    constexpr int G = LPR > 1 ? LPR / 2 : 1, R = 64 / G, PF = kStage / 64, STEP = TB / 64 * R;
+    constexpr int NS = LPR > 1 ? 2 : 1;     // partial sums of a lane
+    constexpr int CELLS = kStage + 64;      // a lane reads eight entries on from its first, past the row's end too
+    __shared__ double sv_all[TB / 64][CELLS];
+    __shared__ int32_t sc_all[TB / 64][CELLS];
+    const int row1 = min(n, row0 + rows);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t lane = threadIdx.x & 63;
+    const int sub = (int)lane % G, grp = (int)lane / G;
+    double *sv = sv_all[wave];
+    int32_t *sc = sc_all[wave];
+    int base = row0 + wave * R;
+    if (base >= row1) return;
+    for (int k = lane; k < CELLS; k += 64) sc[k] = row0;  // from here on every cell holds a column of the matrix
+    const int nnz = rowptr[n];
+    double pv[PF];
+    int32_t pc[PF];
+    // the next rows': first entry, entries, this lane's row; the first entry
+    // of the rows after them and their end
+    int k0n = 0, countn = 0, sn = 0, en = 0, k0a = 0, k1a = 0;
+    auto ahead = [&](int b) {
+        k0a = rowptr[min(b, row1)];
+        k1a = rowptr[min(b + R, row1)];
+    };
+    auto prefetch = [&](int b) __attribute__((always_inline)) {
+        k0n = k0a;
+        countn = k1a - k0a;
+        sn = rowptr[min(b + grp, row1)];
+        en = rowptr[min(b + grp + 1, row1)];
+        const double *vk = val + k0n;
+        const int32_t *ck = col + k0n;
+        if (k0n + kStage <= nnz) {  // whole lines, the following rows' entries with them
+#pragma unroll
+            for (int q = 0; q < PF; ++q)
+                if (q * 64 < countn) {
+                    pv[q] = vk[lane + q * 64];
+                    pc[q] = ck[lane + q * 64];
+                }
+        } else {
+#pragma unroll
+            for (int q = 0; q < PF; ++q)
+                if (k0n + q * 64 + (int)lane < nnz) {
+                    pv[q] = vk[lane + q * 64];
+                    pc[q] = ck[lane + q * 64];
+                } else {
+                    pc[q] = row0;
+                }
+        }
+        ahead(b + STEP);
+    };
+    ahead(base);
+    prefetch(base);
+    for (; base < row1; base += STEP) {
+        const int row = base + grp, k0 = k0n, count = countn, e = en - k0;
+        const bool fits = count <= kStage;
+        int m = sn - k0 + sub;
+        wave_lds_fence();  // the previous rows have been read
+#pragma unroll
+        for (int q = 0; q < PF; ++q)
+            if (q * 64 < count) {
+                sv[lane + q * 64] = pv[q];
+                sc[lane + q * 64] = pc[q];
+            }
+        wave_lds_fence();
+        using T = decltype(load(0));
+        double aa[8], sum[2] = {0.0, 0.0};
+        T u[8];
+        auto gather = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int j = sc[m + q * G];
+                aa[q] = sv[m + q * G];
+                u[q] = load(j);
+            }
+        };
+        auto add = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const double t = fma(aa[q], value(u[q]), sum[q % NS]);
+                sum[q % NS] = m + q * G < e ? t : sum[q % NS];
+            }
+            m += 8 * G;
+        };
+        const T own = load(min(row, row1 - 1));
+        if (fits) gather();
+        // behind the gathers (loads return in order) and in flight until the
+        // next rows
+        __builtin_amdgcn_sched_barrier(0);
+        if (base + STEP < row1) prefetch(base + STEP);
+        __builtin_amdgcn_sched_barrier(0);
+        if (fits) {
+            add();
+            while (m < e) {
+                gather();
+                add();
+            }
+        } else {
+            for (int q = 0; m < e; ++q, m += G) sum[q % NS] = fma(val[k0 + m], value(load(col[k0 + m])), sum[q % NS]);
+        }
+        double t = NS > 1 ? sum[0] + sum[1] : sum[0];
+#pragma unroll
+        for (int o = G / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, G);
+        if (row < row1 && sub == 0) done(row, t, own);
+    }
 }
 
 // A matrix as the row-per-thread kernels read it: the CSR arrays, and the

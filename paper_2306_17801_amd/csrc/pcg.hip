@@ -95,20 +95,11 @@ __device__ __forceinline__ void terminate(SolveState *st, int its, int status, d
 }
 
 // ----------------------------------------------------------------- setup
-constexpr int kStage = 512;  // entries a wavefront stages in LDS at a time
-// What a wavefront's lanes have written to its LDS is read by its other lanes
-// from here on (LDS operations of a wavefront complete in order).
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // dinv = 1/diag(A) (or 1), r0 = b - A x0 (or b), z0 = dinv r0, p_old = 0; partials of
 // z0.r0, residual norm^2, reference norm^2 and the count of bad diagonals.
 // One row per lane; bound by the read of the matrix, which a lane walking its
 // own row asks for in single words, a row apart from its neighbour's.  So a
-// wavefront brings its 64 rows' entries through LDS, kStage at a time, in
+// wavefront brings its 64 rows' entries through LDS, dev::kStage at a time, in
 // whole lines; with x0 = 0 only the columns, and one value where the diagonal
 // is found.  27-entry rows, 96^3: INITMEASURED.
 __global__ __launch_bounds__(VB) void k_pcg_init(int32_t n, const int32_t *__restrict__ rowptr,
@@ -121,8 +112,8 @@ __global__ __launch_bounds__(VB) void k_pcg_init(int32_t n, const int32_t *__res
     if (gate && !gate[0]) return;  // gated off: the solve is a no-op
     const dev::Chunk c = dev::block_chunk(n, per_block);
     double rz = 0.0, nres = 0.0, nref = 0.0, bad = 0.0;
-    __shared__ double sv[VB / 64][kStage];
-    __shared__ int32_t sc[VB / 64][kStage];
+    __shared__ double sv[VB / 64][dev::kStage];
+    __shared__ int32_t sc[VB / 64][dev::kStage];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int64_t base = c.lo + wave * 64; base < c.hi; base += VB) {
         const int64_t i = base + lane;
@@ -131,18 +122,18 @@ __global__ __launch_bounds__(VB) void k_pcg_init(int32_t n, const int32_t *__res
         const int s0 = rowptr[base], e0 = rowptr[min(base + 64, c.hi)];
         double diag = 0.0, ax = 0.0;
         bool found = false;
-        for (int p0 = s0; p0 < e0; p0 += kStage) {
-            const int p1 = min(e0, p0 + kStage);
-            wave_lds_fence();  // the previous piece has been read
+        for (int p0 = s0; p0 < e0; p0 += dev::kStage) {
+            const int p1 = min(e0, p0 + dev::kStage);
+            dev::wave_lds_fence();  // the previous piece has been read
 #pragma unroll
-            for (int q = 0; q < kStage / 64; ++q) {
+            for (int q = 0; q < dev::kStage / 64; ++q) {
                 const int k = q * 64 + lane;
                 if (p0 + k < p1) {
                     sc[wave][k] = col[p0 + k];
                     if (!x0_zero) sv[wave][k] = val[p0 + k];
                 }
             }
-            wave_lds_fence();
+            dev::wave_lds_fence();
             for (int k = max(s, p0); k < min(e, p1); ++k) {
                 const int j = sc[wave][k - p0];
                 if (j == (int)i) {
@@ -311,20 +302,10 @@ __global__ __launch_bounds__(TB) void k_pcg_product(int32_t n, const int32_t *__
 }
 
 
-// The same sums from entries staged in LDS: the wavefront brings the entries
-// of its next 64 / G rows in whole lines while it reduces the present ones, G
-// = LPR / 2 lanes to a row.  A lane forms two of the LPR partial sums of the
-// kernel above, so the row sums are the same to the bit.
-// What bounds the kernel above is how the entries arrive: a row's lanes ask
-// for a few words at a time and wait for them before the gathers.  Here the
-// gathers leave first and the next rows' entries behind them (loads return in
-// order), and nothing is predicated that need not be: a run is loaded in
-// whole lines, a lane reads eight cells from its row's first on and drops
-// what lies past the row's end.  (With a predicate on every load and read the
-// 27-entry product took 104 us; with non-temporal loads 92.)  In the solve,
-// before and after: 27-entry rows, 96^3: 142 and 91 us (3.7 TB/s); 7, 128^3:
-// 90 and 56; 9, 300 x 2000: 35 and 26; 5, 900 x 1000: 27 and 22.
-// A run of rows longer than the stage is read from memory directly.
+// The same sums by dev::staged_rows: LPR / 2 lanes to a row, each with two of
+// the LPR partial sums above, so the row sums are the same to the bit.  In the
+// solve, before and after: 27-entry rows, 96^3: 142 and 91 us (3.7 TB/s); 7,
+// 128^3: 90 and 56; 9, 300 x 2000: 35 and 26; 5, 900 x 1000: 27 and 22.
 template <int LPR, int TB>
 __global__ __launch_bounds__(TB) void k_pcg_product_staged(int32_t n, const int32_t *__restrict__ rowptr,
                                                            const int32_t *__restrict__ col,
@@ -337,122 +318,20 @@ __global__ __launch_bounds__(TB) void k_pcg_product_staged(int32_t n, const int3
                                                            int32_t /*lds_nnz: whole chunks staged only*/) {
     double beta;
     if (!product_prologue<TB>(st, part_res, g_res, parity, tune, &beta)) return;
-    constexpr int G = LPR / 2, R = 64 / G, PF = kStage / 64, STEP = TB / 64 * R;
-    constexpr int CELLS = kStage + 64;  // a lane reads eight entries on from its first, past the row's end too
-    __shared__ double sv_all[TB / 64][CELLS];
-    __shared__ int32_t sc_all[TB / 64][CELLS];
+    struct Pair {
+        double z, pold;
+    };
     const int lb = dev::xcd_block(blockIdx.x, gridDim.x);
-    const int row0 = lb * rows_per_block;
-    const int row1 = min(n, row0 + rows_per_block);
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t lane = threadIdx.x & 63;
-    const int sub = (int)lane % G, grp = (int)lane / G;
-    double *sv = sv_all[wave];
-    int32_t *sc = sc_all[wave];
-    int base = row0 + wave * R;
-    if (base < row1)  // from here on every cell holds a column of the matrix
-        for (int k = lane; k < CELLS; k += 64) sc[k] = row0;
-    const int nnz = rowptr[n];
-    double pv[PF];
-    int32_t pc[PF];
-    // the next rows': first entry, entries, this lane's row; the first entry
-    // of the rows after them and their end
-    int k0n = 0, countn = 0, sn = 0, en = 0, k0a = 0, k1a = 0;
-    auto ahead = [&](int b) {
-        k0a = rowptr[min(b, row1)];
-        k1a = rowptr[min(b + R, row1)];
-    };
-    auto prefetch = [&](int b) __attribute__((always_inline)) {
-        k0n = k0a;
-        countn = k1a - k0a;
-        sn = rowptr[min(b + grp, row1)];
-        en = rowptr[min(b + grp + 1, row1)];
-        const double *vk = val + k0n;
-        const int32_t *ck = col + k0n;
-        if (k0n + kStage <= nnz) {  // whole lines, the following rows' entries with them
-#pragma unroll
-            for (int q = 0; q < PF; ++q)
-                if (q * 64 < countn) {
-                    pv[q] = vk[lane + q * 64];
-                    pc[q] = ck[lane + q * 64];
-                }
-        } else {
-#pragma unroll
-            for (int q = 0; q < PF; ++q)
-                if (k0n + q * 64 + (int)lane < nnz) {
-                    pv[q] = vk[lane + q * 64];
-                    pc[q] = ck[lane + q * 64];
-                } else {
-                    pc[q] = row0;
-                }
-        }
-        ahead(b + STEP);
-    };
-    if (base < row1) {
-        ahead(base);
-        prefetch(base);
-    }
     double acc = 0.0;
-    for (; base < row1; base += STEP) {
-        const int row = base + grp, k0 = k0n, count = countn, e = en - k0;
-        const bool fits = count <= kStage;
-        int m = sn - k0 + sub;
-        wave_lds_fence();  // the previous rows have been read
-#pragma unroll
-        for (int q = 0; q < PF; ++q)
-            if (q * 64 < count) {
-                sv[lane + q * 64] = pv[q];
-                sc[lane + q * 64] = pc[q];
-            }
-        wave_lds_fence();
-        const int own = min(row, row1 - 1);
-        double aa[8], zj[8], pj[8], sum[2] = {0.0, 0.0};
-        auto gather = [&]() __attribute__((always_inline)) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int j = sc[m + q * G];
-                aa[q] = sv[m + q * G];
-                zj[q] = z[j];
-                pj[q] = pold[j];
-            }
-        };
-        auto add = [&]() __attribute__((always_inline)) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const double u = fma(aa[q], pdir(zj[q], beta, pj[q]), sum[q & 1]);
-                sum[q & 1] = m + q * G < e ? u : sum[q & 1];
-            }
-            m += 8 * G;
-        };
-        const double zo = z[own], po = pold[own];
-        if (fits) gather();
-        // behind the gathers (loads return in order) and in flight until the
-        // next rows
-        __builtin_amdgcn_sched_barrier(0);
-        if (base + STEP < row1) prefetch(base + STEP);
-        __builtin_amdgcn_sched_barrier(0);
-        if (fits) {
-            add();
-            while (m < e) {
-                gather();
-                add();
-            }
-        } else {
-            for (int q = 0; m < e; ++q, m += G) {
-                const int j = col[k0 + m];
-                sum[q & 1] = fma(val[k0 + m], pdir(z[j], beta, pold[j]), sum[q & 1]);
-            }
-        }
-        double t = sum[0] + sum[1];
-#pragma unroll
-        for (int o = G / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, G);
-        if (row < row1 && sub == 0) {
-            const double pi = pdir(zo, beta, po);
+    dev::staged_rows<LPR, TB>(
+        n, rowptr, col, val, lb * rows_per_block, rows_per_block, [&](int j) { return Pair{z[j], pold[j]}; },
+        [&](const Pair &q) { return pdir(q.z, beta, q.pold); },
+        [&](int row, double sum, const Pair &own) {
+            const double pi = pdir(own.z, beta, own.pold);
             pnew[row] = pi;
-            w[row] = t;
-            acc = fma(pi, t, acc);
-        }
-    }
+            w[row] = sum;
+            acc = fma(pi, sum, acc);
+        });
     double v[1] = {acc};
     dev::store_partials<TB, 1>(v, part_delta, gridDim.x, lb);
 }
@@ -1351,10 +1230,12 @@ using ProductFn = void (*)(int32_t, const int32_t *, const int32_t *, const doub
 // more than four, so that most of the eight are there.  Microseconds of a
 // product in the solve, unstaged and staged (128^3 with 7 entries a row, 96^3
 // with 27): two lanes for 7 entries 90 and 56, eight for 27 142 and 91; but
-// sixteen for 27 114 and 137, four for 5 (9e5 rows) 30 and 33.
+// sixteen for 27 114 and 137, four for 5 (9e5 rows) 30 and 33.  (One lane: a
+// row of more than eight does not fit the eight cells it reads at once.)
 template <int TB>
 ProductFn product_fn_tb(int lpr, int32_t maxrow) {
-    if (2 * lpr < maxrow && maxrow <= 4 * lpr) switch (lpr) {
+    if (maxrow > (lpr > 1 ? 2 * lpr : 4) && maxrow <= (lpr > 1 ? 4 * lpr : 8)) switch (lpr) {
+        case 1: return k_pcg_product_staged<1, TB>;
         case 2: return k_pcg_product_staged<2, TB>;
         case 4: return k_pcg_product_staged<4, TB>;
         case 8: return k_pcg_product_staged<8, TB>;
@@ -1453,11 +1334,20 @@ void vector_grid(int64_t n, int *G, int64_t *per_block) {
     *per_block = std::max<int64_t>(64, ((pb + 63) / 64) * 64);
 }
 
-apcg_status make_plan(const apcg_mat_s *A, const apcg_spmv_config &cfg, Plan *pl) {
+apcg_status make_plan(const apcg_mat_s *A, const apcg_spmv_config &config, Plan *pl) {
     pl->n = A->n;
-    pl->tb = cfg.block_size == 512 ? 512 : 256;
-    if (cfg.schedule == APCG_SPMV_STREAM && !stream_fits(A, pl->tb))
+    pl->tb = config.block_size == 512 ? 512 : 256;
+    if (config.schedule == APCG_SPMV_STREAM && !stream_fits(A, pl->tb))
         return set_error(APCG_ERR_UNSUPPORTED, "rows too long for the staged schedule");
+    // one row per thread with rows of five to eight entries: staged by
+    // wavefronts, which gives the same row sums without the workgroup's
+    // barriers (7 entries, 128^3: 63 and 56 us in the solve; 5, 900 x 1000: 30
+    // and 22)
+    apcg_spmv_config cfg = config;
+    if (cfg.schedule == APCG_SPMV_STREAM && one_lane_staged(A)) {
+        cfg.schedule = APCG_SPMV_ROWGROUP;
+        cfg.lanes_per_row = 1;
+    }
     pl->lds_nnz = 0;
     pl->lds_bytes = 0;
     pl->a0 = A->rowptr;

@@ -93,6 +93,36 @@ def test_staged_product_uneven_rows(apcg, ctx, lanes):
                 check(apcg, ctx, dA, A, rng.uniform(-1, 1, n), x0)
 
 
+def test_staged_one_lane_and_lone_product(apcg, ctx):
+    """Rows of five to eight entries one to a lane (the staged schedule and one
+    lane per row: the same sums), and y = A x in every number of lanes."""
+    from paper_2306_17801_amd.device import DeviceCSR, DeviceVec
+
+    for n, maxrow in ((9, 8), (63, 5), (64, 7), (65, 8), (129, 6), (4099, 8), (1000, 16), (1000, 32), (700, 64)):
+        A = uneven(n, maxrow, n)
+        print(f"case staged one lane n={n} maxrow={maxrow}", flush=True)
+        dA = DeviceCSR(A)
+        rng = np.random.default_rng(n)
+        x = rng.uniform(-1, 1, n)
+        ref = np.array([np.dot(A.val[s:e], x[A.col[s:e]]) for s, e in zip(A.rowptr, A.rowptr[1:])])
+        big = np.array([np.abs(A.val[s:e] * x[A.col[s:e]]).sum() for s, e in zip(A.rowptr, A.rowptr[1:])])
+        dx, got = DeviceVec(x), {}
+        for sched, lanes in ((1, 1), (0, 1), (0, 2), (0, 4), (0, 8), (0, 16)):
+            if sched == 1 and maxrow > 8:  # too long for the staged schedule
+                continue
+            for block in (256, 512):
+                dy = DeviceVec.zeros(n)
+                apcg.apcg_mat_set_spmv_config(dA.h, lanes, block, 0, sched)
+                apcg.apcg_mat_mult_async(dA.h, dx.h, dy.h, ctx)
+                apcg.apcg_ctx_synchronize(ctx)
+                got[sched, lanes, block] = dy.numpy()
+                # at most 64 additions and products of entries whose magnitudes sum to `big`
+                assert np.all(np.abs(got[sched, lanes, block] - ref) <= 65 * 2.0**-53 * 2 * big)
+                if lanes == 1 and maxrow <= 8:
+                    check(apcg, ctx, dA, A, rng.uniform(-1, 1, n), None)
+        assert all(np.array_equal(v, got[0, 1, 256]) for k, v in got.items() if k[1] == 1)
+
+
 def test_staged_rows_longer_than_the_stage(apcg, ctx):
     """Row 700 names 1100 others: the setup reads it in three pieces.  Then the
     same arrays, made for rows of five entries, are rewritten with it."""
