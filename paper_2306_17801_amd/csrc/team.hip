@@ -465,6 +465,18 @@ apcg_status team_clear(hipStream_t st, uint64_t *words, int64_t n) {
     return APCG_SUCCESS;
 }
 
+apcg_status team_swap(TeamCache *t, hipStream_t st, int64_t words, int64_t tags, uint32_t *tag) {
+    if (t->swap_cap < words || t->tag + tags > (int64_t)1 << 32) {
+        apcg_status s;
+        if ((s = grow(&t->d_swap, &t->swap_cap, std::max<int64_t>(words, 64), t->device, st))) return s;
+        if ((s = team_clear(st, t->d_swap, t->swap_cap))) return s;
+        t->tag = 1;
+    }
+    *tag = (uint32_t)t->tag;
+    t->tag += tags;
+    return APCG_SUCCESS;
+}
+
 apcg_status team_upload(TeamCache *t, hipStream_t st, const void *sys, int64_t sys_bytes,
                         const std::vector<int32_t> &order, const std::vector<int32_t> &members, const char **d_sys,
                         const int2 **d_tickets) {

@@ -472,13 +472,8 @@ apcg_status team_fcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
     // tags of this launch: at most nine exchanges for every iteration and
     // every restart, one restart a system and one more for its start
     const int64_t tags = 9 * ((int64_t)maxit + 4);
-    if (t->swap_cap < swap || t->tag + tags > (int64_t)1 << 32) {
-        if ((s = grow(&t->d_swap, &t->swap_cap, std::max<int64_t>(swap, 64), t->device, st))) return s;
-        if ((s = team_clear(st, t->d_swap, t->swap_cap))) return s;
-        t->tag = 1;
-    }
-    const uint32_t tag = (uint32_t)t->tag;
-    t->tag += tags;
+    uint32_t tag;
+    if ((s = team_swap(t, st, swap, tags, &tag))) return s;
     const int64_t head = (8 + (int64_t)nsys * 4 + 63) / 64 * 64;
     const int64_t sync_bytes = head + 8 * words + marks;
     if ((s = team_memory(t, st, team_desc_bytes((int64_t)sizeof(TeamFcgSys) * nsys, tickets), sync_bytes, 0))) return s;

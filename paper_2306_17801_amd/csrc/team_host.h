@@ -1,4 +1,5 @@
-// team_host.h -- host side of the team solves (team.hip, team_fcg.hip).
+// team_host.h -- host side of the team solves (team.hip, team_fcg.hip,
+// team_tfqmr.hip).
 #pragma once
 
 #include <algorithm>
@@ -105,6 +106,10 @@ inline int64_t team_desc_bytes(int64_t sys_bytes, int64_t tickets) { return sys_
 // Clears n words on stream st (a kernel: a launch may be captured).
 apcg_status team_clear(hipStream_t st, uint64_t *words, int64_t n);
 
+// Makes room for so many words of border exchanges and sets tags aside that
+// no word there carries; *tag is the first.
+apcg_status team_swap(TeamCache *t, hipStream_t st, int64_t words, int64_t tags, uint32_t *tag);
+
 // Uploads the systems' descriptors and the tickets (members[i] of system i,
 // systems in `order`) unless the device holds them already.
 apcg_status team_upload(TeamCache *t, hipStream_t st, const void *sys, int64_t sys_bytes,
@@ -138,6 +143,10 @@ apcg_status team_fcg_solve(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const 
                            const std::vector<int32_t> &order, double rtol, int32_t maxit, const apcg_solve_opts &opts,
                            const apcg_fcg_opts &fo, const float *coeffs, const double *lmax, apcg_solve_info *info,
                            std::vector<int32_t> *left);
+// TFQMR of one system with members of 2048 rows (team_eligible: rows == 4),
+// as apcg_ksp_solve_tfqmr; otherwise as team_pcg_solve.
+apcg_status team_tfqmr_solve(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, double rtol, int32_t maxit,
+                             const apcg_solve_opts &opts, apcg_solve_info *info, std::vector<int32_t> *left);
 // The tags one flexible launch may use are limited (see team_fcg.hip).
 constexpr int32_t kTeamFcgMaxIts = 100000000;
 
