@@ -40,6 +40,7 @@ constexpr int LABEL_Q = 16;
 constexpr double LABEL_SHIFT = 3.0;
 constexpr double LABEL_FLOOR = 1e-3;  // keeps the target's minimum away from zero
 constexpr int OFF_W1 = 0, OFF_B1 = 1024, OFF_W2 = 1088, OFF_B2 = 5184, OFF_W3 = 5248, OFF_B3 = 5824;
+static_assert(OFF_B3 + NC == NPARAM, "parameter layout");
 
 // Row statistics, pass 1 -> partials [7][G] (dev::RowStats order).
 __global__ __launch_bounds__(FB) void k_feat_rows(int32_t n, const int32_t *__restrict__ rowptr,
@@ -215,7 +216,6 @@ __global__ void k_phi_grid(float *phi) {
 
 // One workgroup of 64 threads per sample.
 __global__ __launch_bounds__(64) void k_mlp_fwd(const float *__restrict__ P, const float *__restrict__ X, int B,
-                                                float *__restrict__ H1, float *__restrict__ H2,
                                                 float *__restrict__ C) {
     const int b = blockIdx.x, j = threadIdx.x;
     if (b >= B) return;
@@ -226,13 +226,11 @@ __global__ __launch_bounds__(64) void k_mlp_fwd(const float *__restrict__ P, con
     for (int k = 0; k < NF; ++k) a = fmaf(P[OFF_W1 + j * NF + k], x[k], a);
     const float t1 = tanhf(a);
     h1[j] = t1;
-    if (H1) H1[b * NH + j] = t1;
     __syncthreads();
     a = P[OFF_B2 + j];
     for (int k = 0; k < NH; ++k) a = fmaf(P[OFF_W2 + j * NH + k], h1[k], a);
     const float t2 = tanhf(a);
     h2[j] = t2;
-    if (H2) H2[b * NH + j] = t2;
     __syncthreads();
     if (j < NC) {
         a = P[OFF_B3 + j];
@@ -241,115 +239,237 @@ __global__ __launch_bounds__(64) void k_mlp_fwd(const float *__restrict__ P, con
     }
 }
 
-// Per-sample loss and dL/dc (already divided by B for the mean loss).
-__global__ __launch_bounds__(64) void k_mlp_loss(const float *__restrict__ C, const float *__restrict__ G,
-                                                 const float *__restrict__ h, const float *__restrict__ phi, int B,
-                                                 float mu, float eps, float *__restrict__ dC,
-                                                 float *__restrict__ loss_b) {
-    const int b = blockIdx.x, t = threadIdx.x;
+// Everything of a training step that belongs to one sample, one wavefront
+// each, four to a workgroup that brings the weights through LDS once: the
+// network, the loss, dL/dc (divided by B for the mean loss) and the
+// back-propagated activation gradients dA2 = (dC W3) (1 - h2^2), dA1 =
+// (dA2 W2) (1 - h1^2).  What bounds it is latency: as three kernels of one
+// wavefront a workgroup, each reading its weights row by row from the caches,
+// 11 us for 128 samples; 7.7 here (13 with the loads of one table waiting for
+// those of the last).
+constexpr int SPW = 4;  // samples (wavefronts) per workgroup
+__global__ __launch_bounds__(64 * SPW) void k_mlp_sample(const float *__restrict__ P, const float *__restrict__ X,
+                                                         const float *__restrict__ G, const float *__restrict__ h,
+                                                         const float *__restrict__ phi_in, int B, float mu, float eps,
+                                                         float *__restrict__ H1, float *__restrict__ H2,
+                                                         float *__restrict__ dC, float *__restrict__ dA1,
+                                                         float *__restrict__ dA2, float *__restrict__ loss_b) {
+    // rows an odd number of words apart: lanes reading a column hit different banks
+    __shared__ float w1[NH][NF + 1], w2[NH][NH + 1], w3[NC][NH + 1], b1[NH], b2[NH], b3[NC], phi[QGRID * NC];
+    struct Sample {
+        float x[NF], h1[NH], h2[NH], da2[NH], viol[QGRID], g[NC * NC], h[NC], c[NC], dc[NC], gc[NC];
+    };
+    __shared__ Sample all[SPW];
+    const int tid = threadIdx.x, wave = tid >> 6, j = tid & 63, b = blockIdx.x * SPW + wave;
+    Sample &s = all[wave];
+    // everything this thread brings, all of it in flight before the first use
+    constexpr int NT = 64 * SPW, N3 = (NC * NH + NT - 1) / NT, NP = (QGRID * NC + NT - 1) / NT, NG = (NC * NC + 63) / 64;
+    static_assert(NH * NF % NT == 0 && NH * NH % NT == 0 && 2 * NH + NC <= NT, "shares of a thread");
+    const int bs = min(b, B - 1);
+    float v1[NH * NF / NT], v2[NH * NH / NT], v3[N3], vp[NP], vg[NG];
+    const float vx = X[bs * NF + j % NF], vh = h[bs * NC + j % NC];
+#pragma unroll
+    for (int q = 0; q < NG; ++q) vg[q] = G[bs * NC * NC + min(q * 64 + j, NC * NC - 1)];
+#pragma unroll
+    for (int q = 0; q < NH * NF / NT; ++q) v1[q] = P[OFF_W1 + q * NT + tid];
+#pragma unroll
+    for (int q = 0; q < NH * NH / NT; ++q) v2[q] = P[OFF_W2 + q * NT + tid];
+#pragma unroll
+    for (int q = 0; q < N3; ++q) v3[q] = P[OFF_W3 + min(q * NT + tid, NC * NH - 1)];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) vp[q] = phi_in[min(q * NT + tid, QGRID * NC - 1)];
+    const float vb = P[tid < NH ? OFF_B1 + tid : tid < 2 * NH ? OFF_B2 + tid - NH : OFF_B3 + min(tid - 2 * NH, NC - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+    if (j < NF) s.x[j] = vx;
+    if (j < NC) s.h[j] = vh;
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+        if (q * 64 + j < NC * NC) s.g[q * 64 + j] = vg[q];
+#pragma unroll
+    for (int q = 0; q < NH * NF / NT; ++q) w1[(q * NT + tid) / NF][tid % NF] = v1[q];
+#pragma unroll
+    for (int q = 0; q < NH * NH / NT; ++q) w2[(q * NT + tid) / NH][tid % NH] = v2[q];
+#pragma unroll
+    for (int q = 0; q < N3; ++q)
+        if (q * NT + tid < NC * NH) w3[(q * NT + tid) / NH][tid % NH] = v3[q];
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+        if (q * NT + tid < QGRID * NC) phi[q * NT + tid] = vp[q];
+    if (tid < NH) b1[tid] = vb;
+    else if (tid < 2 * NH) b2[tid - NH] = vb;
+    else if (tid < 2 * NH + NC) b3[tid - 2 * NH] = vb;
+    __syncthreads();
     if (b >= B) return;
-    __shared__ float c[NC], viol[QGRID];
-    if (t < NC) c[t] = C[b * NC + t];
-    __syncthreads();
-    float q = 0.f;
-    for (int j = 0; j < NC; ++j) q = fmaf(phi[t * NC + j], c[j], q);
-    viol[t] = fmaxf(0.f, eps - q);
-    __syncthreads();
-    const float scale = mu / (float)QGRID;
-    if (t < NC) {
-        float g = -2.f * h[b * NC + t];
-        for (int k = 0; k < NC; ++k) g = fmaf(2.f * G[b * NC * NC + t * NC + k], c[k], g);
-        float pen = 0.f;
-        for (int qq = 0; qq < QGRID; ++qq) pen = fmaf(viol[qq], phi[qq * NC + t], pen);
-        g = fmaf(-2.f * scale, pen, g);
-        dC[b * NC + t] = g / (float)B;
+    float a = b1[j];
+#pragma unroll
+    for (int k = 0; k < NF; ++k) a = fmaf(w1[j][k], s.x[k], a);
+    const float h1 = tanhf(a);
+    s.h1[j] = h1;
+    dev::wave_lds_fence();
+    a = b2[j];
+#pragma unroll
+    for (int k = 0; k < NH; ++k) a = fmaf(w2[j][k], s.h1[k], a);
+    const float h2 = tanhf(a);
+    s.h2[j] = h2;
+    dev::wave_lds_fence();
+    if (j < NC) {
+        a = b3[j];
+#pragma unroll
+        for (int k = 0; k < NH; ++k) a = fmaf(w3[j][k], s.h2[k], a);
+        s.c[j] = a;
     }
-    if (t == 0) {
-        float L = 1.f;
-        for (int j = 0; j < NC; ++j) {
-            float gc = 0.f;
-            for (int k = 0; k < NC; ++k) gc = fmaf(G[b * NC * NC + j * NC + k], c[k], gc);
-            L = fmaf(c[j], gc - 2.f * h[b * NC + j], L);
+    dev::wave_lds_fence();
+    float q = 0.f;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) q = fmaf(phi[j * NC + k], s.c[k], q);
+    s.viol[j] = fmaxf(0.f, eps - q);
+    dev::wave_lds_fence();
+    const float scale = mu / (float)QGRID;
+    if (j < NC) {
+        float g = -2.f * s.h[j], gc = 0.f, pen = 0.f;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            g = fmaf(2.f * s.g[j * NC + k], s.c[k], g);
+            gc = fmaf(s.g[j * NC + k], s.c[k], gc);
         }
-        float pen = 0.f;
-        for (int qq = 0; qq < QGRID; ++qq) pen = fmaf(viol[qq], viol[qq], pen);
+#pragma unroll
+        for (int k = 0; k < QGRID; ++k) pen = fmaf(s.viol[k], phi[k * NC + j], pen);
+        g = fmaf(-2.f * scale, pen, g);
+        s.dc[j] = g / (float)B;
+        s.gc[j] = gc;
+        dC[b * NC + j] = s.dc[j];
+    }
+    dev::wave_lds_fence();
+    a = 0.f;
+#pragma unroll
+    for (int o = 0; o < NC; ++o) a = fmaf(s.dc[o], w3[o][j], a);
+    const float d2 = a * (1.f - h2 * h2);
+    s.da2[j] = d2;
+    dev::wave_lds_fence();
+    a = 0.f;
+#pragma unroll
+    for (int k = 0; k < NH; ++k) a = fmaf(s.da2[k], w2[k][j], a);
+    H1[b * NH + j] = h1;
+    H2[b * NH + j] = h2;
+    dA2[b * NH + j] = d2;
+    dA1[b * NH + j] = a * (1.f - h1 * h1);
+    if (j == 0) {
+        float L = 1.f, pen = 0.f;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) L = fmaf(s.c[k], s.gc[k] - 2.f * s.h[k], L);
+#pragma unroll
+        for (int k = 0; k < QGRID; ++k) pen = fmaf(s.viol[k], s.viol[k], pen);
         loss_b[b] = fmaf(scale, pen, L);
     }
 }
 
-// Per-sample back-propagated activation gradients dA2 = (dC W3) (1 - h2^2),
-// dA1 = (dA2 W2) (1 - h1^2).
-__global__ __launch_bounds__(64) void k_mlp_bwd_act(const float *__restrict__ P, const float *__restrict__ dC,
-                                                    const float *__restrict__ H1, const float *__restrict__ H2, int B,
-                                                    float *__restrict__ dA1, float *__restrict__ dA2) {
-    const int b = blockIdx.x, j = threadIdx.x;
-    if (b >= B) return;
-    __shared__ float dc[NC], da2[NH];
-    if (j < NC) dc[j] = dC[b * NC + j];
-    __syncthreads();
-    float a = 0.f;
-    for (int o = 0; o < NC; ++o) a = fmaf(dc[o], P[OFF_W3 + o * NH + j], a);
-    const float h2 = H2[b * NH + j];
-    const float d2 = a * (1.f - h2 * h2);
-    da2[j] = d2;
-    dA2[b * NH + j] = d2;
-    __syncthreads();
-    a = 0.f;
-    for (int k = 0; k < NH; ++k) a = fmaf(da2[k], P[OFF_W2 + k * NH + j], a);
-    const float h1 = H1[b * NH + j];
-    dA1[b * NH + j] = a * (1.f - h1 * h1);
+struct Adam {
+    float *P, *m, *v;  // P == nullptr: no step
+    int t;
+    float lr, b1, b2, eps;
+};
+
+__device__ __forceinline__ void adam_step(const Adam &o, int p, float gi) {
+    const float mi = o.b1 * o.m[p] + (1.f - o.b1) * gi;
+    const float vi = o.b2 * o.v[p] + (1.f - o.b2) * gi * gi;
+    o.m[p] = mi;
+    o.v[p] = vi;
+    const float mh = mi / (1.f - powf(o.b1, (float)o.t));
+    const float vh = vi / (1.f - powf(o.b2, (float)o.t));
+    o.P[p] -= o.lr * mh / (sqrtf(vh) + o.eps);
 }
 
-// Parameter gradients: one thread per parameter, sum over samples in order.
+// Parameter gradients, one thread per parameter, the sum over samples in
+// order, and the Adam step on them; the last workgroup forms the mean loss.
+// Each layer's gradient is the product of two activation arrays over the
+// samples: a workgroup takes 16 x 16 of its entries and brings GCH samples of
+// both arrays through LDS at a time, the next ones in flight (a thread per
+// parameter reading both for every sample waited for the caches: 33 us at 128
+// samples, and 7 and 4 for the loss and the step in kernels of their own;
+// 5.3 in all here).
+constexpr int GCH = 128;
+constexpr int GRAD_TILES = NH / 16 + (NH / 16) * (NH / 16) + NH / 16;
 __global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ X, const float *__restrict__ H1,
                                                   const float *__restrict__ H2, const float *__restrict__ dC,
                                                   const float *__restrict__ dA1, const float *__restrict__ dA2, int B,
-                                                  float *__restrict__ grad) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= NPARAM) return;
-    float g = 0.f;
-    if (p < OFF_B1) {
-        const int j = p / NF, k = p % NF;
-        for (int b = 0; b < B; ++b) g = fmaf(dA1[b * NH + j], X[b * NF + k], g);
-    } else if (p < OFF_W2) {
-        const int j = p - OFF_B1;
-        for (int b = 0; b < B; ++b) g += dA1[b * NH + j];
-    } else if (p < OFF_B2) {
-        const int j = (p - OFF_W2) / NH, k = (p - OFF_W2) % NH;
-        for (int b = 0; b < B; ++b) g = fmaf(dA2[b * NH + j], H1[b * NH + k], g);
-    } else if (p < OFF_W3) {
-        const int j = p - OFF_B2;
-        for (int b = 0; b < B; ++b) g += dA2[b * NH + j];
-    } else if (p < OFF_B3) {
-        const int o = (p - OFF_W3) / NH, k = (p - OFF_W3) % NH;
-        for (int b = 0; b < B; ++b) g = fmaf(dC[b * NC + o], H2[b * NH + k], g);
-    } else {
-        const int o = p - OFF_B3;
-        for (int b = 0; b < B; ++b) g += dC[b * NC + o];
+                                                  const float *__restrict__ loss_b, float *__restrict__ loss,
+                                                  float *__restrict__ grad, Adam adam) {
+    __shared__ float sa[GCH][16], sb[GCH][16];
+    const int tid = threadIdx.x;
+    if (blockIdx.x == GRAD_TILES) {
+        double s = 0.0;
+        float *l = sa[0];
+        for (int c0 = 0; c0 < B; c0 += GCH * 16) {
+            const int cnt = min(GCH * 16, B - c0);
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < GCH * 16 / 256; ++q)
+                if (q * 256 + tid < cnt) l[q * 256 + tid] = loss_b[c0 + q * 256 + tid];
+            __syncthreads();
+            if (tid == 0) {
+#pragma unroll 8
+                for (int k = 0; k < cnt; ++k) s += l[k];
+            }
+        }
+        if (tid == 0) *loss = (float)(s / B);
+        return;
     }
-    grad[p] = g;
-}
-
-__global__ __launch_bounds__(256) void k_adam(float *__restrict__ P, const float *__restrict__ g,
-                                              float *__restrict__ m, float *__restrict__ v, int t, float lr, float b1,
-                                              float b2, float eps) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= NPARAM) return;
-    const float gi = g[p];
-    const float mi = b1 * m[p] + (1.f - b1) * gi;
-    const float vi = b2 * v[p] + (1.f - b2) * gi * gi;
-    m[p] = mi;
-    v[p] = vi;
-    const float mh = mi / (1.f - powf(b1, (float)t));
-    const float vh = vi / (1.f - powf(b2, (float)t));
-    P[p] -= lr * mh / (sqrtf(vh) + eps);
-}
-
-__global__ void k_loss_mean(const float *loss_b, int B, float *out) {
-    if (threadIdx.x != 0) return;
-    double s = 0.0;
-    for (int b = 0; b < B; ++b) s += loss_b[b];
-    *out = (float)(s / B);
+    // entries (row, k) of dA1 x X, dA2 x H1 or dC x H2: rows and columns of
+    // this tile, and where W and the bias of the layer lie
+    const float *ra, *rb;
+    int na, nb, row0, k0, off_w, off_b;
+    const int t = blockIdx.x;
+    if (t < NH / 16) {
+        ra = dA1, rb = X, na = NH, nb = NF, row0 = 16 * t, k0 = 0, off_w = OFF_W1, off_b = OFF_B1;
+    } else if (t < NH / 16 + NH / 16 * (NH / 16)) {
+        const int u = t - NH / 16;
+        ra = dA2, rb = H1, na = NH, nb = NH, row0 = 16 * (u / (NH / 16)), k0 = 16 * (u % (NH / 16));
+        off_w = OFF_W2, off_b = OFF_B2;
+    } else {
+        ra = dC, rb = H2, na = NC, nb = NH, row0 = 0, k0 = 16 * (t - NH / 16 - NH / 16 * (NH / 16));
+        off_w = OFF_W3, off_b = OFF_B3;
+    }
+    const int r = tid / 16, k = tid % 16;
+    constexpr int PT = GCH * 16 / 256;  // staged entries of either array per thread
+    const int ca = row0 + k < na ? row0 + k : 0;  // (the output layer has 9 rows)
+    float va[PT], vb[PT];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int q = 0; q < PT; ++q) {
+            const int b = min(c0 + q * 16 + r, B - 1);
+            va[q] = ra[b * na + ca];
+            vb[q] = rb[b * nb + k0 + k];
+        }
+    };
+    float g = 0.f, gb = 0.f;
+    fetch(0);
+    for (int c0 = 0; c0 < B; c0 += GCH) {
+        const int cnt = min(GCH, B - c0);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PT; ++q) {
+            sa[q * 16 + r][k] = va[q];
+            sb[q * 16 + r][k] = vb[q];
+        }
+        __syncthreads();
+        if (c0 + GCH < B) fetch(c0 + GCH);
+#pragma unroll 16
+        for (int b = 0; b < cnt; ++b) {
+            g = fmaf(sa[b][r], sb[b][k], g);
+            gb += sa[b][r];
+        }
+    }
+    if (row0 + r >= na) return;
+    const int p = off_w + (row0 + r) * nb + k0 + k, pb = off_b + row0 + r;
+    const bool bias = k0 == 0 && k == 0;
+    if (grad) {
+        grad[p] = g;
+        if (bias) grad[pb] = gb;
+    }
+    if (adam.P) {
+        adam_step(adam, p, g);
+        if (bias) adam_step(adam, pb, gb);
+    }
 }
 
 // Column statistics (two-pass) and in-place standardisation of X [B, 16].
@@ -377,17 +497,15 @@ __global__ void k_standardize(float *X, int B, float *mean, float *stdv, int com
 struct MlpScratch {
     int device = 0;
     int64_t cap = 0;
-    float *buf = nullptr;  // H1, H2, C, dC, dA1, dA2, loss_b, grad, phi
+    float *buf = nullptr;  // H1, H2, dA1, dA2, dC, loss_b, phi
     float *H1() const { return buf; }
     float *H2() const { return buf + cap * NH; }
-    float *C() const { return buf + 2 * cap * NH; }
-    float *dC() const { return buf + 2 * cap * NH + cap * NC; }
-    float *dA1() const { return buf + 2 * cap * NH + 2 * cap * NC; }
-    float *dA2() const { return buf + 3 * cap * NH + 2 * cap * NC; }
-    float *loss_b() const { return buf + 4 * cap * NH + 2 * cap * NC; }
-    float *grad() const { return buf + 4 * cap * NH + 2 * cap * NC + cap; }
-    float *phi() const { return grad() + NPARAM; }
-    static size_t floats(int64_t cap) { return (size_t)(4 * cap * NH + 2 * cap * NC + cap + NPARAM + QGRID * NC); }
+    float *dA1() const { return buf + 2 * cap * NH; }
+    float *dA2() const { return buf + 3 * cap * NH; }
+    float *dC() const { return buf + 4 * cap * NH; }
+    float *loss_b() const { return dC() + cap * NC; }
+    float *phi() const { return loss_b() + cap; }
+    static size_t floats(int64_t cap) { return (size_t)(4 * cap * NH + cap * NC + cap + QGRID * NC); }
 };
 
 struct FeatScratch {
@@ -491,8 +609,7 @@ apcg_status mlp_infer(apcg_ctx ctx, const float *params, const float *mean, cons
     if (B < 1) return APCG_SUCCESS;
     hipLaunchKernelGGL(k_standardize, dim3(1), dim3(64), 0, ctx->stream, X, B, (float *)mean, (float *)std, 0);
     APCG_CHECK_LAUNCH("k_standardize");
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(B), dim3(64), 0, ctx->stream, params, (const float *)X, B, (float *)nullptr,
-                       (float *)nullptr, C);
+    hipLaunchKernelGGL(k_mlp_fwd, dim3(B), dim3(64), 0, ctx->stream, params, (const float *)X, B, C);
     APCG_CHECK_LAUNCH("k_mlp_fwd");
     return APCG_SUCCESS;
 }
@@ -662,8 +779,7 @@ apcg_status apcg_ksp_solve_learned(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_ve
         hipLaunchKernelGGL(k_standardize, dim3(1), dim3(64), 0, ctx->stream, feat, 1, (float *)dev_mean,
                            (float *)dev_std, 0);
         APCG_CHECK_LAUNCH("k_standardize");
-        hipLaunchKernelGGL(k_mlp_fwd, dim3(1), dim3(64), 0, ctx->stream, dev_params, (const float *)feat, 1,
-                           (float *)nullptr, (float *)nullptr, coef);
+        hipLaunchKernelGGL(k_mlp_fwd, dim3(1), dim3(64), 0, ctx->stream, dev_params, (const float *)feat, 1, coef);
         APCG_CHECK_LAUNCH("k_mlp_fwd");
         apcg_solve_opts o;
         if (opts) o = *opts;
@@ -701,9 +817,29 @@ apcg_status apcg_mlp_standardize(apcg_ctx ctx, float *dev_X, int32_t B, float *d
 apcg_status apcg_mlp_forward(apcg_ctx ctx, const float *dev_params, const float *dev_X, int32_t B, float *dev_C) {
     if (!ctx || !dev_params || !dev_X || !dev_C || B < 1) return set_error(APCG_ERR_INVALID_ARG, "bad arguments");
     APCG_HIP(hipSetDevice(ctx->device));
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(B), dim3(64), 0, ctx->stream, dev_params, dev_X, B, (float *)nullptr,
-                       (float *)nullptr, dev_C);
+    hipLaunchKernelGGL(k_mlp_fwd, dim3(B), dim3(64), 0, ctx->stream, dev_params, dev_X, B, dev_C);
     APCG_CHECK_LAUNCH("k_mlp_fwd");
+    if (ctx->type == APCG_STREAM_GLOBAL_BLOCKING) APCG_HIP(hipStreamSynchronize(ctx->stream));
+    return APCG_SUCCESS;
+}
+
+// Loss, gradients (dev_grad, may be NULL) and, with adam.P, the Adam step.
+static apcg_status mlp_step(apcg_ctx ctx, const float *dev_params, const float *dev_X, const float *dev_G,
+                            const float *dev_h, int32_t B, float mu, float eps, float *dev_loss, float *dev_grad,
+                            const Adam &adam) {
+    APCG_HIP(hipSetDevice(ctx->device));
+    MlpScratch *ms = mlp_scratch(ctx);
+    apcg_status s;
+    if ((s = ensure_mlp(ctx, ms, B))) return s;
+    hipStream_t st = ctx->stream;
+    hipLaunchKernelGGL(k_mlp_sample, dim3((B + SPW - 1) / SPW), dim3(64 * SPW), 0, st, dev_params, dev_X, dev_G, dev_h,
+                       (const float *)ms->phi(), B, mu, eps, ms->H1(), ms->H2(), ms->dC(), ms->dA1(), ms->dA2(),
+                       ms->loss_b());
+    APCG_CHECK_LAUNCH("k_mlp_sample");
+    hipLaunchKernelGGL(k_mlp_grad, dim3(GRAD_TILES + 1), dim3(256), 0, st, dev_X, (const float *)ms->H1(),
+                       (const float *)ms->H2(), (const float *)ms->dC(), (const float *)ms->dA1(),
+                       (const float *)ms->dA2(), B, (const float *)ms->loss_b(), dev_loss, dev_grad, adam);
+    APCG_CHECK_LAUNCH("k_mlp_grad");
     if (ctx->type == APCG_STREAM_GLOBAL_BLOCKING) APCG_HIP(hipStreamSynchronize(ctx->stream));
     return APCG_SUCCESS;
 }
@@ -713,42 +849,17 @@ apcg_status apcg_mlp_loss_grad(apcg_ctx ctx, const float *dev_params, const floa
                                float *dev_grad) {
     if (!ctx || !dev_params || !dev_X || !dev_G || !dev_h || !dev_loss || !dev_grad || B < 1)
         return set_error(APCG_ERR_INVALID_ARG, "bad arguments");
-    APCG_HIP(hipSetDevice(ctx->device));
-    MlpScratch *ms = mlp_scratch(ctx);
-    apcg_status s;
-    if ((s = ensure_mlp(ctx, ms, B))) return s;
-    hipStream_t st = ctx->stream;
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(B), dim3(64), 0, st, dev_params, dev_X, B, ms->H1(), ms->H2(), ms->C());
-    APCG_CHECK_LAUNCH("k_mlp_fwd");
-    hipLaunchKernelGGL(k_mlp_loss, dim3(B), dim3(64), 0, st, (const float *)ms->C(), dev_G, dev_h,
-                       (const float *)ms->phi(), B, mu, eps, ms->dC(), ms->loss_b());
-    APCG_CHECK_LAUNCH("k_mlp_loss");
-    hipLaunchKernelGGL(k_mlp_bwd_act, dim3(B), dim3(64), 0, st, dev_params, (const float *)ms->dC(),
-                       (const float *)ms->H1(), (const float *)ms->H2(), B, ms->dA1(), ms->dA2());
-    APCG_CHECK_LAUNCH("k_mlp_bwd_act");
-    hipLaunchKernelGGL(k_mlp_grad, dim3((NPARAM + 255) / 256), dim3(256), 0, st, dev_X, (const float *)ms->H1(),
-                       (const float *)ms->H2(), (const float *)ms->dC(), (const float *)ms->dA1(),
-                       (const float *)ms->dA2(), B, dev_grad);
-    APCG_CHECK_LAUNCH("k_mlp_grad");
-    hipLaunchKernelGGL(k_loss_mean, dim3(1), dim3(64), 0, st, (const float *)ms->loss_b(), B, dev_loss);
-    APCG_CHECK_LAUNCH("k_loss_mean");
-    if (ctx->type == APCG_STREAM_GLOBAL_BLOCKING) APCG_HIP(hipStreamSynchronize(ctx->stream));
-    return APCG_SUCCESS;
+    return mlp_step(ctx, dev_params, dev_X, dev_G, dev_h, B, mu, eps, dev_loss, dev_grad, Adam{});
 }
 
 apcg_status apcg_mlp_train_step(apcg_ctx ctx, float *dev_params, float *dev_adam_m, float *dev_adam_v, int32_t t,
                                 float lr, const float *dev_X, const float *dev_G, const float *dev_h, int32_t B,
                                 float mu, float eps, float *dev_loss) {
     if (!dev_adam_m || !dev_adam_v || t < 1) return set_error(APCG_ERR_INVALID_ARG, "bad Adam state");
-    MlpScratch *ms = mlp_scratch(ctx);
-    apcg_status s;
-    if ((s = ensure_mlp(ctx, ms, B))) return s;
-    if ((s = apcg_mlp_loss_grad(ctx, dev_params, dev_X, dev_G, dev_h, B, mu, eps, dev_loss, ms->grad()))) return s;
-    hipLaunchKernelGGL(k_adam, dim3((NPARAM + 255) / 256), dim3(256), 0, ctx->stream, dev_params,
-                       (const float *)ms->grad(), dev_adam_m, dev_adam_v, t, lr, 0.9f, 0.999f, 1e-8f);
-    APCG_CHECK_LAUNCH("k_adam");
-    if (ctx->type == APCG_STREAM_GLOBAL_BLOCKING) APCG_HIP(hipStreamSynchronize(ctx->stream));
-    return APCG_SUCCESS;
+    if (!ctx || !dev_params || !dev_X || !dev_G || !dev_h || !dev_loss || B < 1)
+        return set_error(APCG_ERR_INVALID_ARG, "bad arguments");
+    return mlp_step(ctx, dev_params, dev_X, dev_G, dev_h, B, mu, eps, dev_loss, nullptr,
+                    Adam{dev_params, dev_adam_m, dev_adam_v, t, lr, 0.9f, 0.999f, 1e-8f});
 }
 
 }  // extern "C"
