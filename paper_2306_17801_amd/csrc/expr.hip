@@ -274,10 +274,10 @@ apcg_status apcg_expr_execute(apcg_expr e, apcg_ctx ctx, const apcg_scalar *inpu
         args.nout = e->noutputs;
         for (int i = 0; i < args.ncode; ++i) args.code[i] = e->code[i];
         apcg_status s;
-        if ((s = op_begin(ctx, acc.data(), (int)acc.size()))) return s;
+        if ((s = op_begin(ctx, acc.data(), (int)acc.size(), true))) return s;
         hipLaunchKernelGGL(k_expr, dim3(1), dim3(64), 0, ctx->stream, args);
         APCG_CHECK_LAUNCH("k_expr");
-        return op_end(ctx, acc.data(), (int)acc.size());
+        return op_end(ctx, acc.data(), (int)acc.size(), true);
     } catch (const std::bad_alloc &) {
         return set_error(APCG_ERR_OUT_OF_MEMORY, "host allocation failed");
     }

@@ -69,7 +69,7 @@ extern "C" {
 apcg_status apcg_ctx_get_stream(apcg_ctx ctx, void **stream) {
     if (!ctx || !stream) return set_error(APCG_ERR_INVALID_ARG, "NULL argument");
     *stream = (void *)ctx->stream;
-    return APCG_SUCCESS;
+    return ctx_exact_events(ctx);
 }
 
 apcg_status apcg_memory_register(int32_t device, const void *ptr, int64_t bytes, uint64_t *id) {

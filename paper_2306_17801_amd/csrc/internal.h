@@ -48,6 +48,7 @@ extern Counters g_counters;
 struct Event {
     hipEvent_t e = nullptr;
     int device = 0;
+    struct ::apcg_ctx_s *open = nullptr;  // not recorded yet: the context whose group of operations it will end
     ~Event();
 };
 using EventRef = std::shared_ptr<Event>;
@@ -133,6 +134,10 @@ struct apcg_ctx_s {
     double *partials = nullptr;      // kPartialSlots * kMaxBlocks
     int32_t *pinned_flags = nullptr; // kMaxLookahead host-pinned words
     apcg::EventRef poll_ev[apcg::kMaxLookahead];
+    // one event for a group of brief operations (op_end); both under g_mu
+    apcg::EventRef open;
+    int open_ops = 0;
+    bool exact = false;  // an event after every operation: the caller holds the stream
     apcg::Workspace ws;
     std::vector<apcg::GraphEntry> graphs;
     // kernel timing (solve with kernel_timing = 1)
@@ -234,8 +239,13 @@ namespace apcg {
 
 // context helpers (runtime.hip)
 apcg_status resolve_ctx(apcg_ctx in, int device, apcg_ctx *out);  // NULL -> global default
-apcg_status op_begin(apcg_ctx c, const Acc *acc, int n);
-apcg_status op_end(apcg_ctx c, const Acc *acc, int n);
+// brief: a launch or two that nobody polls (single vector, matrix and scalar
+// operations); the same in both calls.
+apcg_status op_begin(apcg_ctx c, const Acc *acc, int n, bool brief = false);
+apcg_status op_end(apcg_ctx c, const Acc *acc, int n, bool brief = false);
+// From now on every operation of c ends with an event of its own (the caller
+// may queue work on the stream, or capture it).
+apcg_status ctx_exact_events(apcg_ctx c);
 apcg_status ensure_workspace(apcg_ctx c, int64_t n);
 // Whether two vectors share memory: the same handle, or address ranges
 // [d, d + n) that overlap (an empty range overlaps nothing).
