@@ -993,7 +993,7 @@ def main():
     else:
         prod_bytes = 12 * nnz + 4 * (n + 1) + 32 * n  # A; z, p_old read; p, w written
     csr_bytes = 12 * nnz + 4 * (n + 1) + 32 * n
-    upd_bytes = 64 * n  # x, r, p, w, dinv read; x, r, z written
+    upd_bytes = 56 * n  # r, w, dinv read and r, z written; x and both p's read and x written every second launch
     iter_bytes = prod_bytes + upd_bytes
     achieved = prod_bytes / (prod_us * 1e-6) / 1e9
     traffic = None

@@ -475,7 +475,7 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
         if (bc->sys_cap < nsys || bc->ws_cap < ws_total) {
             EventRef ev = event_get(dev);
             if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-            APCG_HIP(hipEventRecord(ev->e, st));
+            APCG_HIP(event_record(ev, st));
             BatchCache old = *bc;
             defer_release({ev}, [old]() {
                 hipSetDevice(old.device);
@@ -547,7 +547,7 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
             if (!bc->exec || bc->graph_hash != gh) {
                 if (bc->exec) {
                     EventRef ev = event_get(dev);
-                    if (ev) hipEventRecord(ev->e, st);
+                    if (ev) event_record(ev, st);
                     hipGraphExec_t oe = bc->exec;
                     hipGraph_t og = bc->graph;
                     defer_release({ev}, [oe, og, dev]() {
@@ -1106,7 +1106,7 @@ apcg_status seg_solve(apcg_ctx ctx, int32_t nsys, const BatchSys *hsys, const Ba
     if (sc->tiles_cap < nt_alloc || sc->sys_cap < nsys || sc->slices_cap < ns_alloc) {
         EventRef ev = event_get(dev);
         if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-        APCG_HIP(hipEventRecord(ev->e, st));
+        APCG_HIP(event_record(ev, st));
         SegCache old = *sc;
         defer_release({ev}, [old, dev]() mutable {
             hipSetDevice(dev);
@@ -1151,7 +1151,7 @@ apcg_status seg_solve(apcg_ctx ctx, int32_t nsys, const BatchSys *hsys, const Ba
         if (sc->tiles_t_cap < ntiles_t) {
             EventRef ev = event_get(dev);
             if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-            APCG_HIP(hipEventRecord(ev->e, st));
+            APCG_HIP(event_record(ev, st));
             SegCache old = *sc;
             defer_release({ev}, [old, dev]() mutable {
                 hipSetDevice(dev);
@@ -1274,7 +1274,7 @@ apcg_status seg_solve(apcg_ctx ctx, int32_t nsys, const BatchSys *hsys, const Ba
             if (!sc->exec || sc->graph_hash != gh) {
                 if (sc->exec) {
                     EventRef ev = event_get(dev);
-                    if (ev) hipEventRecord(ev->e, st);
+                    if (ev) event_record(ev, st);
                     hipGraphExec_t oe = sc->exec;
                     hipGraph_t og = sc->graph;
                     defer_release({ev}, [oe, og, dev]() {
@@ -1297,7 +1297,7 @@ apcg_status seg_solve(apcg_ctx ctx, int32_t nsys, const BatchSys *hsys, const Ba
             if (tail_plan && (!sc->exec_t || sc->graph_hash_t != ght)) {
                 if (sc->exec_t) {
                     EventRef ev = event_get(dev);
-                    if (ev) hipEventRecord(ev->e, st);
+                    if (ev) event_record(ev, st);
                     hipGraphExec_t oe = sc->exec_t;
                     hipGraph_t og = sc->graph_t;
                     defer_release({ev}, [oe, og, dev]() {
@@ -1330,7 +1330,7 @@ apcg_status seg_solve(apcg_ctx ctx, int32_t nsys, const BatchSys *hsys, const Ba
             g_counters.d2h_copies++;
             APCG_HIP(hipMemcpyAsync(&sc->pinned[4 * slot], sc->d_running, 4 * sizeof(int32_t), hipMemcpyDeviceToHost,
                                     st));
-            APCG_HIP(hipEventRecord(sc->poll_ev[slot]->e, st));
+            APCG_HIP(event_record(sc->poll_ev[slot], st));
             if (g >= L - 1) {
                 const int ps = (int)((g - (L - 1)) % L);
                 g_counters.host_polls++;

@@ -846,7 +846,7 @@ static apcg_status bf_core(apcg_ctx ctx, BfCache *bc, int32_t nsys, std::vector<
     if (bc->sys_cap < nsys || bc->tiles_cap < nt_alloc || bc->ws_cap < ws_need || bc->slices_cap < ns_alloc) {
         EventRef ev = event_get(dev);
         if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-        APCG_HIP(hipEventRecord(ev->e, st));
+        APCG_HIP(event_record(ev, st));
         BfCache old = *bc;
         defer_release({ev}, [old]() mutable {
             hipSetDevice(old.device);
@@ -897,7 +897,7 @@ static apcg_status bf_core(apcg_ctx ctx, BfCache *bc, int32_t nsys, std::vector<
         if (bc->tiles_t_cap < ntiles_t) {
             EventRef ev = event_get(dev);
             if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-            APCG_HIP(hipEventRecord(ev->e, st));
+            APCG_HIP(event_record(ev, st));
             BfCache old = *bc;
             defer_release({ev}, [old]() mutable {
                 hipSetDevice(old.device);
@@ -1040,7 +1040,7 @@ static apcg_status bf_core(apcg_ctx ctx, BfCache *bc, int32_t nsys, std::vector<
         if (graph && (!bc->exec || bc->graph_hash != gh)) {
             if (bc->exec) {
                 EventRef ev = event_get(dev);
-                if (ev) hipEventRecord(ev->e, st);
+                if (ev) event_record(ev, st);
                 hipGraphExec_t oe = bc->exec;
                 hipGraph_t og = bc->graph;
                 defer_release({ev}, [oe, og, dev]() {
@@ -1063,7 +1063,7 @@ static apcg_status bf_core(apcg_ctx ctx, BfCache *bc, int32_t nsys, std::vector<
         if (graph && tail_plan && (!bc->exec_t || bc->graph_hash_t != ght)) {
             if (bc->exec_t) {
                 EventRef ev = event_get(dev);
-                if (ev) hipEventRecord(ev->e, st);
+                if (ev) event_record(ev, st);
                 hipGraphExec_t oe = bc->exec_t;
                 hipGraph_t og = bc->graph_t;
                 defer_release({ev}, [oe, og, dev]() {
@@ -1097,7 +1097,7 @@ static apcg_status bf_core(apcg_ctx ctx, BfCache *bc, int32_t nsys, std::vector<
             g_counters.d2h_copies++;
             APCG_HIP(hipMemcpyAsync(&bc->pinned[4 * slot], bc->d_running, 4 * sizeof(int32_t), hipMemcpyDeviceToHost,
                                     st));
-            APCG_HIP(hipEventRecord(bc->poll_ev[slot]->e, st));
+            APCG_HIP(event_record(bc->poll_ev[slot], st));
             if (g >= L - 1) {
                 const int ps = (int)((g - (L - 1)) % L);
                 g_counters.host_polls++;
@@ -1201,7 +1201,7 @@ static apcg_status bf_features(apcg_ctx ctx, BfCache *bc, int32_t nsys, const ap
     if (bc->feat_sys_cap < nsys || bc->feat_tiles_cap < ntiles || bc->xs_cap < xs_need) {
         EventRef ev = event_get(dev);
         if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-        APCG_HIP(hipEventRecord(ev->e, st));
+        APCG_HIP(event_record(ev, st));
         BfCache old = *bc;
         defer_release({ev}, [old]() mutable {
             hipSetDevice(old.device);

@@ -498,7 +498,7 @@ extern "C" apcg_status apcg_ksp_solve_fcg_poly(apcg_ctx ctx, apcg_mat A, apcg_ve
             if (fc->ws) {
                 EventRef ev = event_get(dev);
                 if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-                APCG_HIP(hipEventRecord(ev->e, st));
+                APCG_HIP(event_record(ev, st));
                 double *old = fc->ws;
                 hipGraphExec_t oe = fc->exec;
                 hipGraph_t og = fc->graph;
@@ -593,7 +593,7 @@ extern "C" apcg_status apcg_ksp_solve_fcg_poly(apcg_ctx ctx, apcg_mat A, apcg_ve
                 if (!fc->exec || fc->gK != K || memcmp(key, fc->gkey, sizeof key) != 0) {
                     if (fc->exec) {
                         EventRef ev = event_get(dev);
-                        if (ev) hipEventRecord(ev->e, st);
+                        if (ev) event_record(ev, st);
                         hipGraphExec_t oe = fc->exec;
                         hipGraph_t og = fc->graph;
                         defer_release({ev}, [oe, og, dev]() {
@@ -642,7 +642,7 @@ extern "C" apcg_status apcg_ksp_solve_fcg_poly(apcg_ctx ctx, apcg_mat A, apcg_ve
                 g_counters.d2h_copies++;
                 APCG_HIP(hipMemcpyAsync(&fc->pinned[2 * slot], &fc->st->status, 2 * sizeof(int32_t),
                                         hipMemcpyDeviceToHost, st));
-                APCG_HIP(hipEventRecord(fc->poll_ev[slot]->e, st));
+                APCG_HIP(event_record(fc->poll_ev[slot], st));
                 if (g >= L - 1) {
                     const int ps = (int)((g - (L - 1)) % L);
                     g_counters.host_polls++;

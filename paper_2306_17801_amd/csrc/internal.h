@@ -45,14 +45,20 @@ extern Counters g_counters;
 // ---------------------------------------------------------------------------
 // pooled events and the access registry (ordering rule of Section 3.1.2)
 // ---------------------------------------------------------------------------
+struct StreamHold {  // a context's stream, destroyed when the context and every event recorded on it are gone
+    hipStream_t s = nullptr;
+    ~StreamHold();
+};
 struct Event {
     hipEvent_t e = nullptr;
+    std::shared_ptr<StreamHold> on;  // where it was recorded last
     int device = 0;
     struct ::apcg_ctx_s *open = nullptr;  // not recorded yet: the context whose group of operations it will end
     ~Event();
 };
 using EventRef = std::shared_ptr<Event>;
 EventRef event_get(int device);  // un-recorded event from the device's pool
+hipError_t event_record(const EventRef &ev, hipStream_t st);
 
 struct Record {
     uint64_t writer_ctx = 0;  // 0: never written through the library
@@ -130,6 +136,7 @@ struct apcg_ctx_s {
     int32_t device = 0;
     int32_t type = APCG_STREAM_DEFAULT;
     hipStream_t stream = nullptr;
+    std::shared_ptr<apcg::StreamHold> hold;  // owns the stream
     bool is_default_global = false;
     double *partials = nullptr;      // kPartialSlots * kMaxBlocks
     int32_t *pinned_flags = nullptr; // kMaxLookahead host-pinned words

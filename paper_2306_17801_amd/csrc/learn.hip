@@ -587,7 +587,7 @@ static apcg_status ensure_mlp(apcg_ctx c, MlpScratch *s, int64_t B) {
     if (s->buf) {
         EventRef ev = event_get(c->device);
         if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-        APCG_HIP(hipEventRecord(ev->e, c->stream));
+        APCG_HIP(event_record(ev, c->stream));
         float *old = s->buf;
         const int dev = c->device;
         defer_release({ev}, [old, dev]() {
@@ -629,7 +629,7 @@ static apcg_status feat_prepare(apcg_ctx ctx, FeatScratch *fs, int64_t n) {
         if (fs->x) {
             EventRef ev = event_get(ctx->device);
             if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-            APCG_HIP(hipEventRecord(ev->e, ctx->stream));
+            APCG_HIP(event_record(ev, ctx->stream));
             double *old = fs->x;
             const int dev = ctx->device;
             defer_release({ev}, [old, dev]() {
@@ -728,7 +728,7 @@ apcg_status apcg_pc_label(apcg_ctx ctx, apcg_mat A, apcg_vec b, double rtol, int
             if (fs->lhist) {
                 EventRef ev = event_get(ctx->device);
                 if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-                APCG_HIP(hipEventRecord(ev->e, ctx->stream));
+                APCG_HIP(event_record(ev, ctx->stream));
                 double *old = fs->lhist;
                 const int dev = ctx->device;
                 defer_release({ev}, [old, dev]() {

@@ -1782,7 +1782,7 @@ apcg_status get_graph(apcg_ctx c, const Plan &pl, const Bufs &bf, int K, int pc,
         GraphEntry old = c->graphs.front();
         c->graphs.erase(c->graphs.begin());
         EventRef ev = event_get(c->device);
-        if (ev) hipEventRecord(ev->e, c->stream);
+        if (ev) event_record(ev, c->stream);
         int dev = c->device;
         defer_release({ev}, [old, dev]() {
             hipSetDevice(dev);
@@ -1805,7 +1805,7 @@ apcg_status queue_poll(apcg_ctx c, const Bufs &bf, int slot) {
     g_counters.d2h_copies++;
     APCG_HIP(hipMemcpyAsync(&c->pinned_flags[slot], &bf.ws.state->flag, sizeof(int32_t), hipMemcpyDeviceToHost,
                             c->stream));
-    APCG_HIP(hipEventRecord(c->poll_ev[slot]->e, c->stream));
+    APCG_HIP(event_record(c->poll_ev[slot], c->stream));
     return APCG_SUCCESS;
 }
 
@@ -2019,7 +2019,7 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
         APCG_CHECK_LAUNCH("k_pcg_tail");
         if (opts.kernel_timing) {
             c->tdone = event_get(c->device);
-            if (c->tdone) APCG_HIP(hipEventRecord(c->tdone->e, st));
+            if (c->tdone) APCG_HIP(event_record(c->tdone, st));
         }
         return op_end(c, acc, 4);
     } catch (const std::bad_alloc &) {

@@ -41,6 +41,31 @@ apcg_status hip_error(hipError_t e, const char *what) {
 static std::mutex g_ev_mu;
 static std::map<int, std::vector<hipEvent_t>> g_ev_pool;
 
+// The streams in use.  An event is queried and waited for after its context
+// has gone (an object outlives the context that wrote it), and an event of a
+// destroyed stream still refers to it: so the events keep their stream.
+static std::map<hipStream_t, std::weak_ptr<StreamHold>> g_streams;  // under g_ev_mu
+
+StreamHold::~StreamHold() {
+    if (!s) return;
+    {
+        std::lock_guard<std::mutex> lk(g_ev_mu);
+        g_streams.erase(s);
+    }
+    hipStreamDestroy(s);
+}
+
+hipError_t event_record(const EventRef &ev, hipStream_t st) {
+    std::shared_ptr<StreamHold> hold;
+    {
+        std::lock_guard<std::mutex> lk(g_ev_mu);
+        auto it = g_streams.find(st);
+        if (it != g_streams.end()) hold = it->second.lock();
+    }
+    ev->on = std::move(hold);  // (may destroy the stream it was recorded on before: outside the lock)
+    return hipEventRecord(ev->e, st);
+}
+
 Event::~Event() {
     if (e) {
         std::lock_guard<std::mutex> lk(g_ev_mu);
@@ -138,7 +163,7 @@ static apcg_status end_group(apcg_ctx c) {
     c->open = nullptr;
     c->open_ops = 0;
     ev->open = nullptr;
-    APCG_HIP(hipEventRecord(ev->e, c->stream));
+    APCG_HIP(event_record(ev, c->stream));
     return APCG_SUCCESS;
 }
 
@@ -174,6 +199,12 @@ static apcg_status ctx_init(apcg_ctx c, int32_t device, int32_t type) {
     c->type = type;
     APCG_HIP(hipSetDevice(device));
     APCG_HIP(hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking));
+    c->hold = std::make_shared<StreamHold>();
+    c->hold->s = c->stream;
+    {
+        std::lock_guard<std::mutex> lk(g_ev_mu);
+        g_streams[c->stream] = c->hold;
+    }
     APCG_HIP(hipMalloc((void **)&c->partials, sizeof(double) * kPartialSlots * kMaxBlocks));
     APCG_HIP(hipHostMalloc((void **)&c->pinned_flags, sizeof(int32_t) * kMaxLookahead, hipHostMallocDefault));
     for (int i = 0; i < kMaxLookahead; ++i) c->pinned_flags[i] = 0;
@@ -198,8 +229,7 @@ static void ctx_release_now(apcg_ctx c) {
     if (c->ws.state) hipFree(c->ws.state);
     if (c->partials) hipFree(c->partials);
     if (c->pinned_flags) hipHostFree(c->pinned_flags);
-    if (c->stream) hipStreamDestroy(c->stream);
-    delete c;
+    delete c;  // (and the stream, unless an event still refers to it)
 }
 
 apcg_status resolve_ctx(apcg_ctx in, int device, apcg_ctx *out) {
@@ -332,7 +362,7 @@ apcg_status ensure_workspace(apcg_ctx c, int64_t n) {
     if (c->ws.base) {
         EventRef ev = event_get(c->device);
         if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-        APCG_HIP(hipEventRecord(ev->e, c->stream));
+        APCG_HIP(event_record(ev, c->stream));
         double *old = c->ws.base;
         int dev = c->device;
         // graphs captured with the old buffers are stale now
@@ -465,7 +495,7 @@ apcg_status apcg_ctx_destroy(apcg_ctx ctx) {
     }
     EventRef ev = event_get(ctx->device);
     if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-    APCG_HIP(hipEventRecord(ev->e, ctx->stream));
+    APCG_HIP(event_record(ev, ctx->stream));
     defer_release({ev}, [ctx]() { ctx_release_now(ctx); });
     reap();
     return APCG_SUCCESS;
@@ -479,7 +509,7 @@ apcg_status apcg_ctx_wait_for(apcg_ctx waiter, apcg_ctx waitee) {
     APCG_HIP(hipSetDevice(waitee->device));
     EventRef ev = event_get(waitee->device);
     if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-    APCG_HIP(hipEventRecord(ev->e, waitee->stream));
+    APCG_HIP(event_record(ev, waitee->stream));
     APCG_HIP(hipSetDevice(waiter->device));
     g_counters.stream_waits++;
     APCG_HIP(hipStreamWaitEvent(waiter->stream, ev->e, 0));
@@ -522,7 +552,7 @@ apcg_status apcg_ctx_fork(apcg_ctx parent, int32_t n, apcg_ctx *children) {
     APCG_HIP(hipSetDevice(parent->device));
     EventRef ev = event_get(parent->device);
     if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-    APCG_HIP(hipEventRecord(ev->e, parent->stream));
+    APCG_HIP(event_record(ev, parent->stream));
     for (int32_t i = 0; i < n; ++i) {
         apcg_ctx c = new apcg_ctx_s();
         apcg_status s = ctx_init(c, parent->device, parent->type == APCG_STREAM_GLOBAL_BLOCKING
@@ -1167,7 +1197,7 @@ static apcg_status timer_mark(EventRef *slot, apcg_ctx ctx) {
         *slot = timing_event_get(ctx->device);
         if (!*slot) return set_error(APCG_ERR_HIP, "event creation failed");
     }
-    APCG_HIP(hipEventRecord((*slot)->e, ctx->stream));
+    APCG_HIP(event_record((*slot), ctx->stream));
     return APCG_SUCCESS;
 }
 

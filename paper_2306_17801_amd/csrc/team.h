@@ -159,35 +159,21 @@ __device__ __forceinline__ void load_message(gptr<uint64_t> words, uint32_t i, u
     }
 }
 
-// Eight (four) pairs of words at once, one from each place i of the buffer.
+// Four pairs of words at once, one from each place i of the buffer.
 // (Addresses in vector registers: a scalar base written by the vector unit
 // just before would need wait states that the compiler does not put before an
 // asm block.)
-template <int N>
-__device__ __forceinline__ void load_pairs(gptr<uint64_t> words, const uint32_t (&i)[N], uint64_t (&w)[N][2]) {
-    static_assert(N == 4 || N == 8, "pairs in flight");
+__device__ __forceinline__ void load_pairs(gptr<uint64_t> words, const uint32_t (&i)[4], uint64_t (&w)[4][2]) {
     typedef uint32_t v4 __attribute__((ext_vector_type(4)));
-    v4 a[N];
-    if constexpr (N == 4)
-        asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
-                     "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\t"
-                     "s_waitcnt vmcnt(0)"
-                     : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3])
-                     : "v"(at(words, i[0])), "v"(at(words, i[1])), "v"(at(words, i[2])), "v"(at(words, i[3]))
-                     : "memory");
-    else
-        asm volatile("global_load_dwordx4 %0, %8, off sc1\n\tglobal_load_dwordx4 %1, %9, off sc1\n\t"
-                     "global_load_dwordx4 %2, %10, off sc1\n\tglobal_load_dwordx4 %3, %11, off sc1\n\t"
-                     "global_load_dwordx4 %4, %12, off sc1\n\tglobal_load_dwordx4 %5, %13, off sc1\n\t"
-                     "global_load_dwordx4 %6, %14, off sc1\n\tglobal_load_dwordx4 %7, %15, off sc1\n\t"
-                     "s_waitcnt vmcnt(0)"
-                     : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(a[4]), "=&v"(a[5]), "=&v"(a[6]),
-                       "=&v"(a[7])
-                     : "v"(at(words, i[0])), "v"(at(words, i[1])), "v"(at(words, i[2])), "v"(at(words, i[3])),
-                       "v"(at(words, i[4])), "v"(at(words, i[5])), "v"(at(words, i[6])), "v"(at(words, i[7]))
-                     : "memory");
+    v4 a[4];
+    asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+                 "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3])
+                 : "v"(at(words, i[0])), "v"(at(words, i[1])), "v"(at(words, i[2])), "v"(at(words, i[3]))
+                 : "memory");
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
+    for (int k = 0; k < 4; ++k) {
         w[k][0] = (uint64_t)a[k][1] << 32 | a[k][0];
         w[k][1] = (uint64_t)a[k][3] << 32 | a[k][2];
     }

@@ -166,7 +166,7 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
             long long t0 = 0;
             for (int spin = 0;; ++spin) {
                 uint64_t w[kSide][2];
-                load_pairs<kSide>(z_w, at4, w);
+                load_pairs(z_w, at4, w);
                 bool all = true;
 #pragma unroll
                 for (int u = 0; u < kSide; ++u) {
@@ -405,7 +405,7 @@ TeamFn team_fn(int R, int L) { return L <= 5 ? team_fn_r<5>(R) : team_fn_r<7>(R)
 // ------------------------------------------------------------------- host
 
 std::mutex g_flight_mu;
-std::vector<TeamFlight> g_flight[64];
+std::vector<TeamFlight> *const g_flight = new std::vector<TeamFlight>[64];  // (not taken down at exit)
 
 static std::mutex g_team_mu;
 static std::vector<std::pair<uint64_t, TeamCache *>> g_team;
@@ -523,7 +523,7 @@ apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const std::vec
     g_counters.d2h_copies++;
     APCG_HIP(hipMemcpyAsync(host, t->d_sync, sizeof(uint32_t) * (nsys + 2), hipMemcpyDeviceToHost, st));
     if (!t->ev && !(t->ev = event_get(t->device))) return set_error(APCG_ERR_HIP, "event creation failed");
-    APCG_HIP(hipEventRecord(t->ev->e, st));
+    APCG_HIP(event_record(t->ev, st));
     g_counters.host_polls++;
     APCG_HIP(hipEventSynchronize(t->ev->e));
     for (int32_t i = 0; i < nsys; ++i)
@@ -571,7 +571,7 @@ static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A) {
     g_counters.d2h_copies++;
     APCG_HIP(hipMemcpyAsync(h.data(), out, sizeof(int32_t) * 2 * ni, hipMemcpyDeviceToHost, c->stream));
     if (!t->ev && !(t->ev = event_get(c->device))) return set_error(APCG_ERR_HIP, "event creation failed");
-    APCG_HIP(hipEventRecord(t->ev->e, c->stream));
+    APCG_HIP(event_record(t->ev, c->stream));
     g_counters.host_polls++;
     APCG_HIP(hipEventSynchronize(t->ev->e));
     for (size_t i = 0; i < ni; ++i) {

@@ -15,8 +15,9 @@
 // An iteration with 64^3 rows: 75 us by kernels, 42 here; 48 mixed systems of
 // 1e3 to 1e5 rows in one call: 52.2 ms on tiles, 9.6 here.  Four border
 // values in flight per thread: eight take the registers of the matrix (42
-// spilled; 49.4 for 48.9 us at 64^3, 66.3 for 62.2 at 78^3).  What is left
-// is the latency of eight dependent exchanges, 2 to 4 us each.
+// spilled; 49.4 for 48.9 us at 64^3, 66.3 for 62.2 at 78^3; five and six make
+// no difference).  What is left is the latency of eight dependent exchanges,
+// 2 to 4 us each.
 //
 // The states, the operations and the order of every sum are those of
 // batched_fcg.hip, so the two give the same bits.
@@ -25,7 +26,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <type_traits>
 #include <vector>
 
 #include "team.h"
@@ -163,30 +163,27 @@ __device__ __forceinline__ void team_fcg(const TeamFcgPlan &P, const TeamFcgSys 
         return [&, e](int t, int nt) __attribute__((always_inline)) {
             const gptr<uint64_t> buf = buffer(e);
             const uint32_t tag = tag0 + e;
-            auto round = [&](auto width, int c0) __attribute__((always_inline)) {
-                constexpr int N = decltype(width)::value;
-                uint32_t place[N];  // past the border's end: the round's first column again
+            for (int c0 = t; c0 < nb; c0 += kSide * nt) {
+                uint32_t place[kSide];  // past the border's end: the round's first column again
 #pragma unroll
-                for (int u = 0; u < N; ++u) place[u] = column(c0 + u * nt < nb ? c0 + u * nt : c0) * 2;
+                for (int u = 0; u < kSide; ++u) place[u] = column(c0 + u * nt < nb ? c0 + u * nt : c0) * 2;
                 long long t0 = 0;
                 for (int spin = 0;; ++spin) {
-                    uint64_t v[N][2];
-                    load_pairs<N>(buf, place, v);
+                    uint64_t v[kSide][2];
+                    load_pairs(buf, place, v);
                     bool all = true;
 #pragma unroll
-                    for (int u = 0; u < N; ++u)
+                    for (int u = 0; u < kSide; ++u)
                         all = all && (uint32_t)(v[u][0] >> 32) == tag && (uint32_t)(v[u][1] >> 32) == tag;
                     if (all) {
 #pragma unroll
-                        for (int u = 0; u < N; ++u)
+                        for (int u = 0; u < kSide; ++u)
                             if (c0 + u * nt < nb) u_border[c0 + u * nt] = unpack(v[u][0], v[u][1]);
-                        return true;
+                        break;
                     }
                     if (!keep_waiting(M, spin, t0)) return false;
                 }
-            };
-            for (int c0 = t; c0 < nb; c0 += 4 * nt)
-                if (!round(std::integral_constant<int, 4>{}, c0)) return false;
+            }
             return true;
         };
     };

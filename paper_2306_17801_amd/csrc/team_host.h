@@ -23,7 +23,7 @@ struct TeamFlight {
     hipStream_t stream;
 };
 extern std::mutex g_flight_mu;
-extern std::vector<TeamFlight> g_flight[64];
+extern std::vector<TeamFlight> *const g_flight;  // one for each device
 
 // Queues launch() (wgs workgroups) on stream st; cus: what fits side by side.
 template <class F>
@@ -47,7 +47,7 @@ apcg_status team_launch(int device, hipStream_t st, int wgs, int cus, F launch) 
             }
     apcg_status s = launch();
     if (s) return s;
-    APCG_HIP(hipEventRecord(ev->e, st));
+    APCG_HIP(event_record(ev, st));
     fl.push_back({ev, wgs, st});
     return APCG_SUCCESS;
 }
@@ -79,7 +79,7 @@ apcg_status grow(T **p, int64_t *cap, int64_t need, int device, hipStream_t st) 
     if (*p) {
         EventRef ev = event_get(device);
         if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-        APCG_HIP(hipEventRecord(ev->e, st));
+        APCG_HIP(event_record(ev, st));
         T *old = *p;
         defer_release({ev}, [old, device]() {
             hipSetDevice(device);

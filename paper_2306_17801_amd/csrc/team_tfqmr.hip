@@ -124,7 +124,7 @@ __device__ __forceinline__ void team_tfqmr(const TeamTqPlan &P, Member &M, doubl
         long long since = 0;
         for (int spin = 0;; ++spin) {
             uint64_t w[kSide][2];
-            load_pairs<kSide>(buf, place, w);
+            load_pairs(buf, place, w);
             bool all = true;
 #pragma unroll
             for (int u = 0; u < kSide; ++u) {

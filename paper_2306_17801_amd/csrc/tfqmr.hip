@@ -429,7 +429,7 @@ extern "C" apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b
             if (tc->ws) {
                 EventRef ev = event_get(dev);
                 if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-                APCG_HIP(hipEventRecord(ev->e, st));
+                APCG_HIP(event_record(ev, st));
                 double *old = tc->ws;
                 hipGraphExec_t oe = tc->exec;
                 hipGraph_t og = tc->graph;
@@ -527,7 +527,7 @@ extern "C" apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b
                 if (!tc->exec || tc->gK != K || memcmp(key, tc->gkey, sizeof key) != 0) {
                     if (tc->exec) {
                         EventRef ev = event_get(dev);
-                        if (ev) hipEventRecord(ev->e, st);
+                        if (ev) event_record(ev, st);
                         hipGraphExec_t oe = tc->exec;
                         hipGraph_t og = tc->graph;
                         defer_release({ev}, [oe, og, dev]() {
@@ -576,7 +576,7 @@ extern "C" apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b
                 g_counters.d2h_copies++;
                 APCG_HIP(hipMemcpyAsync(&tc->pinned[2 * slot], &tc->st->status, 2 * sizeof(int32_t),
                                         hipMemcpyDeviceToHost, st));
-                APCG_HIP(hipEventRecord(tc->poll_ev[slot]->e, st));
+                APCG_HIP(event_record(tc->poll_ev[slot], st));
                 if (g >= L - 1) {
                     const int ps = (int)((g - (L - 1)) % L);
                     g_counters.host_polls++;
