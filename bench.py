@@ -259,6 +259,21 @@ def bench_batch(apcg, torch, reps, only=None, tile_rows=0):
         dt = (time.perf_counter() - t0) / reps
         out["batched_autotuned_ms"] = round(1000 * dt, 3)
         best = (dt, "autotuned")
+        # the default schedule: teams for systems that fit the chip, which
+        # the autotuner does not time
+        auto = apcg.apcg_solve_opts_default(x0_is_zero=1)
+        apcg.apcg_ksp_solve_batched(ctx, [a.h for a in As], [b.h for b in bs], [x.h for x in xs], 1e-8, 50000, auto,
+                                    info)
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(reps):
+            apcg.apcg_ksp_solve_batched(ctx, [a.h for a in As], [b.h for b in bs], [x.h for x in xs], 1e-8, 50000,
+                                        auto, info)
+        torch.cuda.synchronize()
+        dt = (time.perf_counter() - t0) / reps
+        out["batched_auto_ms"] = round(1000 * dt, 3)
+        if dt < best[0]:
+            best, o = (dt, "auto"), auto
     res = [apcg.apcg_info_get(info, i) for i in range(nsys)]
     out["batched_schedule"] = best[1]
     out["batched_ms"] = round(1000 * best[0], 3)

@@ -648,7 +648,9 @@ typedef struct apcg_batch_config {
  * APCG_SPMV_ROWGROUP (one lane per row), so that the batch reads the CSR
  * arrays.  The
  * caller passes *best's fields to apcg_solve_opts (batch_schedule,
- * batch_block_size, batch_tile_rows).  Blocks the host. */
+ * batch_block_size, batch_tile_rows).  APCG_BATCH_AUTO's teams (see
+ * apcg_ksp_solve_batched) are not among what it times: for systems that fit
+ * the chip they are the faster choice.  Blocks the host. */
 apcg_status apcg_batch_autotune(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
                                 int32_t kind, int32_t iters, apcg_batch_config *best, double *best_ms,
                                 int32_t *from_cache);
@@ -703,7 +705,10 @@ apcg_status apcg_latency_floors(int32_t device, int32_t reps, double out_us[4]);
  * between solves.  The products read the matrix's sliced-diagonal copy when
  * its pattern allows one (see APCG_SPMV_SDIA; the first such solve of a
  * matrix copies the pattern to the host once, synchronously), else the CSR
- * arrays; both add every row's entries in column order, bitwise alike. */
+ * arrays; both add every row's entries in column order, bitwise alike.  With
+ * APCG_MODE_GRAPH, a system of more than 8192 rows that fits the chip (as in
+ * apcg_ksp_solve, 2048 rows a workgroup) is solved by one launch of a team of
+ * workgroups instead, whose sums run in another fixed order. */
 apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, double rtol, int32_t maxit,
                                  const apcg_solve_opts *opts, apcg_info info, int32_t info_index);
 
