@@ -1963,6 +1963,17 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
                 if ((s = get_graph(c, pl, bf, K, opts.pc, norm_pre, &exec))) return s;
                 const int64_t ngraphs = ((int64_t)maxit + K - 1) / K;
                 for (int64_t g = 0; g < ngraphs; ++g) {
+                    const int64_t rest = (int64_t)maxit - g * K;  // iterations from here to the limit
+                    if (rest <= K / 2) {
+                        // a graph would run more kernels that find the
+                        // solve at its limit than kernels that work (20
+                        // iterations, K = 16: 24 of them, 4.6 us each)
+                        for (int j = 1; j <= (int)rest; ++j) {
+                            if ((s = launch_product(st, pl, bf, j))) return s;
+                            if ((s = launch_update(st, pl, bf, j, norm_pre))) return s;
+                        }
+                        break;
+                    }
                     g_counters.graph_launches++;
                     APCG_HIP(hipGraphLaunch(exec, st));
                     if ((s = queue_poll(c, bf, (int)(g % L)))) return s;

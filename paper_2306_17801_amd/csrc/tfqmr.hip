@@ -561,6 +561,12 @@ extern "C" apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b
             }
             const int64_t periods = ((int64_t)maxit + K - 1) / K;
             for (int64_t g = 0; g < periods; ++g) {
+                const int64_t rest = (int64_t)maxit - g * K;
+                if (opts.mode == APCG_MODE_GRAPH && rest <= K / 2) {  // (as in apcg_ksp_solve)
+                    for (int j = 1; j <= (int)rest; ++j)
+                        if ((s = iteration(j))) return s;
+                    break;
+                }
                 if (opts.mode == APCG_MODE_GRAPH) {
                     g_counters.graph_launches++;
                     APCG_HIP(hipGraphLaunch(tc->exec, st));
