@@ -145,7 +145,9 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
     });
     if (!__syncthreads_and(fits)) return refuse(M);
     const int nb = make_border<R, L>(A, lens, row1 - row0, (uint32_t *)win, list, P.border, area);
-    if (nb > P.border) return refuse(M);
+    // P.border is that of the batch's largest: a system whose z travels tagged
+    // has what the wavefronts beside the collecting ones fetch at once and no more
+    if (nb > P.border || (tagged && nb > kSide * (TT - 64 * M.mw))) return refuse(M);
     for (int i = tid; i < wsize; i += TT) win[i] = 0.0;
     // the column of border place c; the owners keep storing z of these rows
     auto column = [&](int c) { return (uint32_t)(row0 + (int)list[c] - kBias); };
