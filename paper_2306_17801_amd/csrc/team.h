@@ -263,7 +263,9 @@ __device__ __forceinline__ void slices_put(double *red, int q0, const double (&v
 // that they are visible to whoever has received it.
 // Between its own message and the others' the wavefronts that collect no
 // messages run side(thread, threads) -> bool.  red is free again after the
-// next meeting's (other) red has been put.
+// next meeting's (other) red has been put.  A team of one does not end the
+// meeting with a barrier: the caller puts the next sums into another area, or
+// passes a barrier first.
 // Returns false when the launch is given up.
 template <int R, int NV, class Side>
 __device__ __forceinline__ bool team_meet(const Member &M, const double *red, gptr<uint64_t> words, uint32_t tag,

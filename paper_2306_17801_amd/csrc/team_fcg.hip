@@ -240,7 +240,11 @@ __device__ __forceinline__ void team_fcg(const TeamFcgPlan &P, const TeamFcgSys 
         A.keep_packed();
         asm volatile("" : "+v"(share));
         bool sent = false;  // v = D^-1 r has been exchanged
-        if (!restart) {
+        if (restart) {
+            // a meeting of one member ends without a barrier: r.z of the last
+            // step has been read before this step's sums take its place
+            __syncthreads();
+        } else {
             for (int c = tid; c < nb; c += TT) p_border[c] = fma(beta, p_border[c], u_border[c]);
 #pragma unroll
             for (int q = 0; q < R; ++q) p_own[q * TT] = fma(beta, p_own[q * TT], z[q]);
@@ -360,12 +364,12 @@ __device__ __forceinline__ void team_fcg(const TeamFcgPlan &P, const TeamFcgSys 
                 v[2 * q] = r[q] * z[q];
                 v[2 * q + 1] = z[q] * w[q];
             }
-            slices_put<R, 2, R>(red, 0, v);
+            slices_put<R, 2, R>(red + 2 * R * TW, 0, v);  // (beside the residual's, which may still be read)
         }
         // two message areas in turn: after a hand-over this meeting follows the
         // last of its kind with no other between them
         double t2[2];
-        if (!team_meet<R, 2>(M, red, w_init + 12 + 4 * (step & 1u), step, false, t2, take(ex))) return;
+        if (!team_meet<R, 2>(M, red + 2 * R * TW, w_init + 12 + 4 * (step & 1u), step, false, t2, take(ex))) return;
         ++ex;
         const double rz = t2[0], zw = t2[1];
         if (restart) {  // a fresh recurrence from the current x
@@ -404,7 +408,7 @@ __device__ __forceinline__ void team_fcg(const TeamFcgPlan &P, const TeamFcgSys 
 template <int L>
 __global__ __launch_bounds__(TT, 2) void k_team_fcg(TeamFcgPlan P) {
     extern __shared__ double lds[];
-    // sums of the setup, the residual or r.z (4), and of delta (1)
+    // sums of the setup (4) or the residual (1) and r.z with z.w (2, from the third on), and of delta (1)
     __shared__ double red[5 * R * TW], tot[16], cc[DEG + 1];
     __shared__ int area[2 * TW], ok, next;
     if (threadIdx.x == 0) ok = 1;
