@@ -250,6 +250,9 @@ apcg_status resolve_ctx(apcg_ctx in, int device, apcg_ctx *out);  // NULL -> glo
 // operations); the same in both calls.
 apcg_status op_begin(apcg_ctx c, const Acc *acc, int n, bool brief = false);
 apcg_status op_end(apcg_ctx c, const Acc *acc, int n, bool brief = false);
+// Records the event of c's open group of brief operations, before something is
+// queued that those waiting for them shall not wait for; sets c's device.
+apcg_status ctx_end_group(apcg_ctx c);
 // From now on every operation of c ends with an event of its own (the caller
 // may queue work on the stream, or capture it).
 apcg_status ctx_exact_events(apcg_ctx c);

@@ -806,7 +806,7 @@ apcg_status apcg_ksp_solve_learned(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_ve
 apcg_status apcg_mlp_standardize(apcg_ctx ctx, float *dev_X, int32_t B, float *dev_mean, float *dev_std,
                                  int32_t compute_stats) {
     if (!ctx || !dev_X || !dev_mean || !dev_std || B < 1) return set_error(APCG_ERR_INVALID_ARG, "bad arguments");
-    APCG_HIP(hipSetDevice(ctx->device));
+    if (apcg_status gs = ctx_end_group(ctx)) return gs;
     hipLaunchKernelGGL(k_standardize, dim3(1), dim3(64), 0, ctx->stream, dev_X, B, dev_mean, dev_std,
                        compute_stats ? 1 : 0);
     APCG_CHECK_LAUNCH("k_standardize");
@@ -816,7 +816,7 @@ apcg_status apcg_mlp_standardize(apcg_ctx ctx, float *dev_X, int32_t B, float *d
 
 apcg_status apcg_mlp_forward(apcg_ctx ctx, const float *dev_params, const float *dev_X, int32_t B, float *dev_C) {
     if (!ctx || !dev_params || !dev_X || !dev_C || B < 1) return set_error(APCG_ERR_INVALID_ARG, "bad arguments");
-    APCG_HIP(hipSetDevice(ctx->device));
+    if (apcg_status gs = ctx_end_group(ctx)) return gs;
     hipLaunchKernelGGL(k_mlp_fwd, dim3(B), dim3(64), 0, ctx->stream, dev_params, dev_X, B, dev_C);
     APCG_CHECK_LAUNCH("k_mlp_fwd");
     if (ctx->type == APCG_STREAM_GLOBAL_BLOCKING) APCG_HIP(hipStreamSynchronize(ctx->stream));
@@ -827,7 +827,7 @@ apcg_status apcg_mlp_forward(apcg_ctx ctx, const float *dev_params, const float 
 static apcg_status mlp_step(apcg_ctx ctx, const float *dev_params, const float *dev_X, const float *dev_G,
                             const float *dev_h, int32_t B, float mu, float eps, float *dev_loss, float *dev_grad,
                             const Adam &adam) {
-    APCG_HIP(hipSetDevice(ctx->device));
+    if (apcg_status gs = ctx_end_group(ctx)) return gs;
     MlpScratch *ms = mlp_scratch(ctx);
     apcg_status s;
     if ((s = ensure_mlp(ctx, ms, B))) return s;

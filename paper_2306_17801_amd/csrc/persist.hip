@@ -375,7 +375,7 @@ extern "C" apcg_status apcg_ksp_solve_small_noalloc(apcg_ctx ctx, int32_t n, con
         norm_pre = opts->norm_type == APCG_NORM_PRECONDITIONED;
         x0_zero = opts->x0_is_zero ? 1 : 0;
     }
-    APCG_HIP(hipSetDevice(ctx->device));
+    if (apcg_status gs = ctx_end_group(ctx)) return gs;
     // rows and their lengths are not known on the host: the entries are read
     // from the CSR arrays every iteration (the same sums as the register path)
     return launch_pcg_wg(ctx->stream, n, rowptr, col, val, b, x, rtol, maxit, x0_zero, pc, norm_pre, -1, info);

@@ -150,9 +150,11 @@ void reap() {
 // An event recorded after each operation costs its stream more than a small
 // kernel: single vector and scalar operations took 8 to 11 us each, 3.5 to 6
 // without.  So brief operations of a context share one, recorded after
-// kGroupOps of them or when somebody is about to wait for it or a longer
-// operation begins, whichever comes first: a waiter waits for at most that
-// many brief operations more than it has to, and never for a solve.
+// kGroupOps of them, when somebody is about to wait for it, or before
+// something else is queued behind them (a longer operation, a wait for
+// another context's work, work without marks), whichever comes first: a
+// waiter waits for at most that many brief operations more than it has to,
+// and never for a solve.
 constexpr int kGroupOps = 8;
 
 // Records the event of c's open group of operations (g_mu held; the current
@@ -280,6 +282,7 @@ apcg_status op_begin(apcg_ctx c, const Acc *acc, int n, bool brief) {
         if (ws) return ws;
         if (std::find(waited.begin(), waited.end(), e.get()) != waited.end()) return APCG_SUCCESS;
         waited.push_back(e.get());
+        if ((ws = end_group(c))) return ws;  // what is queued so far does not depend on e
         g_counters.stream_waits++;
         APCG_HIP(hipStreamWaitEvent(c->stream, e->e, 0));
         return APCG_SUCCESS;
@@ -345,6 +348,12 @@ apcg_status op_end(apcg_ctx c, const Acc *acc, int n, bool brief) {
         APCG_HIP(hipStreamSynchronize(c->stream));
     }
     return APCG_SUCCESS;
+}
+
+apcg_status ctx_end_group(apcg_ctx c) {
+    std::lock_guard<std::recursive_mutex> lk(g_mu);
+    APCG_HIP(hipSetDevice(c->device));
+    return end_group(c);
 }
 
 apcg_status ctx_exact_events(apcg_ctx c) {
@@ -510,7 +519,8 @@ apcg_status apcg_ctx_wait_for(apcg_ctx waiter, apcg_ctx waitee) {
     EventRef ev = event_get(waitee->device);
     if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
     APCG_HIP(event_record(ev, waitee->stream));
-    APCG_HIP(hipSetDevice(waiter->device));
+    apcg_status s = ctx_end_group(waiter);
+    if (s) return s;
     g_counters.stream_waits++;
     APCG_HIP(hipStreamWaitEvent(waiter->stream, ev->e, 0));
     return APCG_SUCCESS;
