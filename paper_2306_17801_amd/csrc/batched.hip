@@ -454,11 +454,11 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
         // rows: 28.5 ms, segmented 192 (160 on sliced diagonals), persistent
         // 450.  Same sums as the segmented schedule, bit for bit.
         if (opts.batch_schedule == APCG_BATCH_AUTO) {
-            int rows = 0;
-            if ((s = team_eligible(ctx, nsys, A, 1, &rows))) return s;
-            if (rows > 0) {
+            TeamFit fit;
+            if ((s = team_eligible(ctx, nsys, A, 1, &fit))) return s;
+            if (fit.rows > 0) {
                 std::vector<int32_t> left;
-                if ((s = team_pcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, rows, info->d, nullptr, 0, &left)))
+                if ((s = team_pcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, fit, info->d, nullptr, 0, &left)))
                     return s;
                 if ((s = op_end(ctx, acc.data(), (int)acc.size()))) return s;
                 apcg_solve_opts single = opts;

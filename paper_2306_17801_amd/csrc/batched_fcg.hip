@@ -1267,13 +1267,13 @@ static apcg_status bf_teams(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const
     if (opts.batch_schedule != APCG_BATCH_AUTO || opts.batch_tile_rows || opts.batch_tail_tile_rows ||
         maxit > kTeamFcgMaxIts)
         return APCG_SUCCESS;
-    int rows = 0;
+    TeamFit fit;
     apcg_status s;
-    if ((s = team_eligible(ctx, nsys, A, 2, &rows)) || rows == 0) return s;
+    if ((s = team_eligible(ctx, nsys, A, 2, &fit)) || fit.rows == 0) return s;
     std::vector<int32_t> order(nsys), left;
     for (int32_t i = 0; i < nsys; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int32_t p, int32_t q) { return A[p]->n > A[q]->n; });
-    if ((s = team_fcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, fo, coeffs, lmax, info->d, &left))) return s;
+    if ((s = team_fcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, fo, fit, coeffs, lmax, info->d, &left))) return s;
     *done = true;
     if ((s = op_end(ctx, acc.data(), (int)acc.size()))) return s;
     apcg_solve_opts single = opts;

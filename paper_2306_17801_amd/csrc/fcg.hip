@@ -482,12 +482,12 @@ extern "C" apcg_status apcg_ksp_solve_fcg_poly(apcg_ctx ctx, apcg_mat A, apcg_ve
         if ((s = op_begin(ctx, acc, 4))) return s;
         // a system that fits the chip, by a team of workgroups in one launch
         if (opts.mode == APCG_MODE_GRAPH && A->n > kTeamMinRows && maxit <= kTeamFcgMaxIts) {
-            int rows = 0;
-            if ((s = team_eligible(ctx, 1, &A, 2, &rows))) return s;
-            if (rows > 0) {
+            TeamFit fit;
+            if ((s = team_eligible(ctx, 1, &A, 2, &fit))) return s;
+            if (fit.rows > 0) {
                 std::vector<int32_t> left;
-                if ((s = team_fcg_solve(ctx, 1, &A, &b, &x, {0}, rtol, maxit, opts, fo, dev_coeffs, dev_lmax,
-                                        info->d + info_index, &left)))
+                if ((s = team_fcg_solve(ctx, 1, &A, &b, &x, {0}, rtol, maxit, opts, fo, fit, dev_coeffs,
+                                        dev_lmax, info->d + info_index, &left)))
                     return s;
                 if (left.empty()) return op_end(ctx, acc, 4);
                 // given up (see team.h): x is as it was, the kernels below solve it

@@ -170,6 +170,14 @@ struct apcg_vec_s {
     uint64_t mark_id = 0;
 };
 
+namespace apcg {
+// What the team solves remember of a matrix (contexts of several threads may
+// solve with one).
+struct TeamState {
+    std::atomic<int32_t> border[2] = {-1, -1};  // most border columns of a member of 2048 / 4096 rows, -1: not read
+};
+}  // namespace apcg
+
 struct apcg_mat_s {
     uint64_t uid = 0;  // never reused: cached graphs are keyed on it, not on the handle's address
     int32_t device = 0;
@@ -227,7 +235,7 @@ struct apcg_mat_s {
     double *dia_val = nullptr;       // device [dia_ndt][n rounded up to 64]
     apcg::Record rec;
     uint64_t mark_id = 0;
-    int32_t team_border[2] = {-1, -1};  // most border columns of a team's member of 2048 / 4096 rows, -1: not read yet
+    std::shared_ptr<apcg::TeamState> team = std::make_shared<apcg::TeamState>();
     std::string tune_class;  // pattern class of the tuning key (tune.hip), computed once
 };
 

@@ -1917,11 +1917,11 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
         }
         // a system that fits the chip, by a team of workgroups in one launch
         if (opts.mode == APCG_MODE_GRAPH && !gate && A->n > kTeamMinRows) {
-            int rows = 0;
-            if ((s = team_eligible(c, 1, &A, 1, &rows))) return s;
-            if (rows > 0) {
+            TeamFit fit;
+            if ((s = team_eligible(c, 1, &A, 1, &fit))) return s;
+            if (fit.rows > 0) {
                 std::vector<int32_t> left;
-                if ((s = team_pcg_solve(c, 1, &A, &b, &x, {0}, rtol, maxit, opts, rows, info->d + info_index, hist,
+                if ((s = team_pcg_solve(c, 1, &A, &b, &x, {0}, rtol, maxit, opts, fit, info->d + info_index, hist,
                                         hist_cap, &left)))
                     return s;
                 if (left.empty()) return op_end(c, acc, 4);

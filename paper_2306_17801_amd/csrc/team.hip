@@ -531,7 +531,7 @@ apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const std::vec
     for (int32_t i = 0; i < nsys; ++i)
         if (host[2 + i] != (uint32_t)members[i]) left->push_back(i);
     if (host[1] == 2)  // a pattern changed in place: measured again next time
-        for (int32_t i : *left) A[i]->team_border[0] = A[i]->team_border[1] = -1;
+        for (int32_t i : *left) A[i]->team->border[0] = A[i]->team->border[1] = -1;
     if (host[1] == 1) t->rest = 256;  // a wait ran out: the chip is shared, no teams for a while
     return APCG_SUCCESS;
 }
@@ -541,16 +541,20 @@ static int team_width(int maxrow) { return maxrow <= 5 ? 5 : maxrow <= 7 ? 7 : 0
 // The border of every matrix that does not know it yet, in one launch and one
 // readback (once per matrix; a solve checks on the device that the pattern
 // still fits).
-static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A) {
+// border[w][i]: of system i's members of 2048 (w = 0) and 4096 rows.
+static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A, std::vector<int32_t> (&border)[2]) {
     std::vector<BorderItem> items;
-    std::vector<apcg_mat> mats;
+    std::vector<int32_t> which;
     int32_t nmax = 0;
-    for (int32_t i = 0; i < nsys; ++i)
-        if (A[i]->team_border[0] < 0) {
+    for (auto &b : border) b.assign(nsys, 0);
+    for (int32_t i = 0; i < nsys; ++i) {
+        for (int w = 0; w < 2; ++w) border[w][i] = A[i]->team->border[w];
+        if (border[0][i] < 0 || border[1][i] < 0) {
             items.push_back({A[i]->rowptr, A[i]->col, A[i]->n, 0});
-            mats.push_back(A[i]);
+            which.push_back(i);
             nmax = std::max(nmax, A[i]->n);
         }
+    }
     if (items.empty()) return APCG_SUCCESS;
     const size_t ni = items.size();
     TeamCache *t = team_cache(c);
@@ -576,10 +580,8 @@ static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A) {
     APCG_HIP(event_record(t->ev, c->stream));
     g_counters.host_polls++;
     APCG_HIP(hipEventSynchronize(t->ev->e));
-    for (size_t i = 0; i < ni; ++i) {
-        mats[i]->team_border[0] = h[2 * i];
-        mats[i]->team_border[1] = h[2 * i + 1];
-    }
+    for (size_t i = 0; i < ni; ++i)
+        for (int w = 0; w < 2; ++w) A[which[i]]->team->border[w] = border[w][which[i]] = h[2 * i + w];
     return APCG_SUCCESS;
 }
 
@@ -587,7 +589,8 @@ static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A) {
 // run side by side, else eight (of five-entry rows): a member of 4096 rows
 // takes an iteration about 1.25 times as long as one of 2048, so a batch that
 // queues for the compute units finishes sooner.  0: some system does not fit.
-static int team_rows(int32_t nsys, const apcg_mat *A, int cus, int width, int windows) {
+static int team_rows(int32_t nsys, const apcg_mat *A, const std::vector<int32_t> (&border)[2], int cus, int width,
+                     int windows) {
     int best = 0;
     for (int R : {4, 8}) {
         if (R == 8 && (width > 5 || windows > 1)) break;
@@ -595,7 +598,7 @@ static int team_rows(int32_t nsys, const apcg_mat *A, int cus, int width, int wi
         bool ok = true;
         for (int32_t i = 0; i < nsys && ok; ++i) {
             const int64_t T = std::max<int64_t>(1, ((int64_t)A[i]->n + TT * R - 1) / (TT * R));
-            const int nb = A[i]->team_border[R == 8];
+            const int nb = border[R == 8][i];
             ok = T <= cus && nb < 1 << 20 && team_lds(R, nb, windows, rows_in_lds(R)) <= kLdsBytes;
             total += T;
         }
@@ -606,8 +609,8 @@ static int team_rows(int32_t nsys, const apcg_mat *A, int cus, int width, int wi
     return best;
 }
 
-apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windows, int *rows) {
-    *rows = 0;
+apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windows, TeamFit *fit) {
+    fit->rows = 0;
     if (c->type == APCG_STREAM_GLOBAL_BLOCKING) return APCG_SUCCESS;
     int maxrow = 1;
     for (int32_t i = 0; i < nsys; ++i) {
@@ -621,19 +624,21 @@ apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windo
     }
     if (!t->cus) APCG_HIP(hipDeviceGetAttribute(&t->cus, hipDeviceAttributeMultiprocessorCount, c->device));
     apcg_status s;
-    if ((s = team_borders(c, nsys, A))) return s;
-    *rows = team_rows(nsys, A, t->cus, team_width(maxrow), windows);
+    std::vector<int32_t> border[2];
+    if ((s = team_borders(c, nsys, A, border))) return s;
+    fit->rows = team_rows(nsys, A, border, t->cus, team_width(maxrow), windows);
+    fit->border = std::move(border[fit->rows == 8]);
     return APCG_SUCCESS;
 }
 
 apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
                            const std::vector<int32_t> &order, double rtol, int32_t maxit, const apcg_solve_opts &opts,
-                           int rows, apcg_solve_info *info, double *hist, int32_t hist_cap,
+                           const TeamFit &fit, apcg_solve_info *info, double *hist, int32_t hist_cap,
                            std::vector<int32_t> *left) {
     left->clear();
     TeamCache *t = team_cache(c);
     hipStream_t st = c->stream;
-    const int R = rows;
+    const int R = fit.rows;
     int maxrow = 1, border = 0;
     int64_t zn = 0, marks = 0, words = 0, tickets = 0;
     std::vector<TeamSys> sys(nsys);
@@ -648,7 +653,7 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         s.T = (int32_t)std::max<int64_t>(1, ((int64_t)s.n + TT * R - 1) / (TT * R));
         s.info = info + i;
         maxrow = std::max(maxrow, A[i]->sell_maxw);
-        const int nb = s.T == 1 ? 0 : A[i]->team_border[R == 8];
+        const int nb = s.T == 1 ? 0 : fit.border[i];
         border = std::max(border, nb);
         const int64_t ngr = ((int64_t)s.n + kGroupRows - 1) / kGroupRows;
         // what the wavefronts beside at most four that collect messages fetch at once

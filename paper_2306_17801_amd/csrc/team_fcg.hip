@@ -436,8 +436,8 @@ __global__ __launch_bounds__(TT, 2) void k_team_fcg(TeamFcgPlan P) {
 
 apcg_status team_fcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
                            const std::vector<int32_t> &order, double rtol, int32_t maxit, const apcg_solve_opts &opts,
-                           const apcg_fcg_opts &fo, const float *coeffs, const double *lmax, apcg_solve_info *info,
-                           std::vector<int32_t> *left) {
+                           const apcg_fcg_opts &fo, const TeamFit &fit, const float *coeffs, const double *lmax,
+                           apcg_solve_info *info, std::vector<int32_t> *left) {
     left->clear();
     TeamCache *t = team_cache(c);
     hipStream_t st = c->stream;
@@ -457,7 +457,7 @@ apcg_status team_fcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         s.coef = coeffs + (int64_t)i * (DEG + 1);
         s.lmax = lmax + i;
         maxrow = std::max(maxrow, A[i]->sell_maxw);
-        if (s.T > 1) border = std::max(border, A[i]->team_border[0]);
+        if (s.T > 1) border = std::max(border, fit.border[i]);
         s.swap = reinterpret_cast<uint64_t *>(swap);
         s.need = reinterpret_cast<uint8_t *>(marks);
         s.reads = reinterpret_cast<uint8_t *>(marks + ((int64_t)s.n + 63) / 64 * 64);

@@ -121,12 +121,17 @@ apcg_status team_upload(TeamCache *t, hipStream_t st, const void *sys, int64_t s
 apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const std::vector<int32_t> &members,
                         const apcg_mat *A, std::vector<int32_t> *left);
 
+// How teams would solve some systems.
+struct TeamFit {
+    int rows = 0;                 // 64-row slices per wavefront, 0: not by teams
+    std::vector<int32_t> border;  // most border columns of a member, by system
+};
+
 // Whether every system can be solved by teams on ctx's device: rows of at
 // most 7 entries, `windows` windows that fit the LDS (1: PCG, 2: the flexible
-// solve), no system larger than the chip.  *rows receives the 64-row slices
-// per wavefront to use, 0 when it cannot.  Reads the matrices' borders back
+// solve), no system larger than the chip.  Reads the matrices' borders back
 // once per matrix.
-apcg_status team_eligible(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, int windows, int *rows);
+apcg_status team_eligible(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, int windows, TeamFit *fit);
 
 // Jacobi-PCG (or CG) of the systems, started in `order` (largest cost
 // first), results in info[i]; hist as in pcg_solve_marked (one system).
@@ -134,19 +139,20 @@ apcg_status team_eligible(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, int win
 // solve (their x untouched), which the caller solves with another schedule.
 apcg_status team_pcg_solve(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
                            const std::vector<int32_t> &order, double rtol, int32_t maxit, const apcg_solve_opts &opts,
-                           int rows, apcg_solve_info *info, double *hist, int32_t hist_cap,
+                           const TeamFit &fit, apcg_solve_info *info, double *hist, int32_t hist_cap,
                            std::vector<int32_t> *left);
 
 // FCG(1) of the systems with their polynomials coeffs[i][9], lmax[i] (device),
 // as apcg_ksp_solve_batched_fcg_poly; otherwise as team_pcg_solve.
 apcg_status team_fcg_solve(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
                            const std::vector<int32_t> &order, double rtol, int32_t maxit, const apcg_solve_opts &opts,
-                           const apcg_fcg_opts &fo, const float *coeffs, const double *lmax, apcg_solve_info *info,
-                           std::vector<int32_t> *left);
+                           const apcg_fcg_opts &fo, const TeamFit &fit, const float *coeffs, const double *lmax,
+                           apcg_solve_info *info, std::vector<int32_t> *left);
 // TFQMR of one system with members of 2048 rows (team_eligible: rows == 4),
 // as apcg_ksp_solve_tfqmr; otherwise as team_pcg_solve.
 apcg_status team_tfqmr_solve(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, double rtol, int32_t maxit,
-                             const apcg_solve_opts &opts, apcg_solve_info *info, std::vector<int32_t> *left);
+                             const apcg_solve_opts &opts, const TeamFit &fit, apcg_solve_info *info,
+                             std::vector<int32_t> *left);
 // The tags one flexible launch may use are limited (see team_fcg.hip).
 constexpr int32_t kTeamFcgMaxIts = 100000000;
 

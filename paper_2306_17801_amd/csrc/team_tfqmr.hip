@@ -320,7 +320,8 @@ __global__ __launch_bounds__(TT, 2) void k_team_tfqmr(TeamTqPlan P) {
 }  // namespace
 
 apcg_status team_tfqmr_solve(apcg_ctx c, apcg_mat A, apcg_vec b, apcg_vec x, double rtol, int32_t maxit,
-                             const apcg_solve_opts &opts, apcg_solve_info *info, std::vector<int32_t> *left) {
+                             const apcg_solve_opts &opts, const TeamFit &fit, apcg_solve_info *info,
+                             std::vector<int32_t> *left) {
     left->clear();
     TeamCache *t = team_cache(c);
     hipStream_t st = c->stream;
@@ -351,7 +352,7 @@ apcg_status team_tfqmr_solve(apcg_ctx c, apcg_mat A, apcg_vec b, apcg_vec x, dou
     P.done = head_p + 2;
     P.n = n;
     P.T = T;
-    P.border = T == 1 ? 0 : A->team_border[0];
+    P.border = T == 1 ? 0 : fit.border[0];
     P.rtol = rtol;
     P.maxit = maxit;
     P.x0_zero = opts.x0_is_zero ? 1 : 0;

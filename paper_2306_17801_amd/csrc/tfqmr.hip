@@ -416,11 +416,11 @@ extern "C" apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b
         // a system that fits the chip, by a team of workgroups in one launch
         // (as apcg_ksp_solve: GRAPH mode, more than kTeamMinRows rows)
         if (opts.mode == APCG_MODE_GRAPH && n > kTeamMinRows && maxit <= kTeamFcgMaxIts) {
-            int rows = 0;
-            if ((s = team_eligible(ctx, 1, &A, 1, &rows))) return s;
-            if (rows == 4) {
+            TeamFit fit;
+            if ((s = team_eligible(ctx, 1, &A, 1, &fit))) return s;
+            if (fit.rows == 4) {
                 std::vector<int32_t> left;
-                if ((s = team_tfqmr_solve(ctx, A, b, x, rtol, maxit, opts, info->d + info_index, &left))) return s;
+                if ((s = team_tfqmr_solve(ctx, A, b, x, rtol, maxit, opts, fit, info->d + info_index, &left))) return s;
                 if (left.empty()) return op_end(ctx, acc, 4);
                 // given up (see team.h): x is as it was, the kernels below solve it
             }

@@ -76,3 +76,34 @@ def test_border_grown_in_place_beside_a_wider_system(apcg, ctx):
             assert r["status"] == apcg.APCG_SOLVE_CONVERGED and abs(r["iterations"] - ref.its) <= 1, k
             assert rel(xs[k].numpy(), ref.x) <= 1e-9, k
     apcg.apcg_info_destroy(info)
+
+
+def test_threads_share_a_matrix(apcg):
+    """Contexts of several threads solve with one matrix whose border none of
+    them has read yet."""
+    import threading
+
+    from paper_2306_17801_amd.device import DeviceCSR, DeviceVec
+
+    print("case threads share a matrix", flush=True)
+    for rep in range(4):
+        s = grid((110 + rep, 120), rep)
+        dA, got, start = DeviceCSR(s.A), [None] * 4, threading.Barrier(4)
+
+        def work(k):
+            c = apcg.apcg_ctx_create(0)
+            b, x, info = DeviceVec(s.b), DeviceVec.zeros(s.A.n), apcg.apcg_info_create(0, 1)
+            start.wait()
+            for _ in range(3):
+                apcg.apcg_ksp_solve(c, dA.h, b.h, x.h, 0.0, 20, apcg.apcg_solve_opts_default(x0_is_zero=1), info, 0)
+            got[k] = x.numpy()
+            apcg.apcg_info_destroy(info)
+            apcg.apcg_ctx_destroy(c)
+
+        ts = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+        assert all(np.array_equal(g, got[0]) for g in got)
+        assert rel(got[0], oracle.pcg(s.A, s.b, rtol=0.0, maxit=20).x) <= 1e-12
