@@ -99,12 +99,10 @@ __device__ __forceinline__ void team_tfqmr(const TeamTqPlan &P, Member &M, doubl
     if (!team_meet<R, 4>(M, red, w_init, 1u, true, t4, none)) return;
 
     unsigned share = 0;  // bit q: this row of slice q is named by another member
-    if (M.T > 1) {
 #pragma unroll
-        for (int q = 0; q < R; ++q) {
-            const int i = row0 + (q * TW + wave) * 64 + lane;
-            if (i < n && load_shared<uint8_t>(need, (uint32_t)i)) share |= 1u << q;
-        }
+    for (int q = 0; q < R; ++q) {
+        const int i = row0 + (q * TW + wave) * 64 + lane;
+        if (i < n && load_shared<uint8_t>(need, (uint32_t)i)) share |= 1u << q;
     }
     uint32_t ex = 0;  // exchanges so far
     auto buffer = [&](uint32_t e) { return swap + (e & 1u) * 2u * (uint32_t)n; };
@@ -325,9 +323,9 @@ apcg_status team_tfqmr_solve(apcg_ctx c, apcg_mat A, apcg_vec b, apcg_vec x, dou
     left->clear();
     TeamCache *t = team_cache(c);
     hipStream_t st = c->stream;
-    const int32_t n = A->n, T = std::max(1, (n + TT * R - 1) / (TT * R));
-    const int64_t swap = T > 1 ? ((int64_t)n * 4 + 7) / 8 * 8 : 0, marks = T > 1 ? ((int64_t)n + 63) / 64 * 64 : 0;
-    const int64_t words = T > 1 ? ((int64_t)n + kGroupRows - 1) / kGroupRows * kStride : 0;
+    const int32_t n = A->n, T = (n + TT * R - 1) / (TT * R);  // (n > kTeamMinRows: several members)
+    const int64_t swap = ((int64_t)n * 4 + 7) / 8 * 8, marks = ((int64_t)n + 63) / 64 * 64;
+    const int64_t words = ((int64_t)n + kGroupRows - 1) / kGroupRows * kStride;
     apcg_status s;
     uint32_t tag;
     if ((s = team_swap(t, st, swap, 2 * ((int64_t)maxit + 2), &tag))) return s;
@@ -352,7 +350,7 @@ apcg_status team_tfqmr_solve(apcg_ctx c, apcg_mat A, apcg_vec b, apcg_vec x, dou
     P.done = head_p + 2;
     P.n = n;
     P.T = T;
-    P.border = T == 1 ? 0 : fit.border[0];
+    P.border = fit.border[0];
     P.rtol = rtol;
     P.maxit = maxit;
     P.x0_zero = opts.x0_is_zero ? 1 : 0;
