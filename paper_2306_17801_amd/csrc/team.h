@@ -25,10 +25,21 @@
 //
 // Members never wait for a workgroup that has not started: work is handed
 // out by ticket (see TeamPlan), so every workgroup that a member waits for
-// is running or is the next to start.  Every wait is bounded all the same.
+// is running or is the next to start.  Every wait is bounded all the same,
+// and a member whose wait runs out, or whose rows are not what the schedule
+// was chosen for, leaves its system.
+//
+// x is written by all members of a system or by none.  A system's verdict is
+// open until a member that has seen the system's end sets it to done, or one
+// that leaves sets it to something else, whichever is first.  Who has seen
+// the end has every member's last message, so by then every member has sent
+// it and can only be waiting for the others', which are on their way: a
+// member that wants to leave a system that is done goes on waiting instead
+// and finds them.
 #pragma once
 
 #include "internal.h"
+#include "team_host.h"
 
 namespace apcg {
 namespace team {
@@ -48,11 +59,6 @@ constexpr int kStride = 32;
 constexpr int kTree = 256;       // threads of the reduction tree over groups
 constexpr int kSide = 4;         // border entries a thread may fetch during a meeting
 
-// Longest wait for one message (ticks of the 100 MHz clock): far beyond any
-// solve's step; then (other work, another process's team, holds the compute
-// units of members that are due) the launch is given up and the host solves
-// what is left with the other schedules.
-constexpr long long kWaitTicks = 200000000ll;
 
 // Global pointers the compiler keeps in scalar registers: the values read
 // from a device table are the same in every lane, which it cannot see.
@@ -89,27 +95,79 @@ __device__ __forceinline__ void store_shared(gptr<T> p, uint32_t i, T v) {
 // coherence (stores count in vmcnt on this architecture).
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// What a member needs when it waits long or leaves, in LDS: in registers it
+// would push some of the matrix out.
+struct Exit {
+    uint32_t *head;     // the launch's kHeadWords words
+    uint32_t *verdict;  // the system's
+    long long ticks;    // TeamWait
+    uint32_t last;      // one more than the system's last ticket
+    int ok[2];          // 0 once a wait has failed: in a meeting, between meetings
+};
+
 // A member's place in its team, the same in all its threads.
 struct Member {
     int T, m;        // members, this one's index
     int n;           // rows of the system
     int ngr;         // groups of the system
     int mw;          // wavefronts that collect messages (the others are free for a side job)
-    gptr<uint32_t> stop;  // nonzero: the launch is given up
+    int look;        // TeamWait
     double *tot;     // LDS: 4 * 4 tree sums
-    int *ok;         // LDS: 0 once a wait has failed
+    Exit *out;       // LDS
 };
 
-// One look at the clock and the stop word every 256 unsuccessful looks at a
-// message; false when the launch is given up.
+__device__ __forceinline__ uint32_t exchange_if(gptr<uint32_t> p, uint32_t from, uint32_t to) {
+    __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return from;  // what was there
+}
+
+// Whether to look at a message again after so many unsuccessful looks; every
+// now and then that is a question of the clock and of the others.
 __device__ __forceinline__ bool keep_waiting(const Member &M, int spin, long long &t0) {
-    if ((spin & 255) != 255) return true;
+    if (__builtin_expect((spin & M.look) != M.look, 1)) return true;
+    const Exit &E = *M.out;
+    const gptr<uint32_t> head = (gptr<uint32_t>)E.head, verdict = (gptr<uint32_t>)E.verdict;
     const long long now = wall_clock64();
     if (t0 == 0) t0 = now;
-    if (load_shared<uint32_t>(M.stop, 0)) return false;
-    if (now - t0 <= kWaitTicks) return true;
-    store_shared<uint32_t>(M.stop, 0, 1u);
-    return false;
+    const uint32_t v = load_shared<uint32_t>(verdict, 0);
+    if (v == kDone) return now - t0 <= E.ticks + kWaitTicks;  // the messages are on their way
+    if (v != kOpen) return false;                                  // a team mate has left
+    const bool late = now - t0 > E.ticks;
+    if (late) store_shared<uint32_t>(head, kHeadStop, 1u);
+    // once no more tickets are handed out, a system that lacks members will not get them
+    else if (!load_shared<uint32_t>(head, kHeadStop) || load_shared<uint32_t>(head, kHeadNext) >= E.last)
+        return true;
+    return exchange_if(verdict, kOpen, kLeft) == kDone;
+}
+
+// A ticket's exit; thread 0 sets it up while the others wait for the setup's
+// first barrier.
+__device__ __forceinline__ void set_exit(Exit &E, uint32_t *head, uint32_t *verdict, long long ticks, int last) {
+    if (threadIdx.x != 0) return;
+    E.head = head;
+    E.verdict = verdict;
+    E.ticks = ticks;
+    E.last = (uint32_t)last;
+    E.ok[0] = E.ok[1] = 1;
+}
+
+// The next ticket; `tickets` when there is none, or none are handed out any more.
+__device__ __forceinline__ int next_ticket(uint32_t *head, int tickets) {
+    if (__hip_atomic_load(head + kHeadStop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return tickets;
+    return (int)min(atomicAdd(head + kHeadNext, 1u), (uint32_t)tickets);
+}
+
+// At the end of a system, in all threads of a member: whether the member may
+// write its x.
+__device__ __forceinline__ bool finish(const Member &M) {
+    if (M.T == 1) {
+        if (threadIdx.x == 0) *M.out->verdict = kDone;
+        return true;
+    }
+    __syncthreads();  // nobody looks at ok any more
+    if (threadIdx.x == 0 && exchange_if((gptr<uint32_t>)M.out->verdict, kOpen, kDone) > kDone) M.out->ok[0] = 0;
+    __syncthreads();
+    return M.out->ok[0] != 0;
 }
 
 __device__ __forceinline__ double unpack(uint64_t lo, uint64_t hi) {
@@ -180,7 +238,7 @@ __device__ __forceinline__ void load_pairs(gptr<uint64_t> words, const uint32_t 
 }
 
 // Adds the NV doubles of group g's message to acc once it carries `tag`;
-// false when the launch is given up.
+// false when the member leaves its system.
 template <int NV>
 __device__ __forceinline__ bool collect(const Member &M, gptr<uint64_t> words, int g, uint32_t tag,
                                         double (&acc)[NV]) {
@@ -266,7 +324,7 @@ __device__ __forceinline__ void slices_put(double *red, int q0, const double (&v
 // next meeting's (other) red has been put.  A team of one does not end the
 // meeting with a barrier: the caller puts the next sums into another area, or
 // passes a barrier first.
-// Returns false when the launch is given up.
+// Returns false when the member leaves its system.
 template <int R, int NV, class Side>
 __device__ __forceinline__ bool team_meet(const Member &M, const double *red, gptr<uint64_t> words, uint32_t tag,
                                           bool ack, double (&total)[NV], Side side) {
@@ -301,7 +359,7 @@ __device__ __forceinline__ bool team_meet(const Member &M, const double *red, gp
     } else {
         good = side(tid - M.mw * 64, TT - M.mw * 64);
     }
-    if (!good) *M.ok = 0;
+    if (!good) M.out->ok[0] = 0;
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -309,7 +367,7 @@ __device__ __forceinline__ bool team_meet(const Member &M, const double *red, gp
         for (int w = 1; w < M.mw; ++w) t += M.tot[k * (kTree / 64) + w];  // the other wavefronts' sums are zeros
         total[k] = t;
     }
-    return *M.ok != 0;
+    return M.out->ok[0] != 0;
 }
 
 // The rows of a member: matrix entries in registers, the columns as places in
@@ -466,14 +524,11 @@ __device__ __forceinline__ int make_border(Rows<R, L> &A, uint64_t lens, int own
     return nb;
 }
 
-// Gives the launch up: the pattern is not the one the schedule was chosen
-// for.  All threads of the member call it.
-__device__ __forceinline__ void refuse(const Member &M) {
-    if (threadIdx.x == 0) {
-        store_shared<uint32_t>(M.stop, 0, 2u);
-        *M.ok = 0;
-    }
-    __syncthreads();
+// Leaves the system, whose pattern is not the one the schedule was chosen for
+// (why: kUnfit or kOneSided).  Nobody can have seen the system's end: it takes
+// messages that this member has not sent.
+__device__ __forceinline__ void refuse(const Member &M, uint32_t why) {
+    if (threadIdx.x == 0) __hip_atomic_fetch_max(M.out->verdict, why, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace team

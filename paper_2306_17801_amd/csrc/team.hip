@@ -46,7 +46,7 @@ struct TeamSys {
     uint8_t *need;       // n marks: the row is another member's border column
     uint64_t *words;     // kStride per group: messages of the setup (8 words), delta (2, at 8), residual (4, at 12)
     apcg_solve_info *info;
-    uint32_t *done;      // members that have finished
+    uint32_t *verdict;
     int32_t n, T;
     int32_t tagged;      // z travels as tagged words (few border columns)
 };
@@ -54,8 +54,8 @@ struct TeamSys {
 struct TeamPlan {
     const TeamSys *sys;
     const int2 *ticket;   // (system, member), a system's members in a row
-    uint32_t *next;       // next ticket to hand out
-    uint32_t *stop;
+    uint32_t *head;       // kHeadWords words
+    TeamWait wait;
     int32_t tickets, border;  // border: most border columns of any member
     double rtol;
     int32_t maxit, x0_zero, pc, norm_pre;
@@ -143,11 +143,11 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
         }
         slices_put<R, 4, 1>(red, q, v4);
     });
-    if (!__syncthreads_and(fits)) return refuse(M);
+    if (!__syncthreads_and(fits)) return refuse(M, kUnfit);
     const int nb = make_border<R, L>(A, lens, row1 - row0, (uint32_t *)win, list, P.border, area);
     // P.border is that of the batch's largest: a system whose z travels tagged
     // has what the wavefronts beside the collecting ones fetch at once and no more
-    if (nb > P.border || (tagged && nb > kSide * (TT - 64 * M.mw))) return refuse(M);
+    if (nb > P.border || (tagged && nb > kSide * (TT - 64 * M.mw))) return refuse(M, kUnfit);
     for (int i = tid; i < wsize; i += TT) win[i] = 0.0;
     // the column of border place c; the owners keep storing z of these rows
     auto column = [&](int c) { return (uint32_t)(row0 + (int)list[c] - kBias); };
@@ -184,7 +184,9 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
     const auto none = [](int, int) { return true; };
     if (!team_meet<R, 4>(M, red, w_init, 1u, true, t4, none)) return;
     // every row's z carries tag 1 now, whatever an earlier solve left there
-    if (wave >= M.mw && !fetch(1u)(tid - M.mw * 64, TT - M.mw * 64)) *M.ok = 0;
+    if (wave >= M.mw && !fetch(1u)(tid - M.mw * 64, TT - M.mw * 64)) M.out->ok[1] = 0;
+    __syncthreads();
+    if (!M.out->ok[1]) return;
     double rho = t4[0], res = sqrt(t4[1]);
     const double ref = sqrt(t4[2]);
     int status = 0, its = 0;
@@ -299,6 +301,7 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
             rho = rho_new;
         }
     }
+    if (!finish(M)) return;
     // x leaves the registers once (every member read its x0 entries before
     // the setup meeting)
 #pragma unroll
@@ -314,7 +317,6 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
         S.info->res_norm = res;
         S.info->ref_norm = ref;
     }
-    if (tid == 0) atomicAdd(S.done, 1u);
 }
 
 // Persistent members: each takes the next ticket until none is left.  Tickets
@@ -327,24 +329,22 @@ __global__ __launch_bounds__(TT, 2) void k_team_pcg(TeamPlan P) {
     double *win = lds;
     // sums of the setup or the residual (4), and of delta (1)
     __shared__ double red[5 * R * TW], tot[16];
-    __shared__ int area[2 * TW], ok, next;
-    if (threadIdx.x == 0) ok = 1;
+    __shared__ int area[2 * TW], next;
+    __shared__ Exit out;
     for (;;) {
         __syncthreads();  // the previous ticket is finished in every thread
-        if (threadIdx.x == 0)
-            next = __hip_atomic_load(P.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                       ? P.tickets
-                       : (int)min(atomicAdd(P.next, 1u), (uint32_t)P.tickets);
+        if (threadIdx.x == 0) next = next_ticket(P.head, P.tickets);
         __syncthreads();
         const int t = next;
-        if (t >= P.tickets || !ok) return;
+        if (t >= P.tickets) return;
         const int2 tk = P.ticket[t];
         const int sys = __builtin_amdgcn_readfirstlane(tk.x), m = __builtin_amdgcn_readfirstlane(tk.y);
         const TeamSys S = P.sys[sys];
         const int n = __builtin_amdgcn_readfirstlane(S.n);
         const int ngr = (n + kGroupRows - 1) / kGroupRows;
-        Member M{__builtin_amdgcn_readfirstlane(S.T), m, n, ngr, min((ngr + 63) / 64, kTree / 64), uniform(P.stop),
-                 tot, &ok};
+        const int T = __builtin_amdgcn_readfirstlane(S.T);
+        set_exit(out, P.head, S.verdict, P.wait.ticks, t - m + T);
+        Member M{T, m, n, ngr, min((ngr + 63) / 64, kTree / 64), P.wait.look, tot, &out};
         team_pcg<R, L>(P, S, M, win, red, area);
     }
 }
@@ -505,34 +505,34 @@ apcg_status team_upload(TeamCache *t, hipStream_t st, const void *sys, int64_t s
     return APCG_SUCCESS;
 }
 
-apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const std::vector<int32_t> &members,
-                        const apcg_mat *A, std::vector<int32_t> *left) {
+apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const apcg_mat *A, std::vector<int32_t> *left) {
     hipStream_t st = ctx->stream;
-    // a few counts fit the words the context's polls use (pinning memory
+    // a few verdicts fit the words the context's polls use (pinning memory
     // takes longer than a small solve)
     uint32_t *host = reinterpret_cast<uint32_t *>(ctx->pinned_flags);
-    if (nsys + 2 > kMaxLookahead) {
-        if (t->pinned_cap < nsys + 2) {
+    if (nsys > kMaxLookahead) {
+        if (t->pinned_cap < nsys) {
             if (t->pinned) hipHostFree(t->pinned);
             t->pinned = nullptr;
             t->pinned_cap = 0;
-            APCG_HIP(hipHostMalloc((void **)&t->pinned, sizeof(uint32_t) * (nsys + 2), hipHostMallocDefault));
-            t->pinned_cap = nsys + 2;
+            APCG_HIP(hipHostMalloc((void **)&t->pinned, sizeof(uint32_t) * nsys, hipHostMallocDefault));
+            t->pinned_cap = nsys;
         }
         host = t->pinned;
     }
     // observed through an event, like the other schedules' stop flags
     g_counters.d2h_copies++;
-    APCG_HIP(hipMemcpyAsync(host, t->d_sync, sizeof(uint32_t) * (nsys + 2), hipMemcpyDeviceToHost, st));
+    APCG_HIP(hipMemcpyAsync(host, t->d_sync + 4 * kHeadWords, sizeof(uint32_t) * nsys, hipMemcpyDeviceToHost, st));
     if (!t->ev && !(t->ev = event_get(t->device))) return set_error(APCG_ERR_HIP, "event creation failed");
     APCG_HIP(event_record(t->ev, st));
     g_counters.host_polls++;
     APCG_HIP(hipEventSynchronize(t->ev->e));
-    for (int32_t i = 0; i < nsys; ++i)
-        if (host[2 + i] != (uint32_t)members[i]) left->push_back(i);
-    if (host[1] == 2)  // a pattern changed in place: measured again next time
-        for (int32_t i : *left) A[i]->team->border[0] = A[i]->team->border[1] = -1;
-    if (host[1] == 1) t->rest = 256;  // a wait ran out: the chip is shared, no teams for a while
+    for (int32_t i = 0; i < nsys; ++i) {
+        if (host[i] == kDone) continue;
+        left->push_back(i);
+        if (host[i] >= kUnfit) A[i]->team->border[0] = A[i]->team->border[1] = -1;  // (changed in place: read again)
+        else t->rest = 256;  // a wait ran out: the chip is shared, no teams for a while
+    }
     return APCG_SUCCESS;
 }
 
@@ -668,8 +668,8 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         }
         tickets += s.T;
     }
-    // cleared area: next, stop, done counts, messages, marks
-    const int64_t head = (8 + (int64_t)nsys * 4 + 63) / 64 * 64;
+    // cleared area: the head, verdicts, messages, marks
+    const int64_t head = team_head_bytes(nsys);
     const int64_t sync_bytes = head + 8 * words + marks;
     apcg_status s;
     if ((s = team_memory(t, st, team_desc_bytes((int64_t)sizeof(TeamSys) * nsys, tickets), sync_bytes, 8 * zn))) return s;
@@ -679,7 +679,7 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         q.z = t->d_z + reinterpret_cast<int64_t>(q.z);
         q.words = reinterpret_cast<uint64_t *>(t->d_sync + head) + reinterpret_cast<int64_t>(q.words);
         q.need = reinterpret_cast<uint8_t *>(t->d_sync + head + 8 * words) + reinterpret_cast<int64_t>(q.need);
-        q.done = head_p + 2 + i;
+        q.verdict = head_p + kHeadWords + i;
     }
     std::vector<int32_t> members(nsys);
     for (int32_t i = 0; i < nsys; ++i) members[i] = sys[i].T;
@@ -690,8 +690,8 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
     TeamPlan P{};
     P.sys = reinterpret_cast<const TeamSys *>(d_sys);
     P.ticket = d_tickets;
-    P.next = head_p;
-    P.stop = head_p + 1;
+    P.head = head_p;
+    P.wait = t->wait;
     P.tickets = (int32_t)tickets;
     P.border = border;
     P.rtol = rtol;
@@ -713,7 +713,13 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         return APCG_SUCCESS;
     });
     if (s) return s;
-    return team_finish(c, t, nsys, members, A, left);
+    return team_finish(c, t, nsys, A, left);
 }
 
 }  // namespace apcg
+
+// For tests, not part of the interface: the waits of ctx's team launches from
+// now on (TeamWait).
+extern "C" void apcg_internal_set_team_wait(apcg_ctx ctx, int64_t ticks, int32_t look) {
+    apcg::team_cache(ctx)->wait = apcg::TeamWait{ticks, look};
+}

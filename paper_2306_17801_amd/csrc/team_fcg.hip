@@ -50,7 +50,7 @@ struct TeamFcgSys {
     uint64_t *words;     // kStride per group: messages of the setup (8 words), delta (2, at 8), residual (2, at 10),
                          // r.z and z.w (4, at 12 and 16 in turn)
     apcg_solve_info *info;
-    uint32_t *done;      // members that have finished
+    uint32_t *verdict;
     const float *coef;   // 9
     const double *lmax;  // 1
     int32_t n, T;
@@ -59,7 +59,8 @@ struct TeamFcgSys {
 struct TeamFcgPlan {
     const TeamFcgSys *sys;
     const int2 *ticket;
-    uint32_t *next, *stop;
+    uint32_t *head;  // kHeadWords words
+    TeamWait wait;
     int32_t tickets, border;
     double rtol, stall_frac;
     int32_t maxit, x0_zero, stall_min, fallback;
@@ -117,9 +118,9 @@ __device__ __forceinline__ void team_fcg(const TeamFcgPlan &P, const TeamFcgSys 
         }
         slices_put<R, 4, 1>(red, q, v);
     });
-    if (!__syncthreads_and(fits)) return refuse(M);
+    if (!__syncthreads_and(fits)) return refuse(M, kUnfit);
     const int nb = make_border<R, L>(A, lens, row1 - row0, (uint32_t *)win, list, border, area);
-    if (nb > border) return refuse(M);
+    if (nb > border) return refuse(M, kUnfit);
     for (int i = tid; i < 2 * wsize; i += TT) win[i] = 0.0;
     auto column = [&](int c) { return (uint32_t)(row0 + (int)list[c] - kBias); };
     for (int c = tid; c < nb; c += TT) {
@@ -149,7 +150,7 @@ __device__ __forceinline__ void team_fcg(const TeamFcgPlan &P, const TeamFcgSys 
             mutual = mutual && (load_shared<uint8_t>(reads, (uint32_t)(o * M.T + M.m)) != 0) ==
                                    (load_shared<uint8_t>(reads, (uint32_t)(M.m * M.T + o)) != 0);
     }
-    if (!__syncthreads_and(mutual)) return refuse(M);
+    mutual = __syncthreads_and(mutual);
 
     uint32_t ex = 0;  // exchanges so far
     auto buffer = [&](uint32_t e) { return swap + (e & 1u) * 2u * (uint32_t)n; };
@@ -191,9 +192,9 @@ __device__ __forceinline__ void team_fcg(const TeamFcgPlan &P, const TeamFcgSys 
     auto exchange = [&]() __attribute__((always_inline)) {
         const bool good = take(ex)(tid, TT);
         ++ex;
-        if (!good) *M.ok = 0;
+        if (!good) M.out->ok[1] = 0;
         __syncthreads();
-        return *M.ok != 0;
+        return M.out->ok[1] != 0;
     };
 
     const double ref = sqrt(t4[0]);
@@ -218,6 +219,7 @@ __device__ __forceinline__ void team_fcg(const TeamFcgPlan &P, const TeamFcgSys 
             stopped = true;
         }
     }
+    if (!stopped && !mutual) return refuse(M, kOneSided);  // (an end without exchanges needs no readers)
     auto stop = [&](int why) __attribute__((always_inline)) {
         status = mode == MODE_JACOBI ? why | APCG_SOLVE_FALLBACK | reason : why;
         stopped = true;
@@ -389,6 +391,7 @@ __device__ __forceinline__ void team_fcg(const TeamFcgPlan &P, const TeamFcgSys 
             rho = rz;
         }
     }
+    if (!finish(M)) return;
 #pragma unroll
     for (int q = 0; q < R; ++q) {
         const int i = row0 + (q * TW + wave) * 64 + lane;
@@ -402,7 +405,6 @@ __device__ __forceinline__ void team_fcg(const TeamFcgPlan &P, const TeamFcgSys 
         S.info->res_norm = res;
         S.info->ref_norm = ref;
     }
-    if (tid == 0) atomicAdd(S.done, 1u);
 }
 
 template <int L>
@@ -410,24 +412,22 @@ __global__ __launch_bounds__(TT, 2) void k_team_fcg(TeamFcgPlan P) {
     extern __shared__ double lds[];
     // sums of the setup (4) or the residual (1) and r.z with z.w (2, from the third on), and of delta (1)
     __shared__ double red[5 * R * TW], tot[16], cc[DEG + 1];
-    __shared__ int area[2 * TW], ok, next;
-    if (threadIdx.x == 0) ok = 1;
+    __shared__ int area[2 * TW], next;
+    __shared__ Exit out;
     for (;;) {
         __syncthreads();  // the previous ticket is finished in every thread
-        if (threadIdx.x == 0)
-            next = __hip_atomic_load(P.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                       ? P.tickets
-                       : (int)min(atomicAdd(P.next, 1u), (uint32_t)P.tickets);
+        if (threadIdx.x == 0) next = next_ticket(P.head, P.tickets);
         __syncthreads();
         const int t = next;
-        if (t >= P.tickets || !ok) return;
+        if (t >= P.tickets) return;
         const int2 tk = P.ticket[t];
         const int sys = __builtin_amdgcn_readfirstlane(tk.x), m = __builtin_amdgcn_readfirstlane(tk.y);
         const TeamFcgSys S = P.sys[sys];
         const int n = __builtin_amdgcn_readfirstlane(S.n);
         const int ngr = (n + kGroupRows - 1) / kGroupRows;
-        Member M{__builtin_amdgcn_readfirstlane(S.T), m, n, ngr, min((ngr + 63) / 64, kTree / 64), uniform(P.stop),
-                 tot, &ok};
+        const int T = __builtin_amdgcn_readfirstlane(S.T);
+        set_exit(out, P.head, S.verdict, P.wait.ticks, t - m + T);
+        Member M{T, m, n, ngr, min((ngr + 63) / 64, kTree / 64), P.wait.look, tot, &out};
         team_fcg<L>(P, S, M, lds, red, area, cc);
     }
 }
@@ -475,7 +475,7 @@ apcg_status team_fcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
     const int64_t tags = 9 * ((int64_t)maxit + 4);
     uint32_t tag;
     if ((s = team_swap(t, st, swap, tags, &tag))) return s;
-    const int64_t head = (8 + (int64_t)nsys * 4 + 63) / 64 * 64;
+    const int64_t head = team_head_bytes(nsys);
     const int64_t sync_bytes = head + 8 * words + marks;
     if ((s = team_memory(t, st, team_desc_bytes((int64_t)sizeof(TeamFcgSys) * nsys, tickets), sync_bytes, 0))) return s;
     uint32_t *head_p = reinterpret_cast<uint32_t *>(t->d_sync);
@@ -485,7 +485,7 @@ apcg_status team_fcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         q.words = reinterpret_cast<uint64_t *>(t->d_sync + head) + reinterpret_cast<int64_t>(q.words);
         q.need = reinterpret_cast<uint8_t *>(t->d_sync + head + 8 * words) + reinterpret_cast<int64_t>(q.need);
         q.reads = reinterpret_cast<uint8_t *>(t->d_sync + head + 8 * words) + reinterpret_cast<int64_t>(q.reads);
-        q.done = head_p + 2 + i;
+        q.verdict = head_p + kHeadWords + i;
     }
     std::vector<int32_t> members(nsys);
     for (int32_t i = 0; i < nsys; ++i) members[i] = sys[i].T;
@@ -496,8 +496,8 @@ apcg_status team_fcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
     TeamFcgPlan P{};
     P.sys = reinterpret_cast<const TeamFcgSys *>(d_sys);
     P.ticket = d_tickets;
-    P.next = head_p;
-    P.stop = head_p + 1;
+    P.head = head_p;
+    P.wait = t->wait;
     P.tickets = (int32_t)tickets;
     P.border = border;
     P.rtol = rtol;
@@ -519,7 +519,7 @@ apcg_status team_fcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         return APCG_SUCCESS;
     });
     if (s) return s;
-    return team_finish(c, t, nsys, members, A, left);
+    return team_finish(c, t, nsys, A, left);
 }
 
 }  // namespace apcg

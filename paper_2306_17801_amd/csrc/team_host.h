@@ -13,6 +13,24 @@ namespace apcg {
 // Single solves take the team schedule above this many rows.
 constexpr int32_t kTeamMinRows = 8192;
 
+// Longest wait for one message (ticks of the 100 MHz clock): far beyond any
+// solve's step; then (other work, another process's team, holds the compute
+// units of members that are due) the launch is given up and the host solves
+// what is left with the other schedules.
+constexpr long long kWaitTicks = 200000000ll;
+struct TeamWait {
+    long long ticks;
+    int32_t look;  // the clock is read at every look + 1 unsuccessful looks (a power of two less one)
+};
+
+// The words before the verdicts: the next ticket to hand out; nonzero once a
+// wait has run out, after which no tickets are handed out.
+constexpr int kHeadNext = 0, kHeadStop = 1, kHeadWords = 4;
+// A system's verdict: nobody has seen its end or left it; x is solved; a wait
+// has run out; its rows or their border do not fit; one member reads another
+// that does not read it (flexible solve).  The last three: x as it was.
+constexpr uint32_t kOpen = 0, kDone = 1, kLeft = 2, kUnfit = 3, kOneSided = 4;
+
 // Team launches in flight on a device: a member waits for the other members
 // of its team, so the workgroups of all team launches that may run at the
 // same time must fit the chip together (one per compute unit).  A launch that
@@ -56,13 +74,14 @@ apcg_status team_launch(int device, hipStream_t st, int wgs, int cus, F launch) 
 struct TeamCache {
     int device = 0;
     int cus = 0;
+    TeamWait wait{kWaitTicks, 255};
     int rest = 0;            // solves to leave to the other schedules after a wait that ran out
     std::vector<char> desc;  // host copy of d_desc, alive while it is uploaded
     char *mem = nullptr;     // one buffer for the three below (an allocation costs as much as a small solve)
     int64_t mem_cap = 0;
     char *d_desc = nullptr;  // the systems, int2 tickets[]
     uint64_t desc_hash = 0;
-    char *d_sync = nullptr;  // cleared before every launch: next, stop, done[], words, marks
+    char *d_sync = nullptr;  // cleared before every launch: the head, verdicts, words, marks
     uint64_t *d_z = nullptr; // border values
     uint64_t *d_swap = nullptr;  // border exchanges of the flexible solve; tags below tag are used up
     int64_t swap_cap = 0, tag = 1;
@@ -116,10 +135,11 @@ apcg_status team_upload(TeamCache *t, hipStream_t st, const void *sys, int64_t s
                         const std::vector<int32_t> &order, const std::vector<int32_t> &members, const char **d_sys,
                         const int2 **d_tickets);
 
-// Waits for the launch and lists the systems it did not finish; d_sync begins
-// with the next ticket, the stop word and the counts of finished members.
-apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const std::vector<int32_t> &members,
-                        const apcg_mat *A, std::vector<int32_t> *left);
+// Bytes of the head and the verdicts at the start of d_sync.
+inline int64_t team_head_bytes(int32_t nsys) { return (4 * (kHeadWords + (int64_t)nsys) + 63) / 64 * 64; }
+
+// Waits for the launch and lists the systems that are not done.
+apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const apcg_mat *A, std::vector<int32_t> *left);
 
 // How teams would solve some systems.
 struct TeamFit {

@@ -39,7 +39,8 @@ struct TeamTqPlan {
     uint8_t *need;       // n marks: the row is another member's border column
     uint64_t *words;     // kStride per group: messages of the setup (8 words), r0.v (2, at 8), the half-steps (8, at 16)
     apcg_solve_info *info;
-    uint32_t *next, *stop, *done;
+    uint32_t *head, *verdict;
+    TeamWait wait;
     int32_t n, T, border;
     double rtol;
     int32_t maxit, x0_zero, pc;
@@ -88,9 +89,9 @@ __device__ __forceinline__ void team_tfqmr(const TeamTqPlan &P, Member &M, doubl
         }
         slices_put<R, 4, 1>(red, q, v);
     });
-    if (!__syncthreads_and(fits)) return refuse(M);
+    if (!__syncthreads_and(fits)) return refuse(M, kUnfit);
     const int nb = make_border<R, L>(A, lens, row1 - row0, (uint32_t *)win, list, border_max, area);
-    if (nb > border_max) return refuse(M);
+    if (nb > border_max) return refuse(M, kUnfit);
     for (int i = tid; i < wsize; i += TT) win[i] = 0.0;
     auto column = [&](int c) { return (uint32_t)(row0 + (int)list[c] - kBias); };
     for (int c = tid; c < nb; c += TT) store_shared<uint8_t>(need, column(c), 1);
@@ -159,7 +160,7 @@ __device__ __forceinline__ void team_tfqmr(const TeamTqPlan &P, Member &M, doubl
         for (int c = tid; c < nb; c += kSide * TT) {
             double v[kSide];
             if (!take4(e, c, TT, v)) {
-                *M.ok = 0;
+                M.out->ok[1] = 0;
                 return;
             }
 #pragma unroll
@@ -191,7 +192,7 @@ __device__ __forceinline__ void team_tfqmr(const TeamTqPlan &P, Member &M, doubl
                 d[q] = v[q] = u[q] = 0.0;
                 send(q, r0[q]);
             }
-            if (small && wave >= M.mw && !fetch(ex)(first, others)) *M.ok = 0;
+            if (small && wave >= M.mw && !fetch(ex)(first, others)) M.out->ok[1] = 0;
         } else {
 #pragma unroll
             for (int q = 0; q < R; ++q) own[q * TT] = fma(beta, own[q * TT], w[q]);
@@ -199,7 +200,7 @@ __device__ __forceinline__ void team_tfqmr(const TeamTqPlan &P, Member &M, doubl
         apply(ex, [&](double y, double value) { return fma(beta, y, value); });  // (the border starts as zeros)
         ++ex;
         __syncthreads();
-        if (!*M.ok) return;
+        if (!M.out->ok[1]) return;
         {
             double s[R];
 #pragma unroll
@@ -236,7 +237,7 @@ __device__ __forceinline__ void team_tfqmr(const TeamTqPlan &P, Member &M, doubl
                 s[4 * q] = w[q] * w[q];
             }
             __syncthreads();
-            if (!*M.ok) return;
+            if (!M.out->ok[1]) return;
 #pragma unroll
             for (int q = 0; q < R; ++q) {
                 u[q] = bd[q] * A.dot(q, win);
@@ -279,6 +280,7 @@ __device__ __forceinline__ void team_tfqmr(const TeamTqPlan &P, Member &M, doubl
         beta = rho_new / rho;
         rho = rho_new;
     }
+    if (!finish(M)) return;
     // x leaves the registers once (every member read its x0 entries before
     // the setup meeting)
 #pragma unroll
@@ -294,7 +296,6 @@ __device__ __forceinline__ void team_tfqmr(const TeamTqPlan &P, Member &M, doubl
         P.info->res_norm = bound;
         P.info->ref_norm = ref;
     }
-    if (tid == 0) atomicAdd(P.done, 1u);
 }
 
 template <int L>
@@ -302,16 +303,15 @@ __global__ __launch_bounds__(TT, 2) void k_team_tfqmr(TeamTqPlan P) {
     extern __shared__ double lds[];
     // sums of the setup or the half-steps (4), and of r0.v (1)
     __shared__ double red[5 * R * TW], tot[16];
-    __shared__ int area[2 * TW], ok, member;
-    if (threadIdx.x == 0) {
-        ok = 1;
-        member = (int)atomicAdd(P.next, 1u);  // in the order the workgroups start
-    }
+    __shared__ int area[2 * TW], member;
+    __shared__ Exit out;
+    if (threadIdx.x == 0) member = next_ticket(P.head, P.T);  // in the order the workgroups start
     __syncthreads();
     const int m = __builtin_amdgcn_readfirstlane(member);
     if (m >= P.T) return;
     const int ngr = (P.n + kGroupRows - 1) / kGroupRows;
-    Member M{P.T, m, P.n, ngr, min((ngr + 63) / 64, kTree / 64), uniform(P.stop), tot, &ok};
+    set_exit(out, P.head, P.verdict, P.wait.ticks, P.T);
+    Member M{P.T, m, P.n, ngr, min((ngr + 63) / 64, kTree / 64), P.wait.look, tot, &out};
     team_tfqmr<L>(P, M, lds, red, area);
 }
 
@@ -329,8 +329,8 @@ apcg_status team_tfqmr_solve(apcg_ctx c, apcg_mat A, apcg_vec b, apcg_vec x, dou
     apcg_status s;
     uint32_t tag;
     if ((s = team_swap(t, st, swap, 2 * ((int64_t)maxit + 2), &tag))) return s;
-    // cleared area: next, stop, done, messages, marks
-    constexpr int64_t head = 64;
+    // cleared area: the head, the verdict, messages, marks
+    const int64_t head = team_head_bytes(1);
     const int64_t sync_bytes = head + 8 * words + marks;
     t->desc_hash = 0;  // the buffer is laid out anew
     if ((s = team_memory(t, st, 0, sync_bytes, 0))) return s;
@@ -345,9 +345,9 @@ apcg_status team_tfqmr_solve(apcg_ctx c, apcg_mat A, apcg_vec b, apcg_vec x, dou
     P.words = reinterpret_cast<uint64_t *>(t->d_sync + head);
     P.need = reinterpret_cast<uint8_t *>(t->d_sync + head + 8 * words);
     P.info = info;
-    P.next = head_p;
-    P.stop = head_p + 1;
-    P.done = head_p + 2;
+    P.head = head_p;
+    P.verdict = head_p + kHeadWords;
+    P.wait = t->wait;
     P.n = n;
     P.T = T;
     P.border = fit.border[0];
@@ -367,7 +367,7 @@ apcg_status team_tfqmr_solve(apcg_ctx c, apcg_mat A, apcg_vec b, apcg_vec x, dou
         return APCG_SUCCESS;
     });
     if (s) return s;
-    return team_finish(c, t, 1, {T}, &A, left);
+    return team_finish(c, t, 1, &A, left);
 }
 
 }  // namespace apcg
