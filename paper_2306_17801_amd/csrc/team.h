@@ -131,12 +131,13 @@ __device__ __forceinline__ bool keep_waiting(const Member &M, int spin, long lon
     if (t0 == 0) t0 = now;
     const uint32_t v = load_shared<uint32_t>(verdict, 0);
     if (v == kDone) return now - t0 <= E.ticks + kWaitTicks;  // the messages are on their way
-    if (v != kOpen) return false;                                  // a team mate has left
+    if (v != kOpen) return false;                             // a team mate has left
+    // the system lacks members: they come when tickets before its own are through
+    const bool lacks = load_shared<uint32_t>(head, kHeadNext) < E.last;
+    if (lacks && load_shared<uint32_t>(head, kHeadThrough) < E.last - (uint32_t)M.T) t0 = now;
     const bool late = now - t0 > E.ticks;
     if (late) store_shared<uint32_t>(head, kHeadStop, 1u);
-    // once no more tickets are handed out, a system that lacks members will not get them
-    else if (!load_shared<uint32_t>(head, kHeadStop) || load_shared<uint32_t>(head, kHeadNext) >= E.last)
-        return true;
+    else if (!lacks || !load_shared<uint32_t>(head, kHeadStop)) return true;
     return exchange_if(verdict, kOpen, kLeft) == kDone;
 }
 
@@ -151,8 +152,10 @@ __device__ __forceinline__ void set_exit(Exit &E, uint32_t *head, uint32_t *verd
     E.ok[0] = E.ok[1] = 1;
 }
 
-// The next ticket; `tickets` when there is none, or none are handed out any more.
-__device__ __forceinline__ int next_ticket(uint32_t *head, int tickets) {
+// The next ticket (through: the last one is); `tickets` when there is none, or
+// none are handed out any more.
+__device__ __forceinline__ int next_ticket(uint32_t *head, int tickets, bool through) {
+    if (through) __hip_atomic_fetch_add(head + kHeadThrough, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (__hip_atomic_load(head + kHeadStop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return tickets;
     return (int)min(atomicAdd(head + kHeadNext, 1u), (uint32_t)tickets);
 }

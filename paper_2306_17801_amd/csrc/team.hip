@@ -331,9 +331,9 @@ __global__ __launch_bounds__(TT, 2) void k_team_pcg(TeamPlan P) {
     __shared__ double red[5 * R * TW], tot[16];
     __shared__ int area[2 * TW], next;
     __shared__ Exit out;
-    for (;;) {
+    for (bool through = false;; through = true) {
         __syncthreads();  // the previous ticket is finished in every thread
-        if (threadIdx.x == 0) next = next_ticket(P.head, P.tickets);
+        if (threadIdx.x == 0) next = next_ticket(P.head, P.tickets, through);
         __syncthreads();
         const int t = next;
         if (t >= P.tickets) return;

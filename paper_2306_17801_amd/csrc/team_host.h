@@ -13,10 +13,12 @@ namespace apcg {
 // Single solves take the team schedule above this many rows.
 constexpr int32_t kTeamMinRows = 8192;
 
-// Longest wait for one message (ticks of the 100 MHz clock): far beyond any
-// solve's step; then (other work, another process's team, holds the compute
-// units of members that are due) the launch is given up and the host solves
-// what is left with the other schedules.
+// Longest wait for one message (ticks of the 100 MHz clock; 2 s): far beyond
+// any solve's step; then other work, another process's team say, holds the
+// compute units of members that are due: no more tickets are handed out, and
+// what is left is solved by the other schedules.  Not counted is the time in
+// which the first members of a system wait in the setup for workgroups that
+// solve the systems before it, however long that takes.
 constexpr long long kWaitTicks = 200000000ll;
 struct TeamWait {
     long long ticks;
@@ -24,8 +26,9 @@ struct TeamWait {
 };
 
 // The words before the verdicts: the next ticket to hand out; nonzero once a
-// wait has run out, after which no tickets are handed out.
-constexpr int kHeadNext = 0, kHeadStop = 1, kHeadWords = 4;
+// wait has run out, after which no tickets are handed out; tickets that are
+// through.
+constexpr int kHeadNext = 0, kHeadStop = 1, kHeadThrough = 2, kHeadWords = 4;
 // A system's verdict: nobody has seen its end or left it; x is solved; a wait
 // has run out; its rows or their border do not fit; one member reads another
 // that does not read it (flexible solve).  The last three: x as it was.

@@ -305,7 +305,7 @@ __global__ __launch_bounds__(TT, 2) void k_team_tfqmr(TeamTqPlan P) {
     __shared__ double red[5 * R * TW], tot[16];
     __shared__ int area[2 * TW], member;
     __shared__ Exit out;
-    if (threadIdx.x == 0) member = next_ticket(P.head, P.T);  // in the order the workgroups start
+    if (threadIdx.x == 0) member = next_ticket(P.head, P.T, false);  // in the order the workgroups start
     __syncthreads();
     const int m = __builtin_amdgcn_readfirstlane(member);
     if (m >= P.T) return;

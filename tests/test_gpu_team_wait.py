@@ -125,3 +125,33 @@ def test_single_solves_from_x0_whoever_leaves(apcg, wait):
             assert rel(got[0], want) <= 1e-10, kind
             apcg.apcg_ctx_destroy(c)
     apcg.apcg_info_destroy(info)
+
+
+def test_waiting_for_whole_solves_is_no_time_out(apcg):
+    """More members than compute units, and solves of 10,000 iterations (about
+    60 ms): the members of a system that lacks others wait for whole solves,
+    far longer than the limit (15 ms), while those go on."""
+    from paper_2306_17801_amd.device import DeviceCSR, DeviceVec
+
+    print("case team wait whole solves", flush=True)
+    n = 24000  # a chain: as many iterations as rows
+    i = np.repeat(np.arange(n), 3)
+    j = i + np.tile([-1, 0, 1], n)
+    ok = (j >= 0) & (j < n)
+    A = P.CSR(n=n, rowptr=np.concatenate([[0], np.cumsum(np.add.reduceat(ok, np.arange(0, 3 * n, 3)))]).astype(np.int32),
+              col=j[ok].astype(np.int32), val=np.where(i == j, 2.0, -1.0)[ok])
+    rng = np.random.default_rng(4)
+    As = [DeviceCSR(A) for _ in range(60)]
+    bs = [DeviceVec(rng.uniform(-1, 1, n)) for _ in As]
+    xs = [DeviceVec.zeros(n) for _ in As]
+    info = apcg.apcg_info_create(0, len(As))
+    c = impatient(apcg, (1_500_000, 255))
+    for maxit in (10, 10000):
+        apcg.apcg_counters_reset()
+        apcg.apcg_ksp_solve_batched(c, [a.h for a in As], [b.h for b in bs], [x.h for x in xs], 1e-14, maxit,
+                                    apcg.apcg_solve_opts_default(x0_is_zero=1), info)
+        k = apcg.apcg_counters_get()
+        assert k["graph_launches"] == 0 and k["kernel_launches"] <= 4
+        assert [apcg.apcg_info_get(info, q)["iterations"] for q in range(len(As))] == [maxit] * len(As)
+    apcg.apcg_info_destroy(info)
+    apcg.apcg_ctx_destroy(c)
