@@ -377,6 +377,131 @@ static apcg_status check_batch_ranges(int32_t nsys, const apcg_vec *b, const apc
     return APCG_SUCCESS;
 }
 
+// The batch on the persistent or the segmented schedule: descriptors hs (ws
+// holds workspace offsets on entry), results in d_info.  The caller marks the
+// operation.
+static apcg_status batched_kernels(apcg_ctx ctx, BatchCache *bc, const apcg_mat *A, std::vector<BatchSys> &hs,
+                                   const std::vector<double> &cost, const std::vector<int32_t> &order,
+                                   int64_t ws_total, double rtol, int32_t maxit, const apcg_solve_opts &opts,
+                                   BatchedFn fn, int tb, apcg_solve_info *d_info) {
+    const int32_t nsys = (int32_t)hs.size();
+    const int dev = ctx->device;
+    hipStream_t st = ctx->stream;
+    apcg_status s;
+    // (re)allocate device descriptors and workspace; the old buffers may
+    // still be used by queued work, so their release is deferred
+    if (bc->sys_cap < nsys || bc->ws_cap < ws_total) {
+        EventRef ev = event_get(dev);
+        if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
+        APCG_HIP(event_record(ev, st));
+        BatchCache old = *bc;
+        defer_release({ev}, [old]() {
+            hipSetDevice(old.device);
+            if (old.exec) hipGraphExecDestroy(old.exec);
+            if (old.graph) hipGraphDestroy(old.graph);
+            hipFree(old.d_sys);
+            hipFree(old.d_order);
+            hipFree(old.d_queue);
+            hipFree(old.d_ws);
+        });
+        bc->exec = nullptr;
+        bc->graph = nullptr;
+        bc->graph_hash = 0;
+        bc->desc_hash = 0;
+        const int64_t cap = std::max<int64_t>(nsys, bc->sys_cap);
+        APCG_HIP(hipMalloc((void **)&bc->d_sys, sizeof(BatchSys) * cap));
+        APCG_HIP(hipMalloc((void **)&bc->d_order, sizeof(int32_t) * cap));
+        APCG_HIP(hipMalloc((void **)&bc->d_queue, 256));
+        APCG_HIP(hipMalloc((void **)&bc->d_ws, sizeof(double) * std::max<int64_t>(ws_total, 64)));
+        bc->sys_cap = cap;
+        bc->ws_cap = std::max<int64_t>(ws_total, 64);
+    }
+    for (int32_t i = 0; i < nsys; ++i) hs[i].ws = bc->d_ws + reinterpret_cast<int64_t>(hs[i].ws);
+    // refill the sliced-diagonal values of the systems that use them
+    for (int32_t i = 0; i < nsys; ++i)
+        if (hs[i].sval && (s = prepare_sdia(A[i], st))) return s;
+    uint64_t h = fnv1a(hs.data(), sizeof(BatchSys) * nsys);
+    h = fnv1a(order.data(), sizeof(int32_t) * nsys, h);
+    if (h != bc->desc_hash) {
+        g_counters.h2d_copies += 2;
+        APCG_HIP(hipMemcpyAsync(bc->d_sys, hs.data(), sizeof(BatchSys) * nsys, hipMemcpyHostToDevice, st));
+        APCG_HIP(hipMemcpyAsync(bc->d_order, order.data(), sizeof(int32_t) * nsys, hipMemcpyHostToDevice, st));
+        // the host arrays are local: wait until the copies have consumed them
+        g_counters.host_syncs++;
+        APCG_HIP(hipStreamSynchronize(st));
+        bc->desc_hash = h;
+    }
+
+    hipDeviceProp_t prop;
+    APCG_HIP(hipGetDeviceProperties(&prop, dev));
+    int sched = opts.batch_schedule;
+    if (sched == APCG_BATCH_AUTO) {
+        // one workgroup per system finishes no earlier than its costliest
+        // system on one CU; the segmented schedule spreads every system
+        // over the whole chip
+        const double total = std::accumulate(cost.begin(), cost.end(), 0.0);
+        const double worst = *std::max_element(cost.begin(), cost.end());
+        sched = worst * prop.multiProcessorCount <= total ? APCG_BATCH_PERSISTENT : APCG_BATCH_SEGMENTED;
+    }
+    if (sched == APCG_BATCH_SEGMENTED) return seg_solve(ctx, nsys, hs.data(), bc->d_sys, rtol, maxit, opts, d_info);
+    if (sched != APCG_BATCH_PERSISTENT) return set_error(APCG_ERR_INVALID_ARG, "unknown batch schedule");
+    int per_cu = 0;
+    APCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(fn), tb, 0));
+    const int grid = std::max(1, std::min<int>(nsys, std::max(1, per_cu) * prop.multiProcessorCount));
+    const int norm_pre = opts.norm_type == APCG_NORM_PRECONDITIONED;
+    const int x0z = opts.x0_is_zero ? 1 : 0;
+
+    uint64_t gh = fnv1a(&h, sizeof h);
+    double params[2] = {rtol, (double)maxit};
+    int iparams[6] = {grid, tb, x0z, opts.pc, norm_pre, nsys};
+    gh = fnv1a(params, sizeof params, gh);
+    gh = fnv1a(iparams, sizeof iparams, gh);
+    const void *ip = d_info;
+    gh = fnv1a(&ip, sizeof ip, gh);
+    if (opts.mode == APCG_MODE_GRAPH) {
+        if (!bc->exec || bc->graph_hash != gh) {
+            if (bc->exec) {
+                EventRef ev = event_get(dev);
+                if (ev) event_record(ev, st);
+                hipGraphExec_t oe = bc->exec;
+                hipGraph_t og = bc->graph;
+                defer_release({ev}, [oe, og, dev]() {
+                    hipSetDevice(dev);
+                    hipGraphExecDestroy(oe);
+                    hipGraphDestroy(og);
+                });
+                bc->exec = nullptr;
+                bc->graph = nullptr;
+            }
+            APCG_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed));
+            hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, st, bc->d_queue);
+            hipLaunchKernelGGL(fn, dim3(grid), dim3(tb), 0, st, (const BatchSys *)bc->d_sys,
+                               (const int32_t *)bc->d_order, nsys, bc->d_queue, rtol, maxit, x0z, opts.pc,
+                               norm_pre, d_info);
+            hipGraph_t g = nullptr;
+            hipError_t e = hipStreamEndCapture(st, &g);
+            if (e != hipSuccess) return hip_error(e, "hipStreamEndCapture(batched)");
+            e = hipGraphInstantiate(&bc->exec, g, nullptr, nullptr, 0);
+            if (e != hipSuccess) {
+                hipGraphDestroy(g);
+                return hip_error(e, "hipGraphInstantiate(batched)");
+            }
+            bc->graph = g;
+            bc->graph_hash = gh;
+        }
+        g_counters.graph_launches++;
+        APCG_HIP(hipGraphLaunch(bc->exec, st));
+    } else {
+        hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, st, bc->d_queue);
+        APCG_CHECK_LAUNCH("k_queue_reset");
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(tb), 0, st, (const BatchSys *)bc->d_sys,
+                           (const int32_t *)bc->d_order, nsys, bc->d_queue, rtol, maxit, x0z, opts.pc, norm_pre,
+                           d_info);
+        APCG_CHECK_LAUNCH("k_pcg_batched");
+    }
+    return APCG_SUCCESS;
+}
+
 extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b,
                                               const apcg_vec *x, double rtol, int32_t maxit,
                                               const apcg_solve_opts *opts_in, apcg_info info) {
@@ -444,7 +569,11 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
         acc.push_back({&info->rec, ACC_W});
         apcg_status s;
         if ((s = op_begin(ctx, acc.data(), (int)acc.size()))) return s;
-        hipStream_t st = ctx->stream;
+        std::vector<int32_t> rest(nsys);  // systems not solved by teams
+        std::iota(rest.begin(), rest.end(), 0);
+        std::vector<apcg_mat> mats(A, A + nsys);
+        apcg_solve_info *d_info = info->d;
+        LeftRecords records;
 
         // Systems that fit the chip are solved by teams of workgroups, each
         // system's vectors and matrix in registers from the first iteration
@@ -460,136 +589,41 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
                 std::vector<int32_t> left;
                 if ((s = team_pcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, fit, info->d, nullptr, 0, &left)))
                     return s;
-                if ((s = op_end(ctx, acc.data(), (int)acc.size()))) return s;
-                apcg_solve_opts single = opts;
-                single.mode = APCG_MODE_STREAM;
-                for (int32_t i : left)  // a launch that was given up (see team.h)
-                    if ((s = pcg_solve_marked(ctx, A[i], b[i], x[i], rtol, maxit, &single, info, i, nullptr, 0)))
-                        return s;
-                return APCG_SUCCESS;
+                if (left.empty()) return op_end(ctx, acc.data(), (int)acc.size());
+                rest = std::move(left);  // systems that members have left (see team.h): x is as it was
             }
         }
-
-        // (re)allocate device descriptors and workspace; the old buffers may
-        // still be used by queued work, so their release is deferred
-        if (bc->sys_cap < nsys || bc->ws_cap < ws_total) {
-            EventRef ev = event_get(dev);
-            if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
-            APCG_HIP(event_record(ev, st));
-            BatchCache old = *bc;
-            defer_release({ev}, [old]() {
-                hipSetDevice(old.device);
-                if (old.exec) hipGraphExecDestroy(old.exec);
-                if (old.graph) hipGraphDestroy(old.graph);
-                hipFree(old.d_sys);
-                hipFree(old.d_order);
-                hipFree(old.d_queue);
-                hipFree(old.d_ws);
-            });
-            bc->exec = nullptr;
-            bc->graph = nullptr;
-            bc->graph_hash = 0;
-            bc->desc_hash = 0;
-            const int64_t cap = std::max<int64_t>(nsys, bc->sys_cap);
-            APCG_HIP(hipMalloc((void **)&bc->d_sys, sizeof(BatchSys) * cap));
-            APCG_HIP(hipMalloc((void **)&bc->d_order, sizeof(int32_t) * cap));
-            APCG_HIP(hipMalloc((void **)&bc->d_queue, 256));
-            APCG_HIP(hipMalloc((void **)&bc->d_ws, sizeof(double) * std::max<int64_t>(ws_total, 64)));
-            bc->sys_cap = cap;
-            bc->ws_cap = std::max<int64_t>(ws_total, 64);
-        }
-        for (int32_t i = 0; i < nsys; ++i) hs[i].ws = bc->d_ws + reinterpret_cast<int64_t>(hs[i].ws);
-        // refill the sliced-diagonal values of the systems that use them
-        for (int32_t i = 0; i < nsys; ++i)
-            if (hs[i].sval && (s = prepare_sdia(A[i], st))) return s;
-        uint64_t h = fnv1a(hs.data(), sizeof(BatchSys) * nsys);
-        h = fnv1a(order.data(), sizeof(int32_t) * nsys, h);
-        if (h != bc->desc_hash) {
-            g_counters.h2d_copies += 2;
-            APCG_HIP(hipMemcpyAsync(bc->d_sys, hs.data(), sizeof(BatchSys) * nsys, hipMemcpyHostToDevice, st));
-            APCG_HIP(hipMemcpyAsync(bc->d_order, order.data(), sizeof(int32_t) * nsys, hipMemcpyHostToDevice, st));
-            // the host arrays are local: wait until the copies have consumed them
-            g_counters.host_syncs++;
-            APCG_HIP(hipStreamSynchronize(st));
-            bc->desc_hash = h;
-        }
-
-        hipDeviceProp_t prop;
-        APCG_HIP(hipGetDeviceProperties(&prop, dev));
-        int sched = opts.batch_schedule;
-        if (sched == APCG_BATCH_AUTO) {
-            // one workgroup per system finishes no earlier than its costliest
-            // system on one CU; the segmented schedule spreads every system
-            // over the whole chip
-            const double total = std::accumulate(cost.begin(), cost.end(), 0.0);
-            const double worst = *std::max_element(cost.begin(), cost.end());
-            sched = worst * prop.multiProcessorCount <= total ? APCG_BATCH_PERSISTENT : APCG_BATCH_SEGMENTED;
-        }
-        if (sched == APCG_BATCH_SEGMENTED) {
-            if ((s = seg_solve(ctx, nsys, hs.data(), bc->d_sys, rtol, maxit, opts, info->d))) return s;
-            return op_end(ctx, acc.data(), (int)acc.size());
-        }
-        if (sched != APCG_BATCH_PERSISTENT) return set_error(APCG_ERR_INVALID_ARG, "unknown batch schedule");
-        int per_cu = 0;
-        APCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(fn), tb, 0));
-        const int grid = std::max(1, std::min<int>(nsys, std::max(1, per_cu) * prop.multiProcessorCount));
-        const int norm_pre = opts.norm_type == APCG_NORM_PRECONDITIONED;
-        const int x0z = opts.x0_is_zero ? 1 : 0;
-
-        uint64_t gh = fnv1a(&h, sizeof h);
-        double params[2] = {rtol, (double)maxit};
-        int iparams[6] = {grid, tb, x0z, opts.pc, norm_pre, nsys};
-        gh = fnv1a(params, sizeof params, gh);
-        gh = fnv1a(iparams, sizeof iparams, gh);
-        const void *ip = info->d;
-        gh = fnv1a(&ip, sizeof ip, gh);
-        if (opts.mode == APCG_MODE_GRAPH) {
-            if (!bc->exec || bc->graph_hash != gh) {
-                if (bc->exec) {
-                    EventRef ev = event_get(dev);
-                    if (ev) event_record(ev, st);
-                    hipGraphExec_t oe = bc->exec;
-                    hipGraph_t og = bc->graph;
-                    defer_release({ev}, [oe, og, dev]() {
-                        hipSetDevice(dev);
-                        hipGraphExecDestroy(oe);
-                        hipGraphDestroy(og);
-                    });
-                    bc->exec = nullptr;
-                    bc->graph = nullptr;
-                }
-                APCG_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed));
-                hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, st, bc->d_queue);
-                hipLaunchKernelGGL(fn, dim3(grid), dim3(tb), 0, st, (const BatchSys *)bc->d_sys,
-                                   (const int32_t *)bc->d_order, nsys, bc->d_queue, rtol, maxit, x0z, opts.pc,
-                                   norm_pre, info->d);
-                hipGraph_t g = nullptr;
-                hipError_t e = hipStreamEndCapture(st, &g);
-                if (e != hipSuccess) return hip_error(e, "hipStreamEndCapture(batched)");
-                e = hipGraphInstantiate(&bc->exec, g, nullptr, nullptr, 0);
-                if (e != hipSuccess) {
-                    hipGraphDestroy(g);
-                    return hip_error(e, "hipGraphInstantiate(batched)");
-                }
-                bc->graph = g;
-                bc->graph_hash = gh;
+        if ((int32_t)rest.size() < nsys) {
+            std::vector<BatchSys> h;
+            std::vector<double> c;
+            std::vector<apcg_mat> m;
+            ws_total = 0;
+            for (int32_t i : rest) {
+                h.push_back(hs[i]);
+                h.back().ws = reinterpret_cast<double *>(ws_total);
+                ws_total += ((6 * (int64_t)hs[i].n + 63) / 64) * 64;
+                c.push_back(cost[i]);
+                m.push_back(A[i]);
             }
-            g_counters.graph_launches++;
-            APCG_HIP(hipGraphLaunch(bc->exec, st));
-        } else {
-            hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, st, bc->d_queue);
-            APCG_CHECK_LAUNCH("k_queue_reset");
-            hipLaunchKernelGGL(fn, dim3(grid), dim3(tb), 0, st, (const BatchSys *)bc->d_sys,
-                               (const int32_t *)bc->d_order, nsys, bc->d_queue, rtol, maxit, x0z, opts.pc, norm_pre,
-                               info->d);
-            APCG_CHECK_LAUNCH("k_pcg_batched");
+            hs = std::move(h);
+            cost = std::move(c);
+            mats = std::move(m);
+            order.resize(rest.size());
+            std::iota(order.begin(), order.end(), 0);
+            std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t c) { return cost[a] > cost[c]; });
+            nsys = (int32_t)rest.size();
+            opts.batch_schedule = APCG_BATCH_SEGMENTED;  // the same bits as the teams'
+            if ((s = records.open(ctx, nsys))) return s;
+            d_info = records.info;
         }
+        if ((s = batched_kernels(ctx, bc, mats.data(), hs, cost, order, ws_total, rtol, maxit, opts, fn, tb, d_info)))
+            return s;
+        if (records.info && (s = records.copy_back(rest, info->d))) return s;
         return op_end(ctx, acc.data(), (int)acc.size());
     } catch (const std::bad_alloc &) {
         return set_error(APCG_ERR_OUT_OF_MEMORY, "host allocation failed");
     }
 }
-
 // ===========================================================================
 // Segmented schedule: the batch as one block-diagonal system.
 //

@@ -1255,34 +1255,49 @@ static apcg_status bf_features(apcg_ctx ctx, BfCache *bc, int32_t nsys, const ap
 
 using namespace apcg;
 
-// Systems that fit the chip are solved by teams of workgroups (see
-// apcg_ksp_solve_batched; the same bits as the tiles): 48 mixed systems of 1e3
-// to 1e5 rows 52.2 ms on tiles, 9.6 on teams.  A caller who sets the
-// tiles gets them.  Ends the marked operation when it solves the batch (*done).
-static apcg_status bf_teams(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
+// Solves the batch whose descriptors bf_systems has built.  Systems that fit
+// the chip are solved by teams of workgroups (see apcg_ksp_solve_batched; the
+// same bits as the tiles): 48 mixed systems of 1e3 to 1e5 rows 52.2 ms on
+// tiles, 9.6 on teams.  A caller who sets the tiles gets them.
+static apcg_status bf_solve(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
+                            std::vector<FSys> &hs, int64_t ws_total, const std::vector<apcg_mat_s *> &refill,
                             double rtol, int32_t maxit, const apcg_solve_opts &opts, const apcg_fcg_opts &fo,
-                            const float *coeffs, const double *lmax, apcg_info info, const std::vector<Acc> &acc,
-                            bool *done) {
-    *done = false;
-    if (opts.batch_schedule != APCG_BATCH_AUTO || opts.batch_tile_rows || opts.batch_tail_tile_rows ||
-        maxit > kTeamFcgMaxIts)
-        return APCG_SUCCESS;
-    TeamFit fit;
+                            const float *coeffs, const double *lmax, apcg_solve_info *info) {
     apcg_status s;
-    if ((s = team_eligible(ctx, nsys, A, 2, &fit)) || fit.rows == 0) return s;
+    BfRun run;
+    run.coeffs = coeffs;
+    run.lmax = lmax;
+    TeamFit fit;
+    if (opts.batch_schedule == APCG_BATCH_AUTO && !opts.batch_tile_rows && !opts.batch_tail_tile_rows &&
+        maxit <= kTeamFcgMaxIts && (s = team_eligible(ctx, nsys, A, 2, &fit)))
+        return s;
+    if (fit.rows == 0)
+        return bf_core(ctx, bf_cache(ctx), nsys, hs, ws_total, refill, rtol, maxit, opts, fo, run, info);
     std::vector<int32_t> order(nsys), left;
     for (int32_t i = 0; i < nsys; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int32_t p, int32_t q) { return A[p]->n > A[q]->n; });
-    if ((s = team_fcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, fo, fit, coeffs, lmax, info->d, &left))) return s;
-    *done = true;
-    if ((s = op_end(ctx, acc.data(), (int)acc.size()))) return s;
-    apcg_solve_opts single = opts;
-    single.mode = APCG_MODE_STREAM;
-    for (int32_t i : left)  // a launch that was given up (see team.h)
-        if ((s = apcg_ksp_solve_fcg_poly(ctx, A[i], b[i], x[i], rtol, maxit, coeffs + 9 * (int64_t)i, lmax + i, &single,
-                                         &fo, info, i)))
-            return s;
-    return APCG_SUCCESS;
+    if ((s = team_fcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, fo, fit, coeffs, lmax, info, &left)) ||
+        left.empty())
+        return s;
+    // systems that members have left (see team.h): x is as it was, the tiles solve them
+    std::vector<FSys> h;
+    std::vector<apcg_mat_s *> copies;
+    LeftRecords records;
+    ws_total = 0;
+    for (int32_t i : left) {
+        h.push_back(hs[i]);
+        h.back().ws = reinterpret_cast<double *>(ws_total);
+        ws_total += ((9 * (int64_t)hs[i].n + 63) / 64) * 64;
+        if (hs[i].sval) copies.push_back(A[i]);
+    }
+    if ((s = records.open(ctx, (int32_t)left.size()))) return s;
+    if ((s = records.copy_polynomials(left, coeffs, lmax))) return s;
+    run.coeffs = records.coeffs;
+    run.lmax = records.lmax;
+    if ((s = bf_core(ctx, bf_cache(ctx), (int32_t)left.size(), h, ws_total, copies, rtol, maxit, opts, fo, run,
+                     records.info)))
+        return s;
+    return records.copy_back(left, info);
 }
 
 extern "C" apcg_status apcg_ksp_solve_batched_fcg_poly(apcg_ctx ctx, int32_t nsys, const apcg_mat *A,
@@ -1322,13 +1337,9 @@ extern "C" apcg_status apcg_ksp_solve_batched_fcg_poly(apcg_ctx ctx, int32_t nsy
         }
         acc.push_back({&info->rec, ACC_W});
         if ((s = op_begin(ctx, acc.data(), (int)acc.size()))) return s;
-        bool done = false;
-        if ((s = bf_teams(ctx, nsys, A, b, x, rtol, maxit, opts, fo, dev_coeffs, dev_lmax, info, acc, &done)) || done)
+        if ((s = bf_solve(ctx, nsys, A, b, x, hs, ws_total, refill, rtol, maxit, opts, fo, dev_coeffs, dev_lmax,
+                          info->d)))
             return s;
-        BfRun run;
-        run.coeffs = dev_coeffs;
-        run.lmax = dev_lmax;
-        if ((s = bf_core(ctx, bf_cache(ctx), nsys, hs, ws_total, refill, rtol, maxit, opts, fo, run, info->d))) return s;
         return op_end(ctx, acc.data(), (int)acc.size());
     } catch (const std::bad_alloc &) {
         return set_error(APCG_ERR_OUT_OF_MEMORY, "host allocation failed");
@@ -1397,13 +1408,8 @@ extern "C" apcg_status apcg_ksp_solve_batched_learned(apcg_ctx ctx, int32_t nsys
         BfCache *bc = bf_cache(ctx);
         if ((s = bf_features(ctx, bc, nsys, A, b, nullptr, nullptr))) return s;
         if ((s = mlp_infer(ctx, dev_params, dev_mean, dev_std, bc->d_X, nsys, bc->d_C))) return s;
-        bool done = false;
-        if ((s = bf_teams(ctx, nsys, A, b, x, rtol, maxit, opts, fo, bc->d_C, bc->d_L, info, acc, &done)) || done)
+        if ((s = bf_solve(ctx, nsys, A, b, x, hs, ws_total, refill, rtol, maxit, opts, fo, bc->d_C, bc->d_L, info->d)))
             return s;
-        BfRun run;
-        run.coeffs = bc->d_C;
-        run.lmax = bc->d_L;
-        if ((s = bf_core(ctx, bc, nsys, hs, ws_total, refill, rtol, maxit, opts, fo, run, info->d))) return s;
         return op_end(ctx, acc.data(), (int)acc.size());
     } catch (const std::bad_alloc &) {
         return set_error(APCG_ERR_OUT_OF_MEMORY, "host allocation failed");

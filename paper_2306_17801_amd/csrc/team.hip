@@ -441,6 +441,46 @@ void team_cache_release(uint64_t ctx_id, int device) {
     delete t;
 }
 
+apcg_status LeftRecords::open(apcg_ctx ctx, int32_t n) {
+    char *p = nullptr;
+    APCG_HIP(hipMalloc((void **)&p, (sizeof(apcg_solve_info) + sizeof(double) + 9 * sizeof(float)) * n));
+    ctx_ = ctx;
+    info = reinterpret_cast<apcg_solve_info *>(p);
+    lmax = reinterpret_cast<double *>(info + n);
+    coeffs = reinterpret_cast<float *>(lmax + n);
+    return APCG_SUCCESS;
+}
+
+apcg_status LeftRecords::copy_polynomials(const std::vector<int32_t> &left, const float *all_coeffs,
+                                          const double *all_lmax) {
+    hipStream_t st = ctx_->stream;
+    for (size_t k = 0; k < left.size(); ++k) {
+        APCG_HIP(hipMemcpyAsync(coeffs + 9 * k, all_coeffs + 9 * (size_t)left[k], 9 * sizeof(float),
+                                hipMemcpyDeviceToDevice, st));
+        APCG_HIP(hipMemcpyAsync(lmax + k, all_lmax + left[k], sizeof(double), hipMemcpyDeviceToDevice, st));
+    }
+    return APCG_SUCCESS;
+}
+
+apcg_status LeftRecords::copy_back(const std::vector<int32_t> &left, apcg_solve_info *all) {
+    for (size_t k = 0; k < left.size(); ++k)
+        APCG_HIP(hipMemcpyAsync(all + left[k], info + k, sizeof(apcg_solve_info), hipMemcpyDeviceToDevice,
+                                ctx_->stream));
+    return APCG_SUCCESS;
+}
+
+LeftRecords::~LeftRecords() {
+    if (!info) return;
+    EventRef ev = event_get(ctx_->device);
+    if (!ev || event_record(ev, ctx_->stream) != hipSuccess) return;
+    const int dev = ctx_->device;
+    apcg_solve_info *p = info;
+    defer_release({ev}, [p, dev]() {
+        hipSetDevice(dev);
+        hipFree(p);
+    });
+}
+
 int64_t team_lds(int R, int nb, int windows, bool own_vectors) {
     const int64_t doubles = (int64_t)windows * window_size(R, nb) + (own_vectors ? 2 * TT * R : 0);
     return std::max<int64_t>(8 * doubles, 8 * kMarkWords) + (2 * (int64_t)nb + 15) / 8 * 8;
@@ -528,10 +568,19 @@ apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const apcg_mat
     g_counters.host_polls++;
     APCG_HIP(hipEventSynchronize(t->ev->e));
     for (int32_t i = 0; i < nsys; ++i) {
-        if (host[i] == kDone) continue;
+        if (host[i] == kDone) {
+            A[i]->team->unfit = 0;
+            continue;
+        }
         left->push_back(i);
-        if (host[i] >= kUnfit) A[i]->team->border[0] = A[i]->team->border[1] = -1;  // (changed in place: read again)
-        else t->rest = 256;  // a wait ran out: the chip is shared, no teams for a while
+        if (host[i] == kUnfit) {  // (changed in place)
+            ++A[i]->team->unfit;
+            A[i]->team->border[0] = A[i]->team->border[1] = -1;
+        } else if (host[i] == kOneSided) {
+            A[i]->team->one_sided = true;
+        } else {
+            t->rest = 256;  // a wait ran out: the chip is shared, no teams for a while
+        }
     }
     return APCG_SUCCESS;
 }
@@ -616,6 +665,7 @@ apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windo
     for (int32_t i = 0; i < nsys; ++i) {
         maxrow = std::max(maxrow, A[i]->sell_maxw);
         if (!team_width(maxrow) || A[i]->n > 256 * TT * kMaxRows) return APCG_SUCCESS;
+        if (A[i]->team->unfit > 1 || (windows > 1 && A[i]->team->one_sided)) return APCG_SUCCESS;
     }
     TeamCache *t = team_cache(c);
     if (t->rest > 0) {

@@ -73,6 +73,22 @@ apcg_status team_launch(int device, hipStream_t st, int wgs, int cus, F launch) 
     return APCG_SUCCESS;
 }
 
+// Records of the systems that teams have left, by their place among them: the
+// results, and the flexible solve's polynomials.  Given back once ctx's work
+// queued until then has run.
+struct LeftRecords {
+    apcg_solve_info *info = nullptr;
+    double *lmax = nullptr;
+    float *coeffs = nullptr;
+    apcg_status open(apcg_ctx ctx, int32_t n);
+    apcg_status copy_polynomials(const std::vector<int32_t> &left, const float *all_coeffs, const double *all_lmax);
+    apcg_status copy_back(const std::vector<int32_t> &left, apcg_solve_info *all);
+    ~LeftRecords();
+
+private:
+    apcg_ctx ctx_ = nullptr;
+};
+
 // Per-context buffers of the team solves.
 struct TeamCache {
     int device = 0;
@@ -152,8 +168,8 @@ struct TeamFit {
 
 // Whether every system can be solved by teams on ctx's device: rows of at
 // most 7 entries, `windows` windows that fit the LDS (1: PCG, 2: the flexible
-// solve), no system larger than the chip.  Reads the matrices' borders back
-// once per matrix.
+// solve), no system larger than the chip, none that members have refused.
+// Reads the matrices' borders back once per matrix.
 apcg_status team_eligible(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, int windows, TeamFit *fit);
 
 // Jacobi-PCG (or CG) of the systems, started in `order` (largest cost

@@ -107,3 +107,97 @@ def test_threads_share_a_matrix(apcg):
             t.join()
         assert all(np.array_equal(g, got[0]) for g in got)
         assert rel(got[0], oracle.pcg(s.A, s.b, rtol=0.0, maxit=20).x) <= 1e-12
+
+
+def test_refusing_system_leaves_the_others_and_is_remembered(apcg, ctx):
+    """A batch in which one matrix is read one way only (row 2048 names row 2047
+    of the member before it, which names nothing back): the members of that
+    system refuse the flexible solve, the others finish, the tiles solve the
+    rest to the same bits; the next call goes to the tiles at once."""
+    import torch
+    from oracle import learned as OL
+    from paper_2306_17801_amd.device import DeviceCSR, DeviceVec
+
+    S = [grid((70, 71), 1), grid((1, 10000), 2), grid((1, 900), 3), grid((90, 50), 4)]
+    A = S[1].A
+    keep = np.ones(A.col.size, bool)
+    keep[[e for e in range(A.rowptr[2047], A.rowptr[2048]) if A.col[e] == 2048]] = False
+    rp = np.concatenate([[0], np.cumsum(np.add.reduceat(keep, A.rowptr[:-1]))]).astype(np.int32)
+    S[1] = P.System(A=P.CSR(n=A.n, rowptr=rp, col=A.col[keep], val=A.val[keep]), b=S[1].b)
+    lms = [oracle.gershgorin(s.A)[1] for s in S]
+    C = torch.from_numpy(np.concatenate([OL.chebyshev_iteration_coeffs(l / 100, l) for l in lms]).astype(
+        np.float32)).cuda()
+    L = torch.tensor(lms, dtype=torch.float64).cuda()
+    torch.cuda.synchronize()
+    As, bs = [DeviceCSR(s.A) for s in S], [DeviceVec(s.b) for s in S]
+    info = apcg.apcg_info_create(0, len(S))
+    print("case one-sided matrix in a batch", flush=True)
+
+    def solve(tiles):
+        xs = [DeviceVec.zeros(s.A.n) for s in S]
+        apcg.apcg_counters_reset()
+        apcg.apcg_ksp_solve_batched_fcg_poly(
+            ctx, [a.h for a in As], [b.h for b in bs], [x.h for x in xs], 0.0, 6, C, L,
+            apcg.apcg_solve_opts_default(x0_is_zero=1, batch_tile_rows=256 if tiles else 0), None, info)
+        n = apcg.apcg_counters_get()
+        return [apcg.apcg_info_get(info, k) for k in range(len(S))], [x.numpy() for x in xs], n
+
+    want = solve(True)
+    first, second = solve(False), solve(False)
+    for got in (first, second):
+        assert got[0] == want[0] and all(np.array_equal(p, q) for p, q in zip(got[1], want[1]))
+        assert got[2]["graph_launches"] > 0  # (the tiles, not one system after the other)
+    assert second[2]["kernel_launches"] <= want[2]["kernel_launches"] < first[2]["kernel_launches"]
+    apcg.apcg_info_destroy(info)
+
+
+def test_rows_grown_in_place_are_given_up_twice_at_most(apcg, ctx):
+    """Row lengths rewritten in place past what a member holds (9 entries): the
+    launch finds it, reads the border again, finds it again and leaves the
+    matrix to the other schedules from then on."""
+    import torch
+    from paper_2306_17801_amd.device import DeviceCSR, DeviceVec
+
+    n = 9000
+    i = np.arange(n)
+    thin = pairs(n, i ^ 1)
+    # no more entries than before: of every 100 rows the first nine couple to each other, the others to none
+    rows, cols = [], []
+    for r0 in range(0, n, 100):
+        for r in range(100):
+            c = range(9) if r < 9 else [r]
+            rows += [r0 + r] * len(c)
+            cols += [r0 + q for q in c]
+    rows, cols = np.array(rows), np.array(cols)
+    short = 2 * n - rows.size
+    assert short >= 0
+    thick_val = np.where(rows == cols, 12.0, -1.0)
+    rp = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int32)
+    thick = P.CSR(n=n, rowptr=rp, col=cols.astype(np.int32), val=thick_val)
+    assert np.diff(rp).max() == 9
+    b = np.random.default_rng(8).uniform(-1, 1, n)
+    other = grid((60, 61), 5)
+    As, bs = [DeviceCSR(thin), DeviceCSR(other.A)], [DeviceVec(b), DeviceVec(other.b)]
+    xs = [DeviceVec.zeros(n), DeviceVec.zeros(other.A.n)]
+    info = apcg.apcg_info_create(0, 2)
+    print("case rows grown in place", flush=True)
+
+    def solve(sched):
+        apcg.apcg_counters_reset()
+        apcg.apcg_ksp_solve_batched(ctx, [a.h for a in As], [v.h for v in bs], [v.h for v in xs], 1e-10, 20000,
+                                    apcg.apcg_solve_opts_default(x0_is_zero=1, batch_schedule=sched), info)
+        return apcg.apcg_counters_get()["kernel_launches"], [x.numpy() for x in xs]
+
+    assert solve(0)[0] <= 4  # teams
+    pad = np.zeros(short, np.int32)
+    As[0].rowptr.copy_(torch.from_numpy(thick.rowptr))
+    As[0].col.copy_(torch.from_numpy(np.concatenate([thick.col, pad])))
+    As[0].val.copy_(torch.from_numpy(np.concatenate([thick.val, np.zeros(short)])))
+    torch.cuda.synchronize()
+    kernels, want = solve(2)
+    ref = oracle.pcg(thick, b, rtol=1e-10, maxit=20000)
+    assert rel(want[0], ref.x) <= 1e-9
+    tries = [solve(0) for _ in range(4)]
+    assert all(np.array_equal(p, q) for _, got in tries for p, q in zip(got, want))
+    assert [k > kernels for k, _ in tries] == [True, True, False, False]
+    apcg.apcg_info_destroy(info)
