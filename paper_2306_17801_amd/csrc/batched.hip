@@ -133,9 +133,11 @@ __device__ __forceinline__ double row_product_z(const dev::glob_t<int32_t> *col,
     return sum;
 }
 
-template <int TB>
+// HIST: alpha and beta of the first hist_cap iterations go to hist[0..] and
+// hist[hist_cap..], as pcg_solve_marked records them.
+template <int TB, bool HIST = false>
 __device__ void solve_one(const BatchSys &S, double rtol, int32_t maxit, int x0_zero, int pc, int norm_pre,
-                          apcg_solve_info *out, double *lds) {
+                          apcg_solve_info *out, double *lds, double *hist = nullptr, int32_t hist_cap = 0) {
     const int n = S.n;
     // global pointers: the system's pointers come from a table in memory
     // (generic to the compiler), and flat accesses would also count in lgkmcnt
@@ -238,6 +240,10 @@ __device__ void solve_one(const BatchSys &S, double rtol, int32_t maxit, int x0_
         else if (res <= rtol * ref) status = APCG_SOLVE_CONVERGED;
         else if (!(rho_new > 0.0)) status = APCG_SOLVE_BREAKDOWN_RZ;
         else if (k >= maxit) status = APCG_SOLVE_MAXIT;
+        if (HIST && threadIdx.x == 0 && k <= hist_cap) {
+            hist[k - 1] = alpha;
+            if (!status) hist[hist_cap + k - 1] = rho_new / rho;
+        }
         if (!status) {
             beta = rho_new / rho;
             rho = rho_new;
@@ -271,6 +277,23 @@ __global__ __launch_bounds__(TB) void k_pcg_batched(const BatchSys *sys, const i
     }
 }
 
+// What a team launch that nobody waits for has left, one workgroup per system
+// (sys == nullptr: the one); usually nothing, and then 2 us.
+template <int TB, bool HIST>
+__global__ __launch_bounds__(TB) void k_pcg_left(const BatchSys *sys, BatchSys one, const uint32_t *verdicts,
+                                                 uint64_t *report, uint64_t launch, double rtol, int32_t maxit,
+                                                 int x0_zero, int pc, int norm_pre, apcg_solve_info *info,
+                                                 double *hist, int32_t hist_cap) {
+    __shared__ double lds[4 * (TB / 64)];
+    const int id = blockIdx.x;
+    const uint32_t v = verdicts[id];
+    if (v == kDone) return;
+    if (threadIdx.x == 0)
+        __hip_atomic_store(report, launch | (uint64_t)(id + 1) << 8 | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const BatchSys S = sys ? sys[id] : one;
+    solve_one<TB, HIST>(S, rtol, maxit, x0_zero, pc, norm_pre, info + id, lds, hist, hist_cap);
+}
+
 __global__ void k_queue_reset(unsigned *queue) {
     if (threadIdx.x == 0) *queue = 0u;
 }
@@ -298,9 +321,29 @@ uint64_t fnv1a(const void *p, size_t n, uint64_t h = 1469598103934665603ull) {
 
 }  // namespace
 
+apcg_status launch_pcg_left(hipStream_t st, const TeamLater &later, const apcg_mat_s *A, const double *b, double *x,
+                            double *ws, double rtol, int32_t maxit, const apcg_solve_opts &opts, apcg_solve_info *info,
+                            double *hist, int32_t hist_cap) {
+    BatchSys one{};
+    one.rowptr = A->rowptr;
+    one.col = A->col;
+    one.val = A->val;
+    one.b = b;
+    one.x = x;
+    one.ws = ws;
+    one.n = A->n;
+    hipLaunchKernelGGL((hist ? k_pcg_left<1024, true> : k_pcg_left<1024, false>), dim3(1), dim3(1024), 0, st,
+                       (const BatchSys *)nullptr, one, later.verdicts, later.report, later.launch, rtol, maxit,
+                       opts.x0_is_zero ? 1 : 0, opts.pc, opts.norm_type == APCG_NORM_PRECONDITIONED ? 1 : 0, info, hist,
+                       hist_cap);
+    APCG_CHECK_LAUNCH("k_pcg_left");
+    return APCG_SUCCESS;
+}
+
 // Per-context batch resources (kept in a side table keyed by context id).
 struct BatchCache {
     int device = 0;
+    int cus = 0;
     BatchSys *d_sys = nullptr;
     int32_t *d_order = nullptr;
     unsigned *d_queue = nullptr;
@@ -377,17 +420,13 @@ static apcg_status check_batch_ranges(int32_t nsys, const apcg_vec *b, const apc
     return APCG_SUCCESS;
 }
 
-// The batch on the persistent or the segmented schedule: descriptors hs (ws
-// holds workspace offsets on entry), results in d_info.  The caller marks the
-// operation.
-static apcg_status batched_kernels(apcg_ctx ctx, BatchCache *bc, const apcg_mat *A, std::vector<BatchSys> &hs,
-                                   const std::vector<double> &cost, const std::vector<int32_t> &order,
-                                   int64_t ws_total, double rtol, int32_t maxit, const apcg_solve_opts &opts,
-                                   BatchedFn fn, int tb, apcg_solve_info *d_info) {
+// Room for the batch in bc, its descriptors (ws holds workspace offsets on
+// entry) on the device; *hash is that of what lies there.
+static apcg_status batch_upload(apcg_ctx ctx, BatchCache *bc, std::vector<BatchSys> &hs,
+                                const std::vector<int32_t> &order, int64_t ws_total, uint64_t *hash) {
     const int32_t nsys = (int32_t)hs.size();
     const int dev = ctx->device;
     hipStream_t st = ctx->stream;
-    apcg_status s;
     // (re)allocate device descriptors and workspace; the old buffers may
     // still be used by queued work, so their release is deferred
     if (bc->sys_cap < nsys || bc->ws_cap < ws_total) {
@@ -417,11 +456,9 @@ static apcg_status batched_kernels(apcg_ctx ctx, BatchCache *bc, const apcg_mat 
         bc->ws_cap = std::max<int64_t>(ws_total, 64);
     }
     for (int32_t i = 0; i < nsys; ++i) hs[i].ws = bc->d_ws + reinterpret_cast<int64_t>(hs[i].ws);
-    // refill the sliced-diagonal values of the systems that use them
-    for (int32_t i = 0; i < nsys; ++i)
-        if (hs[i].sval && (s = prepare_sdia(A[i], st))) return s;
     uint64_t h = fnv1a(hs.data(), sizeof(BatchSys) * nsys);
     h = fnv1a(order.data(), sizeof(int32_t) * nsys, h);
+    *hash = h;
     if (h != bc->desc_hash) {
         g_counters.h2d_copies += 2;
         APCG_HIP(hipMemcpyAsync(bc->d_sys, hs.data(), sizeof(BatchSys) * nsys, hipMemcpyHostToDevice, st));
@@ -431,18 +468,39 @@ static apcg_status batched_kernels(apcg_ctx ctx, BatchCache *bc, const apcg_mat 
         APCG_HIP(hipStreamSynchronize(st));
         bc->desc_hash = h;
     }
+    return APCG_SUCCESS;
+}
+
+// AUTO without teams: one workgroup per system finishes no earlier than its
+// costliest system on one CU; the segmented schedule spreads every system
+// over the whole chip.
+static int batch_auto(const std::vector<double> &cost, int cus) {
+    const double total = std::accumulate(cost.begin(), cost.end(), 0.0);
+    const double worst = *std::max_element(cost.begin(), cost.end());
+    return worst * cus <= total ? APCG_BATCH_PERSISTENT : APCG_BATCH_SEGMENTED;
+}
+
+// The batch on the persistent or the segmented schedule: descriptors hs (ws
+// holds workspace offsets on entry), results in d_info.  The caller marks the
+// operation.
+static apcg_status batched_kernels(apcg_ctx ctx, BatchCache *bc, const apcg_mat *A, std::vector<BatchSys> &hs,
+                                   const std::vector<double> &cost, const std::vector<int32_t> &order,
+                                   int64_t ws_total, double rtol, int32_t maxit, const apcg_solve_opts &opts,
+                                   BatchedFn fn, int tb, apcg_solve_info *d_info) {
+    const int32_t nsys = (int32_t)hs.size();
+    const int dev = ctx->device;
+    hipStream_t st = ctx->stream;
+    apcg_status s;
+    uint64_t h;
+    if ((s = batch_upload(ctx, bc, hs, order, ws_total, &h))) return s;
+    // refill the sliced-diagonal values of the systems that use them
+    for (int32_t i = 0; i < nsys; ++i)
+        if (hs[i].sval && (s = prepare_sdia(A[i], st))) return s;
 
     hipDeviceProp_t prop;
     APCG_HIP(hipGetDeviceProperties(&prop, dev));
     int sched = opts.batch_schedule;
-    if (sched == APCG_BATCH_AUTO) {
-        // one workgroup per system finishes no earlier than its costliest
-        // system on one CU; the segmented schedule spreads every system
-        // over the whole chip
-        const double total = std::accumulate(cost.begin(), cost.end(), 0.0);
-        const double worst = *std::max_element(cost.begin(), cost.end());
-        sched = worst * prop.multiProcessorCount <= total ? APCG_BATCH_PERSISTENT : APCG_BATCH_SEGMENTED;
-    }
+    if (sched == APCG_BATCH_AUTO) sched = batch_auto(cost, prop.multiProcessorCount);
     if (sched == APCG_BATCH_SEGMENTED) return seg_solve(ctx, nsys, hs.data(), bc->d_sys, rtol, maxit, opts, d_info);
     if (sched != APCG_BATCH_PERSISTENT) return set_error(APCG_ERR_INVALID_ARG, "unknown batch schedule");
     int per_cu = 0;
@@ -583,8 +641,37 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
         // rows: 28.5 ms, segmented 192 (160 on sliced diagonals), persistent
         // 450.  Same sums as the segmented schedule, bit for bit.
         if (opts.batch_schedule == APCG_BATCH_AUTO) {
+            // Where the schedules that teams replace are queued without a look
+            // at the device (one workgroup per system; a few periods), nobody
+            // waits for the teams either: what they leave is solved by one
+            // workgroup per system, or the periods are queued as ever.
+            if (!bc->cus) APCG_HIP(hipDeviceGetAttribute(&bc->cus, hipDeviceAttributeMultiprocessorCount, dev));
+            int64_t rows = 0, most = 0;
+            for (int32_t i = 0; i < nsys; ++i) {
+                rows += A[i]->n;
+                most = std::max<int64_t>(most, A[i]->n);
+            }
+            const int K = std::max(2, (opts.iters_per_graph + 1) / 2 * 2);
+            const bool persistent = batch_auto(cost, bc->cus) == APCG_BATCH_PERSISTENT;
+            const bool polled = !persistent && ((int64_t)maxit + K - 1) / K >= std::max(1, opts.lookahead);
+            const bool alone =
+                !polled && (persistent || (most * maxit <= kLeftWork && rows * maxit <= 64 * kLeftWork));
             TeamFit fit;
-            if ((s = team_eligible(ctx, nsys, A, 1, &fit))) return s;
+            if ((polled || alone) && (s = team_eligible(ctx, nsys, A, 1, true, &fit))) return s;
+            if (fit.rows > 0 && alone) {
+                uint64_t h;
+                TeamLater later;
+                if ((s = batch_upload(ctx, bc, hs, order, ws_total, &h))) return s;
+                if ((s = team_pcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, fit, info->d, nullptr, 0, nullptr,
+                                        &later)))
+                    return s;
+                hipLaunchKernelGGL((k_pcg_left<512, false>), dim3(nsys), dim3(512), 0, ctx->stream,
+                                   (const BatchSys *)bc->d_sys, BatchSys{}, later.verdicts, later.report, later.launch,
+                                   rtol, maxit, opts.x0_is_zero ? 1 : 0, opts.pc,
+                                   opts.norm_type == APCG_NORM_PRECONDITIONED ? 1 : 0, info->d, (double *)nullptr, 0);
+                APCG_CHECK_LAUNCH("k_pcg_left");
+                return op_end(ctx, acc.data(), (int)acc.size());
+            }
             if (fit.rows > 0) {
                 std::vector<int32_t> left;
                 if ((s = team_pcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, fit, info->d, nullptr, 0, &left)))

@@ -1268,11 +1268,21 @@ static apcg_status bf_solve(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const
     run.coeffs = coeffs;
     run.lmax = lmax;
     TeamFit fit;
-    if (opts.batch_schedule == APCG_BATCH_AUTO && !opts.batch_tile_rows && !opts.batch_tail_tile_rows &&
-        maxit <= kTeamFcgMaxIts && (s = team_eligible(ctx, nsys, A, 2, &fit)))
-        return s;
-    if (fit.rows == 0)
-        return bf_core(ctx, bf_cache(ctx), nsys, hs, ws_total, refill, rtol, maxit, opts, fo, run, info);
+    const int K = std::max(2, (opts.iters_per_graph + 1) / 2 * 2);
+    const bool polled = ((int64_t)maxit + 2 + K - 1) / K >= std::max(1, opts.lookahead);
+    const bool automatic =
+        opts.batch_schedule == APCG_BATCH_AUTO && !opts.batch_tile_rows && !opts.batch_tail_tile_rows;
+    if (automatic && polled && maxit <= kTeamFcgMaxIts && (s = team_eligible(ctx, nsys, A, 2, true, &fit))) return s;
+    if (fit.rows == 0) {
+        apcg_solve_opts o = opts;
+        if (automatic && !polled) {
+            // a team launch is waited for: so few iterations are queued on the
+            // tiles, no more than are asked for and not worth a capture
+            o.mode = APCG_MODE_STREAM;
+            o.iters_per_graph = (int32_t)std::min<int64_t>(K, ((int64_t)maxit + 3) / 2 * 2);
+        }
+        return bf_core(ctx, bf_cache(ctx), nsys, hs, ws_total, refill, rtol, maxit, o, fo, run, info);
+    }
     std::vector<int32_t> order(nsys), left;
     for (int32_t i = 0; i < nsys; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int32_t p, int32_t q) { return A[p]->n > A[q]->n; });

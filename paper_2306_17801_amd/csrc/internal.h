@@ -176,10 +176,11 @@ namespace apcg {
 struct TeamState {
     std::atomic<int32_t> border[2] = {-1, -1};  // most border columns of a member of 2048 / 4096 rows, -1: not read
     // found by members: rows or borders other than those remembered, once (the
-    // border is read again) and again after that (rows that have grown; no
-    // teams any more); a member reads another that does not read it (no
-    // flexible solves by teams)
+    // border is read again) and again although it had not changed (rows that
+    // have grown; no teams any more); a member reads another that does not
+    // read it (no flexible solves by teams)
     std::atomic<int32_t> unfit{0};
+    std::atomic<bool> reread{false};
     std::atomic<bool> one_sided{false};
 };
 }  // namespace apcg

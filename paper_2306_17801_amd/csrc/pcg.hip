@@ -1917,8 +1917,24 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
         }
         // a system that fits the chip, by a team of workgroups in one launch
         if (opts.mode == APCG_MODE_GRAPH && !gate && A->n > kTeamMinRows) {
+            // Where the kernels' iterations are queued without a look at the
+            // device, nobody waits for the team either: what it leaves is
+            // solved by one workgroup, or the kernels solve it all.
+            const bool polled = ((int64_t)maxit + K - 1) / K >= opts.lookahead;
+            const bool alone = !polled && (int64_t)A->n * maxit <= kLeftWork;
             TeamFit fit;
-            if ((s = team_eligible(c, 1, &A, 1, &fit))) return s;
+            if ((polled || alone) && (s = team_eligible(c, 1, &A, 1, polled, &fit))) return s;
+            if (fit.rows > 0 && alone) {
+                TeamLater later;
+                if ((s = ensure_workspace(c, A->n))) return s;
+                if ((s = team_pcg_solve(c, 1, &A, &b, &x, {0}, rtol, maxit, opts, fit, info->d + info_index, hist,
+                                        hist_cap, nullptr, &later)))
+                    return s;
+                if ((s = launch_pcg_left(st, later, A, b->d, x->d, c->ws.base, rtol, maxit, opts, info->d + info_index,
+                                         hist, hist_cap)))
+                    return s;
+                return op_end(c, acc, 4);
+            }
             if (fit.rows > 0) {
                 std::vector<int32_t> left;
                 if ((s = team_pcg_solve(c, 1, &A, &b, &x, {0}, rtol, maxit, opts, fit, info->d + info_index, hist,

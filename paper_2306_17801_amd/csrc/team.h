@@ -30,11 +30,11 @@
 // was chosen for, leaves its system.
 //
 // x is written by all members of a system or by none.  A system's verdict is
-// open until a member that has seen the system's end sets it to done, or one
-// that leaves sets it to something else, whichever is first.  Who has seen
-// the end has every member's last message, so by then every member has sent
-// it and can only be waiting for the others', which are on their way: a
-// member that wants to leave a system that is done goes on waiting instead
+// open until member 0, when it has seen the system's end, sets it to done, or
+// one that leaves sets it to something else, whichever is first; the others
+// wait for it.  Member 0 has every member's last message then, so every member
+// has sent it and can only be waiting for the others', which are on their way:
+// a member that wants to leave a system that is done goes on waiting instead
 // and finds them.
 #pragma once
 
@@ -121,24 +121,37 @@ __device__ __forceinline__ uint32_t exchange_if(gptr<uint32_t> p, uint32_t from,
     return from;  // what was there
 }
 
-// Whether to look at a message again after so many unsuccessful looks; every
-// now and then that is a question of the clock and of the others.
-__device__ __forceinline__ bool keep_waiting(const Member &M, int spin, long long &t0) {
-    if (__builtin_expect((spin & M.look) != M.look, 1)) return true;
-    const Exit &E = *M.out;
-    const gptr<uint32_t> head = (gptr<uint32_t>)E.head, verdict = (gptr<uint32_t>)E.verdict;
+// The rare part of keep_waiting: the time from which the wait counts (t0: since
+// when it did, 0 at first), or -1 when the member leaves its system.  A call in
+// the PCG kernels, where it cost 3 to 8% of an iteration with 240 members to
+// have it in every loop that waits (700 x 700: 8.7 us, 8.0 as a call); the
+// flexible solve and TFQMR are 1% to 4% better off without calls.
+#ifndef TEAM_ASK
+#define TEAM_ASK __forceinline__
+#endif
+__device__ TEAM_ASK long long ask(const Exit *E, int T, long long t0) {
+    const gptr<uint32_t> head = (gptr<uint32_t>)E->head, verdict = (gptr<uint32_t>)E->verdict;
     const long long now = wall_clock64();
     if (t0 == 0) t0 = now;
     const uint32_t v = load_shared<uint32_t>(verdict, 0);
-    if (v == kDone) return now - t0 <= E.ticks + kWaitTicks;  // the messages are on their way
-    if (v != kOpen) return false;                             // a team mate has left
+    if (v == kDone) return now - t0 <= E->ticks + kWaitTicks ? t0 : -1;  // the messages are on their way
+    if (v != kOpen) return -1;                                          // a team mate has left
     // the system lacks members: they come when tickets before its own are through
-    const bool lacks = load_shared<uint32_t>(head, kHeadNext) < E.last;
-    if (lacks && load_shared<uint32_t>(head, kHeadThrough) < E.last - (uint32_t)M.T) t0 = now;
-    const bool late = now - t0 > E.ticks;
+    const bool lacks = load_shared<uint32_t>(head, kHeadNext) < E->last;
+    if (lacks && load_shared<uint32_t>(head, kHeadThrough) < E->last - (uint32_t)T) t0 = now;
+    const bool late = now - t0 > E->ticks;
     if (late) store_shared<uint32_t>(head, kHeadStop, 1u);
-    else if (!lacks || !load_shared<uint32_t>(head, kHeadStop)) return true;
-    return exchange_if(verdict, kOpen, kLeft) == kDone;
+    else if (!lacks || !load_shared<uint32_t>(head, kHeadStop)) return t0;
+    return exchange_if(verdict, kOpen, kLeft) == kDone ? t0 : -1;
+}
+
+// Whether to look at a message again after so many unsuccessful looks (counted
+// by the caller, in a scalar register); every now and then that is a question
+// of the clock and of the others.  t0: 0 at first.
+__device__ __forceinline__ bool keep_waiting(const Member &M, int spin, long long &t0) {
+    if (__builtin_expect((spin & M.look) != M.look, 1)) return true;
+    t0 = ask(M.out, M.T, t0);
+    return t0 >= 0;
 }
 
 // A ticket's exit; thread 0 sets it up while the others wait for the setup's
@@ -168,7 +181,15 @@ __device__ __forceinline__ bool finish(const Member &M) {
         return true;
     }
     __syncthreads();  // nobody looks at ok any more
-    if (threadIdx.x == 0 && exchange_if((gptr<uint32_t>)M.out->verdict, kOpen, kDone) > kDone) M.out->ok[0] = 0;
+    if (threadIdx.x == 0) {
+        const gptr<uint32_t> verdict = (gptr<uint32_t>)M.out->verdict;
+        // one member says so, the others wait for it (an exchange by each of 240 takes 10 us)
+        uint32_t v = M.m == 0 ? exchange_if(verdict, kOpen, kDone) : kOpen;
+        if (M.m == 0 && v == kOpen) v = kDone;
+        long long t0 = 0;
+        for (int spin = 0; v == kOpen && keep_waiting(M, spin, t0); ++spin) v = load_shared<uint32_t>(verdict, 0);
+        if (v != kDone) M.out->ok[0] = 0;
+    }
     __syncthreads();
     return M.out->ok[0] != 0;
 }

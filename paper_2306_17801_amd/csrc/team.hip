@@ -30,6 +30,7 @@
 #include <mutex>
 #include <vector>
 
+#define TEAM_ASK __attribute__((noinline))  // (see there)
 #include "team.h"
 #include "team_host.h"
 
@@ -49,6 +50,7 @@ struct TeamSys {
     uint32_t *verdict;
     int32_t n, T;
     int32_t tagged;      // z travels as tagged words (few border columns)
+    int32_t limit;       // border columns a member may have: there is room for more, but no plan
 };
 
 struct TeamPlan {
@@ -56,7 +58,7 @@ struct TeamPlan {
     const int2 *ticket;   // (system, member), a system's members in a row
     uint32_t *head;       // kHeadWords words
     TeamWait wait;
-    int32_t tickets, border;  // border: most border columns of any member
+    int32_t tickets;
     double rtol;
     int32_t maxit, x0_zero, pc, norm_pre;
     double *hist;         // one system only: alpha, beta of the first hist_cap iterations
@@ -86,7 +88,7 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
     const int row0 = M.m * kOwn<R>, row1 = min(n, row0 + kOwn<R>);
     // LDS: the window (of p), D^-1 and x where the registers do not hold them,
     // the border's columns
-    const int wsize = window_size(R, P.border);
+    const int limit = __builtin_amdgcn_readfirstlane(S.limit), wsize = window_size(R, limit);
     double *own = win + kPad + wave * 64 + lane;  // this thread's row of slice 0; rows past the last hold zeros
     double *dl = win + wsize + wave * 64 + lane, *xl = dl + kOwn<R>;
     uint16_t *list = (uint16_t *)(win + wsize + (rows_in_lds(R) ? 2 * kOwn<R> : 0));
@@ -144,10 +146,8 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
         slices_put<R, 4, 1>(red, q, v4);
     });
     if (!__syncthreads_and(fits)) return refuse(M, kUnfit);
-    const int nb = make_border<R, L>(A, lens, row1 - row0, (uint32_t *)win, list, P.border, area);
-    // P.border is that of the batch's largest: a system whose z travels tagged
-    // has what the wavefronts beside the collecting ones fetch at once and no more
-    if (nb > P.border || (tagged && nb > kSide * (TT - 64 * M.mw))) return refuse(M, kUnfit);
+    const int nb = make_border<R, L>(A, lens, row1 - row0, (uint32_t *)win, list, limit, area);
+    if (nb > limit) return refuse(M, kUnfit);
     for (int i = tid; i < wsize; i += TT) win[i] = 0.0;
     // the column of border place c; the owners keep storing z of these rows
     auto column = [&](int c) { return (uint32_t)(row0 + (int)list[c] - kBias); };
@@ -438,6 +438,8 @@ void team_cache_release(uint64_t ctx_id, int device) {
     hipFree(t->mem);
     hipFree(t->d_swap);
     if (t->pinned) hipHostFree(t->pinned);
+    if (t->reports) hipHostFree(t->reports);
+    if (t->border_pinned) hipHostFree(t->border_pinned);
     delete t;
 }
 
@@ -529,20 +531,69 @@ apcg_status team_upload(TeamCache *t, hipStream_t st, const void *sys, int64_t s
     for (int32_t i : order)
         for (int m = 0; m < members[i]; ++m) tk.push_back(make_int2(i, m));
     const int64_t tk_bytes = (int64_t)sizeof(int2) * tickets;
-    t->desc.resize((size_t)(sys_bytes + tk_bytes));
-    memcpy(t->desc.data(), sys, (size_t)sys_bytes);
-    memcpy(t->desc.data() + sys_bytes, tk.data(), (size_t)tk_bytes);
+    auto desc = std::make_shared<std::vector<char>>((size_t)(sys_bytes + tk_bytes));
+    memcpy(desc->data(), sys, (size_t)sys_bytes);
+    memcpy(desc->data() + sys_bytes, tk.data(), (size_t)tk_bytes);
     uint64_t h = 1469598103934665603ull ^ (uint64_t)(uintptr_t)t->d_desc;
-    for (char ch : t->desc) h = (h ^ (unsigned char)ch) * 1099511628211ull;
+    for (char ch : *desc) h = (h ^ (unsigned char)ch) * 1099511628211ull;
     if (h == 0) h = 1;
     if (h != t->desc_hash) {
         g_counters.h2d_copies++;
-        APCG_HIP(hipMemcpyAsync(t->d_desc, t->desc.data(), t->desc.size(), hipMemcpyHostToDevice, st));
+        APCG_HIP(hipMemcpyAsync(t->d_desc, desc->data(), desc->size(), hipMemcpyHostToDevice, st));
         t->desc_hash = h;
+        EventRef ev = event_get(t->device);
+        if (!ev) return set_error(APCG_ERR_HIP, "event creation failed");
+        APCG_HIP(event_record(ev, st));
+        defer_release({ev}, [desc]() {});  // the host's copy lives until it has been read
     }
     *d_sys = t->d_desc;
     *d_tickets = reinterpret_cast<const int2 *>(t->d_desc + sys_bytes);
     return APCG_SUCCESS;
+}
+
+// What a verdict other than done says about the matrix (may be null) and the chip.
+static void team_left(TeamCache *t, TeamState *m, uint32_t verdict) {
+    if (verdict == kUnfit) {  // (changed in place)
+        if (!m) return;
+        ++m->unfit;
+        m->reread = true;
+    } else if (verdict == kOneSided) {
+        if (m) m->one_sided = true;
+    } else {
+        t->rest = 256;  // a wait ran out: the chip is shared, no teams for a while
+    }
+}
+
+// Numbers a launch that nobody waits for.
+static apcg_status team_later(TeamCache *t, int32_t nsys, const apcg_mat *A, TeamLater *later) {
+    if (!t->reports) {
+        APCG_HIP(hipHostMalloc((void **)&t->reports, sizeof(uint64_t) * kReports, hipHostMallocDefault));
+        memset(t->reports, 0, sizeof(uint64_t) * kReports);
+    }
+    const uint64_t k = ++t->launches;
+    auto &mats = t->reported[k % kReports];
+    mats.clear();
+    for (int32_t i = 0; i < nsys; ++i) mats.push_back(A[i]->team);
+    later->verdicts = reinterpret_cast<const uint32_t *>(t->d_sync) + kHeadWords;
+    later->report = t->reports + k % kReports;
+    later->launch = k << 40;
+    return APCG_SUCCESS;
+}
+
+// Reads what those launches have reported (the last of a launch's systems).
+static void team_reports(TeamCache *t) {
+    if (!t->reports) return;
+    for (int q = 0; q < kReports; ++q) {
+        volatile uint64_t *word = t->reports + q;
+        const uint64_t w = *word;
+        if (!w) continue;
+        *word = 0;
+        const uint64_t now = t->launches - (t->launches - (uint64_t)q) % kReports;  // the launch this word is for now
+        const size_t i = (size_t)((w >> 8 & 0xffffffffull) - 1);
+        const auto &mats = t->reported[q];
+        const bool known = (w >> 40) == (now & 0xffffffull) && i < mats.size();
+        team_left(t, known ? mats[i].lock().get() : nullptr, (uint32_t)(w & 255));
+    }
 }
 
 apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const apcg_mat *A, std::vector<int32_t> *left) {
@@ -568,19 +619,9 @@ apcg_status team_finish(apcg_ctx ctx, TeamCache *t, int32_t nsys, const apcg_mat
     g_counters.host_polls++;
     APCG_HIP(hipEventSynchronize(t->ev->e));
     for (int32_t i = 0; i < nsys; ++i) {
-        if (host[i] == kDone) {
-            A[i]->team->unfit = 0;
-            continue;
-        }
+        if (host[i] == kDone) continue;
         left->push_back(i);
-        if (host[i] == kUnfit) {  // (changed in place)
-            ++A[i]->team->unfit;
-            A[i]->team->border[0] = A[i]->team->border[1] = -1;
-        } else if (host[i] == kOneSided) {
-            A[i]->team->one_sided = true;
-        } else {
-            t->rest = 256;  // a wait ran out: the chip is shared, no teams for a while
-        }
+        team_left(t, A[i]->team.get(), host[i]);
     }
     return APCG_SUCCESS;
 }
@@ -590,23 +631,35 @@ static int team_width(int maxrow) { return maxrow <= 5 ? 5 : maxrow <= 7 ? 7 : 0
 // The border of every matrix that does not know it yet, in one launch and one
 // readback (once per matrix; a solve checks on the device that the pattern
 // still fits).
-// border[w][i]: of system i's members of 2048 (w = 0) and 4096 rows.
-static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A, std::vector<int32_t> (&border)[2]) {
+// border[w][i]: of system i's members of 2048 (w = 0) and 4096 rows; without
+// may_wait (one system) -1 until it has arrived.
+static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A, bool may_wait,
+                                std::vector<int32_t> (&border)[2]) {
     std::vector<BorderItem> items;
     std::vector<int32_t> which;
     int32_t nmax = 0;
+    auto set = [](TeamState &m, const int32_t *b) {
+        if (m.reread.exchange(false) && (m.border[0] != b[0] || m.border[1] != b[1])) m.unfit = 0;
+        for (int w = 0; w < 2; ++w) m.border[w] = b[w];
+    };
+    TeamCache *t = team_cache(c);
+    if (t->border_ev && hipEventQuery(t->border_ev->e) == hipSuccess) {
+        t->border_ev = nullptr;
+        if (auto m = t->border_of.lock()) set(*m, t->border_pinned);
+    }
+    (void)hipGetLastError();  // hipErrorNotReady of the query
     for (auto &b : border) b.assign(nsys, 0);
     for (int32_t i = 0; i < nsys; ++i) {
-        for (int w = 0; w < 2; ++w) border[w][i] = A[i]->team->border[w];
+        TeamState &m = *A[i]->team;
+        for (int w = 0; w < 2; ++w) border[w][i] = m.reread ? -1 : m.border[w].load();
         if (border[0][i] < 0 || border[1][i] < 0) {
             items.push_back({A[i]->rowptr, A[i]->col, A[i]->n, 0});
             which.push_back(i);
             nmax = std::max(nmax, A[i]->n);
         }
     }
-    if (items.empty()) return APCG_SUCCESS;
+    if (items.empty() || (!may_wait && t->border_ev)) return APCG_SUCCESS;
     const size_t ni = items.size();
-    TeamCache *t = team_cache(c);
     apcg_status s;
     const int64_t bytes = (int64_t)(sizeof(BorderItem) * ni + sizeof(int32_t) * 2 * ni);
     t->desc_hash = 0;  // the descriptor buffer is used as scratch
@@ -624,13 +677,24 @@ static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A, std
         APCG_CHECK_LAUNCH("k_border");
     }
     g_counters.d2h_copies++;
+    if (!may_wait) {
+        if (!t->border_pinned)
+            APCG_HIP(hipHostMalloc((void **)&t->border_pinned, 2 * sizeof(int32_t), hipHostMallocDefault));
+        APCG_HIP(hipMemcpyAsync(t->border_pinned, out, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+        if (!(t->border_ev = event_get(c->device))) return set_error(APCG_ERR_HIP, "event creation failed");
+        t->border_of = A[0]->team;
+        APCG_HIP(event_record(t->border_ev, c->stream));
+        return APCG_SUCCESS;
+    }
     APCG_HIP(hipMemcpyAsync(h.data(), out, sizeof(int32_t) * 2 * ni, hipMemcpyDeviceToHost, c->stream));
     if (!t->ev && !(t->ev = event_get(c->device))) return set_error(APCG_ERR_HIP, "event creation failed");
     APCG_HIP(event_record(t->ev, c->stream));
     g_counters.host_polls++;
     APCG_HIP(hipEventSynchronize(t->ev->e));
-    for (size_t i = 0; i < ni; ++i)
-        for (int w = 0; w < 2; ++w) A[which[i]]->team->border[w] = border[w][which[i]] = h[2 * i + w];
+    for (size_t i = 0; i < ni; ++i) {
+        set(*A[which[i]]->team, &h[2 * i]);
+        for (int w = 0; w < 2; ++w) border[w][which[i]] = h[2 * i + w];
+    }
     return APCG_SUCCESS;
 }
 
@@ -648,7 +712,7 @@ static int team_rows(int32_t nsys, const apcg_mat *A, const std::vector<int32_t>
         for (int32_t i = 0; i < nsys && ok; ++i) {
             const int64_t T = std::max<int64_t>(1, ((int64_t)A[i]->n + TT * R - 1) / (TT * R));
             const int nb = border[R == 8][i];
-            ok = T <= cus && nb < 1 << 20 && team_lds(R, nb, windows, rows_in_lds(R)) <= kLdsBytes;
+            ok = T <= cus && nb >= 0 && nb < 1 << 20 && team_lds(R, nb, windows, rows_in_lds(R)) <= kLdsBytes;
             total += T;
         }
         if (!ok) continue;
@@ -658,7 +722,7 @@ static int team_rows(int32_t nsys, const apcg_mat *A, const std::vector<int32_t>
     return best;
 }
 
-apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windows, TeamFit *fit) {
+apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windows, bool may_wait, TeamFit *fit) {
     fit->rows = 0;
     if (c->type == APCG_STREAM_GLOBAL_BLOCKING) return APCG_SUCCESS;
     int maxrow = 1;
@@ -668,6 +732,7 @@ apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windo
         if (A[i]->team->unfit > 1 || (windows > 1 && A[i]->team->one_sided)) return APCG_SUCCESS;
     }
     TeamCache *t = team_cache(c);
+    team_reports(t);
     if (t->rest > 0) {
         --t->rest;
         return APCG_SUCCESS;
@@ -675,7 +740,7 @@ apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windo
     if (!t->cus) APCG_HIP(hipDeviceGetAttribute(&t->cus, hipDeviceAttributeMultiprocessorCount, c->device));
     apcg_status s;
     std::vector<int32_t> border[2];
-    if ((s = team_borders(c, nsys, A, border))) return s;
+    if ((s = team_borders(c, nsys, A, may_wait, border))) return s;
     fit->rows = team_rows(nsys, A, border, t->cus, team_width(maxrow), windows);
     fit->border = std::move(border[fit->rows == 8]);
     return APCG_SUCCESS;
@@ -684,8 +749,7 @@ apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windo
 apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
                            const std::vector<int32_t> &order, double rtol, int32_t maxit, const apcg_solve_opts &opts,
                            const TeamFit &fit, apcg_solve_info *info, double *hist, int32_t hist_cap,
-                           std::vector<int32_t> *left) {
-    left->clear();
+                           std::vector<int32_t> *left, TeamLater *later) {
     TeamCache *t = team_cache(c);
     hipStream_t st = c->stream;
     const int R = fit.rows;
@@ -708,6 +772,7 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         const int64_t ngr = ((int64_t)s.n + kGroupRows - 1) / kGroupRows;
         // what the wavefronts beside at most four that collect messages fetch at once
         s.tagged = R <= 4 && nb <= kSide * (TT - kTree) ? 1 : 0;
+        s.limit = s.tagged ? kSide * (TT - kTree) : INT32_MAX;  // (and that of the widest, for which there is room)
         s.z = reinterpret_cast<uint64_t *>(zn);
         s.need = reinterpret_cast<uint8_t *>(marks);
         s.words = reinterpret_cast<uint64_t *>(words);
@@ -732,7 +797,10 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         q.verdict = head_p + kHeadWords + i;
     }
     std::vector<int32_t> members(nsys);
-    for (int32_t i = 0; i < nsys; ++i) members[i] = sys[i].T;
+    for (int32_t i = 0; i < nsys; ++i) {
+        members[i] = sys[i].T;
+        sys[i].limit = std::min(sys[i].limit, border);
+    }
     const char *d_sys;
     const int2 *d_tickets;
     if ((s = team_upload(t, st, sys.data(), (int64_t)sizeof(TeamSys) * nsys, order, members, &d_sys, &d_tickets)))
@@ -743,7 +811,6 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
     P.head = head_p;
     P.wait = t->wait;
     P.tickets = (int32_t)tickets;
-    P.border = border;
     P.rtol = rtol;
     P.maxit = maxit;
     P.x0_zero = opts.x0_is_zero ? 1 : 0;
@@ -763,7 +830,7 @@ apcg_status team_pcg_solve(apcg_ctx c, int32_t nsys, const apcg_mat *A, const ap
         return APCG_SUCCESS;
     });
     if (s) return s;
-    return team_finish(c, t, nsys, A, left);
+    return left ? team_finish(c, t, nsys, A, left) : team_later(t, nsys, A, later);
 }
 
 }  // namespace apcg

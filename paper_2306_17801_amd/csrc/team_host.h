@@ -34,13 +34,13 @@ constexpr int kHeadNext = 0, kHeadStop = 1, kHeadThrough = 2, kHeadWords = 4;
 // that does not read it (flexible solve).  The last three: x as it was.
 constexpr uint32_t kOpen = 0, kDone = 1, kLeft = 2, kUnfit = 3, kOneSided = 4;
 
-// Team launches in flight on a device: a member waits for the other members
-// of its team, so the workgroups of all team launches that may run at the
-// same time must fit the chip together (one per compute unit).  A launch that
-// would not fit is queued behind the ones in flight.
+// Team launches in flight on a device, by stream: a member waits for the other
+// members of its team, so the workgroups of all team launches that may run at
+// the same time must fit the chip together (one per compute unit).  A launch
+// that would not fit is queued behind the ones in flight.
 struct TeamFlight {
-    EventRef ev;
-    int wgs;
+    EventRef ev;         // of the stream's last launch (it keeps the stream, so no other has its name)
+    int wgs;             // of its largest since it had none
     hipStream_t stream;
 };
 extern std::mutex g_flight_mu;
@@ -58,8 +58,10 @@ apcg_status team_launch(int device, hipStream_t st, int wgs, int cus, F launch) 
              fl.end());
     (void)hipGetLastError();  // hipErrorNotReady of the queries
     int sum = wgs;
-    for (const auto &f : fl)
-        if (f.stream != st) sum += f.wgs;  // launches of this stream run one after the other
+    TeamFlight *own = nullptr;
+    for (auto &f : fl)
+        if (f.stream != st) sum += f.wgs;  // (launches of one stream run one after the other)
+        else own = &f;
     if (sum > cus)
         for (const auto &f : fl)
             if (f.stream != st) {
@@ -69,9 +71,21 @@ apcg_status team_launch(int device, hipStream_t st, int wgs, int cus, F launch) 
     apcg_status s = launch();
     if (s) return s;
     APCG_HIP(event_record(ev, st));
-    fl.push_back({ev, wgs, st});
+    if (own) *own = {ev, std::max(own->wgs, wgs), st};
+    else fl.push_back({ev, wgs, st});
     return APCG_SUCCESS;
 }
+
+// A launch nobody waits for: what it leaves is solved by a kernel queued behind
+// it (launch_pcg_left), which reports each such system to the host: where the
+// verdicts lie, and what to write where (pinned memory).
+struct TeamLater {
+    const uint32_t *verdicts = nullptr;
+    uint64_t *report = nullptr;
+    uint64_t launch = 0;  // its number, in the upper 24 bits
+};
+// Its report of system i: the launch, i + 1 (32 bits), the verdict (8 bits).
+constexpr int kReports = 64;  // launches whose reports the host can still tell apart
 
 // Records of the systems that teams have left, by their place among them: the
 // results, and the flexible solve's polynomials.  Given back once ctx's work
@@ -94,8 +108,14 @@ struct TeamCache {
     int device = 0;
     int cus = 0;
     TeamWait wait{kWaitTicks, 255};
+    uint64_t launches = 0;   // that nobody waits for
+    uint64_t *reports = nullptr;  // pinned, kReports words: of launch k in word k modulo kReports
+    std::vector<std::weak_ptr<TeamState>> reported[kReports];  // the matrices of those launches
+    // a border that is being read without waiting for it
+    EventRef border_ev;
+    std::weak_ptr<TeamState> border_of;
+    int32_t *border_pinned = nullptr;
     int rest = 0;            // solves to leave to the other schedules after a wait that ran out
-    std::vector<char> desc;  // host copy of d_desc, alive while it is uploaded
     char *mem = nullptr;     // one buffer for the three below (an allocation costs as much as a small solve)
     int64_t mem_cap = 0;
     char *d_desc = nullptr;  // the systems, int2 tickets[]
@@ -169,17 +189,20 @@ struct TeamFit {
 // Whether every system can be solved by teams on ctx's device: rows of at
 // most 7 entries, `windows` windows that fit the LDS (1: PCG, 2: the flexible
 // solve), no system larger than the chip, none that members have refused.
-// Reads the matrices' borders back once per matrix.
-apcg_status team_eligible(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, int windows, TeamFit *fit);
+// Reads the matrices' borders back once per matrix; without may_wait (one
+// system) the answer is no until the border has arrived.
+apcg_status team_eligible(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, int windows, bool may_wait, TeamFit *fit);
 
 // Jacobi-PCG (or CG) of the systems, started in `order` (largest cost
 // first), results in info[i]; hist as in pcg_solve_marked (one system).
 // Returns once the launch has finished; *left holds the systems it did not
 // solve (their x untouched), which the caller solves with another schedule.
+// Without left, returns at once, and the caller queues what solves the systems
+// whose verdict is not done (*later).
 apcg_status team_pcg_solve(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
                            const std::vector<int32_t> &order, double rtol, int32_t maxit, const apcg_solve_opts &opts,
                            const TeamFit &fit, apcg_solve_info *info, double *hist, int32_t hist_cap,
-                           std::vector<int32_t> *left);
+                           std::vector<int32_t> *left, TeamLater *later = nullptr);
 
 // FCG(1) of the systems with their polynomials coeffs[i][9], lmax[i] (device),
 // as apcg_ksp_solve_batched_fcg_poly; otherwise as team_pcg_solve.
@@ -194,5 +217,13 @@ apcg_status team_tfqmr_solve(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
                              std::vector<int32_t> *left);
 // The tags one flexible launch may use are limited (see team_fcg.hip).
 constexpr int32_t kTeamFcgMaxIts = 100000000;
+
+// When nobody waits for a launch, one workgroup per system solves what is left:
+// up to so many rows times iterations (about a second).
+constexpr int64_t kLeftWork = (int64_t)1 << 25;
+// One system (batched.hip): ws holds 5 n doubles.
+apcg_status launch_pcg_left(hipStream_t st, const TeamLater &later, const apcg_mat_s *A, const double *b, double *x,
+                            double *ws, double rtol, int32_t maxit, const apcg_solve_opts &opts, apcg_solve_info *info,
+                            double *hist, int32_t hist_cap);
 
 }  // namespace apcg

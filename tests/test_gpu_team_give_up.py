@@ -138,7 +138,8 @@ def test_refusing_system_leaves_the_others_and_is_remembered(apcg, ctx):
         apcg.apcg_counters_reset()
         apcg.apcg_ksp_solve_batched_fcg_poly(
             ctx, [a.h for a in As], [b.h for b in bs], [x.h for x in xs], 0.0, 6, C, L,
-            apcg.apcg_solve_opts_default(x0_is_zero=1, batch_tile_rows=256 if tiles else 0), None, info)
+            apcg.apcg_solve_opts_default(x0_is_zero=1, iters_per_graph=2, batch_tile_rows=256 if tiles else 0), None,
+            info)
         n = apcg.apcg_counters_get()
         return [apcg.apcg_info_get(info, k) for k in range(len(S))], [x.numpy() for x in xs], n
 

@@ -58,37 +58,74 @@ SHAPES = [(64, 64), (1, 8193), (90, 100), (64, 300), (200, 180), (9, 1000)]
 @pytest.mark.parametrize("wait", WAITS, ids=str)
 @pytest.mark.parametrize("copies", [1, 8])
 def test_pcg_batch_solves_from_x0_whoever_leaves(apcg, wait, copies):
-    """copies = 8: more members than compute units, tickets wait for others."""
+    """copies = 8: more members than compute units, tickets wait for others.
+    To a tolerance, the host waits for the launch and the segmented schedule
+    solves what is left, to the same bits; 12 iterations are queued with what
+    solves the rest, one workgroup per system."""
     from paper_2306_17801_amd.device import DeviceCSR, DeviceVec
 
     print(f"case team wait pcg {wait} copies={copies}", flush=True)
     base = [grid(s, i) for i, s in enumerate(SHAPES)]
     rng = np.random.default_rng(1)
     x0 = [rng.uniform(-1, 1, s.A.n) for s in base]
-    want = [oracle.pcg(s.A, s.b, x0=v, rtol=0.0, maxit=20).x for s, v in zip(base, x0)]
-    bits = None  # those of the segmented schedule, whoever solves a system
     As = [DeviceCSR(s.A) for s in base] * copies
     bs = [DeviceVec(s.b) for s in base] * copies
     info = apcg.apcg_info_create(0, len(As))
-    left = 0
-    for sched in (2, 0, 0, 0, 0):
+
+    def solve(sched, rtol, maxit):
         xs = [DeviceVec(v) for v in x0 * copies]
         c = impatient(apcg, wait)
-        opts = apcg.apcg_solve_opts_default(batch_schedule=sched)
         apcg.apcg_counters_reset()
-        apcg.apcg_ksp_solve_batched(c, [a.h for a in As], [b.h for b in bs], [x.h for x in xs], 0.0, 20, opts, info)
+        apcg.apcg_ksp_solve_batched(c, [a.h for a in As], [b.h for b in bs], [x.h for x in xs], rtol, maxit,
+                                    apcg.apcg_solve_opts_default(batch_schedule=sched), info)
         n = apcg.apcg_counters_get()
-        left += sched == 0 and n["graph_launches"] > 0
-        for k, x in enumerate(xs):
-            r = apcg.apcg_info_get(info, k)
-            assert (r["status"], r["iterations"]) == (apcg.APCG_SOLVE_MAXIT, 20), k
-            assert rel(x.numpy(), want[k % len(want)]) <= 1e-12, k
-        got = [x.numpy() for x in xs]
-        bits = bits or got
-        assert all(np.array_equal(p, q) for p, q in zip(got, bits))
+        out = [apcg.apcg_info_get(info, k) for k in range(len(xs))], [x.numpy() for x in xs]
         apcg.apcg_ctx_destroy(c)
+        return out, n["graph_launches"] > 0
+
+    want, left = solve(2, 1e-8, 20000)[0], 0
+    for _ in range(4):
+        got, graphs = solve(0, 1e-8, 20000)
+        left += graphs
+        assert got[0] == want[0] and all(np.array_equal(p, q) for p, q in zip(got[1], want[1]))
     assert left > 0 or wait[0] > 0
+    want = [oracle.pcg(s.A, s.b, x0=v, rtol=0.0, maxit=12).x for s, v in zip(base, x0)]
+    for _ in range(4):
+        got, graphs = solve(0, 0.0, 12)
+        assert not graphs
+        for k, (r, x) in enumerate(zip(*got)):
+            assert (r["status"], r["iterations"]) == (apcg.APCG_SOLVE_MAXIT, 12), k
+            assert rel(x, want[k % len(want)]) <= 1e-12, k
     apcg.apcg_info_destroy(info)
+
+
+@pytest.mark.parametrize("wait", WAITS, ids=str)
+def test_features_whoever_leaves(apcg, wait):
+    """The feature run's alpha and beta, from whichever kernel."""
+    import torch
+    from paper_2306_17801_amd.device import DeviceCSR, DeviceVec
+
+    print(f"case team wait features {wait}", flush=True)
+    s = grid((150, 150), 6)
+    dA, db = DeviceCSR(s.A), DeviceVec(s.b)
+    calm = apcg.apcg_ctx_create(0)
+
+    def features(c):
+        F, L = torch.zeros(16, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        apcg.apcg_pc_features(c, dA.h, db.h, F, L)
+        apcg.apcg_ctx_synchronize(c)
+        return F.cpu().numpy(), float(L)
+
+    want = features(calm)
+    for _ in range(6):
+        c = impatient(apcg, wait)
+        for _ in range(3):
+            got = features(c)
+            assert got[1] == want[1]
+            np.testing.assert_allclose(got[0], want[0], rtol=2e-6, atol=2e-6)  # FP32 of values equal to about 1e-10
+        apcg.apcg_ctx_destroy(c)
+    apcg.apcg_ctx_destroy(calm)
 
 
 @pytest.mark.parametrize("wait", WAITS, ids=str)
