@@ -1126,7 +1126,7 @@ __global__ __launch_bounds__(256) void k_dia_symcheck(int32_t n, int32_t *__rest
 // order, in one pass over x instead of two (seven passes over vectors an
 // iteration on average instead of eight; 128^3: 21.2 us each, 13.8 and 24.5 in turn here).
 // ODD: an odd iteration, whose step of x is left to the next one or to
-// k_pcg_tail.
+// k_pcg_finish.
 template <bool ODD>
 __global__ __launch_bounds__(VB) void k_pcg_update(int64_t n, double *__restrict__ x, double *__restrict__ r,
                                                    const double *__restrict__ p, const double *__restrict__ p_odd,
@@ -1202,40 +1202,47 @@ __global__ __launch_bounds__(VB) void k_pcg_update(int64_t n, double *__restrict
     dev::store_partials<VB, 2>(v, part_res, gridDim.x, dev::xcd_block(blockIdx.x, gridDim.x));
 }
 
-// The pending step of x when the solve ended after an odd iteration (runs
-// after k_pcg_finish; p_odd still holds that iteration's direction: only the
-// next odd product overwrites it).
-__global__ __launch_bounds__(VB) void k_pcg_tail(int64_t n, double *__restrict__ x, const double *__restrict__ p_odd,
-                                                 const SolveState *st, int64_t per_block) {
-    if (!(st->out_its & 1)) return;
+// Applies the tests of the last launched iteration when no later product
+// kernel did, copies the terminal state into the caller's info record and does
+// the pending step of x when the solve ended after an odd iteration (p_odd
+// still holds that iteration's direction: only the next odd product overwrites
+// it).  One launch: the step in one of its own cost every solve 2.5 us.
+__global__ __launch_bounds__(VB) void k_pcg_finish(SolveState *st, const double *part_res, int g_res,
+                                                   apcg_solve_info *out, int64_t n, double *__restrict__ x,
+                                                   const double *__restrict__ p_odd, int64_t per_block) {
+    int its = st->out_its;
+    if (!st->flag) {
+        const PcgRecord last = st->rec[st->rec[1].k > st->rec[0].k ? 1 : 0];
+        its = last.k;
+        if (blockIdx.x == 0 && threadIdx.x < 64) {
+            double v[2] = {0.0, 0.0};
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                for (int i = threadIdx.x; i < g_res; i += 64) v[k] += part_res[k * g_res + i];
+                v[k] = dev::wave_sum(v[k]);
+            }
+            if (threadIdx.x == 0) {
+                const double res = sqrt(v[1]);
+                const int status = iteration_status(v[0], res, st, its);
+                // (not the flag, which other workgroups may still have to read)
+                st->out_its = its;
+                st->out_status = status ? status : APCG_SOLVE_MAXIT;  // the host stopped at maxit
+                st->out_res = res;
+            }
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        out->iterations = its;
+        out->status = st->out_status;
+        out->fcg_iterations = 0;
+        out->half_steps = 0;
+        out->res_norm = st->out_res;
+        out->ref_norm = st->ref;
+    }
+    if (!(its & 1)) return;
     const double alpha = st->alpha_odd;
     const dev::Chunk c = dev::block_chunk(n, per_block);
     for (int64_t i = c.lo + threadIdx.x; i < c.hi; i += VB) x[i] = fma(alpha, p_odd[i], x[i]);
-}
-
-// Applies the tests of the last launched iteration when no later product
-// kernel did, then copies the terminal state into the caller's info record.
-__global__ __launch_bounds__(64) void k_pcg_finish(SolveState *st, const double *part_res, int g_res,
-                                                   apcg_solve_info *out) {
-    if (!st->flag) {
-        const int q = st->rec[1].k > st->rec[0].k ? 1 : 0;
-        const PcgRecord last = st->rec[q];
-        double v[2];
-        dev::reduce_partials<64, 2>(part_res, g_res, v);
-        if (threadIdx.x == 0) {
-            const double res = sqrt(v[1]);
-            int status = iteration_status(v[0], res, st, last.k);
-            if (!status) status = APCG_SOLVE_MAXIT;  // the host stopped at maxit
-            terminate(st, last.k, status, res);
-        }
-    }
-    if (threadIdx.x != 0) return;
-    out->iterations = st->out_its;
-    out->status = st->out_status;
-    out->fcg_iterations = 0;
-    out->half_steps = 0;
-    out->res_norm = st->out_res;
-    out->ref_norm = st->ref;
 }
 
 __global__ __launch_bounds__(VB) void k_tune_fill(double *r, double *dinv, double *p, double *z, int64_t n) {
@@ -2038,12 +2045,9 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
                 }
             }
         }
-        hipLaunchKernelGGL(k_pcg_finish, dim3(1), dim3(64), 0, st, c->ws.state, (const double *)bf.part_res(),
-                           pl.g_vec, info->d + info_index);
+        hipLaunchKernelGGL(k_pcg_finish, dim3(pl.g_vec), dim3(VB), 0, st, c->ws.state, (const double *)bf.part_res(),
+                           pl.g_vec, info->d + info_index, (int64_t)A->n, x->d, (const double *)c->ws.p(1), pl.pb_vec);
         APCG_CHECK_LAUNCH("k_pcg_finish");
-        hipLaunchKernelGGL(k_pcg_tail, dim3(pl.g_vec), dim3(VB), 0, st, (int64_t)A->n, x->d,
-                           (const double *)c->ws.p(1), (const SolveState *)c->ws.state, pl.pb_vec);
-        APCG_CHECK_LAUNCH("k_pcg_tail");
         if (opts.kernel_timing) {
             c->tdone = event_get(c->device);
             if (c->tdone) APCG_HIP(event_record(c->tdone, st));
