@@ -99,10 +99,11 @@ __device__ __forceinline__ void terminate(SolveState *st, int its, int status, d
 // dinv = 1/diag(A) (or 1), r0 = b - A x0 (or b), z0 = dinv r0, p_old = 0; partials of
 // z0.r0, residual norm^2, reference norm^2 and the count of bad diagonals.
 // One row per lane; bound by the read of the matrix, which a lane walking its
-// own row asks for in single words, a row apart from its neighbour's.  So a
-// wavefront brings its 64 rows' entries through LDS, dev::kStage at a time, in
-// whole lines; with x0 = 0 only the columns, and one value where the diagonal
-// is found.  27-entry rows, 96^3: INITMEASURED.
+// own row asks for in single words, a row apart from its neighbour's.  So
+// (STAGED) a wavefront brings its 64 rows' entries through LDS, dev::kStage at
+// a time, in whole lines; with x0 = 0 only the columns, and one value where
+// the diagonal is found.
+template <bool STAGED>
 __global__ __launch_bounds__(VB) void k_pcg_init(int32_t n, const int32_t *__restrict__ rowptr,
                                                  const int32_t *__restrict__ col, const double *__restrict__ val,
                                                  const double *__restrict__ b, double *__restrict__ x,
@@ -113,35 +114,48 @@ __global__ __launch_bounds__(VB) void k_pcg_init(int32_t n, const int32_t *__res
     if (gate && !gate[0]) return;  // gated off: the solve is a no-op
     const dev::Chunk c = dev::block_chunk(n, per_block);
     double rz = 0.0, nres = 0.0, nref = 0.0, bad = 0.0;
-    __shared__ double sv[VB / 64][dev::kStage];
-    __shared__ int32_t sc[VB / 64][dev::kStage];
+    constexpr int CELLS = STAGED ? dev::kStage : 1;
+    __shared__ double sv[VB / 64][CELLS];
+    __shared__ int32_t sc[VB / 64][CELLS];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int64_t base = c.lo + wave * 64; base < c.hi; base += VB) {
         const int64_t i = base + lane;
         const bool in = i < c.hi;
         const int s = rowptr[in ? i : c.hi], e = rowptr[in ? i + 1 : c.hi];
-        const int s0 = rowptr[base], e0 = rowptr[min(base + 64, c.hi)];
         double diag = 0.0, ax = 0.0;
         bool found = false;
-        for (int p0 = s0; p0 < e0; p0 += dev::kStage) {
-            const int p1 = min(e0, p0 + dev::kStage);
-            dev::wave_lds_fence();  // the previous piece has been read
-#pragma unroll
-            for (int q = 0; q < dev::kStage / 64; ++q) {
-                const int k = q * 64 + lane;
-                if (p0 + k < p1) {
-                    sc[wave][k] = col[p0 + k];
-                    if (!x0_zero) sv[wave][k] = val[p0 + k];
-                }
-            }
-            dev::wave_lds_fence();
-            for (int k = max(s, p0); k < min(e, p1); ++k) {
-                const int j = sc[wave][k - p0];
+        if constexpr (!STAGED) {
+            for (int k = s; k < e; ++k) {
+                const int j = col[k];
+                const double a = val[k];
                 if (j == (int)i) {
-                    diag = val[k];
+                    diag = a;
                     found = true;
                 }
-                if (!x0_zero) ax = fma(sv[wave][k - p0], x[j], ax);
+                if (!x0_zero) ax = fma(a, x[j], ax);
+            }
+        } else {
+            const int s0 = rowptr[base], e0 = rowptr[min(base + 64, c.hi)];
+            for (int p0 = s0; p0 < e0; p0 += dev::kStage) {
+                const int p1 = min(e0, p0 + dev::kStage);
+                dev::wave_lds_fence();  // the previous piece has been read
+#pragma unroll
+                for (int q = 0; q < dev::kStage / 64; ++q) {
+                    const int k = q * 64 + lane;
+                    if (p0 + k < p1) {
+                        sc[wave][k] = col[p0 + k];
+                        if (!x0_zero) sv[wave][k] = val[p0 + k];
+                    }
+                }
+                dev::wave_lds_fence();
+                for (int k = max(s, p0); k < min(e, p1); ++k) {
+                    const int j = sc[wave][k - p0];
+                    if (j == (int)i) {
+                        diag = val[k];
+                        found = true;
+                    }
+                    if (!x0_zero) ax = fma(sv[wave][k - p0], x[j], ax);
+                }
             }
         }
         if (!in) continue;
@@ -1342,6 +1356,18 @@ ProductFn product_fn(const apcg_spmv_config &cfg, int32_t lds_nnz, int32_t sell_
                                  : product_fn_tb<256>(cfg.lanes_per_row, sell_maxw);
 }
 
+// Whether the setup brings the rows through LDS (k_pcg_init): where lanes that
+// walk their own rows find the lines they share gone before they come back to
+// them.  Setup and end of a solve without iterations, us, rows walked and
+// staged: 27 entries 96^3 623 and 105 (x0 given 794 and 295), 7 entries 128^3
+// 83 and 77 (92 and 115), 6 to 16 entries 150,000 rows 25 and 22 (32 and 32);
+// but 17 to 24 entries 40,000 rows 19 and 22 (25 and 34), 48 to 64 entries
+// 100,000 rows 122 and 76 (146 and 162), 10,000 rows 21 and 61 (29 and 127).
+bool init_staged(const apcg_mat_s *A, int x0_zero) {
+    const int64_t n = A->n;
+    return x0_zero ? n >= 98304 && A->nnz >= 6 * n : n >= 131072 && A->nnz >= 10 * n;
+}
+
 // Launch geometry of one solve.
 struct Plan {
     int32_t n;
@@ -1962,7 +1988,7 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
         if ((s = make_plan(A, A->cfg, &pl))) return s;
         Bufs bf{A, x->d, b->d, c->ws, c->partials};
 
-        hipLaunchKernelGGL(k_pcg_init, dim3(pl.g_vec), dim3(VB), 0, st, A->n, A->rowptr, A->col, A->val, b->d, x->d,
+        hipLaunchKernelGGL((init_staged(A, opts.x0_is_zero) ? k_pcg_init<true> : k_pcg_init<false>), dim3(pl.g_vec), dim3(VB), 0, st, A->n, A->rowptr, A->col, A->val, b->d, x->d,
                            c->ws.r(), c->ws.dinv(), c->ws.z(), c->ws.p(0), bf.part_res(), pl.pb_vec,
                            opts.x0_is_zero ? 1 : 0, opts.pc, norm_pre, gate);
         APCG_CHECK_LAUNCH("k_pcg_init");
