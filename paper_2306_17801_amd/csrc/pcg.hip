@@ -1949,7 +1949,9 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
             if (A->cfg.schedule == APCG_SPMV_DIA && (s = prepare_dia(A, c->stream))) return s;
         }
         // a system that fits the chip, by a team of workgroups in one launch
-        if (opts.mode == APCG_MODE_GRAPH && !gate && A->n > kTeamMinRows) {
+        // (without iterations loading the matrix is all there is: 64^3 73 us,
+        // 24 by the kernels)
+        if (opts.mode == APCG_MODE_GRAPH && !gate && A->n > kTeamMinRows && maxit > 0) {
             // Where the kernels' iterations are queued without a look at the
             // device, nobody waits for the team either: what it leaves is
             // solved by one workgroup, or the kernels solve it all.
