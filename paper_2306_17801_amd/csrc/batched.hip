@@ -321,6 +321,15 @@ uint64_t fnv1a(const void *p, size_t n, uint64_t h = 1469598103934665603ull) {
 
 }  // namespace
 
+// A batch of systems that fill the chip one by one takes a persistent workgroup
+// for each, and no teams, up to so many rows, or rows times iterations: two of
+// them share a compute unit, and a team's setup takes longer.  Microseconds of
+// 512 systems, teams and persistent: to 1e-8 11 x 11 503 and 324, 16 x 16 665
+// and 499, 20 x 20 784 and 749, 22 x 22 832 and 866, 7^3 340 and 380; twenty
+// iterations 22 x 22 324 and 278, 8^3 295 and 289, 28 x 28 324 and 365; five
+// iterations 31 x 31 285 and 241, 40 x 40 282 and 261, 12^3 277 and 275.
+constexpr int64_t kSmallSystem = 320, kSmallWork = 10000;
+
 apcg_status launch_pcg_left(hipStream_t st, const TeamLater &later, const apcg_mat_s *A, const double *b, double *x,
                             double *ws, double rtol, int32_t maxit, const apcg_solve_opts &opts, apcg_solve_info *info,
                             double *hist, int32_t hist_cap) {
@@ -657,7 +666,8 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
             const bool alone =
                 !polled && (persistent || (most * maxit <= kLeftWork && rows * maxit <= 64 * kLeftWork));
             TeamFit fit;
-            if ((polled || alone) && (s = team_eligible(ctx, nsys, A, 1, true, &fit))) return s;
+            const bool small = persistent && (most <= kSmallSystem || most * maxit <= kSmallWork);
+            if ((polled || alone) && !small && maxit > 0 && (s = team_eligible(ctx, nsys, A, 1, true, &fit))) return s;
             if (fit.rows > 0 && alone) {
                 uint64_t h;
                 TeamLater later;
