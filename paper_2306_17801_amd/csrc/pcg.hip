@@ -1229,12 +1229,24 @@ __global__ __launch_bounds__(VB) void k_pcg_finish(SolveState *st, const double 
         const PcgRecord last = st->rec[st->rec[1].k > st->rec[0].k ? 1 : 0];
         its = last.k;
         if (blockIdx.x == 0 && threadIdx.x < 64) {
+            // in the order of dev::reduce_partials<64, 2>, sixteen of a
+            // thread's partials of either sum loaded before they are added
             double v[2] = {0.0, 0.0};
+            constexpr int UA = 16;
+            for (int i = threadIdx.x; i < g_res; i += UA * 64) {
+                double t[2][UA];
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                for (int i = threadIdx.x; i < g_res; i += 64) v[k] += part_res[k * g_res + i];
-                v[k] = dev::wave_sum(v[k]);
+                for (int a = 0; a < UA; ++a)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) t[k][a] = i + a * 64 < g_res ? part_res[k * g_res + i + a * 64] : 0.0;
+#pragma unroll
+                for (int a = 0; a < UA; ++a)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+                        if (i + a * 64 < g_res) v[k] += t[k][a];
             }
+            v[0] = dev::wave_sum(v[0]);
+            v[1] = dev::wave_sum(v[1]);
             if (threadIdx.x == 0) {
                 const double res = sqrt(v[1]);
                 const int status = iteration_status(v[0], res, st, its);
