@@ -226,9 +226,11 @@ apcg_status spmv_tb(hipStream_t s, const apcg_mat_s *A, const apcg_spmv_config &
     const int G = normalise_blocks(cfg.blocks, (A->n + rpp - 1) / rpp);
     int32_t rpb = (int32_t)((A->n + G - 1) / G);
     if (rpb < 1) rpb = 1;
-    // staged where a lane has five to eight entries of a row (as the fused
-    // product; one lane: a lane's eight entries are the row)
-    if (A->sell_maxw <= (lpr > 1 ? 4 * lpr : 8) && A->sell_maxw > (lpr > 1 ? 2 * lpr : 4)) {
+    // staged where a lane has five to eight entries of the longest row (one
+    // lane: a lane's eight entries are the row) and more than half of the
+    // eight of an average one: one to eight entries, 400,000 rows 13.7 us by
+    // the schedule below, 9.7 staged; two to 16 22.1 and 20.1; 17 19.6 and 20.3
+    if (staged_fits(A, lpr) && (lpr == 1 || staged_share(A, lpr) >= 4.4)) {
         void (*k)(int32_t, const int32_t *, const int32_t *, const double *, const double *, double *, int32_t) = nullptr;
         switch (lpr) {
             case 1: k = k_spmv_staged<1, TB>; break;
@@ -347,7 +349,7 @@ apcg_status launch_scalar_set(hipStream_t s, double *out, double v) {
 // for a lone product on a sliced schedule).
 static apcg_status spmv_with(hipStream_t s, const apcg_mat_s *A, const apcg_spmv_config &cfg, const double *x,
                              double *y) {
-    if (cfg.schedule == APCG_SPMV_STREAM && one_lane_staged(A)) {  // the same sums, one row per lane as below
+    if (cfg.schedule == APCG_SPMV_STREAM && staged_fits(A, 1)) {  // the same sums, one row per lane as below
         const apcg_spmv_config one{1, cfg.block_size, cfg.blocks, APCG_SPMV_ROWGROUP};
         return spmv_with(s, A, one, x, y);
     }

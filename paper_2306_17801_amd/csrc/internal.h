@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 #include <functional>
@@ -365,8 +366,30 @@ inline bool stream_fits(const apcg_mat_s *A, int tb) {
     return (tb == 256 || tb == 512) && A->max_block_nnz[tb == 512 ? 1 : 0] <= kStreamMaxNnz;
 }
 
-// Rows that dev::staged_rows takes one to a lane.
-inline bool one_lane_staged(const apcg_mat_s *A) { return A->sell_maxw > 4 && A->sell_maxw <= 8; }
+// Rows that dev::staged_rows may take with lpr lanes a row (lpr / 2 of them at
+// work; one: one): the longest row leaves a lane at most eight entries, so that
+// a wavefront's rows fit its stage, and more than four.
+inline bool staged_fits(const apcg_mat_s *A, int lpr) {
+    return lpr <= 16 && A->sell_maxw > (lpr > 1 ? 2 * lpr : 4) && A->sell_maxw <= (lpr > 1 ? 4 * lpr : 8);
+}
+// Entries of an average row that a lane then has; it reads eight.
+inline double staged_share(const apcg_mat_s *A, int lpr) {
+    return (double)A->nnz / ((double)std::max<int64_t>(1, A->n) * (lpr > 1 ? lpr / 2 : 1));
+}
+// Whether the fused product is better off staged.  Us of twenty iterations, not
+// staged and staged, by that share.  Rows alike, stencils: 4.5 (nine entries,
+// 300 x 2000) 35 and 26 a product, 5 (five, 900 x 1000) 30 and 22, 6.8 (27,
+// 96^3) 142 and 91; columns at random within 3000: 4.1 (33) 838 and 908, 4.3
+// (17) 912 and 942, 4.5 (nine) 903 and 957, 6.8 (27) 2293 and 1588, 7.5 (15)
+// 802 and 632, 8 (64) 1157 and 868.  Uneven rows: 3 (one to five) 500 and 557,
+// 4.5 (one to eight) 603 and 645, 4.5 (two to 16) 942 and 1029, 5.3 (nine to
+// twelve) 773 and 814, 5.5 (six to 16) 1057 and 1050, 6.5 (20 to 32) 673 and
+// 608.
+inline bool staged_pays(const apcg_mat_s *A, int lpr) {
+    const double share = staged_share(A, lpr);
+    const bool alike = (double)A->nnz >= 0.9 * A->sell_maxw * (double)A->n;
+    return staged_fits(A, lpr) && (share >= 5.5 || (alike && share >= 4.4));
+}
 
 // Grid and chunk for an elementwise pass over n entries: 2048 workgroups at
 // most, chunks a multiple of 64 entries (512-byte aligned for doubles).

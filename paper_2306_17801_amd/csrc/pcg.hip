@@ -1284,16 +1284,9 @@ using ProductFn = void (*)(int32_t, const int32_t *, const int32_t *, const doub
                            const double *, double *, double *, SolveState *, const double *, int, double *, int32_t,
                            int, int, int32_t);
 
-// Lanes per row: the staged kernel where the longest row (maxrow) leaves a
-// lane at most eight entries, so that a wavefront's rows fit its stage, and
-// more than four, so that most of the eight are there.  Microseconds of a
-// product in the solve, unstaged and staged (128^3 with 7 entries a row, 96^3
-// with 27): two lanes for 7 entries 90 and 56, eight for 27 142 and 91; but
-// sixteen for 27 114 and 137, four for 5 (9e5 rows) 30 and 33.  (One lane: a
-// row of more than eight does not fit the eight cells it reads at once.)
 template <int TB>
-ProductFn product_fn_tb(int lpr, int32_t maxrow) {
-    if (maxrow > (lpr > 1 ? 2 * lpr : 4) && maxrow <= (lpr > 1 ? 4 * lpr : 8)) switch (lpr) {
+ProductFn product_fn_tb(int lpr, bool staged) {
+    if (staged) switch (lpr) {
         case 1: return k_pcg_product_staged<1, TB>;
         case 2: return k_pcg_product_staged<2, TB>;
         case 4: return k_pcg_product_staged<4, TB>;
@@ -1324,8 +1317,8 @@ ProductFn stream_fn(int32_t lds_nnz) {
     return k_pcg_product_stream<TB, 21>;  // 21 * 256 >= kStreamMaxNnz
 }
 
-ProductFn product_fn(const apcg_spmv_config &cfg, int32_t lds_nnz, int32_t sell_maxw, int32_t sdia_mp,
-                     int32_t sdia_ps) {
+ProductFn product_fn(const apcg_mat_s *A, const apcg_spmv_config &cfg, int32_t lds_nnz) {
+    const int32_t sell_maxw = A->sell_maxw, sdia_mp = A->sdia_mp, sdia_ps = A->sdia_ps;
     if (cfg.schedule == APCG_SPMV_DIA) {
         const bool b512 = cfg.block_size == 512;
         if (cfg.lanes_per_row > 1 && (lds_nnz >> 16) > 0) {  // plane marching
@@ -1364,8 +1357,9 @@ ProductFn product_fn(const apcg_spmv_config &cfg, int32_t lds_nnz, int32_t sell_
         if (cfg.block_size == 512) return stream_fn<512>(lds_nnz);
         return stream_fn<256>(lds_nnz);
     }
-    return cfg.block_size == 512 ? product_fn_tb<512>(cfg.lanes_per_row, sell_maxw)
-                                 : product_fn_tb<256>(cfg.lanes_per_row, sell_maxw);
+    const bool staged = staged_pays(A, cfg.lanes_per_row);
+    return cfg.block_size == 512 ? product_fn_tb<512>(cfg.lanes_per_row, staged)
+                                 : product_fn_tb<256>(cfg.lanes_per_row, staged);
 }
 
 // Whether the setup brings the rows through LDS (k_pcg_init): where lanes that
@@ -1411,11 +1405,11 @@ apcg_status make_plan(const apcg_mat_s *A, const apcg_spmv_config &config, Plan 
     if (config.schedule == APCG_SPMV_STREAM && !stream_fits(A, pl->tb))
         return set_error(APCG_ERR_UNSUPPORTED, "rows too long for the staged schedule");
     // one row per thread with rows of five to eight entries: staged by
-    // wavefronts, which gives the same row sums without the workgroup's
-    // barriers (7 entries, 128^3: 63 and 56 us in the solve; 5, 900 x 1000: 30
-    // and 22)
+    // wavefronts where that pays, which gives the same row sums without the
+    // workgroup's barriers (7 entries, 128^3: 63 and 56 us in the solve; 5, 900
+    // x 1000: 30 and 22)
     apcg_spmv_config cfg = config;
-    if (cfg.schedule == APCG_SPMV_STREAM && one_lane_staged(A)) {
+    if (cfg.schedule == APCG_SPMV_STREAM && staged_pays(A, 1)) {
         cfg.schedule = APCG_SPMV_ROWGROUP;
         cfg.lanes_per_row = 1;
     }
@@ -1484,7 +1478,7 @@ apcg_status make_plan(const apcg_mat_s *A, const apcg_spmv_config &config, Plan 
         int64_t rpb = ((int64_t)A->n + pl->g_prod - 1) / pl->g_prod;
         pl->rpb = (int32_t)std::max<int64_t>(1, rpb);
     }
-    pl->prod = product_fn(cfg, pl->lds_nnz, A->sell_maxw, A->sdia_mp, A->sdia_ps);
+    pl->prod = product_fn(A, cfg, pl->lds_nnz);
     if (!pl->prod) return set_error(APCG_ERR_INVALID_ARG, "unsupported lanes_per_row");
     vector_grid(A->n, &pl->g_vec, &pl->pb_vec);
     return APCG_SUCCESS;

@@ -983,10 +983,13 @@ apcg_status apcg_mat_wrap_csr(int32_t device, int32_t n, int64_t nnz, const int3
     }
     spmv_default_config(n, nnz, &A->cfg);
     // one row per thread, unless rows of more than eight entries fit the lanes
-    // of the row groups (9 entries, 300 x 2000, product in the solve: 41 us
-    // with one row per thread, 25 with four lanes)
-    const bool lanes = A->sell_maxw > 8 && A->sell_maxw > 2 * A->cfg.lanes_per_row &&
-                       A->sell_maxw <= 4 * A->cfg.lanes_per_row;
+    // of the row groups (nine entries, 300 x 2000, product in the solve: 41 us
+    // with one row per thread, 25 with four lanes), and are staged if those are
+    // more than four (17 entries, 200,000 rows, twenty iterations: 775 us with
+    // one row per thread, 912 with eight lanes)
+    const int32_t l = A->cfg.lanes_per_row;
+    const bool lanes =
+        A->sell_maxw > 8 && A->sell_maxw > 2 * l && A->sell_maxw <= 4 * l && (l <= 4 || staged_pays(A, l));
     if (stream_fits(A, 256) && !lanes) A->cfg = apcg_spmv_config{1, 256, 1024, APCG_SPMV_STREAM};
     *out = A;
     return APCG_SUCCESS;
