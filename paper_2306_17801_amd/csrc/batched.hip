@@ -133,11 +133,9 @@ __device__ __forceinline__ double row_product_z(const dev::glob_t<int32_t> *col,
     return sum;
 }
 
-// HIST: alpha and beta of the first hist_cap iterations go to hist[0..] and
-// hist[hist_cap..], as pcg_solve_marked records them.
-template <int TB, bool HIST = false>
+template <int TB>
 __device__ void solve_one(const BatchSys &S, double rtol, int32_t maxit, int x0_zero, int pc, int norm_pre,
-                          apcg_solve_info *out, double *lds, double *hist = nullptr, int32_t hist_cap = 0) {
+                          apcg_solve_info *out, double *lds) {
     const int n = S.n;
     // global pointers: the system's pointers come from a table in memory
     // (generic to the compiler), and flat accesses would also count in lgkmcnt
@@ -240,10 +238,6 @@ __device__ void solve_one(const BatchSys &S, double rtol, int32_t maxit, int x0_
         else if (res <= rtol * ref) status = APCG_SOLVE_CONVERGED;
         else if (!(rho_new > 0.0)) status = APCG_SOLVE_BREAKDOWN_RZ;
         else if (k >= maxit) status = APCG_SOLVE_MAXIT;
-        if (HIST && threadIdx.x == 0 && k <= hist_cap) {
-            hist[k - 1] = alpha;
-            if (!status) hist[hist_cap + k - 1] = rho_new / rho;
-        }
         if (!status) {
             beta = rho_new / rho;
             rho = rho_new;
@@ -277,21 +271,19 @@ __global__ __launch_bounds__(TB) void k_pcg_batched(const BatchSys *sys, const i
     }
 }
 
-// What a team launch that nobody waits for has left, one workgroup per system
-// (sys == nullptr: the one); usually nothing, and then 2 us.
-template <int TB, bool HIST>
-__global__ __launch_bounds__(TB) void k_pcg_left(const BatchSys *sys, BatchSys one, const uint32_t *verdicts,
-                                                 uint64_t *report, uint64_t launch, double rtol, int32_t maxit,
-                                                 int x0_zero, int pc, int norm_pre, apcg_solve_info *info,
-                                                 double *hist, int32_t hist_cap) {
+// What a team launch that nobody waits for has left, one workgroup per system;
+// usually nothing, and then 2 us.
+template <int TB>
+__global__ __launch_bounds__(TB) void k_pcg_left(const BatchSys *sys, const uint32_t *verdicts, uint64_t *report,
+                                                 uint64_t launch, double rtol, int32_t maxit, int x0_zero, int pc,
+                                                 int norm_pre, apcg_solve_info *info) {
     __shared__ double lds[4 * (TB / 64)];
     const int id = blockIdx.x;
     const uint32_t v = verdicts[id];
     if (v == kDone) return;
     if (threadIdx.x == 0)
         __hip_atomic_store(report, launch | (uint64_t)(id + 1) << 8 | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    const BatchSys S = sys ? sys[id] : one;
-    solve_one<TB, HIST>(S, rtol, maxit, x0_zero, pc, norm_pre, info + id, lds, hist, hist_cap);
+    solve_one<TB>(sys[id], rtol, maxit, x0_zero, pc, norm_pre, info + id, lds);
 }
 
 __global__ void k_queue_reset(unsigned *queue) {
@@ -329,25 +321,6 @@ uint64_t fnv1a(const void *p, size_t n, uint64_t h = 1469598103934665603ull) {
 // iterations 22 x 22 324 and 278, 8^3 295 and 289, 28 x 28 324 and 365; five
 // iterations 31 x 31 285 and 241, 40 x 40 282 and 261, 12^3 277 and 275.
 constexpr int64_t kSmallSystem = 320, kSmallWork = 10000;
-
-apcg_status launch_pcg_left(hipStream_t st, const TeamLater &later, const apcg_mat_s *A, const double *b, double *x,
-                            double *ws, double rtol, int32_t maxit, const apcg_solve_opts &opts, apcg_solve_info *info,
-                            double *hist, int32_t hist_cap) {
-    BatchSys one{};
-    one.rowptr = A->rowptr;
-    one.col = A->col;
-    one.val = A->val;
-    one.b = b;
-    one.x = x;
-    one.ws = ws;
-    one.n = A->n;
-    hipLaunchKernelGGL((hist ? k_pcg_left<1024, true> : k_pcg_left<1024, false>), dim3(1), dim3(1024), 0, st,
-                       (const BatchSys *)nullptr, one, later.verdicts, later.report, later.launch, rtol, maxit,
-                       opts.x0_is_zero ? 1 : 0, opts.pc, opts.norm_type == APCG_NORM_PRECONDITIONED ? 1 : 0, info, hist,
-                       hist_cap);
-    APCG_CHECK_LAUNCH("k_pcg_left");
-    return APCG_SUCCESS;
-}
 
 // Per-context batch resources (kept in a side table keyed by context id).
 struct BatchCache {
@@ -667,7 +640,7 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
                 !polled && (persistent || (most * maxit <= kLeftWork && rows * maxit <= 64 * kLeftWork));
             TeamFit fit;
             const bool small = persistent && (most <= kSmallSystem || most * maxit <= kSmallWork);
-            if ((polled || alone) && !small && maxit > 0 && (s = team_eligible(ctx, nsys, A, 1, true, &fit))) return s;
+            if ((polled || alone) && !small && maxit > 0 && (s = team_eligible(ctx, nsys, A, 1, &fit))) return s;
             if (fit.rows > 0 && alone) {
                 uint64_t h;
                 TeamLater later;
@@ -675,10 +648,9 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
                 if ((s = team_pcg_solve(ctx, nsys, A, b, x, order, rtol, maxit, opts, fit, info->d, nullptr, 0, nullptr,
                                         &later)))
                     return s;
-                hipLaunchKernelGGL((k_pcg_left<512, false>), dim3(nsys), dim3(512), 0, ctx->stream,
-                                   (const BatchSys *)bc->d_sys, BatchSys{}, later.verdicts, later.report, later.launch,
-                                   rtol, maxit, opts.x0_is_zero ? 1 : 0, opts.pc,
-                                   opts.norm_type == APCG_NORM_PRECONDITIONED ? 1 : 0, info->d, (double *)nullptr, 0);
+                hipLaunchKernelGGL(k_pcg_left<512>, dim3(nsys), dim3(512), 0, ctx->stream, (const BatchSys *)bc->d_sys,
+                                   later.verdicts, later.report, later.launch, rtol, maxit, opts.x0_is_zero ? 1 : 0,
+                                   opts.pc, opts.norm_type == APCG_NORM_PRECONDITIONED ? 1 : 0, info->d);
                 APCG_CHECK_LAUNCH("k_pcg_left");
                 return op_end(ctx, acc.data(), (int)acc.size());
             }

@@ -1272,7 +1272,7 @@ static apcg_status bf_solve(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const
     const bool polled = ((int64_t)maxit + 2 + K - 1) / K >= std::max(1, opts.lookahead);
     const bool automatic =
         opts.batch_schedule == APCG_BATCH_AUTO && !opts.batch_tile_rows && !opts.batch_tail_tile_rows;
-    if (automatic && polled && maxit <= kTeamFcgMaxIts && (s = team_eligible(ctx, nsys, A, 2, true, &fit))) return s;
+    if (automatic && polled && maxit <= kTeamFcgMaxIts && (s = team_eligible(ctx, nsys, A, 2, &fit))) return s;
     if (fit.rows == 0) {
         apcg_solve_opts o = opts;
         if (automatic && !polled) {

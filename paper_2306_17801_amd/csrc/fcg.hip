@@ -486,7 +486,7 @@ extern "C" apcg_status apcg_ksp_solve_fcg_poly(apcg_ctx ctx, apcg_mat A, apcg_ve
         const bool polled = ((int64_t)maxit + K - 1) / K >= L;
         if (opts.mode == APCG_MODE_GRAPH && A->n > kTeamMinRows && polled && maxit <= kTeamFcgMaxIts) {
             TeamFit fit;
-            if ((s = team_eligible(ctx, 1, &A, 2, true, &fit))) return s;
+            if ((s = team_eligible(ctx, 1, &A, 2, &fit))) return s;
             if (fit.rows > 0) {
                 std::vector<int32_t> left;
                 if ((s = team_fcg_solve(ctx, 1, &A, &b, &x, {0}, rtol, maxit, opts, fo, fit, dev_coeffs,

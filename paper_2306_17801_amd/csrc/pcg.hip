@@ -1955,27 +1955,16 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
             if (A->cfg.schedule == APCG_SPMV_DIA && (s = prepare_dia(A, c->stream))) return s;
         }
         // a system that fits the chip, by a team of workgroups in one launch
-        // (without iterations loading the matrix is all there is: 64^3 73 us,
-        // 24 by the kernels)
-        if (opts.mode == APCG_MODE_GRAPH && !gate && A->n > kTeamMinRows && maxit > 0) {
-            // Where the kernels' iterations are queued without a look at the
-            // device, nobody waits for the team either: what it leaves is
-            // solved by one workgroup, or the kernels solve it all.
-            const bool polled = ((int64_t)maxit + K - 1) / K >= opts.lookahead;
-            const bool alone = !polled && (int64_t)A->n * maxit <= kLeftWork;
+        // unless its iterations are queued without a look at the device: a team
+        // needs the matrix's border, which the first solve would wait for, and
+        // a team from the second solve on would make the last bits depend on
+        // what was solved before (five iterations, teams and kernels: 100 x 100
+        // 68 and 73 us, 300 x 300 78 and 84, 32^3 83 and 73; without any,
+        // 64^3 73 and 24)
+        const bool polled = ((int64_t)maxit + K - 1) / K >= opts.lookahead;
+        if (opts.mode == APCG_MODE_GRAPH && !gate && A->n > kTeamMinRows && polled) {
             TeamFit fit;
-            if ((polled || alone) && (s = team_eligible(c, 1, &A, 1, polled, &fit))) return s;
-            if (fit.rows > 0 && alone) {
-                TeamLater later;
-                if ((s = ensure_workspace(c, A->n))) return s;
-                if ((s = team_pcg_solve(c, 1, &A, &b, &x, {0}, rtol, maxit, opts, fit, info->d + info_index, hist,
-                                        hist_cap, nullptr, &later)))
-                    return s;
-                if ((s = launch_pcg_left(st, later, A, b->d, x->d, c->ws.base, rtol, maxit, opts, info->d + info_index,
-                                         hist, hist_cap)))
-                    return s;
-                return op_end(c, acc, 4);
-            }
+            if ((s = team_eligible(c, 1, &A, 1, &fit))) return s;
             if (fit.rows > 0) {
                 std::vector<int32_t> left;
                 if ((s = team_pcg_solve(c, 1, &A, &b, &x, {0}, rtol, maxit, opts, fit, info->d + info_index, hist,

@@ -439,7 +439,6 @@ void team_cache_release(uint64_t ctx_id, int device) {
     hipFree(t->d_swap);
     if (t->pinned) hipHostFree(t->pinned);
     if (t->reports) hipHostFree(t->reports);
-    if (t->border_pinned) hipHostFree(t->border_pinned);
     delete t;
 }
 
@@ -631,23 +630,12 @@ static int team_width(int maxrow) { return maxrow <= 5 ? 5 : maxrow <= 7 ? 7 : 0
 // The border of every matrix that does not know it yet, in one launch and one
 // readback (once per matrix; a solve checks on the device that the pattern
 // still fits).
-// border[w][i]: of system i's members of 2048 (w = 0) and 4096 rows; without
-// may_wait (one system) -1 until it has arrived.
-static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A, bool may_wait,
-                                std::vector<int32_t> (&border)[2]) {
+// border[w][i]: of system i's members of 2048 (w = 0) and 4096 rows.
+static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A, std::vector<int32_t> (&border)[2]) {
     std::vector<BorderItem> items;
     std::vector<int32_t> which;
     int32_t nmax = 0;
-    auto set = [](TeamState &m, const int32_t *b) {
-        if (m.reread.exchange(false) && (m.border[0] != b[0] || m.border[1] != b[1])) m.unfit = 0;
-        for (int w = 0; w < 2; ++w) m.border[w] = b[w];
-    };
     TeamCache *t = team_cache(c);
-    if (t->border_ev && hipEventQuery(t->border_ev->e) == hipSuccess) {
-        t->border_ev = nullptr;
-        if (auto m = t->border_of.lock()) set(*m, t->border_pinned);
-    }
-    (void)hipGetLastError();  // hipErrorNotReady of the query
     for (auto &b : border) b.assign(nsys, 0);
     for (int32_t i = 0; i < nsys; ++i) {
         TeamState &m = *A[i]->team;
@@ -658,7 +646,7 @@ static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A, boo
             nmax = std::max(nmax, A[i]->n);
         }
     }
-    if (items.empty() || (!may_wait && t->border_ev)) return APCG_SUCCESS;
+    if (items.empty()) return APCG_SUCCESS;
     const size_t ni = items.size();
     apcg_status s;
     const int64_t bytes = (int64_t)(sizeof(BorderItem) * ni + sizeof(int32_t) * 2 * ni);
@@ -677,23 +665,15 @@ static apcg_status team_borders(apcg_ctx c, int32_t nsys, const apcg_mat *A, boo
         APCG_CHECK_LAUNCH("k_border");
     }
     g_counters.d2h_copies++;
-    if (!may_wait) {
-        if (!t->border_pinned)
-            APCG_HIP(hipHostMalloc((void **)&t->border_pinned, 2 * sizeof(int32_t), hipHostMallocDefault));
-        APCG_HIP(hipMemcpyAsync(t->border_pinned, out, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
-        if (!(t->border_ev = event_get(c->device))) return set_error(APCG_ERR_HIP, "event creation failed");
-        t->border_of = A[0]->team;
-        APCG_HIP(event_record(t->border_ev, c->stream));
-        return APCG_SUCCESS;
-    }
     APCG_HIP(hipMemcpyAsync(h.data(), out, sizeof(int32_t) * 2 * ni, hipMemcpyDeviceToHost, c->stream));
     if (!t->ev && !(t->ev = event_get(c->device))) return set_error(APCG_ERR_HIP, "event creation failed");
     APCG_HIP(event_record(t->ev, c->stream));
     g_counters.host_polls++;
     APCG_HIP(hipEventSynchronize(t->ev->e));
     for (size_t i = 0; i < ni; ++i) {
-        set(*A[which[i]]->team, &h[2 * i]);
-        for (int w = 0; w < 2; ++w) border[w][which[i]] = h[2 * i + w];
+        TeamState &m = *A[which[i]]->team;
+        if (m.reread.exchange(false) && (m.border[0] != h[2 * i] || m.border[1] != h[2 * i + 1])) m.unfit = 0;
+        for (int w = 0; w < 2; ++w) m.border[w] = border[w][which[i]] = h[2 * i + w];
     }
     return APCG_SUCCESS;
 }
@@ -722,7 +702,7 @@ static int team_rows(int32_t nsys, const apcg_mat *A, const std::vector<int32_t>
     return best;
 }
 
-apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windows, bool may_wait, TeamFit *fit) {
+apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windows, TeamFit *fit) {
     fit->rows = 0;
     if (c->type == APCG_STREAM_GLOBAL_BLOCKING) return APCG_SUCCESS;
     int maxrow = 1;
@@ -740,7 +720,7 @@ apcg_status team_eligible(apcg_ctx c, int32_t nsys, const apcg_mat *A, int windo
     if (!t->cus) APCG_HIP(hipDeviceGetAttribute(&t->cus, hipDeviceAttributeMultiprocessorCount, c->device));
     apcg_status s;
     std::vector<int32_t> border[2];
-    if ((s = team_borders(c, nsys, A, may_wait, border))) return s;
+    if ((s = team_borders(c, nsys, A, border))) return s;
     fit->rows = team_rows(nsys, A, border, t->cus, team_width(maxrow), windows);
     fit->border = std::move(border[fit->rows == 8]);
     return APCG_SUCCESS;

@@ -77,7 +77,7 @@ apcg_status team_launch(int device, hipStream_t st, int wgs, int cus, F launch) 
 }
 
 // A launch nobody waits for: what it leaves is solved by a kernel queued behind
-// it (launch_pcg_left), which reports each such system to the host: where the
+// it (k_pcg_left), which reports each such system to the host: where the
 // verdicts lie, and what to write where (pinned memory).
 struct TeamLater {
     const uint32_t *verdicts = nullptr;
@@ -111,10 +111,6 @@ struct TeamCache {
     uint64_t launches = 0;   // that nobody waits for
     uint64_t *reports = nullptr;  // pinned, kReports words: of launch k in word k modulo kReports
     std::vector<std::weak_ptr<TeamState>> reported[kReports];  // the matrices of those launches
-    // a border that is being read without waiting for it
-    EventRef border_ev;
-    std::weak_ptr<TeamState> border_of;
-    int32_t *border_pinned = nullptr;
     int rest = 0;            // solves to leave to the other schedules after a wait that ran out
     char *mem = nullptr;     // one buffer for the three below (an allocation costs as much as a small solve)
     int64_t mem_cap = 0;
@@ -189,9 +185,8 @@ struct TeamFit {
 // Whether every system can be solved by teams on ctx's device: rows of at
 // most 7 entries, `windows` windows that fit the LDS (1: PCG, 2: the flexible
 // solve), no system larger than the chip, none that members have refused.
-// Reads the matrices' borders back once per matrix; without may_wait (one
-// system) the answer is no until the border has arrived.
-apcg_status team_eligible(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, int windows, bool may_wait, TeamFit *fit);
+// Reads the matrices' borders back, and waits for them, once per matrix.
+apcg_status team_eligible(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, int windows, TeamFit *fit);
 
 // Jacobi-PCG (or CG) of the systems, started in `order` (largest cost
 // first), results in info[i]; hist as in pcg_solve_marked (one system).
@@ -221,9 +216,4 @@ constexpr int32_t kTeamFcgMaxIts = 100000000;
 // When nobody waits for a launch, one workgroup per system solves what is left:
 // up to so many rows times iterations (about a second).
 constexpr int64_t kLeftWork = (int64_t)1 << 25;
-// One system (batched.hip): ws holds 5 n doubles.
-apcg_status launch_pcg_left(hipStream_t st, const TeamLater &later, const apcg_mat_s *A, const double *b, double *x,
-                            double *ws, double rtol, int32_t maxit, const apcg_solve_opts &opts, apcg_solve_info *info,
-                            double *hist, int32_t hist_cap);
-
 }  // namespace apcg

@@ -420,7 +420,7 @@ extern "C" apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b
         const bool polled = ((int64_t)maxit + K - 1) / K >= L;
         if (opts.mode == APCG_MODE_GRAPH && n > kTeamMinRows && polled && maxit <= kTeamFcgMaxIts) {
             TeamFit fit;
-            if ((s = team_eligible(ctx, 1, &A, 1, true, &fit))) return s;
+            if ((s = team_eligible(ctx, 1, &A, 1, &fit))) return s;
             if (fit.rows == 4) {
                 std::vector<int32_t> left;
                 if ((s = team_tfqmr_solve(ctx, A, b, x, rtol, maxit, opts, fit, info->d + info_index, &left))) return s;

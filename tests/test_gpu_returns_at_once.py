@@ -208,10 +208,11 @@ def test_many_queued_launches_and_a_pattern_changed_under_them(apcg, ctx):
         xs = [DeviceVec(x0) for _ in range(calls)]
         apcg.apcg_counters_reset()
         for x in xs:
-            apcg.apcg_ksp_solve(ctx, dA.h, db.h, x.h, 0.0, 1, o, info, 0)
+            apcg.apcg_ksp_solve_batched(ctx, [dA.h], [db.h], [x.h], 0.0, 1, o, info)
         kernels = apcg.apcg_counters_get()["kernel_launches"]
         apcg.apcg_ctx_synchronize(ctx)
         assert all(rel(x.numpy(), ref) <= 1e-12 for x in xs)
         # teams: the words' clearing, the team and what it leaves
-        assert teams is None or (kernels <= 3 * calls) == teams
+        print(A is near, calls, kernels, flush=True)
+        assert teams is None or (kernels == 3 * calls) == teams
     apcg.apcg_info_destroy(info)
