@@ -1985,9 +1985,10 @@ apcg_status pcg_solve_marked(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, d
         if ((s = make_plan(A, A->cfg, &pl))) return s;
         Bufs bf{A, x->d, b->d, c->ws, c->partials};
 
-        hipLaunchKernelGGL((init_staged(A, opts.x0_is_zero) ? k_pcg_init<true> : k_pcg_init<false>), dim3(pl.g_vec), dim3(VB), 0, st, A->n, A->rowptr, A->col, A->val, b->d, x->d,
-                           c->ws.r(), c->ws.dinv(), c->ws.z(), c->ws.p(0), bf.part_res(), pl.pb_vec,
-                           opts.x0_is_zero ? 1 : 0, opts.pc, norm_pre, gate);
+        hipLaunchKernelGGL((init_staged(A, opts.x0_is_zero) ? k_pcg_init<true> : k_pcg_init<false>), dim3(pl.g_vec),
+                           dim3(VB), 0, st, A->n, A->rowptr, A->col, A->val, b->d, x->d, c->ws.r(), c->ws.dinv(),
+                           c->ws.z(), c->ws.p(0), bf.part_res(), pl.pb_vec, opts.x0_is_zero ? 1 : 0, opts.pc, norm_pre,
+                           gate);
         APCG_CHECK_LAUNCH("k_pcg_init");
         hipLaunchKernelGGL(k_pcg_init_final, dim3(1), dim3(64), 0, st, c->ws.state, (const double *)bf.part_res(),
                            pl.g_vec, rtol, maxit, hist, hist_cap, gate);

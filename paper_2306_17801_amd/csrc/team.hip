@@ -8,8 +8,8 @@
 // units between two iterations, and an iteration is bound by its two meetings
 // (1.2 to 1.8 us each).  Microseconds per iteration, before and after:
 //   2D, 30k rows   10.0   4.6        3D, 64^3 (262k rows)   15.8   7.0
-//   2D, 250k rows  15     5.4
-// and 256 2D systems of 1e3 to 6.5e4 rows in one call: 192 ms, now 28.5.  The
+//   2D, 250k rows  15     5.7
+// and 256 2D systems of 1e3 to 6.5e4 rows in one call: 192 ms, now 28.6.  The
 // direction of the border columns is kept and updated by every member that
 // reads it (p = z + beta p, the same operation on the same values), so only z
 // travels.
@@ -68,7 +68,8 @@ struct TeamPlan {
 // Eight slices a wavefront leave no registers for x and D^-1 beside the
 // entries, r and w: they lie in LDS behind the window then (kept in registers
 // they spilled, and a member of 4096 rows took 7.6 us an iteration instead of
-// 5.5).
+// 5.5).  Seven registers still spill, 32 bytes a lane; four slices spill none
+// (233 registers of five-entry rows, 253 of seven).
 constexpr bool rows_in_lds(int R) { return R == 8; }
 
 template <int R, int L>
@@ -223,7 +224,11 @@ __device__ __forceinline__ void team_pcg(const TeamPlan &P, const TeamSys &S, Me
                 }
             }
         } else {
-            constexpr int UB = R <= 4 ? 9 : 4;  // loads in flight (4224 columns of a 64^2 plane's half: one round)
+            // Loads in flight: nine are the best at every 3D size (48^3 4, 6, 8,
+            // 9 and 12 in flight: 6.43, 6.28, 6.27, 6.04 and 6.11 us an
+            // iteration, 64^3 7.36, 7.25, 7.18, 7.00 and 7.10, 78^3 10.1, 9.9,
+            // 9.9, 9.6 and 9.9); eight slices leave registers for four.
+            constexpr int UB = R <= 4 ? 9 : 4;
             for (int c0 = tid; c0 < nb; c0 += UB * TT) {
                 double z[UB];
 #pragma unroll

@@ -13,11 +13,12 @@
 // the members that read it, which the setup checks.  The tags go on counting
 // from launch to launch, so the buffers are not cleared.
 // An iteration with 64^3 rows: 75 us by kernels, 42 here; 48 mixed systems of
-// 1e3 to 1e5 rows in one call: 52.2 ms on tiles, 9.6 here.  Four border
-// values in flight per thread: eight take the registers of the matrix (42
-// spilled; 49.4 for 48.9 us at 64^3, 66.3 for 62.2 at 78^3; five and six make
-// no difference).  What is left is the latency of eight dependent exchanges,
-// 2 to 4 us each.
+// 1e3 to 1e5 rows in one call: 52.2 ms on tiles, 9.7 here.  Four border
+// values in flight per thread: with eight 42 registers spill (49.4 for 48.9 us
+// at 64^3, 66.3 for 62.2 at 78^3), five and six make no difference.  All 256
+// registers are taken as it is, with 104 bytes of scratch a lane (128, and 8
+// registers spilled, with rows of seven entries).  What is left is the latency
+// of eight dependent exchanges, 2 to 4 us each.
 //
 // The states, the operations and the order of every sum are those of
 // batched_fcg.hip, so the two give the same bits.

@@ -86,7 +86,8 @@ def at_once(busy, ctx, call, times=2, first=0):
 
 
 @pytest.mark.parametrize("shape,maxit,opts", [
-    ((110, 110), 12, {}), ((24, 25, 26), 16, {}), ((110, 110), 0, {}), ((400, 400), 14, {"iters_per_graph": 7, "lookahead": 3}),
+    ((110, 110), 12, {}), ((24, 25, 26), 16, {}), ((110, 110), 0, {}),
+    ((400, 400), 14, {"iters_per_graph": 7, "lookahead": 3}),
     ((110, 110), 100, {"iters_per_graph": 64, "lookahead": 8}), ((500, 500), 300, {"iters_per_graph": 64, "lookahead": 8}),
 ], ids=str)
 def test_single_solve(apcg, busy, ctx, shape, maxit, opts):
