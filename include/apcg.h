@@ -527,7 +527,7 @@ typedef struct apcg_solve_opts {
 } apcg_solve_opts;
 
 /* Schedules of apcg_ksp_solve_batched. */
-#define APCG_BATCH_AUTO 0       /* persistent when the batch is balanced enough */
+#define APCG_BATCH_AUTO 0       /* teams, else by the largest system's share   */
 #define APCG_BATCH_PERSISTENT 1 /* one launch; one workgroup per system        */
 #define APCG_BATCH_SEGMENTED 2  /* the batch as one block-diagonal system      */
 
@@ -561,20 +561,29 @@ apcg_status apcg_info_get(apcg_info info, int32_t index, apcg_solve_info *out);
  * With APCG_MODE_GRAPH/STREAM no kernel waits on the host: the host thread
  * returns once it has enqueued enough work to reach convergence or maxit,
  * having observed the device flag only through events `lookahead` periods
- * behind the queue.  With APCG_MODE_GRAPH (and AUTO), a system of more than
- * 8192 rows that fits the chip -- rows of at most 5 entries up to 1,048,576
- * rows, of at most 7 up to 524,288, every 2048 (4096) rows naming a few
- * thousand other rows at most, within 32,768 -- is solved by one launch of a team of workgroups instead, each
- * holding its rows' entries and vectors in registers; its sums run in another
- * fixed order than the kernels' of STREAM and HOST_CHECK (same tests, same
- * counts up to rounding).  With APCG_MODE_PERSISTENT (or AUTO at n <=
- * APCG_PERSISTENT_MAX_N) the whole solve is one launch of one 512-thread
- * workgroup that keeps each row's r, D^-1, p and A p in registers and shares
- * p through LDS; its sums run in another
- * fixed order than the multi-kernel modes' (same tests, same counts up to
- * rounding).  n > APCG_PERSISTENT_MAX_N with PERSISTENT returns
+ * behind the queue.
+ *
+ * With APCG_MODE_GRAPH (and AUTO), a system of more than 8192 rows that fits
+ * the chip -- rows of at most 5 entries up to 1,048,576 rows, of at most 7 up
+ * to 524,288, every 2048 (4096) rows naming a few thousand other rows at most,
+ * within 32,768 -- is solved by one launch of a team of workgroups instead,
+ * each holding its rows' entries and vectors in registers, when maxit is at
+ * least (lookahead - 1) iters_per_graph + 1 (17 by default: fewer iterations
+ * are queued without any event to wait for, and stay with the kernels).  A
+ * team solve returns after it has finished: what a team gives up -- its pattern
+ * is not the one that was counted, or other work holds the compute units for
+ * two seconds -- is solved by the kernels, from the same x0.  The first team
+ * solve of a matrix also reads two counts of its pattern back.  A team's sums
+ * run in another fixed order than the kernels' of STREAM and HOST_CHECK (same
+ * tests, same counts up to rounding).
+ *
+ * With APCG_MODE_PERSISTENT (or AUTO at n <= APCG_PERSISTENT_MAX_N) the whole
+ * solve is one launch of one 512-thread workgroup that keeps each row's r,
+ * D^-1, p and A p in registers and shares p through LDS; its sums run in
+ * another fixed order than the multi-kernel modes' (same tests, same counts up
+ * to rounding).  n > APCG_PERSISTENT_MAX_N with PERSISTENT returns
  * APCG_ERR_INVALID_ARG.  On a globally blocking context the call returns
- * after the solve has finished. */
+ * after the solve has finished, by the kernels. */
 apcg_status apcg_ksp_solve(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, double rtol, int32_t maxit,
                            const apcg_solve_opts *opts, apcg_info info, int32_t info_index);
 
@@ -648,9 +657,12 @@ typedef struct apcg_batch_config {
  * APCG_SPMV_ROWGROUP (one lane per row), so that the batch reads the CSR
  * arrays.  The
  * caller passes *best's fields to apcg_solve_opts (batch_schedule,
- * batch_block_size, batch_tile_rows).  APCG_BATCH_AUTO's teams (see
- * apcg_ksp_solve_batched) are not among what it times: for systems that fit
- * the chip they are the faster choice.  Blocks the host. */
+ * batch_block_size, batch_tile_rows).  It chooses between the two schedules
+ * that a batch can be told to take.  APCG_BATCH_AUTO's teams (see
+ * apcg_ksp_solve_batched) are not one of them and not timed: a batch whose
+ * systems fit the chip is solved faster when it is left on AUTO (256 2D
+ * systems of 1e3 to 6.5e4 rows: 29 ms, 157 on the schedule chosen here).
+ * Blocks the host. */
 apcg_status apcg_batch_autotune(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b, const apcg_vec *x,
                                 int32_t kind, int32_t iters, apcg_batch_config *best, double *best_ms,
                                 int32_t *from_cache);
@@ -707,8 +719,9 @@ apcg_status apcg_latency_floors(int32_t device, int32_t reps, double out_us[4]);
  * matrix copies the pattern to the host once, synchronously), else the CSR
  * arrays; both add every row's entries in column order, bitwise alike.  With
  * APCG_MODE_GRAPH, a system of more than 8192 rows that fits the chip (as in
- * apcg_ksp_solve, 2048 rows a workgroup) is solved by one launch of a team of
- * workgroups instead, whose sums run in another fixed order. */
+ * apcg_ksp_solve, 2048 rows a workgroup, from as many iterations on) is solved
+ * by one launch of a team of workgroups instead, whose sums run in another
+ * fixed order, and the call returns after it has finished. */
 apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, double rtol, int32_t maxit,
                                  const apcg_solve_opts *opts, apcg_info info, int32_t info_index);
 
@@ -730,22 +743,28 @@ apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec 
  *     The tile product walks 5, 7 or 8 offset slots per row, the fewest
  *     that cover every such system of the batch.
  *   APCG_BATCH_AUTO: teams when every system's rows hold at most 7 entries and
- *     it fits the chip (see apcg_ksp_solve): one launch, each system held in
- *     the registers of as many workgroups as it needs (the flexible solves
- *     below likewise, unless their tiles' sizes are set); the segmented
- *     schedule's sums, bit for bit, whatever copies of the matrices exist.
- *     Otherwise persistent when no system costs more than 1/CUs of the batch,
- *     else segmented.
+ *     it fits the chip (see apcg_ksp_solve; any number of rows): one launch,
+ *     each system held in the registers of as many workgroups as it needs (the
+ *     flexible solves below likewise, unless their tiles' sizes are set); the
+ *     segmented schedule's sums, bit for bit, whatever copies of the matrices
+ *     exist.  Otherwise persistent when no system costs more than 1/CUs of the
+ *     batch, else segmented; so also without iterations, where the batch would
+ *     be persistent with no system of more than 320 rows, or of more than
+ *     10,000 rows times maxit, and where it would be segmented without a poll
+ *     with a system of more than 2^25 rows times maxit (2^31 in all).
  * A, b, x: arrays of nsys handles on ctx's device; the memory of each x[i]
  * may overlap no other x[j] and no b[j] (checked on the host over the
- * vectors' address ranges: APCG_ERR_INVALID_ARG); x[i] holds x0 (ignored with x0_is_zero) and receives
- * the solution; info must hold >= nsys records, record i for system i.
- * opts->mode APCG_MODE_GRAPH (default) replays captured graphs (cached while
- * the batch is unchanged).  The context keeps 6 sum(n_i) doubles of
- * workspace and the batch descriptors.  Returns once the work is enqueued
- * (after a one-time upload of the descriptors when the batch changed; the
- * segmented schedule polls the device's count of running systems one graph
- * behind, as apcg_ksp_solve does). */
+ * vectors' address ranges: APCG_ERR_INVALID_ARG); x[i] holds x0 (ignored with
+ * x0_is_zero) and receives the solution; info must hold >= nsys records,
+ * record i for system i.  opts->mode APCG_MODE_GRAPH (default) replays
+ * captured graphs (cached while the batch is unchanged).  The context keeps
+ * 6 sum(n_i) doubles of workspace and the batch descriptors.  Returns once the
+ * work is enqueued (after a one-time upload of the descriptors when the batch
+ * changed), except that the segmented schedule polls the device's count of
+ * running systems one graph behind, as apcg_ksp_solve does, and teams that
+ * stand in for it where it would poll are waited for; what they give up (see
+ * there) is solved on the segmented schedule then.  Teams that are not waited
+ * for have it solved by one workgroup per system. */
 apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b,
                                    const apcg_vec *x, double rtol, int32_t maxit, const apcg_solve_opts *opts,
                                    apcg_info info);
@@ -801,8 +820,9 @@ apcg_status apcg_mlp_forward(apcg_ctx ctx, const float *dev_params, const float 
 
 /* Mean loss over B systems (dev_loss[1]) and its gradient with respect to
  * the 5833 parameters (dev_grad), given each system's dev_G[B][81] and
- * dev_h[B][9] (from apcg_pc_label); penalty weight mu and floor eps of the positivity term
- * mu / 64 sum_q max(0, eps - p(t_q))^2 over 64 points of [0, lmax]. */
+ * dev_h[B][9] (from apcg_pc_label); penalty weight mu and floor eps of the
+ * positivity term mu / 64 sum_q max(0, eps - p(t_q))^2 over 64 points of
+ * [0, lmax]. */
 apcg_status apcg_mlp_loss_grad(apcg_ctx ctx, const float *dev_params, const float *dev_X, const float *dev_G,
                                const float *dev_h, int32_t B, float mu, float eps, float *dev_loss, float *dev_grad);
 
@@ -834,8 +854,10 @@ apcg_status apcg_fcg_opts_default(apcg_fcg_opts *opts);
  * APCG_SOLVE_FALLBACK and the reason; iterations count both phases;
  * fcg_iterations the flexible ones).  Stopping: ||r|| <= rtol ||b||.
  * opts: mode (graph/stream), iters_per_graph, lookahead and x0_is_zero as
- * for apcg_ksp_solve.  The host waits once, at the end of the flexible
- * phase, to decide on the fallback. */
+ * for apcg_ksp_solve, and so are the systems that a team solves, the flexible
+ * phase and the fallback in one launch (those whose blocks of 2048 rows read
+ * one another both ways, with two windows of their rows in the LDS).
+ * The kernels decide on the fallback on the device. */
 apcg_status apcg_ksp_solve_fcg_poly(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_vec x, double rtol, int32_t maxit,
                                     const float *dev_coeffs, const double *dev_lmax, const apcg_solve_opts *opts,
                                     const apcg_fcg_opts *fopts, apcg_info info, int32_t info_index);
@@ -851,9 +873,13 @@ apcg_status apcg_ksp_solve_fcg_poly(apcg_ctx ctx, apcg_mat A, apcg_vec b, apcg_v
  * info[i] receives system i's record.  opts: mode (graph/stream),
  * iters_per_graph, lookahead, x0_is_zero.  The memory of each x[i] may
  * overlap no other x[j] and no b[j] (checked on the host:
- * APCG_ERR_INVALID_ARG).  A system whose matrix is on APCG_SPMV_SDIA with 8 offset slots per slice
- * has its products and Clenshaw steps read the sliced-diagonal copy (same
- * row sums, bit for bit; refilled at the start of every call). */
+ * APCG_ERR_INVALID_ARG).  A system whose matrix is on APCG_SPMV_SDIA with 8
+ * offset slots per slice has its products and Clenshaw steps read the
+ * sliced-diagonal copy (same row sums, bit for bit; refilled at the start of
+ * every call).  With APCG_BATCH_AUTO and no tile sizes, systems that teams can
+ * hold are solved by them, with the tiles' bits, where the tiles would poll
+ * (maxit + 2 iterations reach the first poll); the call then returns after
+ * they have finished, and what they give up is solved on the tiles. */
 apcg_status apcg_ksp_solve_batched_fcg_poly(apcg_ctx ctx, int32_t nsys, const apcg_mat *A, const apcg_vec *b,
                                             const apcg_vec *x, double rtol, int32_t maxit, const float *dev_coeffs,
                                             const double *dev_lmax, const apcg_solve_opts *opts,
@@ -913,7 +939,8 @@ typedef struct apcg_counters {
     int64_t kernel_launches; /* kernels enqueued outside graphs              */
     int64_t graph_launches;  /* hipGraphLaunch calls                         */
     int64_t host_syncs;      /* host waits on streams/devices                */
-    int64_t host_polls;      /* host waits on events queued >= 1 period back */
+    int64_t host_polls;      /* host waits on events: queued >= 1 period back, */
+                             /* behind a team's launch, a pattern's counts   */
     int64_t d2h_copies;      /* device-to-host copies                        */
     int64_t h2d_copies;      /* host-to-device copies                        */
     int64_t stream_waits;    /* cross-context waits inserted by the registry */

@@ -620,7 +620,7 @@ extern "C" apcg_status apcg_ksp_solve_batched(apcg_ctx ctx, int32_t nsys, const 
         // to the last (team.hip): the segmented schedule streams both through
         // the caches four kernels an iteration, and a persistent workgroup
         // works on one system from memory.  256 2D systems of 1e3 to 6.5e4
-        // rows: 28.5 ms, segmented 192 (160 on sliced diagonals), persistent
+        // rows: 28.6 ms, segmented 192 (160 on sliced diagonals), persistent
         // 450.  Same sums as the segmented schedule, bit for bit.
         if (opts.batch_schedule == APCG_BATCH_AUTO) {
             // Where the schedules that teams replace are queued without a look

@@ -414,9 +414,9 @@ extern "C" apcg_status apcg_ksp_solve_tfqmr(apcg_ctx ctx, apcg_mat A, apcg_vec b
         if ((s = op_begin(ctx, acc, 4))) return s;
         const int64_t n = A->n;
         // a system that fits the chip, by a team of workgroups in one launch
-        // (as apcg_ksp_solve: GRAPH mode, more than kTeamMinRows rows)
-        // (not one whose iterations are queued without a look at the device: a
-        // team launch is waited for)
+        // (as apcg_ksp_solve: GRAPH mode, more than kTeamMinRows rows, and not
+        // if its iterations are queued without a look at the device: a team
+        // launch is waited for)
         const bool polled = ((int64_t)maxit + K - 1) / K >= L;
         if (opts.mode == APCG_MODE_GRAPH && n > kTeamMinRows && polled && maxit <= kTeamFcgMaxIts) {
             TeamFit fit;
